@@ -475,6 +475,7 @@ enum { EPI_BIAS = 1, EPI_PRE = 2, EPI_GATE = 4, EPI_RESID = 8, EPI_ACTF = 16 };
 template <typename T, int FM, int FN, int MODE, int ACT>
 __device__ __forceinline__ void fast_bands(f32x16 (&acc)[FM][FN], float* patch, const GemmArgs& a, int g, int mrow0,
                                            int ncol0, int lane, size_t out_off) {
+#pragma clang fp contract(off)  // see tile_epilogue
   constexpr bool CT = MODE >= 0;
   constexpr int SP = FN * 32 + 4, LPR = FN * 4, RPP = 64 / LPR, NP = 32 / RPP;
   const int lrow = lane & 31, lgrp = lane >> 5;
@@ -560,6 +561,9 @@ template <typename T, int FM, int FN, bool UPD, int SPEC = -1>
 __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[FM][FN], float* patch, const GemmArgs& a,
                                               const typename UpdSel<UPD>::type& upd, int g, int mrow0, int ncol0, int lane,
                                               size_t out_off = 0) {
+// one operation at a time: whether the compiler joins a product (gate, multiplier) and a sum (residual) differs from kernel
+// to kernel, and every tile shape has to give the same bits
+#pragma clang fp contract(off)
   constexpr int SP = FN * 32 + 4;          // patch pitch in floats (+4: spreads rows over banks)
   constexpr int LPR = FN * 4;              // lanes per row (8 elements each)
   constexpr int RPP = 64 / LPR;            // rows per pass
@@ -924,38 +928,51 @@ __device__ __forceinline__ void load_to_lds_b128(u32x4 rs, unsigned lds_addr, un
 
 // One operand tile of ROWS rows in the ring: what a lane contributes to the direct loads of a sub-tile and where it
 // reads its MFMA fragments.  NW = waves of the workgroup; load i of wave w fills slots [(i*NW + w)*64, +64).
-// BKW = k per sub-tile: 32, or 64 (a k-contiguous row is then 128 contiguous bytes per load: whole cache lines).
-template <bool KMAJ, int ROWS, int NW, int BKW = 32>
+// BKW = k per sub-tile: four 16-byte chunks per k-contiguous row (32 bf16, 16 fp32), or for bf16 eight (64: a row is
+// then 128 contiguous bytes per load, a whole cache line).
+// fp32, k as the slow index: k-rows of ROWS elements as for bf16; a fragment is four 4-byte reads (k..k+3 of one tile
+// row).  The two halves of a wave read k-rows 4 apart, which the XOR with ((k>>2)&1)<<3 sends to different halves of
+// the banks.  A k-row of 64 bf16 is half of the banks, so k-rows of equal parity share them and only (k>>1)&1 may move
+// its chunks.
+template <typename T, bool KMAJ, int ROWS, int NW, int BKW>
 struct RingOperand {
-  static constexpr int CPR = BKW / 8;                 // 16-byte chunks per k-contiguous row
+  static constexpr int E = Elem<T>::E;
+  static constexpr int CPR = BKW / E;                 // 16-byte chunks per k-contiguous row
+  static constexpr int RC = ROWS / E;                 // 16-byte chunks per k-row of a k-slow operand
   static constexpr int NLD = ROWS * CPR / 64 / NW;    // loads per wave and sub-tile (a sub-tile is ROWS*CPR slots either way)
   static_assert(ROWS * CPR % (64 * NW) == 0, "tile rows must divide over the waves");
-  static_assert(BKW == 32 || BKW == 64, "sub-tile depth");
-  static __device__ __forceinline__ int swz(int row) { return BKW == 32 ? swz4(row) : swz8(row); }
+  static_assert(CPR == 4 || CPR == 8 || CPR == 16, "sub-tile depth");
+  static_assert(RC >= 8, "k-rows too short for the chunk permutation");
+  static __device__ __forceinline__ int swz(int row) { return CPR == 4 ? swz4(row) : CPR == 8 ? swz8(row) : row & 15; }
+  static __device__ __forceinline__ int kswz(int k) {
+    if (sizeof(T) == 4) return ((k >> 2) & 1) << 2;
+    return RC >= 16 ? (k & 3) << 2 : ((k >> 1) & 1) << 2;
+  }
   u32x4 rs;
   unsigned voff[NLD];   // byte offset of the lane's chunk in sub-tile 0, relative to the descriptor's base
   int kofs[NLD];        // k (inside a sub-tile) of the lane's chunk: a chunk at or past K is loaded as zeros
   unsigned step;        // bytes from one sub-tile to the next
   // base/ld/row0/nrows: the matrix, its leading dimension, the tile's first row and the matrix's row count
-  __device__ __forceinline__ void init(const bf16_t* base, int ld, int row0, int nrows, int K, int wave, int lane) {
+  __device__ __forceinline__ void init(const T* base, int ld, int row0, int nrows, int K, int wave, int lane) {
+    constexpr unsigned SZ = sizeof(T);
     if (KMAJ) {
-      rs = rsrc_words(base, (long)row0 * ld * 2, (long)nrows * ld * 2);  // rows past the matrix read as zero
-      step = 2u * BKW;
+      rs = rsrc_words(base, (long)row0 * ld * SZ, (long)nrows * ld * SZ);  // rows past the matrix read as zero
+      step = SZ * BKW;
     } else {
-      rs = rsrc_words(base, (long)row0 * 2, (long)K * ld * 2);           // k-rows past K read as zero
-      step = 2u * BKW * (unsigned)ld;
+      rs = rsrc_words(base, (long)row0 * SZ, (long)K * ld * SZ);           // k-rows past K read as zero
+      step = SZ * BKW * (unsigned)ld;
     }
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
       const int sl = (i * NW + wave) * 64 + lane;
       if (KMAJ) {
         const int row = sl / CPR;
-        kofs[i] = ((sl % CPR) ^ swz(row)) * 8;
-        voff[i] = ((unsigned)row * (unsigned)ld + (unsigned)kofs[i]) * 2u;
+        kofs[i] = ((sl % CPR) ^ swz(row)) * E;
+        voff[i] = ((unsigned)row * (unsigned)ld + (unsigned)kofs[i]) * SZ;
       } else {
-        const int k = sl / (ROWS / 8), rc = (sl % (ROWS / 8)) ^ ((k & 3) << 2);
+        const int k = sl / RC, rc = (sl % RC) ^ kswz(k);
         kofs[i] = k;
-        voff[i] = ((unsigned)k * (unsigned)ld + (unsigned)rc * 8u) * 2u;
+        voff[i] = ((unsigned)k * (unsigned)ld + (unsigned)(rc * E)) * SZ;
       }
     }
   }
@@ -965,7 +982,7 @@ struct RingOperand {
     load_to_lds_b128(rs, st + (unsigned)((i * NW + wave) * 64 * 16), t * BKW + kofs[i] < K ? voff[i] + (unsigned)t * step : 0xfffffff0u);
   }
   // byte offset inside the operand's part of a stage of the lane's fragment of rows [rowbase, rowbase+32) for MFMA step
-  // mfma_step of the sub-tile (k-contiguous: every step has its own offset because of the XOR; k-slow: 16 k-rows each)
+  // mfma_step of the sub-tile (k-contiguous: every step has its own offset because of the XOR; k-slow: 2 E k-rows each)
   static __device__ __forceinline__ int frag_offset(int rowbase, int lane, int mfma_step) {
     if (KMAJ) {
       const int row = rowbase + (lane & 31);
@@ -973,7 +990,7 @@ struct RingOperand {
     }
     const int j = lane & 15, grp = lane >> 4, k = 16 * mfma_step + 8 * (grp >> 1) + (j >> 2);
     const int rc = rowbase / 8 + 2 * (grp & 1) + ((j & 3) >> 1);
-    return (k * (ROWS / 8) + (rc ^ ((k & 3) << 2))) * 16 + (j & 1) * 8;
+    return (k * RC + (rc ^ kswz(k))) * 16 + (j & 1) * 8;
   }
   static __device__ __forceinline__ uint4 read_frag(const char* stage_part, int off) {
     if (KMAJ) return *reinterpret_cast<const uint4*>(stage_part + off);
@@ -981,9 +998,19 @@ struct RingOperand {
     typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
     const unsigned a0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)(stage_part + off);
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)a0);
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(a0 + 4u * (ROWS / 8) * 16u));  // k + 4
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(a0 + 4u * RC * 16u));  // k + 4 (same kswz)
     uint2 l = __builtin_bit_cast(uint2, lo), h = __builtin_bit_cast(uint2, hi);
     return make_uint4(l.x, l.y, h.x, h.y);
+  }
+  // k-contiguous operand whose K is not a multiple of E: zero the elements past K in the chunk that holds them, in the
+  // landed sub-tile that holds K - 1 (kin = K inside it).  NT threads; the caller separates it with barriers.
+  static __device__ __forceinline__ void mask_k(char* stage_part, int kin, int tid) {
+    if (!KMAJ) return;
+    uint4* const p = reinterpret_cast<uint4*>(stage_part);
+    for (int row = tid; row < ROWS; row += NW * 64) {
+      uint4& c = p[row * CPR + ((kin / E) ^ swz(row))];
+      c = mask_tail<T>(c, kin % E);
+    }
   }
 };
 
@@ -991,16 +1018,16 @@ struct RingOperand {
 // stores its fp32 partial tile at element offset sp*M*ldo of out (row sums at sp*M); splitk_finish_kernel adds them.
 // BK = 64 (with NS = 2): sub-tiles of 64 k, so that a load of a k-contiguous operand covers 128 contiguous bytes per
 // row; one barrier per sub-tile, before its last MFMA step, and the loads of sub-tile t+2 follow that barrier.
-template <int WM, int WN, int FM, int FN, int NS, bool X_KMAJ, bool W_KMAJ, bool UPD, bool SPLITK = false, int BK = 32>
+template <typename T, int WM, int WN, int FM, int FN, int NS, bool X_KMAJ, bool W_KMAJ, bool UPD, bool SPLITK = false,
+          int BK = 4 * Elem<T>::E>
 __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a, const typename UpdSel<UPD>::type upd) {
   static_assert(!SPLITK || !UPD, "partial sums are stored plainly");
-  static_assert(BK == 32 || (BK == 64 && NS == 2), "ring shape");
-  typedef bf16_t T;
+  constexpr int CPR = BK / Elem<T>::E;               // 16-byte chunks of k per sub-tile: 4, or 8 (bf16)
   constexpr int BM = WM * FM * 32, BN = WN * FN * 32, NW = WM * WN;
-  constexpr int XPART = BM * (BK / 8) * 16;          // bytes of the X part of a stage
-  constexpr int STAGE = (BM + BN) * (BK / 8) * 16;   // bytes per stage: X part, then W part
-  typedef RingOperand<X_KMAJ, BM, NW, BK> RX;
-  typedef RingOperand<W_KMAJ, BN, NW, BK> RW;
+  constexpr int XPART = BM * CPR * 16;          // bytes of the X part of a stage
+  constexpr int STAGE = (BM + BN) * CPR * 16;   // bytes per stage: X part, then W part
+  typedef RingOperand<T, X_KMAJ, BM, NW, BK> RX;
+  typedef RingOperand<T, W_KMAJ, BN, NW, BK> RW;
   constexpr int NL = RX::NLD + RW::NLD;
   extern __shared__ uint4 lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1047,7 +1074,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
   const int lrow = lane & 31, lgrp = lane >> 5;
-  constexpr int NSTEP = BK / 16;   // MFMA steps per sub-tile
+  constexpr int NSTEP = CPR / 2;   // MFMA steps per sub-tile
   int fx[NSTEP][FM], fw[NSTEP][FN];  // fragment byte offsets inside a stage per MFMA step
 #pragma unroll
   for (int s = 0; s < NSTEP; ++s) {
@@ -1056,19 +1083,29 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
 #pragma unroll
     for (int j = 0; j < FN; ++j) fw[s][j] = XPART + RW::frag_offset((wn * FN + j) * 32, lane, s);
   }
-  // loads of this wave that may still be in flight when the next sub-tile must have landed (BK = 64: none, the loads
-  // of the sub-tile after it are issued behind the barrier); in the prologue sub-tile 0 must have landed
-  constexpr int ALLOW = BK == 32 ? (NS - 2) * NL : 0;
-  constexpr int ALLOW0 = BK == 32 ? ALLOW : NL;
+  // loads of this wave that may still be in flight when the next sub-tile must have landed (eight chunks: the loads of
+  // the sub-tile that replaces the current one are issued behind the barrier); in the prologue sub-tile 0 must have landed
+  constexpr int ALLOW = (NS - 2) * NL;
+  constexpr int ALLOW0 = CPR == 4 ? ALLOW : (NS - 1) * NL;
   static_assert(ALLOW < 64 && ALLOW0 < 64, "vmcnt field");
   constexpr int WAIT_VM = (ALLOW & 15) | ((ALLOW >> 4) << 14) | (7 << 4);  // s_waitcnt vmcnt(ALLOW) lgkmcnt(0)
   constexpr int WAIT_VM0 = (ALLOW0 & 15) | ((ALLOW0 >> 4) << 14) | (7 << 4) | (15 << 8);  // vmcnt(ALLOW0) only
 #pragma unroll
-  for (int t = 0; t < (BK == 32 ? NS - 1 : 2); ++t)
+  for (int t = 0; t < (CPR == 4 ? NS - 1 : NS); ++t)
 #pragma unroll
     for (int nd = 0; nd < NL; ++nd) load_one(t, nd);
   __builtin_amdgcn_s_waitcnt(WAIT_VM0);
   __builtin_amdgcn_s_barrier();
+  // K not a multiple of a chunk: the elements past K in a k-contiguous operand's last chunk are cleared in LDS once the
+  // last sub-tile has landed (tail: uniform over the launch)
+  const bool tail = (X_KMAJ || W_KMAJ) && K % Elem<T>::E != 0;
+  auto mask_tail_of = [&](int t) {
+    char* const st = reinterpret_cast<char*>(lds) + (t % NS) * STAGE;
+    RX::mask_k(st, K - (kb + t) * BK, tid);
+    RW::mask_k(st + XPART, K - (kb + t) * BK, tid);
+    __syncthreads();
+  };
+  if (tail && nk == 1) mask_tail_of(0);
   uint4 xa[FM], wa[FN], xb[FM], wb[FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i) xa[i] = RX::read_frag(lds_c, fx[0][i]);
@@ -1085,21 +1122,26 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
   // (xn, wn) and, with tl >= 0, the loads of sub-tile tl are issued; the order is pinned so that LDS reads and
   // loads sit between the MFMAs that hide them.
   auto step = [&](uint4(&xc)[FM], uint4(&wc)[FN], uint4(&xn)[FM], uint4(&wn_)[FN], const char* sn, int s, int tl) {
+    constexpr int T_ = FM * FN, RPM = (FM + FN + T_ - 1) / T_;  // MFMAs per step; fragment reads ahead of each
     int nr = 0, nd = 0;
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
       for (int j = 0; j < FN; ++j) {
         const int q = i * FN + j;
-        if (tl >= 0 && nd < NL && nd * (FM * FN) <= q * NL) {
-          load_one(tl, nd);
-          ++nd;
-        }
-        if (nr < FM + FN) {
-          if (nr < FM) xn[nr] = RX::read_frag(sn, fx[s][nr]);
-          else wn_[nr - FM] = RW::read_frag(sn, fw[s][nr - FM]);
-          ++nr;
-        }
+#pragma unroll
+        for (int u = 0; u < NL; ++u)
+          if (tl >= 0 && nd < NL && nd * T_ <= q * NL + (NL > T_ ? NL - T_ : 0)) {
+            load_one(tl, nd);
+            ++nd;
+          }
+#pragma unroll
+        for (int u = 0; u < RPM; ++u)
+          if (nr < FM + FN) {
+            if (nr < FM) xn[nr] = RX::read_frag(sn, fx[s][nr]);
+            else wn_[nr - FM] = RW::read_frag(sn, fw[s][nr - FM]);
+            ++nr;
+          }
         mma<T>(acc[i][j], wc[j], xc[i]);
         if (RS && j == 0) rs[i] = chunk_sum<T>(xc[i], rs[i]);
         __builtin_amdgcn_sched_barrier(0);
@@ -1108,18 +1150,20 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
   for (int t = 0; t < nk; ++t) {
     const char* st = lds_c + (t % NS) * STAGE;
     const char* sn = lds_c + ((t + 1) % NS) * STAGE;
-    if constexpr (BK == 32) {
+    if constexpr (CPR == 4) {
       step(xa, wa, xb, wb, st, 1, t + NS - 1);
       __builtin_amdgcn_s_waitcnt(WAIT_VM);
       __builtin_amdgcn_s_barrier();
+      if (tail && t + 2 == nk) mask_tail_of(t + 1);
       step(xb, wb, xa, wa, sn, 0, -1);
     } else {
       step(xa, wa, xb, wb, st, 1, -1);
       step(xb, wb, xa, wa, st, 2, -1);
       step(xa, wa, xb, wb, st, 3, -1);
-      __builtin_amdgcn_s_waitcnt(WAIT_VM);  // sub-tile t+1 (issued one sub-tile ago) has landed; own reads of stage t are done
+      __builtin_amdgcn_s_waitcnt(WAIT_VM);  // sub-tile t+1 has landed; own reads of stage t are done
       __builtin_amdgcn_s_barrier();
-      step(xb, wb, xa, wa, sn, 0, t + 2);    // stage t is free: sub-tile t+2 goes there
+      if (tail && t + 2 == nk) mask_tail_of(t + 1);
+      step(xb, wb, xa, wa, sn, 0, t + NS);   // stage t is free: sub-tile t+NS goes there
     }
   }
   if (do_rs && wn == 0) {
@@ -1136,10 +1180,333 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
   constexpr int SP = FN * 32 + 4;
   static_assert((size_t)NW * 32 * SP * 4 <= (size_t)NS * STAGE, "epilogue patch exceeds LDS");
   float* patch = reinterpret_cast<float*>(lds) + wave * (32 * SP);
-  constexpr int SPEC = SPLITK ? -1 : (UPD || FM != 4 || FN != 2 || !X_KMAJ) ? 0 : (W_KMAJ ? 1 : 2);
+  constexpr int SPEC = SPLITK ? -1 : (UPD || !X_KMAJ) ? 0 : (W_KMAJ ? 1 : 2);
   tile_epilogue<T, FM, FN, UPD, SPEC>(acc, patch, a, upd, g, m0 + wm * FM * 32, n0 + wn * FN * 32, lane,
                                       SPLITK ? (size_t)sp * a.M * a.ldo : 0);
 }
+
+// ---- few output tiles: one latency chain per tile ------------------------------------------------------------------
+//
+// A launch with at most a few tiles per CU is bound by neither the matrix pipes nor memory but by what a workgroup does
+// one thing after the other.  Timestamps inside the 128x128 kernel on 4 x [1024 tokens, 1024 -> 256] (us): arguments 0.3,
+// first loads issued 1.0, k-loop 7.4 (0.2 per sub-tile of 32 k: a barrier, an LDS round trip and four dependent MFMAs),
+// epilogue 8-10 with activation.  These kernels take the same operands through the same ring, with
+//  * tiles of 64x64 (bf16; a wave owns one 32x32 accumulator) or 32x32 (fp32; a wave owns 16x16), so that four to sixteen
+//    times the workgroups share the work and the epilogue;
+//  * 256 (128) bytes of k per row and stage: one barrier and one LDS round trip per 8 (4) MFMA steps, all fragments of a
+//    stage being requested together while the previous stage's MFMAs run;
+//  * a grid of (tile row, tile column, problem): no divisions before the operand pointers are read;
+//  * an epilogue compiled per operand combination (bf16, as the big tile's) or without the LDS patch (fp32).
+// Same MFMA chain per output element, same bits as the other kernels.  Kernel time before | now, us: 4 x [1024 tokens]
+// 1024 -> 256 forward 17.8 | 9.4, 256 -> 1024 input gradient with gate 19.0 | 9.8, 256 x 256 weight gradient with Adam 17.0 | 9.4,
+// 256 x 1024 22.3 | 13.2; 3 x [96, 320 -> 320] 8.4 | 5.9; fp32 4 x [64, 784 -> 768] input gradient 24.0 | 12.4.
+// 30 or 40 KB of LDS more or less does not show: two workgroups per CU (64 KB each) or one (128 KB) are level on
+// launches of up to 256 tiles, and two are a third faster beyond.
+//
+// bf16.  CPR = 16-byte chunks of k per row and stage, NS stages: 16 x 2, or 8 x 4 for long sums (three stages in flight
+// instead of one: 2 x [300 rows, 8192 -> 512] 47 -> 40 us, 1 x 1024 x 1024 weight gradient over 4096 tokens 28.6 -> 24.3;
+// at K = 1024 it is 3-10 % behind).
+template <int CPR, int NS, bool X_KMAJ, bool W_KMAJ, bool UPD>
+__global__ __launch_bounds__(256) void gemm_small_kernel(const GemmArgs a, const typename UpdSel<UPD>::type upd) {
+  typedef bf16_t T;
+  constexpr int E = Elem<T>::E, BK = CPR * E, NSTEP = CPR / 2;
+  constexpr int BM = 64, BN = 64;
+  constexpr int XPART = BM * CPR * 16, STAGE = (BM + BN) * CPR * 16;
+  typedef RingOperand<T, X_KMAJ, BM, 4, BK> RX;
+  typedef RingOperand<T, W_KMAJ, BN, 4, BK> RW;
+  constexpr int NL = RX::NLD + RW::NLD;
+  extern __shared__ uint4 lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int g = blockIdx.z, m0 = blockIdx.x * BM, n0 = blockIdx.y * BN, K = a.K;
+  RX ox;
+  RW ow;
+  ox.init(static_cast<const T*>(a.X[g]), a.ldx, m0, a.M, K, wave, lane);
+  ow.init(static_cast<const T*>(a.W[g]), a.ldw, n0, a.N, K, wave, lane);
+  char* const lds_c = reinterpret_cast<char*>(lds);
+  const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+  const int nk = (K + BK - 1) / BK;
+  auto load = [&](int t) {
+    const unsigned st = lds_base + (unsigned)((t % NS) * STAGE);
+#pragma unroll
+    for (int i = 0; i < RX::NLD; ++i) ox.issue(i, t, st, K, wave);
+#pragma unroll
+    for (int i = 0; i < RW::NLD; ++i) ow.issue(i, t, st + (unsigned)XPART, K, wave);
+  };
+#pragma unroll
+  for (int t = 0; t < NS; ++t) load(t);
+  int fx[NSTEP], fw[NSTEP];
+#pragma unroll
+  for (int s = 0; s < NSTEP; ++s) {
+    fx[s] = RX::frag_offset(wm * 32, lane, s);
+    fw[s] = XPART + RW::frag_offset(wn * 32, lane, s);
+  }
+  f32x16 acc[1][1];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.f;
+  constexpr bool RS = !X_KMAJ && !W_KMAJ;
+  const bool do_rs = RS && a.rowsum[g] != nullptr && n0 == 0;
+  float rs = 0.f;
+  const bool tail = (X_KMAJ || W_KMAJ) && K % E != 0;
+  uint4 x0[NSTEP], w0[NSTEP], x1[NSTEP], w1[NSTEP];
+  constexpr int AL0 = (NS - 1) * NL, AL = (NS - 2) * NL;
+  static_assert(AL0 < 64, "vmcnt field");
+  auto take = [&](int t, uint4 (&x)[NSTEP], uint4 (&w)[NSTEP]) {
+    char* const st = lds_c + (t % NS) * STAGE;
+    if (tail && t + 1 == nk) {
+      RX::mask_k(st, K - t * BK, tid);
+      RW::mask_k(st + XPART, K - t * BK, tid);
+      __syncthreads();
+    }
+#pragma unroll
+    for (int s = 0; s < NSTEP; ++s) {
+      x[s] = RX::read_frag(st, fx[s]);
+      w[s] = RW::read_frag(st, fw[s]);
+    }
+  };
+  auto body = [&](int t, uint4 (&xc)[NSTEP], uint4 (&wc)[NSTEP], uint4 (&xn)[NSTEP], uint4 (&wn_)[NSTEP]) {
+    __builtin_amdgcn_s_waitcnt((AL & 15) | ((AL >> 4) << 14) | (7 << 4));  // vmcnt(AL) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    load(t + NS);
+    take(t + 1, xn, wn_);
+#pragma unroll
+    for (int s = 0; s < NSTEP; ++s) {
+      mma<T>(acc[0][0], wc[s], xc[s]);
+      if (RS) rs = chunk_sum<T>(xc[s], rs);
+    }
+  };
+  __builtin_amdgcn_s_waitcnt((AL0 & 15) | ((AL0 >> 4) << 14) | (7 << 4) | (15 << 8));
+  __builtin_amdgcn_s_barrier();
+  take(0, x0, w0);
+  for (int t = 0; t < nk; t += 2) {
+    body(t, x0, w0, x1, w1);
+    if (t + 1 < nk) body(t + 1, x1, w1, x0, w0);
+  }
+  const int lrow = lane & 31, lgrp = lane >> 5;
+  if (do_rs && wn == 0) {
+    const float total = rs + __shfl_xor(rs, 32, 64);
+    const int m = m0 + wm * 32 + lrow;
+    if (lgrp == 0 && m < a.M) a.rowsum[g][m] = total;
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  constexpr int SP = 36;
+  float* patch = reinterpret_cast<float*>(lds) + wave * (32 * SP);
+  tile_epilogue<T, 1, 1, UPD, UPD ? 0 : (!X_KMAJ ? 0 : (W_KMAJ ? 1 : 2))>(acc, patch, a, upd, g, m0 + wm * 32, n0 + wn * 32, lane);
+}
+
+// fp32.  A 32x32 accumulator costs 64 cycles of one SIMD per 2 k (10 us for K = 768, which nothing can hide where a launch
+// has fewer tiles than SIMDs); v_mfma_f32_16x16x4 does a quarter of the tile with 4 k in 32 cycles.  It sums its four k
+// one after the other with the rounding of fmaf, as v_mfma_f32_32x32x2 does its two (compared bit by bit with each other and
+// with a chain of fmaf on the CPU), so a lane group q = lane/16 that supplies k = 8 s + 4 (q%2) + e + q/2 (e = 0, 2) gives
+// the bits of the 32x32 tiles' chain.
+template <int NS, bool X_KMAJ, bool W_KMAJ, bool UPD>
+__global__ __launch_bounds__(256) void gemm_small_f32_kernel(const GemmArgs a, const typename UpdSel<UPD>::type upd) {
+  typedef float T;
+  constexpr int CPR = 16, E = 4, BK = CPR * E, NSTEP = CPR / 2;
+  constexpr int BM = 32, BN = 32;
+  constexpr int XPART = BM * CPR * 16, STAGE = (BM + BN) * CPR * 16;
+  typedef RingOperand<T, X_KMAJ, BM, 4, BK> RX;
+  typedef RingOperand<T, W_KMAJ, BN, 4, BK> RW;
+  constexpr int NL = RX::NLD + RW::NLD;
+  extern __shared__ uint4 lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1, r16 = lane & 15, q = lane >> 4;
+  const int g = blockIdx.z, m0 = blockIdx.x * BM, n0 = blockIdx.y * BN, K = a.K;
+  RX ox;
+  RW ow;
+  ox.init(static_cast<const T*>(a.X[g]), a.ldx, m0, a.M, K, wave, lane);
+  ow.init(static_cast<const T*>(a.W[g]), a.ldw, n0, a.N, K, wave, lane);
+  char* const lds_c = reinterpret_cast<char*>(lds);
+  const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+  const int nk = (K + BK - 1) / BK;
+  auto load = [&](int t) {
+    const unsigned st = lds_base + (unsigned)((t % NS) * STAGE);
+#pragma unroll
+    for (int i = 0; i < RX::NLD; ++i) ox.issue(i, t, st, K, wave);
+#pragma unroll
+    for (int i = 0; i < RW::NLD; ++i) ow.issue(i, t, st + (unsigned)XPART, K, wave);
+  };
+#pragma unroll
+  for (int t = 0; t < NS; ++t) load(t);
+  const int xrow = wm * 16 + r16, wrow = wn * 16 + r16;
+  auto frag = [&](const char* part, bool kmaj, int row, int s) {  // k = 8 s + 4 (q%2) + q/2 and that k + 2
+    if (kmaj) {
+      const float* p = reinterpret_cast<const float*>(part) + ((row * CPR + ((2 * s + (q & 1)) ^ (row & 15))) * 4 + (q >> 1));
+      return make_float2(p[0], p[2]);
+    }
+    const int k = 8 * s + 4 * (q & 1) + (q >> 1);
+    const float* p = reinterpret_cast<const float*>(part) + ((k * (BM / E) + ((row >> 2) ^ RX::kswz(k))) * 4 + (row & 3));
+    return make_float2(p[0], p[2 * BM]);
+  };
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  constexpr bool RS = !X_KMAJ && !W_KMAJ;
+  const bool do_rs = RS && a.rowsum[g] != nullptr && n0 == 0 && wn == 0;
+  float rs = 0.f;
+  const bool tail = (X_KMAJ || W_KMAJ) && K % E != 0;
+  float2 x0[NSTEP], w0[NSTEP], x1[NSTEP], w1[NSTEP];
+  constexpr int AL0 = (NS - 1) * NL, AL = (NS - 2) * NL;
+  static_assert(AL0 < 64, "vmcnt field");
+  auto take = [&](int t, float2 (&x)[NSTEP], float2 (&w)[NSTEP]) {
+    char* const st = lds_c + (t % NS) * STAGE;
+    if (tail && t + 1 == nk) {
+      RX::mask_k(st, K - t * BK, tid);
+      RW::mask_k(st + XPART, K - t * BK, tid);
+      __syncthreads();
+    }
+#pragma unroll
+    for (int s = 0; s < NSTEP; ++s) {
+      x[s] = frag(st, X_KMAJ, xrow, s);
+      w[s] = frag(st + XPART, W_KMAJ, wrow, s);
+    }
+    if (RS && do_rs) {  // as chunk_sum in the other kernels: half (lane/16)%2 adds k = 8 s + 4 half + 0..3 in ascending k
+#pragma clang fp contract(off)
+#pragma unroll
+      for (int s = 0; s < NSTEP; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int k = 8 * s + 4 * (q & 1) + e;
+          rs = rs + *(reinterpret_cast<const float*>(st) + ((k * (BM / E) + ((xrow >> 2) ^ RX::kswz(k))) * 4 + (xrow & 3)));
+        }
+    }
+  };
+  auto body = [&](int t, float2 (&xc)[NSTEP], float2 (&wc)[NSTEP], float2 (&xn)[NSTEP], float2 (&wn_)[NSTEP]) {
+    __builtin_amdgcn_s_waitcnt((AL & 15) | ((AL >> 4) << 14) | (7 << 4));  // vmcnt(AL) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    load(t + NS);
+    if (t + 1 < nk) take(t + 1, xn, wn_);
+#pragma unroll
+    for (int s = 0; s < NSTEP; ++s) {
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[s].x, xc[s].x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[s].y, xc[s].y, acc, 0, 0, 0);
+    }
+  };
+  __builtin_amdgcn_s_waitcnt((AL0 & 15) | ((AL0 >> 4) << 14) | (7 << 4) | (15 << 8));
+  __builtin_amdgcn_s_barrier();
+  take(0, x0, w0);
+  for (int t = 0; t < nk; t += 2) {
+    body(t, x0, w0, x1, w1);
+    if (t + 1 < nk) body(t + 1, x1, w1, x0, w0);
+  }
+  const int m = m0 + xrow, n = n0 + wn * 16 + 4 * q;
+  if (RS && do_rs) {
+    const float total = rs + __shfl_xor(rs, 16, 64);
+    if (q == 0 && m < a.M) a.rowsum[g][m] = total;
+  }
+  if (m >= a.M || n >= a.N) return;
+  if constexpr (UPD) {  // N is a multiple of 8
+    const size_t ix = (size_t)m * a.ldo + n;
+    const OptimHp h = upd.hp[g];
+    const f32x4 p = *reinterpret_cast<const f32x4*>(upd.p[g] + ix);
+    float pe[4] = {p.x, p.y, p.z, p.w}, me[4] = {0.f, 0.f, 0.f, 0.f}, ve[4] = {0.f, 0.f, 0.f, 0.f};
+    if (upd.opt == 1) {
+      const f32x4 mm = *reinterpret_cast<const f32x4*>(upd.m[g] + ix), vv = *reinterpret_cast<const f32x4*>(upd.v[g] + ix);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { me[e] = mm[e]; ve[e] = vv[e]; }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) optim_step<1>(pe[e], me[e], ve[e], acc[e], h);
+      *reinterpret_cast<f32x4*>(upd.m[g] + ix) = f32x4{me[0], me[1], me[2], me[3]};
+      *reinterpret_cast<f32x4*>(upd.v[g] + ix) = f32x4{ve[0], ve[1], ve[2], ve[3]};
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) optim_step<0>(pe[e], me[e], ve[e], acc[e], h);
+    }
+    *reinterpret_cast<f32x4*>(upd.p[g] + ix) = f32x4{pe[0], pe[1], pe[2], pe[3]};
+    if (upd.w16[g]) *reinterpret_cast<uint2*>(upd.w16[g] + ix) = make_uint2(pack_bf16x2(pe[0], pe[1]), pack_bf16x2(pe[2], pe[3]));
+    if (a.out[g]) *reinterpret_cast<f32x4*>(static_cast<float*>(a.out[g]) + ix) = acc;
+  } else {
+#pragma clang fp contract(off)  // see tile_epilogue
+    const float* bias = a.bias[g];
+    float* pre = static_cast<float*>(a.pre[g]);
+    const float* gate = static_cast<const float*>(a.gate[g]);
+    const float* resid = static_cast<const float*>(a.resid[g]);
+    const float* mul = static_cast<const float*>(a.mul[g]);
+    float* out = static_cast<float*>(a.out[g]);
+    const size_t ix = (size_t)m * a.ldo + n;
+    float v[4] = {acc.x, acc.y, acc.z, acc.w}, z[4];
+    const int cnt = a.N - n;
+    auto get = [&](const float* p, float (&d)[4]) {
+      if (cnt >= 4) {
+        const f32x4 t = *reinterpret_cast<const f32x4*>(p);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] = t[e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] = e < cnt ? p[e] : 0.f;
+      }
+    };
+    auto put = [&](float* p) {
+      if (cnt >= 4) *reinterpret_cast<f32x4*>(p) = f32x4{v[0], v[1], v[2], v[3]};
+      else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (e < cnt) p[e] = v[e];
+      }
+    };
+    if (bias) {
+      get(bias + n, z);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += z[e];
+    }
+    if (pre) put(pre + ix);
+    if (gate) {
+      get(gate + (size_t)m * a.ldg + n, z);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] *= act_grad(z[e], a.act);
+    } else if (a.act != EPI_ACT_NONE) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = act_fwd(v[e], a.act);
+    }
+    if (mul) {
+      get(mul + ix, z);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] *= z[e];
+    }
+    if (resid) {
+      get(resid + (size_t)m * a.ldr + n, z);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += z[e];
+    }
+    put(out + ix);
+  }
+}
+
+// Launchers of the two kernels above: a grid of (tile row, tile column, problem), so that a workgroup needs no division to find
+// its tile and the operand pointers are the first things it waits for.
+template <typename T, int CPR, int NS>
+struct SmallTile {
+  static constexpr int BT = sizeof(T) == 2 ? 64 : 32;
+  static constexpr size_t LDS = (size_t)NS * 2 * BT * CPR * 16;
+  static long tiles(const GemmArgs& a) { return (long)((a.M + BT - 1) / BT) * ((a.N + BT - 1) / BT) * a.G; }
+  template <bool XK, bool WK, bool UPD>
+  static constexpr auto kernel() {
+    if constexpr (sizeof(T) == 2) return &gemm_small_kernel<CPR, NS, XK, WK, UPD>;
+    else return &gemm_small_f32_kernel<NS, XK, WK, UPD>;
+  }
+  template <bool XK, bool WK, bool UPD, typename U>
+  static hipError_t go(const GemmArgs& a, const U& u, hipStream_t s) {
+    hipLaunchKernelGGL((kernel<XK, WK, UPD>()), dim3((a.M + BT - 1) / BT, (a.N + BT - 1) / BT, a.G), dim3(256), LDS, s, a, u);
+    return hipGetLastError();
+  }
+  static hipError_t run(const GemmArgs& a, hipStream_t s) {
+    if (a.x_kmajor) return a.w_kmajor ? go<true, true, false>(a, NoUpdate(), s) : go<true, false, false>(a, NoUpdate(), s);
+    return a.w_kmajor ? go<false, true, false>(a, NoUpdate(), s) : go<false, false, false>(a, NoUpdate(), s);
+  }
+  static hipError_t run_update(const GemmArgs& a, const GemmUpdate& u, hipStream_t s) { return go<false, false, true>(a, u, s); }
+  template <bool XK, bool WK, bool UPD = false>
+  static hipError_t attr1() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel<XK, WK, UPD>()), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)LDS);
+  }
+  static hipError_t attr() {
+    hipError_t e;
+    if ((e = attr1<true, true>()) != hipSuccess) return e;
+    if ((e = attr1<true, false>()) != hipSuccess) return e;
+    if ((e = attr1<false, true>()) != hipSuccess) return e;
+    if ((e = attr1<false, false>()) != hipSuccess) return e;
+    return attr1<false, false, true>();
+  }
+};
 
 // Second launch of a split weight gradient: element (m, n) of problem g = the S partial sums added in ascending
 // order, then stored (fp32) and/or fed to the parameter update exactly as the one-launch epilogue would.
@@ -1237,9 +1604,9 @@ struct DmaBig {  // 256 x 256, 8 waves (2 x 4, each 128 x 64), ring of 4 stages 
   template <bool XK, bool WK>
   static hipError_t run1(const GemmArgs& a, hipStream_t s) {
     if constexpr (XK && WK)
-      hipLaunchKernelGGL((gemm_dma_kernel<WM, WN, FM, FN, 2, XK, WK, false, false, 64>), dim3(grid_of(a)), dim3(NT), LDS, s, a, NoUpdate());
+      hipLaunchKernelGGL((gemm_dma_kernel<bf16_t, WM, WN, FM, FN, 2, XK, WK, false, false, 64>), dim3(grid_of(a)), dim3(NT), LDS, s, a, NoUpdate());
     else
-      hipLaunchKernelGGL((gemm_dma_kernel<WM, WN, FM, FN, NS, XK, WK, false>), dim3(grid_of(a)), dim3(NT), LDS, s, a, NoUpdate());
+      hipLaunchKernelGGL((gemm_dma_kernel<bf16_t, WM, WN, FM, FN, NS, XK, WK, false>), dim3(grid_of(a)), dim3(NT), LDS, s, a, NoUpdate());
     return hipGetLastError();
   }
   static hipError_t run(const GemmArgs& a, hipStream_t s) {
@@ -1247,21 +1614,21 @@ struct DmaBig {  // 256 x 256, 8 waves (2 x 4, each 128 x 64), ring of 4 stages 
     return a.w_kmajor ? run1<false, true>(a, s) : run1<false, false>(a, s);
   }
   static hipError_t run_update(const GemmArgs& a, const GemmUpdate& u, hipStream_t s) {
-    hipLaunchKernelGGL((gemm_dma_kernel<WM, WN, FM, FN, NS, false, false, true>), dim3(grid_of(a)), dim3(NT), LDS, s, a, u);
+    hipLaunchKernelGGL((gemm_dma_kernel<bf16_t, WM, WN, FM, FN, NS, false, false, true>), dim3(grid_of(a)), dim3(NT), LDS, s, a, u);
     return hipGetLastError();
   }
   static hipError_t run_split(const GemmArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL((gemm_dma_kernel<WM, WN, FM, FN, NS, false, false, false, true>), dim3(grid_of(a) * a.split_k), dim3(NT), LDS,
+    hipLaunchKernelGGL((gemm_dma_kernel<bf16_t, WM, WN, FM, FN, NS, false, false, false, true>), dim3(grid_of(a) * a.split_k), dim3(NT), LDS,
                        s, a, NoUpdate());
     return hipGetLastError();
   }
   template <bool XK, bool WK, bool UPD>
   static hipError_t attr1() {
     if constexpr (XK && WK && !UPD)
-      return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<WM, WN, FM, FN, 2, XK, WK, false, false, 64>),
+      return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<bf16_t, WM, WN, FM, FN, 2, XK, WK, false, false, 64>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
     else
-      return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<WM, WN, FM, FN, NS, XK, WK, UPD>),
+      return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<bf16_t, WM, WN, FM, FN, NS, XK, WK, UPD>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
   }
   static hipError_t attr() {
@@ -1270,7 +1637,7 @@ struct DmaBig {  // 256 x 256, 8 waves (2 x 4, each 128 x 64), ring of 4 stages 
     if ((e = attr1<true, false, false>()) != hipSuccess) return e;
     if ((e = attr1<false, true, false>()) != hipSuccess) return e;
     if ((e = attr1<false, false, false>()) != hipSuccess) return e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<WM, WN, FM, FN, NS, false, false, false, true>),
+    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<bf16_t, WM, WN, FM, FN, NS, false, false, false, true>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS)) != hipSuccess)
       return e;
     return attr1<false, false, true>();
@@ -1279,14 +1646,17 @@ struct DmaBig {  // 256 x 256, 8 waves (2 x 4, each 128 x 64), ring of 4 stages 
 // Measured against the register-staged 128 x 128 tile on one model's 8192-token products (d = 1024): forward 8-11 %
 // faster, input gradient 21-31 %, weight gradient 23-46 %; with the update in the epilogue (8 x [4096 x 4096], 512
 // tokens) 720 -> 663 us per launch.
-struct DmaMid {  // 128 x 128, 4 waves (2 x 2, each 64 x 64), ring of 4 stages of 16 KB: two workgroups per CU
-  static constexpr int WM = 2, WN = 2, FM = 2, FN = 2, NS = 4;
+template <typename T, int WM, int WN, int FM, int FN, int NS, int BK = 4 * Elem<T>::E>
+struct Dma {
   static constexpr int BM = WM * FM * 32, BN = WN * FN * 32, NT = WM * WN * 64;
-  static constexpr size_t LDS = (size_t)NS * (BM + BN) * 4 * 16;
+  static constexpr size_t LDS = (size_t)NS * (BM + BN) * (BK / Elem<T>::E) * 16;
+  static dim3 grid_of(const GemmArgs& a) {
+    const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN) * a.G;
+    return dim3((tiles + 7) / 8 * 8);
+  }
   template <bool XK, bool WK>
   static hipError_t run1(const GemmArgs& a, hipStream_t s) {
-    const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN) * a.G;
-    hipLaunchKernelGGL((gemm_dma_kernel<WM, WN, FM, FN, NS, XK, WK, false>), dim3((tiles + 7) / 8 * 8), dim3(NT), LDS, s, a, NoUpdate());
+    hipLaunchKernelGGL((gemm_dma_kernel<T, WM, WN, FM, FN, NS, XK, WK, false, false, BK>), grid_of(a), dim3(NT), LDS, s, a, NoUpdate());
     return hipGetLastError();
   }
   static hipError_t run(const GemmArgs& a, hipStream_t s) {
@@ -1294,34 +1664,43 @@ struct DmaMid {  // 128 x 128, 4 waves (2 x 2, each 64 x 64), ring of 4 stages o
     return a.w_kmajor ? run1<false, true>(a, s) : run1<false, false>(a, s);
   }
   static hipError_t run_update(const GemmArgs& a, const GemmUpdate& u, hipStream_t s) {
-    const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN) * a.G;
-    hipLaunchKernelGGL((gemm_dma_kernel<WM, WN, FM, FN, NS, false, false, true>), dim3((tiles + 7) / 8 * 8), dim3(NT), LDS, s, a, u);
+    hipLaunchKernelGGL((gemm_dma_kernel<T, WM, WN, FM, FN, NS, false, false, true, false, BK>), grid_of(a), dim3(NT), LDS, s, a, u);
     return hipGetLastError();
   }
-  template <bool XK, bool WK>
+  template <bool XK, bool WK, bool UPD = false>
   static hipError_t attr1() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<WM, WN, FM, FN, NS, XK, WK, false>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<T, WM, WN, FM, FN, NS, XK, WK, UPD, false, BK>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
+  }
+  static hipError_t run_x(const GemmArgs& a, hipStream_t s) {  // k-contiguous X only
+    return a.w_kmajor ? run1<true, true>(a, s) : run1<true, false>(a, s);
+  }
+  static hipError_t attr_x() {
+    const hipError_t e = attr1<true, true>();
+    return e != hipSuccess ? e : attr1<true, false>();
   }
   static hipError_t attr() {
     hipError_t e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<WM, WN, FM, FN, NS, false, false, true>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS)) != hipSuccess)
-      return e;
-    if ((e = attr1<true, true>()) != hipSuccess) return e;
-    if ((e = attr1<true, false>()) != hipSuccess) return e;
+    if ((e = attr_x()) != hipSuccess) return e;
     if ((e = attr1<false, true>()) != hipSuccess) return e;
-    return attr1<false, false>();
+    if ((e = attr1<false, false>()) != hipSuccess) return e;
+    return attr1<false, false, true>();
   }
 };
-// The direct-to-LDS kernel takes bf16 problems.  A k-contiguous operand needs K to be a multiple of 8 (a 16-byte
-// chunk is then entirely inside or outside the matrix); an operand with k as the slow index is addressed from the
-// tile's first element with 32-bit offsets, so its K x ld bytes must stay below 2 GiB.
+// 128 x 128, 4 waves (2 x 2, each 64 x 64), ring of 4 stages of 16 KB: two workgroups per CU
+typedef Dma<bf16_t, 2, 2, 2, 2, 4> DmaMid;
+// 256 x 128, 8 waves (4 x 2, each 64 x 64), ring of 3 stages of 48 KB with 64 k each: one workgroup per CU, and a load of a
+// k-contiguous X covers 128 contiguous bytes per row.  For launches that it fits into one pass over the chip while
+// 256 x 256 tiles would leave half of it idle: 4 x [2432 rows, 30522 -> 768] input gradient 502 us, 128 x 128 tiles 670,
+// 256 x 256 tiles 634; 2 x [2048, 2048 -> 2048] forward 37 | 43 | 47, input gradient 39 | 39 | 43.
+typedef Dma<bf16_t, 4, 2, 2, 2, 3, 64> DmaWide;
+// What the direct-to-LDS kernels address: an operand with k as the slow index is read from the tile's first element with
+// 32-bit offsets, so its K x ld bytes must stay below 2 GiB.  (A k-contiguous operand may have any K: the last chunk's
+// elements past K are cleared in LDS.)
 inline bool dma_eligible(const GemmArgs& a) {
-  if (a.dtype != GEMM_BF16) return false;
-  if ((a.x_kmajor || a.w_kmajor) && a.K % 8 != 0) return false;
-  if (!a.x_kmajor && (long)a.K * a.ldx * 2 >= 0x7fffffffL) return false;
-  if (!a.w_kmajor && (long)a.K * a.ldw * 2 >= 0x7fffffffL) return false;
+  const long sz = a.dtype == GEMM_F32 ? 4 : 2;
+  if (!a.x_kmajor && (long)a.K * a.ldx * sz >= 0x7fffffffL) return false;
+  if (!a.w_kmajor && (long)a.K * a.ldw * sz >= 0x7fffffffL) return false;
   return true;
 }
 
@@ -1421,12 +1800,33 @@ int split_for(const GemmArgs& a) {
   return S;
 }
 
+// Tiles that are chosen but cannot be asked for by number
+enum { TILE_SMALL = 101, TILE_SMALL_DEEP = 102, TILE_WIDE = 103 };
+typedef SmallTile<bf16_t, 16, 2> SmallBf16;
+typedef SmallTile<bf16_t, 8, 4> SmallBf16Deep;
+typedef SmallTile<float, 16, 2> SmallF32;
+
+// A choice never changes a result (every tile sums in the same order), only the time.  Measured in kernel time with the
+// tiles of every kind side by side; figures are us, small | 128x128 (| 32x128 for fp32).
 int choose_tile(const GemmArgs& a) {
   if (a.tile) return a.tile;
   auto tiles = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.G; };
   const long big = tiles(256, 256), mid = tiles(128, 128);
   if (a.M >= 192 && big >= 192) return 1;  // the big tile fills the chip
+  const bool dma = dma_eligible(a);
+  if (a.dtype == GEMM_F32) {
+    // three 32x32 tiles per CU are as fast as 32x128 ones (800 tiles: 24.5-27.5 | 61 | 25.6-27.0; 256 tiles: 15 | 76 | 30;
+    // 1024 tiles: 22.5 | 45 | 20)
+    if (dma && tiles(32, 32) <= 768) return TILE_SMALL;
+    // 128x128 tiles need one for every CU (224 tiles: 67 against 57 for 32x128; 256 tiles: 85 | 86 and 87 | 90)
+    return a.M >= 96 && mid >= 256 ? 2 : 3;
+  }
+  // About one 64x64 tile per CU: ahead of 128x128 tiles by a third up to there (256 tiles: K = 1024 9.4 | 13.4,
+  // K = 4096 26 | 35), level at 330 tiles (19-17.4 | 22.8-16.7), behind beyond (512 tiles, K = 2048: 26 | 21-24;
+  // 768 tiles 16.6 | 15).  Fewer than 96 rows would leave much of a 128-row tile empty.
+  if (dma && (tiles(64, 64) <= 320 || a.M < 96)) return a.K > 1024 ? TILE_SMALL_DEEP : TILE_SMALL;
   if (a.M >= 96 && mid >= 64) {
+    if (const long wide = tiles(256, 128); dma && a.x_kmajor && a.M >= 192 && wide >= 160 && wide <= 256) return TILE_WIDE;
     // Too few big tiles for 256 CUs: 128 x 128 tiles win while they fit in one pass over the chip (two
     // workgroups per CU); beyond that a partly filled pass of big tiles is still the faster choice.
     return (a.M >= 192 && big >= 128 && mid > 512) ? 1 : 2;
@@ -1434,15 +1834,49 @@ int choose_tile(const GemmArgs& a) {
   return 3;
 }
 
+// Weight gradient with the update: the epilogue moves 14-26 bytes per output element, the k-loop is as long as the batch.
+int choose_update_tile(const GemmArgs& a) {
+  if (a.tile) return a.tile;
+  auto tiles = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.G; };
+  const long big = tiles(256, 256);
+  const bool dma = dma_eligible(a);
+  if (a.dtype == GEMM_F32) {
+    // 32x32 tiles are ahead until the sums get short against the number of tiles (us, 32x32 | 128x128 | 32x128: 2400 tiles,
+    // K = 256 25 | 41 | 32; 2048 tiles, K = 2048 89 | 161 | 106; K = 64 14.6 | 25 | 14.5; 4096 tiles, K = 24 27 | 28 | 22)
+    const long sm = tiles(32, 32);
+    if (dma && (sm <= 1024 || (sm <= 4096 && a.K >= 64))) return TILE_SMALL;
+    if (big < 192) return 3;
+  } else {
+    // 64x64 tiles: the state of a tile is small enough to hide behind the other workgroups' k-loops (us, 64x64 | 128x128:
+    // 256 tiles, K = 1024 13 | 22; K = 4096 31 | 46; 600 tiles, K = 700 24 | 25; 2048 tiles, K = 1024 60-65 | 57-69), but
+    // a long sum wants the 128x128 tile's reuse (1024 tiles, K = 8192 119 | 104; 2048 tiles, K = 2048 84 | 77)
+    const long sm = tiles(64, 64);
+    if (dma && (sm <= 512 || (sm <= 2048 && a.K <= 1024))) return a.K > 1024 ? TILE_SMALL_DEEP : TILE_SMALL;
+  }
+  const int tile = choose_tile(a);
+  if (tile == TILE_WIDE) return 2;
+  if (tile == 1 && a.K < 2048) {
+    // With a short k-loop the state traffic of the epilogue dominates: with two workgroups per CU one streams
+    // state while the other runs its k-loop, which the 256x256 tile (one workgroup per CU) cannot do; with at most two
+    // 256x256 tiles per CU it is ahead all the same (us, 256x256 | 128x128: 256 tiles, K = 24 84 | 95, K = 256 85 | 96; 512
+    // tiles, K = 24 157 | 173, K = 128 157 | 220; 2048 tiles, K = 128 656 | 612, K = 512 731 | 628).
+    return a.dtype != GEMM_F32 && big <= 512 ? 1 : 2;
+  }
+  return tile;
+}
+
 template <typename T>
 hipError_t dispatch_update(const GemmArgs& a, const GemmUpdate& u, hipStream_t s) {
   if (const int S = split_for(a); S > 1) return run_split(a, &u, S, s);
-  int tile = choose_tile(a);
-  // With a short k-loop the state traffic of the epilogue dominates: with two workgroups per CU one streams
-  // state while the other runs its k-loop, which the 256x256 tile (one workgroup per CU) cannot do.
-  if (!a.tile && tile == 1 && a.K < 2048) tile = 2;
-  if (tile == 1 && dma_eligible(a)) return DmaBig::run_update(a, u, s);
-  if (tile == 2 && dma_eligible(a)) return DmaMid::run_update(a, u, s);
+  const int tile = choose_update_tile(a);
+  if constexpr (sizeof(T) == 2) {
+    if (tile == TILE_SMALL) return SmallBf16::run_update(a, u, s);
+    if (tile == TILE_SMALL_DEEP) return SmallBf16Deep::run_update(a, u, s);
+    if (tile == 1 && dma_eligible(a)) return DmaBig::run_update(a, u, s);
+    if (tile == 2 && dma_eligible(a)) return DmaMid::run_update(a, u, s);
+  } else {
+    if (tile == TILE_SMALL) return SmallF32::run_update(a, u, s);
+  }
   switch (tile) {
     case 1:
     case 4: return Tiles<T>::Big::run_update(a, u, s);
@@ -1456,8 +1890,15 @@ template <typename T>
 hipError_t dispatch(const GemmArgs& a, hipStream_t s) {
   if (const int S = split_for(a); S > 1) return run_split(a, nullptr, S, s);
   const int tile = choose_tile(a);
-  if (tile == 1 && dma_eligible(a)) return DmaBig::run(a, s);
-  if (tile == 2 && dma_eligible(a)) return DmaMid::run(a, s);
+  if constexpr (sizeof(T) == 2) {
+    if (tile == TILE_SMALL) return SmallBf16::run(a, s);
+    if (tile == TILE_SMALL_DEEP) return SmallBf16Deep::run(a, s);
+    if (tile == TILE_WIDE) return DmaWide::run_x(a, s);
+    if (tile == 1 && dma_eligible(a)) return DmaBig::run(a, s);
+    if (tile == 2 && dma_eligible(a)) return DmaMid::run(a, s);
+  } else {
+    if (tile == TILE_SMALL) return SmallF32::run(a, s);
+  }
   switch (tile) {
     case 1:
     case 4: return Tiles<T>::Big::run(a, s);
@@ -1481,6 +1922,10 @@ hipError_t gemm_init() {
   hipError_t e = DmaBig::attr();
   if (e != hipSuccess) return e;
   if ((e = DmaMid::attr()) != hipSuccess) return e;
+  if ((e = SmallBf16::attr()) != hipSuccess) return e;
+  if ((e = SmallBf16Deep::attr()) != hipSuccess) return e;
+  if ((e = SmallF32::attr()) != hipSuccess) return e;
+  if ((e = DmaWide::attr_x()) != hipSuccess) return e;
   e = init_tiles<bf16_t>();
   return e != hipSuccess ? e : init_tiles<float>();
 }
@@ -1495,7 +1940,7 @@ hipError_t kernels_init() {
 static hipError_t check_gemm(const GemmArgs& a, bool need_out) {
   const int E = a.dtype == GEMM_F32 ? 4 : 8;
   auto rup = [&](int v) { return (v + E - 1) / E * E; };
-  if (a.G < 1 || a.G > MAXG || a.M < 1 || a.N < 1 || a.K < 1) return hipErrorInvalidValue;
+  if (a.G < 1 || a.G > MAXG || a.M < 1 || a.N < 1 || a.K < 1 || a.tile < 0 || a.tile > 4) return hipErrorInvalidValue;
   if (a.ldx % E || a.ldw % E) return hipErrorInvalidValue;
   if (a.ldx < rup(a.x_kmajor ? a.K : a.M) || a.ldw < rup(a.w_kmajor ? a.K : a.N)) return hipErrorInvalidValue;
   if (a.ldo < a.N) return hipErrorInvalidValue;

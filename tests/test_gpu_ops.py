@@ -564,3 +564,67 @@ def test_split_weight_gradient_matches_oracle_and_ignores_tile_and_group(torch, 
     keep = keep.reshape(-1)
     for a, b in ((P1, P2), (M1, M2), (V1, V2), (W1.float(), W2.float())):
         assert np.array_equal(a.cpu().numpy()[keep], b.cpu().numpy()[keep])
+
+
+@pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
+@pytest.mark.parametrize("dtype,M,N,K,G", [
+    (1, 64, 64, 64, 2), (1, 96, 320, 320, 3), (1, 70, 40, 50, 2), (1, 33, 8, 5, 1), (1, 257, 136, 2047, 2), (1, 17, 1000, 129, 2),
+    (1, 600, 3000, 77, 3), (1, 2300, 1000, 300, 2), (0, 32, 32, 64, 2), (0, 64, 784, 768, 2), (0, 70, 40, 50, 2), (0, 33, 8, 5, 1),
+    (0, 129, 136, 1027, 2), (0, 1000, 264, 40, 3)])
+def test_chosen_tile_gives_the_bits_of_the_general_one(torch, ops, dtype, M, N, K, G, layout):
+    """Sizes at which the automatic choice takes the 64x64, 32x32 and 256x128 tiles (edges of a tile, a sum that ends inside a
+    16-byte chunk with NaN stored behind it, one stage of k and several): the same bits as the 32x128 tile, for the plain
+    product, the epilogues and the update, in any group."""
+    td = torch.float32 if dtype == 0 else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(M * 7 + N * 3 + K)
+    xk, wk = layout != "wgrad", layout == "fwd"
+
+    def mat(rows, cols, t=td):
+        x = torch.randn(rows, _ld(cols), generator=gen, device="cuda").to(t)
+        x[:, cols:] = float("nan")
+        return x
+
+    X = [mat(M, K) if xk else mat(K, M) for _ in range(G)]
+    W = [mat(N, K) if wk else mat(K, N) for _ in range(G)]
+    lds = dict(x_kmajor=int(xk), w_kmajor=int(wk), ldx=X[0].shape[1], ldw=W[0].shape[1], ldo=_ld(N))
+    side = dict(bias=[torch.randn(_ld(N), generator=gen, device="cuda") for _ in range(G)], resid=[mat(M, N) for _ in range(G)],
+                gate=[mat(M, N) for _ in range(G)])
+    combos = {"fwd": [(), ("bias", "pre", "act"), ("bias", "resid")], "dgrad": [(), ("gate",), ("gate", "resid")], "wgrad": [()]}[layout]
+    for combo in combos:
+        kw = {k: side[k] for k in combo if k in side}
+        if "resid" in kw:
+            kw["ldr"] = _ld(N)
+        if "gate" in kw:
+            kw["ldg"] = _ld(N)
+        if "act" in combo or "gate" in combo:
+            kw["act"] = ops.EPI_GELU
+        got = {}
+        for tile, n in ((0, G), (3, G), (0, 1)):
+            out = [torch.zeros(M, _ld(N), device="cuda", dtype=td if combo else torch.float32) for _ in range(n)]
+            pre = [torch.zeros(M, _ld(N), device="cuda", dtype=td) for _ in range(n)] if "pre" in combo else None
+            rs = [torch.zeros(M, device="cuda") for _ in range(n)] if layout == "wgrad" else None
+            one = {k: v[:n] if isinstance(v, list) else v for k, v in kw.items()}
+            ops.hydra_op_gemm(dtype, M, N, K, X[:n], W[:n], out, tile=tile, out_f32=not combo, pre=pre, rowsum=rs, **lds, **one)
+            got[tile, n] = [t[0][:, :N].float() for t in (out, pre) if t is not None] + ([rs[0]] if rs else [])
+        for key, res in got.items():
+            for a, b in zip(res, got[3, G]):
+                assert torch.equal(a, b), (layout, combo, key)
+    if layout == "wgrad" and N % 8 == 0:
+        st = [[mat(M, N, torch.float32).nan_to_num() for _ in range(G)] for _ in range(3)]
+        st[2] = [t.abs() for t in st[2]]
+        got = {}
+        for tile in (0, 3):
+            p, m, v = ([t.clone() for t in u] for u in st)
+            w16 = [torch.zeros(M, N, device="cuda", dtype=torch.bfloat16) for _ in range(G)]
+            rs = [torch.zeros(M, device="cuda") for _ in range(G)]
+            ops.hydra_op_gemm_update(dtype, M, N, K, X, W, 1, p, m, v, w16, [(1e-3, 0.9, 0.999, 1e-8, 1.5, 1.2)] * G, tile=tile,
+                                     rowsum=rs, ldx=lds["ldx"], ldw=lds["ldw"], ldo=N)
+            got[tile] = p + m + v + w16 + rs
+        assert all(torch.equal(a, b) for a, b in zip(got[0], got[3]))
+
+
+def test_unknown_tile_numbers_are_refused(torch, ops):
+    x = torch.zeros(64, 64, device="cuda")
+    for tile in (-1, 5, 101, 102, 103):
+        with pytest.raises(Exception):
+            ops.hydra_op_gemm(0, 64, 64, 64, [x], [x], [torch.zeros_like(x)], x_kmajor=1, w_kmajor=1, ldx=64, ldw=64, ldo=64, tile=tile)
