@@ -435,16 +435,19 @@ __device__ __forceinline__ void update_bands(f32x16 (&acc)[FM][FN], float* patch
   }
 }
 
-// Epilogue of a wave that stores its fp32 sums as they are (a gradient, or a partial sum of a split one) and whose
-// block lies inside the matrix: 4 consecutive columns per lane in two rows, so that each 16-byte store instruction of
-// the wave covers contiguous row segments; no tests per element.
-template <int FM, int FN>
-__device__ __forceinline__ void plain_f32_bands(f32x16 (&acc)[FM][FN], float* patch, float* out, size_t ldo, int mrow0,
-                                                int ncol0, int lane) {
+// Epilogue of a wave that stores its fp32 sums as they are (a gradient, or a partial sum of a split one) or with a bias
+// (logits) and whose block lies inside the matrix: 4 consecutive columns per lane in two rows, so that each 16-byte
+// store instruction of the wave covers contiguous row segments; no tests per element.  Logits are written once and read
+// by a later launch: streaming stores.  With a bias, 4 x [2432, 768 -> 30522] through the general path: 705 us, here 552.
+template <int FM, int FN, bool BIAS>
+__device__ __forceinline__ void plain_f32_bands(f32x16 (&acc)[FM][FN], float* patch, float* out, const float* bias, size_t ldo,
+                                                int mrow0, int ncol0, int lane) {
   constexpr int SP = FN * 32 + 4, LPR = FN * 4, RPP = 64 / LPR, LPR4 = FN * 8, RPH = 64 / LPR4;
   const int lrow = lane & 31, lgrp = lane >> 5;
   const int c = (lane % LPR4) * 4, rl = lane / LPR4;
   float* const o = out + (size_t)(mrow0 + rl) * ldo + ncol0 + c;
+  f32x4 bv = {0.f, 0.f, 0.f, 0.f};
+  if (BIAS) bv = *reinterpret_cast<const f32x4*>(bias + ncol0 + c);
 #pragma unroll
   for (int i = 0; i < FM; ++i) {
 #pragma unroll
@@ -459,7 +462,13 @@ __device__ __forceinline__ void plain_f32_bands(f32x16 (&acc)[FM][FN], float* pa
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf) {
         const int r = p * RPP + hf * RPH;
-        *reinterpret_cast<float4*>(o + (size_t)(i * 32 + r) * ldo) = *reinterpret_cast<const float4*>(&patch[(r + rl) * SP + c]);
+        f32x4 v = *reinterpret_cast<const f32x4*>(&patch[(r + rl) * SP + c]);
+        if (BIAS) {
+          v += bv;
+          __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(o + (size_t)(i * 32 + r) * ldo));
+        } else {
+          *reinterpret_cast<f32x4*>(o + (size_t)(i * 32 + r) * ldo) = v;
+        }
       }
     wave_lds_sync();
   }
@@ -578,8 +587,10 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[FM][FN], float* patc
   const bool vec4_ok = a.ldo % 4 == 0 && (reinterpret_cast<uintptr_t>(a.out[g]) & 15) == 0 && out_off % 4 == 0 &&
                       (reinterpret_cast<uintptr_t>(bias) & 15) == 0;
   if constexpr (!UPD) {
-    if (plain_f32 && !bias && vec4_ok && mrow0 + FM * 32 <= a.M && ncol0 + FN * 32 <= a.N) {
-      plain_f32_bands<FM, FN>(acc, patch, static_cast<float*>(a.out[g]) + out_off, (size_t)a.ldo, mrow0, ncol0, lane);
+    if (plain_f32 && vec4_ok && mrow0 + FM * 32 <= a.M && ncol0 + FN * 32 <= a.N) {
+      float* const o = static_cast<float*>(a.out[g]) + out_off;
+      if (bias) plain_f32_bands<FM, FN, true>(acc, patch, o, bias, (size_t)a.ldo, mrow0, ncol0, lane);
+      else plain_f32_bands<FM, FN, false>(acc, patch, o, nullptr, (size_t)a.ldo, mrow0, ncol0, lane);
       return;
     }
   }

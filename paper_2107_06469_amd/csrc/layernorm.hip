@@ -5,16 +5,17 @@
 //             dgamma = sum_rows dy*xhat; dbeta = sum_rows dy.
 // One wavefront owns a row (in the backward pass only up to 1024 elements; wider rows are shared by the four
 // waves of a workgroup): each lane keeps its 16-byte chunks of the row in registers, statistics are
-// butterfly reductions over the 64 lanes (fixed order).  The column sums of the backward pass are
+// butterfly reductions over the 64 lanes (wave_math.h, fixed order).  The column sums of the backward pass are
 // accumulated per workgroup over a fixed range of rows, written as partial sums, and added over
 // workgroups in index order by a second kernel: no atomics, so results do not depend on timing.
 #include "kernels.h"
+#include "wave_math.h"
 
 namespace hydra {
 namespace {
 
 // MAXC = 8-element chunks a lane may own: d <= 8*64*MAXC (2 -> 1024, 4 -> 2048, 8 -> 4096)
-constexpr int LN_ROWS_PER_WG = 64;  // rows per workgroup in the backward pass (4 waves x 16 rows)
+constexpr int LN_ROWS_PER_WG = 64;  // rows per workgroup in the backward pass
 // Rows wider than this are taken by a whole workgroup at a time (ln_bwd_wide_kernel), 32 rows per workgroup.
 constexpr int LN_WAVE_ROW_MAX = 1024;
 constexpr int LN_WIDE_ROWS_PER_WG = 32;
@@ -48,6 +49,21 @@ __device__ __forceinline__ void ld8<bf16_t>(const bf16_t* p, float (&v)[8]) {
     v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
   }
 }
+// the 16-byte pieces of 8 elements as they lie in memory -> 8 floats
+template <typename T>
+__device__ __forceinline__ void unpack8(const uint4 (&raw)[sizeof(T) == 2 ? 1 : 2], float (&v)[8]) {
+  if constexpr (sizeof(T) == 2) {
+    const uint32_t w[4] = {raw[0].x, raw[0].y, raw[0].z, raw[0].w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      v[2 * q] = __uint_as_float(w[q] << 16);
+      v[2 * q + 1] = __uint_as_float(w[q] & 0xffff0000u);
+    }
+  } else {
+    v[0] = __uint_as_float(raw[0].x); v[1] = __uint_as_float(raw[0].y); v[2] = __uint_as_float(raw[0].z); v[3] = __uint_as_float(raw[0].w);
+    v[4] = __uint_as_float(raw[1].x); v[5] = __uint_as_float(raw[1].y); v[6] = __uint_as_float(raw[1].z); v[7] = __uint_as_float(raw[1].w);
+  }
+}
 template <typename T>
 __device__ __forceinline__ void st8(T* p, const float (&v)[8]);
 template <>
@@ -63,72 +79,105 @@ __device__ __forceinline__ void st8<bf16_t>(bf16_t* p, const float (&v)[8]) {
   *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-template <typename T, int LN_MAXC>
+// R = rows per wave.  Their loads are all issued before the first is reduced, and gamma and beta (fp32: four times the bytes of a
+// 16-bit row) are read once for the R rows.  A row's result does not depend on R.  Four rows (two of fp32) where that still
+// leaves every SIMD eight waves: 4 x [16384, 768] bf16 49 -> 34 us (5.9 TB/s); fewer rows stay one to a wave.
+template <typename T, int LN_MAXC, int R>
 __global__ __launch_bounds__(256) void ln_fwd_kernel(const LnArgs a) {
   const int g = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int row = blockIdx.x * 4 + wave;
-  if (row >= a.rows) return;
-  const T* x = static_cast<const T*>(a.x[g]) + (size_t)row * a.ld;
-  T* y = static_cast<T*>(a.y[g]) + (size_t)row * a.ld;
+  const int row0 = (blockIdx.x * 4 + wave) * R;
+  if (row0 >= a.rows) return;
+  const int nrow = min(R, a.rows - row0);
+  const T* x = static_cast<const T*>(a.x[g]) + (size_t)row0 * a.ld;
+  T* y = static_cast<T*>(a.y[g]) + (size_t)row0 * a.ld;
   const int nch = a.d >> 3;
-  float v[LN_MAXC][8];
-  float s = 0.f;
+  constexpr int RW = sizeof(T) == 2 ? 1 : 2;  // 16-byte pieces per 8 elements
+  uint4 raw[R][LN_MAXC][RW];
 #pragma unroll
-  for (int i = 0; i < LN_MAXC; ++i) {
-    const int c = lane + 64 * i;
-    if (c < nch) {
-      ld8<T>(x + 8 * c, v[i]);
+  for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) s += v[i][e];
-    }
-  }
-  const float mu = wave_sum(s) / (float)a.d;
-  float q = 0.f;
+    for (int i = 0; i < LN_MAXC; ++i) {
+      const int c = lane + 64 * i;
 #pragma unroll
-  for (int i = 0; i < LN_MAXC; ++i) {
-    const int c = lane + 64 * i;
-    if (c < nch) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float t = v[i][e] - mu;
-        q += t * t;
+      for (int q = 0; q < RW; ++q) {
+        raw[r][i][q] = make_uint4(0, 0, 0, 0);
+        if (c < nch && r < nrow) raw[r][i][q] = reinterpret_cast<const uint4*>(x + (size_t)r * a.ld)[c * RW + q];
       }
     }
-  }
-  const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)a.d + a.eps);
   const float* gamma = a.gamma[g];
   const float* beta = a.beta[g];
+  float ga[LN_MAXC][8], be[LN_MAXC][8];
 #pragma unroll
   for (int i = 0; i < LN_MAXC; ++i) {
     const int c = lane + 64 * i;
     if (c < nch) {
-      float ga[8], be[8], o[8];
-      ld8<float>(gamma + 8 * c, ga);
-      ld8<float>(beta + 8 * c, be);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] = (v[i][e] - mu) * rstd * ga[e] + be[e];
-      st8<T>(y + 8 * c, o);
+      ld8<float>(gamma + 8 * c, ga[i]);
+      ld8<float>(beta + 8 * c, be[i]);
     }
   }
-  if (lane == 0) {
-    a.mean[g][row] = mu;
-    a.rstd[g][row] = rstd;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (r >= nrow) break;
+    float v[LN_MAXC][8];
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < LN_MAXC; ++i) {
+      unpack8<T>(raw[r][i], v[i]);
+      if (lane + 64 * i < nch) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += v[i][e];
+      }
+    }
+    const float mu = wave_sum(s) / (float)a.d;
+    float q = 0.f;
+#pragma unroll
+    for (int i = 0; i < LN_MAXC; ++i)
+      if (lane + 64 * i < nch) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float t = v[i][e] - mu;
+          q += t * t;
+        }
+      }
+    const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)a.d + a.eps);
+#pragma unroll
+    for (int i = 0; i < LN_MAXC; ++i) {
+      const int c = lane + 64 * i;
+      if (c < nch) {
+        float o[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = (v[i][e] - mu) * rstd * ga[i][e] + be[i][e];
+        st8<T>(y + (size_t)r * a.ld + 8 * c, o);
+      }
+    }
+    if (lane == 0) {
+      a.mean[g][row0 + r] = mu;
+      a.rstd[g][row0 + r] = rstd;
+    }
   }
 }
 
-// dx and per-workgroup partial column sums, rows of up to 1024 elements.  Workgroup b owns rows [b*64, b*64+64); wave w takes rows
-// b*64 + w, +4, +8, ...; partial sums go to part[g][b][2][d].
-template <typename T, int LN_MAXC>
-__global__ __launch_bounds__(256) void ln_bwd_kernel(const LnBwdArgs a) {
-  extern __shared__ float red[];  // [4][2][d]
+// dx and per-workgroup partial column sums, rows of up to 1024 elements.  Workgroup b owns rows [b*64, b*64+64); wave w of NW takes
+// rows b*64 + w, + NW, ...; partial sums go to part[g][b][2][d].
+// A wave takes its rows in batches of NB: all loads of a batch (x, dy, the additive term, the statistics) are issued
+// before its first row is reduced, so that the batch costs one round trip to memory.  Small launches are bound by a
+// wave's serial rows, large ones by memory; 4 waves of 16 rows, the next row's loads ahead of the current one's
+// reduction, against this form (us): 4 x [1024, 256] bf16 18.1 | 8.7, 4 x [4096, 512] 22 | 13.8, 4 x [1024, 768] 20.7 | 14.5,
+// 4 x [16384, 512] 51 | 46, 4 x [16384, 768] 87 | 86 (4.7 TB/s: a device copy's rate), fp32 165 | 161.
+template <typename T, int LN_MAXC, int NW, int NB>
+__global__ __launch_bounds__(NW * 64) void ln_bwd_kernel(const LnBwdArgs a) {
+  extern __shared__ float red[];  // [NW][2][d]
   const int g = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nch = a.d >> 3;
+  constexpr int RW = sizeof(T) == 2 ? 1 : 2;  // 16-byte pieces per 8 elements
+  static_assert(LN_ROWS_PER_WG % (NW * NB) == 0, "whole batches");
+  const int row0 = blockIdx.x * LN_ROWS_PER_WG + wave;
+  const T* X = static_cast<const T*>(a.x[g]);
+  const T* DY = static_cast<const T*>(a.dy[g]);
+  const T* ADD = static_cast<const T*>(a.add[g]);
+  T* DX = static_cast<T*>(a.dx[g]);
+  const float* mean = a.mean[g];
+  const float* rs = a.rstd[g];
   const float* gamma = a.gamma[g];
   float ga[LN_MAXC][8], sg[LN_MAXC][8], sb[LN_MAXC][8];
 #pragma unroll
@@ -138,128 +187,88 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const LnBwdArgs a) {
     for (int e = 0; e < 8; ++e) sg[i][e] = sb[i][e] = ga[i][e] = 0.f;
     if (c < nch) ld8<float>(gamma + 8 * c, ga[i]);
   }
-  const int row0 = blockIdx.x * LN_ROWS_PER_WG;
-  // A wave's rows are software-pipelined: the loads of its next row (x, dy, the additive term, the statistics) are
-  // issued before the current row is reduced, and stay in flight as raw registers until that row's turn.
-  // Only where the extra registers cost no spill and little occupancy: 16-bit rows of at most 1024 elements.  The
-  // other shapes fetch each row at its own turn (and its additive term after the reductions).
-  constexpr bool PF = sizeof(T) == 2 && LN_MAXC <= 2;
-  constexpr int RW = sizeof(T) == 2 ? 1 : 2;  // 16-byte pieces per 8 elements
-  uint4 nx[LN_MAXC][RW], ndy[LN_MAXC][RW], nadd[LN_MAXC][RW];
-  float nmu = 0.f, nrstd = 0.f;
-  auto fetch_row = [&](int row) {
-    const uint4* x = reinterpret_cast<const uint4*>(static_cast<const T*>(a.x[g]) + (size_t)row * a.ld);
-    const uint4* dy = reinterpret_cast<const uint4*>(static_cast<const T*>(a.dy[g]) + (size_t)row * a.ld);
-    const uint4* add = a.add[g] ? reinterpret_cast<const uint4*>(static_cast<const T*>(a.add[g]) + (size_t)row * a.ld) : nullptr;
+  for (int r0 = 0; r0 < LN_ROWS_PER_WG; r0 += NW * NB) {
+    if (row0 + r0 >= a.rows) break;
+    uint4 rx[NB][LN_MAXC][RW], rdy[NB][LN_MAXC][RW], radd[NB][LN_MAXC][RW];
+    float mu[NB], rstd[NB];
 #pragma unroll
-    for (int i = 0; i < LN_MAXC; ++i) {
-      const int c = lane + 64 * i;
-      if (c < nch) {
+    for (int b = 0; b < NB; ++b) {
+      const int row = row0 + r0 + b * NW;
+      const bool live = row < a.rows;
+      const size_t o = (size_t)(live ? row : row0) * a.ld;
+      mu[b] = live ? mean[row] : 0.f;
+      rstd[b] = live ? rs[row] : 0.f;
 #pragma unroll
-        for (int q = 0; q < RW; ++q) {
-          nx[i][q] = x[c * RW + q];
-          ndy[i][q] = dy[c * RW + q];
-          if (PF && add) nadd[i][q] = add[c * RW + q];
-        }
-      }
-    }
-    nmu = a.mean[g][row];
-    nrstd = a.rstd[g][row];
-  };
-  auto unpack = [&](const uint4 (&raw)[RW], float (&v)[8]) {
-    if constexpr (sizeof(T) == 2) {
-      const uint32_t w[4] = {raw[0].x, raw[0].y, raw[0].z, raw[0].w};
+      for (int i = 0; i < LN_MAXC; ++i) {
+        const int c = lane + 64 * i;
+        if (live && c < nch) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        v[2 * q] = __uint_as_float(w[q] << 16);
-        v[2 * q + 1] = __uint_as_float(w[q] & 0xffff0000u);
-      }
-    } else {
-      v[0] = __uint_as_float(raw[0].x); v[1] = __uint_as_float(raw[0].y); v[2] = __uint_as_float(raw[0].z); v[3] = __uint_as_float(raw[0].w);
-      v[4] = __uint_as_float(raw[RW - 1].x); v[5] = __uint_as_float(raw[RW - 1].y); v[6] = __uint_as_float(raw[RW - 1].z); v[7] = __uint_as_float(raw[RW - 1].w);
-    }
-  };
-  if (PF && row0 + wave < a.rows) fetch_row(row0 + wave);
-  for (int r = wave; r < LN_ROWS_PER_WG; r += 4) {
-    const int row = row0 + r;
-    if (row >= a.rows) break;
-    // this row's values move out of the prefetch registers; then the next row's loads are issued
-    uint4 cx[LN_MAXC][RW], cdy[LN_MAXC][RW], cadd[LN_MAXC][RW];
-#pragma unroll
-    for (int i = 0; i < LN_MAXC; ++i)
-#pragma unroll
-      for (int q = 0; q < RW; ++q) { cx[i][q] = nx[i][q]; cdy[i][q] = ndy[i][q]; cadd[i][q] = nadd[i][q]; }
-    const float mu = PF ? nmu : a.mean[g][row], rstd = PF ? nrstd : a.rstd[g][row];
-    if (PF && r + 4 < LN_ROWS_PER_WG && row + 4 < a.rows) fetch_row(row + 4);
-    float xh[LN_MAXC][8], gg[LN_MAXC][8];
-    float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-    for (int i = 0; i < LN_MAXC; ++i) {
-      const int c = lane + 64 * i;
-      if (c < nch) {
-        float xv[8], dv[8];
-        if constexpr (PF) {
-          unpack(cx[i], xv);
-          unpack(cdy[i], dv);
-        } else {
-          ld8<T>(static_cast<const T*>(a.x[g]) + (size_t)row * a.ld + 8 * c, xv);
-          ld8<T>(static_cast<const T*>(a.dy[g]) + (size_t)row * a.ld + 8 * c, dv);
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          xh[i][e] = (xv[e] - mu) * rstd;
-          gg[i][e] = dv[e] * ga[i][e];
-          s1 += gg[i][e];
-          s2 += gg[i][e] * xh[i][e];
-          sg[i][e] += dv[e] * xh[i][e];
-          sb[i][e] += dv[e];
-        }
-      }
-    }
-    const float c1 = wave_sum(s1) / (float)a.d, c2 = wave_sum(s2) / (float)a.d;
-    T* dx = static_cast<T*>(a.dx[g]) + (size_t)row * a.ld;
-    const bool add = a.add[g] != nullptr;
-#pragma unroll
-    for (int i = 0; i < LN_MAXC; ++i) {
-      const int c = lane + 64 * i;
-      if (c < nch) {
-        float o[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = rstd * (gg[i][e] - c1 - xh[i][e] * c2);
-        if (add) {
-          float av[8];
-          if constexpr (PF) {
-            unpack(cadd[i], av);
-          } else {
-            ld8<T>(static_cast<const T*>(a.add[g]) + (size_t)row * a.ld + 8 * c, av);
+          for (int q = 0; q < RW; ++q) {
+            rx[b][i][q] = reinterpret_cast<const uint4*>(X + o)[c * RW + q];
+            rdy[b][i][q] = reinterpret_cast<const uint4*>(DY + o)[c * RW + q];
+            if (ADD) radd[b][i][q] = reinterpret_cast<const uint4*>(ADD + o)[c * RW + q];
           }
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] += av[e];
         }
-        st8<T>(dx + 8 * c, o);
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int row = row0 + r0 + b * NW;
+      if (row >= a.rows) break;
+      float xh[LN_MAXC][8], gg[LN_MAXC][8];
+      float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+      for (int i = 0; i < LN_MAXC; ++i) {
+        if (lane + 64 * i < nch) {
+          float xv[8], dv[8];
+          unpack8<T>(rx[b][i], xv);
+          unpack8<T>(rdy[b][i], dv);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            xh[i][e] = (xv[e] - mu[b]) * rstd[b];
+            gg[i][e] = dv[e] * ga[i][e];
+            s1 += gg[i][e];
+            s2 += gg[i][e] * xh[i][e];
+            sg[i][e] += dv[e] * xh[i][e];
+            sb[i][e] += dv[e];
+          }
+        }
+      }
+      const float c1 = wave_sum(s1) / (float)a.d, c2 = wave_sum(s2) / (float)a.d;
+#pragma unroll
+      for (int i = 0; i < LN_MAXC; ++i) {
+        const int c = lane + 64 * i;
+        if (c < nch) {
+          float o[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o[e] = rstd[b] * (gg[i][e] - c1 - xh[i][e] * c2);
+          if (ADD) {
+            float av[8];
+            unpack8<T>(radd[b][i], av);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] += av[e];
+          }
+          st8<T>(DX + (size_t)row * a.ld + 8 * c, o);
+        }
       }
     }
   }
-  // the four waves' partial sums are added in wave order
+  // the waves' partial sums are added in wave order
 #pragma unroll
   for (int i = 0; i < LN_MAXC; ++i) {
     const int c = lane + 64 * i;
     if (c < nch) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        red[(wave * 2 + 0) * a.d + 8 * c + e] = sg[i][e];
-        red[(wave * 2 + 1) * a.d + 8 * c + e] = sb[i][e];
-      }
+      st8<float>(&red[(wave * 2 + 0) * a.d + 8 * c], sg[i]);
+      st8<float>(&red[(wave * 2 + 1) * a.d + 8 * c], sb[i]);
     }
   }
   __syncthreads();
   float* part = a.part[g] + (size_t)blockIdx.x * 2 * a.d;
-  for (int j = threadIdx.x; j < 2 * a.d; j += 256) {
-    const int which = j / a.d, col = j % a.d;
+  for (int j = threadIdx.x; j < 2 * a.d; j += NW * 64) {  // red is [wave][2 d]
     float t = 0.f;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) t += red[(w * 2 + which) * a.d + col];
-    part[which * a.d + col] = t;
+    for (int w = 0; w < NW; ++w) t += red[w * 2 * a.d + j];
+    part[j] = t;
   }
 }
 
@@ -306,19 +315,6 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const LnBwdArgs a) {
     nmu = a.mean[g][row];
     nrstd = a.rstd[g][row];
   };
-  auto unpack = [&](const uint4 (&raw)[RW], float (&v)[8]) {
-    if constexpr (sizeof(T) == 2) {
-      const uint32_t w[4] = {raw[0].x, raw[0].y, raw[0].z, raw[0].w};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        v[2 * q] = __uint_as_float(w[q] << 16);
-        v[2 * q + 1] = __uint_as_float(w[q] & 0xffff0000u);
-      }
-    } else {
-      v[0] = __uint_as_float(raw[0].x); v[1] = __uint_as_float(raw[0].y); v[2] = __uint_as_float(raw[0].z); v[3] = __uint_as_float(raw[0].w);
-      v[4] = __uint_as_float(raw[RW - 1].x); v[5] = __uint_as_float(raw[RW - 1].y); v[6] = __uint_as_float(raw[RW - 1].z); v[7] = __uint_as_float(raw[RW - 1].w);
-    }
-  };
   const int row0 = blockIdx.x * LN_WIDE_ROWS_PER_WG;
   const int nrow = min(LN_WIDE_ROWS_PER_WG, a.rows - row0);  // the same for every thread: the barriers below are uniform
   if (PF && nrow > 0) fetch_row(row0);
@@ -339,8 +335,8 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const LnBwdArgs a) {
       const int c = tid + 256 * i;
       if (c < nch) {
         float xv[8], dv[8];
-        unpack(cx[i], xv);
-        unpack(cdy[i], dv);
+        unpack8<T>(cx[i], xv);
+        unpack8<T>(cdy[i], dv);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           xh[i][e] = (xv[e] - mu) * rstd;
@@ -378,7 +374,7 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const LnBwdArgs a) {
         for (int e = 0; e < 8; ++e) o[e] = rstd * (gg[i][e] - c1 - xh[i][e] * c2);
         if (has_add) {
           float av[8];
-          unpack(cadd[i], av);
+          unpack8<T>(cadd[i], av);
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[e] += av[e];
         }
@@ -431,16 +427,16 @@ static bool ln_shape_ok(int G, int rows, int d, int ld) {
   return G >= 1 && G <= MAXG && rows >= 1 && d >= 8 && !(d & 7) && d <= 4096 && ld >= d && !(ld & 7);
 }
 
-template <typename T, int C>
+template <typename T, int C, int R>
 static hipError_t ln_fwd_run(const LnArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((ln_fwd_kernel<T, C>), dim3((a.rows + 3) / 4, a.G), dim3(256), 0, s, a);
+  hipLaunchKernelGGL((ln_fwd_kernel<T, C, R>), dim3((a.rows + 4 * R - 1) / (4 * R), a.G), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 template <typename T>
 static hipError_t ln_fwd_pick(const LnArgs& a, hipStream_t s) {
-  if (a.d <= 1024) return ln_fwd_run<T, 2>(a, s);
-  if (a.d <= 2048) return ln_fwd_run<T, 4>(a, s);
-  return ln_fwd_run<T, 8>(a, s);
+  if (a.d <= 1024) return (long)a.rows * a.G >= 32768 ? ln_fwd_run<T, 2, sizeof(T) == 2 ? 4 : 2>(a, s) : ln_fwd_run<T, 2, 1>(a, s);
+  if (a.d <= 2048) return ln_fwd_run<T, 4, 1>(a, s);
+  return ln_fwd_run<T, 8, 1>(a, s);
 }
 
 hipError_t launch_ln_fwd(const LnArgs& a, hipStream_t s) {
@@ -452,8 +448,10 @@ template <typename T>
 static hipError_t ln_bwd_pick(const LnBwdArgs& a, hipStream_t s) {
   const dim3 grid(ln_bwd_blocks(a.rows, a.d), a.G);
   if (a.d <= LN_WAVE_ROW_MAX) {
-    const size_t lds = (size_t)4 * 2 * a.d * sizeof(float);
-    hipLaunchKernelGGL((ln_bwd_kernel<T, 2>), grid, dim3(256), lds, s, a);
+    // 64 rows over 16 waves (one batch each) where a lane owns at most 8 columns, over 8 waves beyond (the cross-wave sums
+    // need NW x 8 d bytes of LDS: 64 KB either way)
+    if (a.d <= 512) hipLaunchKernelGGL((ln_bwd_kernel<T, 1, 16, sizeof(T) == 2 ? 4 : 2>), grid, dim3(1024), (size_t)16 * 8 * a.d, s, a);
+    else hipLaunchKernelGGL((ln_bwd_kernel<T, 2, 8, 2>), grid, dim3(512), (size_t)8 * 8 * a.d, s, a);
   } else if (a.d <= 2048) {
     hipLaunchKernelGGL((ln_bwd_wide_kernel<T, 1>), grid, dim3(256), 0, s, a);
   } else {
@@ -470,7 +468,7 @@ hipError_t launch_ln_bwd(const LnBwdArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// nothing to set up: the wave-per-row kernel needs at most 32 KB of LDS
+// nothing to set up: the wave-per-row kernel needs at most 64 KB of LDS
 hipError_t ln_init() { return hipSuccess; }
 
 }  // namespace hydra

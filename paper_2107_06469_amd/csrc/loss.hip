@@ -9,6 +9,7 @@
 #include <stdint.h>
 
 #include "kernels.h"
+#include "wave_math.h"
 
 namespace hydra {
 namespace {
@@ -16,17 +17,6 @@ namespace {
 __device__ __forceinline__ bf16_t f2bf(float v) {
   __bf16 h = (__bf16)v;
   return __builtin_bit_cast(bf16_t, h);
-}
-
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
 }
 
 template <typename T>

@@ -192,3 +192,35 @@ def test_embedding_forward_and_backward(torch, ops, dtype):
         assert np.all(np.abs(xs[g].double().cpu().numpy().reshape(B, S, d) - x) <= tol * np.abs(x) + 1e-7)
         assert np.allclose(dtoks[g].cpu().numpy(), dtok, rtol=1e-5, atol=1e-5)
         assert np.allclose(dposs[g].cpu().numpy(), dpos, rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("G,rows,d", [(2, 63, 512), (2, 129, 520), (1, 64, 8), (3, 65, 1024), (1, 1, 504), (4, 8193, 128), (16, 2051, 1016)])
+def test_layernorm_row_batches(torch, ops, dtype, G, rows, d):
+    """Row counts around a workgroup's 64 rows and a wave's batch, widths around the 512- and 1024-column limits, and launches large
+    enough for several rows per wave in the forward pass, against fp64 (the column sums to 1e-5 of their terms' size)."""
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(rows * 31 + d)
+    mk = lambda *sh: torch.randn(*sh, generator=gen, device="cuda")  # noqa: E731
+    x, dy, add = ([mk(rows, d).to(t) for _ in range(G)] for _ in range(3))
+    gamma, beta = [1 + 0.1 * mk(d) for _ in range(G)], [0.1 * mk(d) for _ in range(G)]
+    y, dx = ([torch.zeros_like(u) for u in x] for _ in range(2))
+    mean, rstd = ([torch.zeros(rows, device="cuda") for _ in range(G)] for _ in range(2))
+    dg, db = ([torch.zeros(d, device="cuda") for _ in range(G)] for _ in range(2))
+    part = [torch.zeros(ops.hydra_op_layernorm_part_floats(rows, d), device="cuda") for _ in range(G)]
+    D = ops.BF16 if dtype == "bf16" else ops.F32
+    ops.hydra_op_layernorm_fwd(D, rows, d, d, 1e-5, x, y, gamma, beta, mean, rstd)
+    ops.hydra_op_layernorm_bwd(D, rows, d, d, x, dy, add, dx, gamma, mean, rstd, part, dg, db)
+    tol = 2.0 ** -8 if dtype == "bf16" else 2e-6
+    for g in range(G):
+        xd, dyd = x[g].double(), dy[g].double()
+        mu = xd.mean(1, keepdim=True)
+        rs = ((xd - mu).square().mean(1, keepdim=True) + 1e-5).rsqrt()
+        xh, gg = (xd - mu) * rs, dyd * gamma[g].double()
+        want_y = xh * gamma[g].double() + beta[g].double()
+        want_dx = rs * (gg - gg.mean(1, keepdim=True) - xh * (gg * xh).mean(1, keepdim=True)) + add[g].double()
+        for got, want in ((y[g], want_y), (dx[g], want_dx)):
+            err = (got.double() - want).abs()
+            assert (err <= tol * (want.abs() + want.abs().mean())).all(), err.max()
+        for got, term in ((dg[g], dyd * xh), (db[g], dyd)):
+            assert ((got.double() - term.sum(0)).abs() <= 1e-5 * term.abs().sum(0) + 1e-6).all()
