@@ -30,6 +30,7 @@
 
 #include "act_math.h"
 #include "kernels.h"
+#include "lds_dma.h"
 #include "optim_math.h"
 
 namespace hydra {
@@ -917,26 +918,6 @@ __device__ __forceinline__ int swz4(int row) { return ((row >> 2) & 3) ^ (row & 
 // chunk permutation of a 128-byte row (8 chunks): 16 consecutive rows, read at one chunk index, spread over all banks
 __device__ __forceinline__ int swz8(int row) { return ((row >> 1) & 3) | (((row & 1) ^ ((row >> 3) & 1)) << 2); }
 
-// 128-bit buffer descriptor (base, stride 0, size in bytes, raw dword format) for bytes [first, total) of a matrix;
-// reads beyond it return zero
-__device__ __forceinline__ u32x4 rsrc_words(const void* base, long first, long total) {
-  long rem = total - first;
-  rem = rem < 0 ? 0 : (rem > 0x7fffffffL ? 0x7fffffffL : rem);
-  const uint64_t p = (uint64_t)(uintptr_t)base + (uint64_t)(rem > 0 ? first : 0);
-  u32x4 r;
-  r.x = __builtin_amdgcn_readfirstlane((unsigned)p);
-  r.y = __builtin_amdgcn_readfirstlane((unsigned)(p >> 32) & 0xffffu);
-  r.z = __builtin_amdgcn_readfirstlane((unsigned)rem);
-  r.w = 0x00020000u;
-  return r;
-}
-// One wave-wide load of 16 bytes per lane from a buffer into LDS: lane l's bytes land at lds_addr + 16 l (lds_addr is
-// a byte address inside the workgroup's LDS, uniform over the wave).  The compiler does not see the LDS write:
-// callers order it against LDS reads with an explicit vmcnt wait and a barrier.
-__device__ __forceinline__ void load_to_lds_b128(u32x4 rs, unsigned lds_addr, unsigned voff) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voff), "s"(rs) : "m0");
-}
-
 // One operand tile of ROWS rows in the ring: what a lane contributes to the direct loads of a sub-tile and where it
 // reads its MFMA fragments.  NW = waves of the workgroup; load i of wave w fills slots [(i*NW + w)*64, +64).
 // BKW = k per sub-tile: four 16-byte chunks per k-contiguous row (32 bf16, 16 fp32), or for bf16 eight (64: a row is
@@ -1030,7 +1011,7 @@ struct RingOperand {
 // BK = 64 (with NS = 2): sub-tiles of 64 k, so that a load of a k-contiguous operand covers 128 contiguous bytes per
 // row; one barrier per sub-tile, before its last MFMA step, and the loads of sub-tile t+2 follow that barrier.
 template <typename T, int WM, int WN, int FM, int FN, int NS, bool X_KMAJ, bool W_KMAJ, bool UPD, bool SPLITK = false,
-          int BK = 4 * Elem<T>::E>
+          int BK = 4 * Elem<T>::E, bool RAGK = false>
 __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a, const typename UpdSel<UPD>::type upd) {
   static_assert(!SPLITK || !UPD, "partial sums are stored plainly");
   constexpr int CPR = BK / Elem<T>::E;               // 16-byte chunks of k per sub-tile: 4, or 8 (bf16)
@@ -1107,9 +1088,9 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
     for (int nd = 0; nd < NL; ++nd) load_one(t, nd);
   __builtin_amdgcn_s_waitcnt(WAIT_VM0);
   __builtin_amdgcn_s_barrier();
-  // K not a multiple of a chunk: the elements past K in a k-contiguous operand's last chunk are cleared in LDS once the
-  // last sub-tile has landed (tail: uniform over the launch)
-  const bool tail = (X_KMAJ || W_KMAJ) && K % Elem<T>::E != 0;
+  // RAGK (K not a multiple of a chunk): the elements past K in a k-contiguous operand's last chunk are cleared in LDS once
+  // the last sub-tile has landed.  A version of its own: a uniform branch per sub-tile costs the others 0.7 %.
+  constexpr bool tail = RAGK && (X_KMAJ || W_KMAJ);
   auto mask_tail_of = [&](int t) {
     char* const st = reinterpret_cast<char*>(lds) + (t % NS) * STAGE;
     RX::mask_k(st, K - (kb + t) * BK, tid);
@@ -1616,6 +1597,8 @@ struct DmaBig {  // 256 x 256, 8 waves (2 x 4, each 128 x 64), ring of 4 stages 
   static hipError_t run1(const GemmArgs& a, hipStream_t s) {
     if constexpr (XK && WK)
       hipLaunchKernelGGL((gemm_dma_kernel<bf16_t, WM, WN, FM, FN, 2, XK, WK, false, false, 64>), dim3(grid_of(a)), dim3(NT), LDS, s, a, NoUpdate());
+    else if (XK && a.K % 8)
+      hipLaunchKernelGGL((gemm_dma_kernel<bf16_t, WM, WN, FM, FN, NS, true, false, false, false, 32, true>), dim3(grid_of(a)), dim3(NT), LDS, s, a, NoUpdate());
     else
       hipLaunchKernelGGL((gemm_dma_kernel<bf16_t, WM, WN, FM, FN, NS, XK, WK, false>), dim3(grid_of(a)), dim3(NT), LDS, s, a, NoUpdate());
     return hipGetLastError();
@@ -1642,8 +1625,13 @@ struct DmaBig {  // 256 x 256, 8 waves (2 x 4, each 128 x 64), ring of 4 stages 
       return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<bf16_t, WM, WN, FM, FN, NS, XK, WK, UPD>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
   }
+  // An input gradient may have any K (the columns of an output head); elsewhere a k-contiguous operand needs whole chunks
+  static bool eligible(const GemmArgs& a) { return a.K % 8 == 0 || !a.w_kmajor; }
   static hipError_t attr() {
     hipError_t e;
+    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<bf16_t, WM, WN, FM, FN, NS, true, false, false, false, 32, true>),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS)) != hipSuccess)
+      return e;
     if ((e = attr1<true, true, false>()) != hipSuccess) return e;
     if ((e = attr1<true, false, false>()) != hipSuccess) return e;
     if ((e = attr1<false, true, false>()) != hipSuccess) return e;
@@ -1667,6 +1655,11 @@ struct Dma {
   }
   template <bool XK, bool WK>
   static hipError_t run1(const GemmArgs& a, hipStream_t s) {
+    if constexpr (XK || WK)
+      if (a.K % Elem<T>::E) {
+        hipLaunchKernelGGL((gemm_dma_kernel<T, WM, WN, FM, FN, NS, XK, WK, false, false, BK, true>), grid_of(a), dim3(NT), LDS, s, a, NoUpdate());
+        return hipGetLastError();
+      }
     hipLaunchKernelGGL((gemm_dma_kernel<T, WM, WN, FM, FN, NS, XK, WK, false, false, BK>), grid_of(a), dim3(NT), LDS, s, a, NoUpdate());
     return hipGetLastError();
   }
@@ -1680,6 +1673,11 @@ struct Dma {
   }
   template <bool XK, bool WK, bool UPD = false>
   static hipError_t attr1() {
+    if constexpr (XK || WK) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<T, WM, WN, FM, FN, NS, XK, WK, UPD, false, BK, true>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
+      if (e != hipSuccess) return e;
+    }
     return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<T, WM, WN, FM, FN, NS, XK, WK, UPD, false, BK>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
   }
@@ -1905,7 +1903,7 @@ hipError_t dispatch(const GemmArgs& a, hipStream_t s) {
     if (tile == TILE_SMALL) return SmallBf16::run(a, s);
     if (tile == TILE_SMALL_DEEP) return SmallBf16Deep::run(a, s);
     if (tile == TILE_WIDE) return DmaWide::run_x(a, s);
-    if (tile == 1 && dma_eligible(a)) return DmaBig::run(a, s);
+    if (tile == 1 && dma_eligible(a) && DmaBig::eligible(a)) return DmaBig::run(a, s);
     if (tile == 2 && dma_eligible(a)) return DmaMid::run(a, s);
   } else {
     if (tile == TILE_SMALL) return SmallF32::run(a, s);
