@@ -16,12 +16,17 @@
 // column).  The tiles stay row-major in LDS (rows of DH values, 16-byte chunks XOR-swizzled by the row) and that
 // operand comes from transposing LDS reads (ds_read_b64_tr_b16: within 16 lanes, source lane j supplies four
 // consecutive columns of row j/4 and lane i receives column i of rows 0..3), two per fragment, so every tile is
-// loaded once and nothing is transposed in memory.  Tile loads are software-pipelined: the global loads of tile
-// t+1 are issued into registers before the products of tile t and stored to LDS after them.  Softmax statistics
+// loaded once and nothing is transposed in memory.  Tiles go from memory straight into one of two LDS buffers (buffer
+// loads with LDS as their destination): the loads of tile t+1 are issued when every wave has left tile t-1 and land under
+// the products of tile t; one barrier per tile.  Softmax statistics
 // of a query live in the two lanes l and l^32 and are combined with one cross-lane exchange.  A wavefront owns 32
 // queries (or 32 keys) and loops over tiles of 64 keys (queries) shared through LDS by the four wavefronts of the
 // workgroup.  All sums run in a fixed order; dq and dk/dv are separate kernels so that no atomics are needed.
+#include <type_traits>
+
 #include "kernels.h"
+#include "lds_dma.h"
+#include "wave_math.h"
 
 namespace hydra {
 
@@ -54,8 +59,6 @@ __device__ __forceinline__ f32x16 mfma(const uint4& a, const uint4& b, f32x16 c)
 
 // ---- LDS tiles of 64 rows x DH columns ---------------------------------------------------------------
 // uint4 chunk (row, kc) sits at row*NCH + (kc ^ swz(row)), NCH = DH/8.
-// A tile load is split in two so that it can be pipelined: fetch (global -> registers, rows past nrows as zero)
-// and put (registers -> LDS).
 // Work item of a workgroup.  The hardware deals consecutive workgroup ids to the 8 XCDs in turn; items are numbered so
 // that each XCD gets a contiguous run of them, and the 128-row blocks of one (batch, head) are consecutive items: the
 // blocks that read the same K/V (or Q/dO) tiles then run on one XCD and share them through its L2, instead of
@@ -83,55 +86,46 @@ __device__ __forceinline__ int swz(int row) {
   return 4 * ((row >> 1) & 1) + ((row >> 2) & 3);
 }
 
-template <int DH>
-struct TileRegs {
-  static constexpr int NCH = DH / 8, N = 64 * NCH / 256;
-  uint4 r[N];
-  __device__ __forceinline__ void fetch(const bf16_t* src, int ld, int row0, int nrows, int tid) {
+// A tile's way into LDS: load i of wave w fills slots [(4 i + w) 64, + 64), lane l slot + l, with the chunk that belongs there.
+// Rows at or past nrows read as zero (the descriptor ends with row nrows - 1; it is made per tile, so that the lane's
+// offset is the same for every tile).  ONE: the rows of load i are those of load 0 plus 16 or 32 i, which have the same XOR
+// terms, so one offset per lane serves every load and the descriptor, in scalar registers, moves on: for the kernel
+// that has no vector register to spare (the others would only spill scalar registers for it).
+template <int DH, bool ONE = false>
+struct TileDma {
+  static constexpr int NCH = DH / 8, N = 64 * NCH / 256, STEP = 256 / NCH;  // loads per wave, rows between them
+  unsigned voff[ONE ? 1 : N];
+  __device__ __forceinline__ void init(int ld, int wave, int lane) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int c = tid + 256 * i, row = c / NCH, kc = c % NCH;
-      r[i] = make_uint4(0, 0, 0, 0);
-      if (row0 + row < nrows) r[i] = *reinterpret_cast<const uint4*>(src + (size_t)(row0 + row) * ld + 8 * kc);
+    for (int i = 0; i < (ONE ? 1 : N); ++i) {
+      const int sl = (4 * i + wave) * 64 + lane, row = sl / NCH;
+      voff[i] = ((unsigned)row * (unsigned)ld + (unsigned)((sl % NCH) ^ swz<DH>(row)) * 8u) * 2u;
     }
   }
-  __device__ __forceinline__ void put(uint4* tile, int tid) const {
+  // src: row 0 of the sequence at the head's columns, which start col elements into a row of ld
+  __device__ __forceinline__ void issue(const bf16_t* src, int ld, int col, int row0, int nrows, unsigned lds_addr, int wave) const {
+    const long total = ((long)nrows * ld - col) * 2;
+    const rsrc_u32x4 rs = rsrc_words(src, (long)row0 * ld * 2, total);
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int c = tid + 256 * i, row = c / NCH, kc = c % NCH;
-      tile[row * NCH + (kc ^ swz<DH>(row))] = r[i];
-    }
+    for (int i = 0; i < N; ++i)
+      load_to_lds_b128(ONE ? rsrc_words(src, (long)(row0 + STEP * i) * ld * 2, total) : rs,
+                       lds_addr + (unsigned)((4 * i + wave) * 64 * 16), voff[ONE ? 0 : i]);
   }
 };
+// every load of this wave has landed, then every wave's
+__device__ __forceinline__ void tile_landed() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+}
+__device__ __forceinline__ unsigned lds_byte_addr(const void* p) {
+  return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)reinterpret_cast<const char*>(p);
+}
 
 // A operand along the slow index of a row-major tile: lane l gets, for column col0 + l%32, the values of rows
 // row0 + 4g + {0..3} and row0 + 8 + 4g + {0..3} (g = l/32), the k order the accumulator rows of the first product
 // have.  Two transposing reads: in the 16-lane group, source lane j reads 8 bytes at row 4g + j/4, column
 // 16*(group&1) + 4*(j%4) of the block.
-template <int DH>
-__device__ __forceinline__ uint4 read_cols(const uint4* tile, int col0, int row0, int lane) {
-  constexpr int NCH = DH / 8;
-  typedef __attribute__((ext_vector_type(4))) short s16x4;
-  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-  const int j = lane & 15, grp = lane >> 4;
-  const int col = col0 + 16 * (grp & 1) + 4 * (j & 3), kc = col >> 3, half = (col >> 2) & 1;
-  const int r0 = row0 + 4 * (grp >> 1) + (j >> 2), r1 = r0 + 8;
-  const unsigned base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)reinterpret_cast<const char*>(tile);
-  const unsigned a0 = base + (unsigned)((r0 * NCH + (kc ^ swz<DH>(r0))) * 16 + half * 8);
-  const unsigned a1 = base + (unsigned)((r1 * NCH + (kc ^ swz<DH>(r1))) * 16 + half * 8);
-  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)a0);
-  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)a1);
-  const uint2 l = __builtin_bit_cast(uint2, lo), h = __builtin_bit_cast(uint2, hi);
-  return make_uint4(l.x, l.y, h.x, h.y);
-}
-
-template <int DH>
-__device__ __forceinline__ uint4 read_rows(const uint4* tile, int row, int kc) {
-  constexpr int NCH = DH / 8;
-  return tile[row * NCH + (kc ^ swz<DH>(row))];
-}
-
-// The same two reads with the lane's part of the address computed once: for rows row0 + l%32 (row0 a multiple of
+// The lane's part of an address is computed once: for rows row0 + l%32 (row0 a multiple of
 // NCH) the XOR term depends on the lane alone, so a tile's later row blocks, and a second tile that follows the first
 // in LDS, are constant offsets from one pointer per chunk (they go into the instruction's offset field).
 template <int DH>
@@ -139,7 +133,7 @@ __device__ __forceinline__ const uint4* rows_base(const uint4* tile, int li, int
   constexpr int NCH = DH / 8;
   return tile + li * NCH + (kc ^ swz<DH>(li));
 }
-// byte addresses of read_cols' two reads (rows r0 and r0 + 8) for row0 = 0; row0 (a multiple of 16) adds
+// byte addresses of the two transposing reads (rows r0 and r0 + 8) for row0 = 0; row0 (a multiple of 16) adds
 // row0 * NCH * 16 to both
 struct ColsBase { unsigned a0, a1; };
 template <int DH>
@@ -148,7 +142,7 @@ __device__ __forceinline__ ColsBase cols_base(const uint4* tile, int col0, int l
   const int j = lane & 15, grp = lane >> 4;
   const int col = col0 + 16 * (grp & 1) + 4 * (j & 3), kc = col >> 3, half = (col >> 2) & 1;
   const int r0 = 4 * (grp >> 1) + (j >> 2), r1 = r0 + 8;
-  const unsigned base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)reinterpret_cast<const char*>(tile);
+  const unsigned base = lds_byte_addr(tile);
   ColsBase b;
   b.a0 = base + (unsigned)((r0 * NCH + (kc ^ swz<DH>(r0))) * 16 + half * 8);
   b.a1 = base + (unsigned)((r1 * NCH + (kc ^ swz<DH>(r1))) * 16 + half * 8);
@@ -170,18 +164,32 @@ __device__ __forceinline__ uint4 pack_half(const f32x16& p, int x) {
 }
 
 // ---- forward ---------------------------------------------------------------------------------------------
+// Bound by the VALU: a score costs a multiply-add, an exponential (four times a plain instruction's cycles), an addition, half a
+// maximum, half a conversion and (where a maximum grew) a multiplication, 8 issue slots for 1.3 of MFMA at DH = 64.  128
+// registers (four waves per SIMD; 153 when tiles passed through registers); us before | now: 4 x [32 x 12 heads, 512, 64]
+// 179 | 172, 8 x 32 heads, 2048, 128, causal 410 | 405, 2 x [4 x 16, 1024, 128] 90 | 85.
 template <int DH>
-__global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_fwd_kernel(const AttnArgs a) {
+__global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const AttnArgs a) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
   extern __shared__ uint4 lds[];
-  uint4* tK = lds;             // [64][NCH]
-  uint4* tV = lds + 64 * NCH;  // [64][NCH]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 31, g = lane >> 5;
+  // two buffers of K [64][NCH], V [64][NCH]
+  uint4* tK = lds;
+  uint4* tV = lds + 64 * NCH;
+  constexpr int BUF = 2 * 64 * NCH;  // chunks per buffer
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, g = lane >> 5;
   AttnItem item;
   if (!attn_item((a.S + 127) / 128, a.B * a.H, a.G, item)) return;
   const int gi = item.gi, bh = item.bh, b = bh / a.H, h = bh % a.H, blk = item.blk;
   const int d = a.H * DH;
   const bf16_t* base = a.qkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
+  TileDma<DH> dma;
+  dma.init(a.ld_qkv, wave, lane);
+  const unsigned lds0 = lds_byte_addr(lds);
+  auto fetch = [&](int t, unsigned buf) {
+    dma.issue(base + d, a.ld_qkv, d + h * DH, t * 64, a.S, lds0 + buf, wave);
+    dma.issue(base + 2 * d, a.ld_qkv, 2 * d + h * DH, t * 64, a.S, lds0 + buf + 64 * NCH * 16, wave);
+  };
+  fetch(0, 0);
   const int iq = blk * 128 + wave * 32 + li;  // this lane's query
   uint4 qf[NK];
 #pragma unroll
@@ -198,32 +206,24 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_fwd_kernel(const A
   const float sc = a.scale * LOG2E;
   const int q_hi = min(a.S, blk * 128 + 128) - 1;          // last query of the workgroup
   const int n_tiles = a.causal ? (q_hi / 64 + 1) : (a.S + 63) / 64;
-  TileRegs<DH> pk, pv;
-  pk.fetch(base + d, a.ld_qkv, 0, a.S, tid);
-  pv.fetch(base + 2 * d, a.ld_qkv, 0, a.S, tid);
   const uint4* kr[NK];   // K rows l%32, chunk 2kk + g
   ColsBase vc[NC];       // V columns c*32.., rows from 0
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) kr[kk] = rows_base<DH>(tK, li, 2 * kk + g);
 #pragma unroll
   for (int c = 0; c < NC; ++c) vc[c] = cols_base<DH>(tV, c * 32, lane);
-  for (int t = 0; t < n_tiles; ++t) {
+  auto tile = [&](int t, auto buf_) {
+    constexpr int B = decltype(buf_)::value * BUF;  // chunks to the tile's buffer
     const int j0 = t * 64;
-    __syncthreads();
-    pk.put(tK, tid);
-    pv.put(tV, tid);
-    __syncthreads();
-    if (t + 1 < n_tiles) {  // in flight while this tile is multiplied
-      pk.fetch(base + d, a.ld_qkv, j0 + 64, a.S, tid);
-      pv.fetch(base + 2 * d, a.ld_qkv, j0 + 64, a.S, tid);
-    }
+    tile_landed();
+    if (t + 1 < n_tiles) fetch(t + 1, (unsigned)((BUF - B) * 16));
     f32x16 s[2];
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[sub][r] = 0.f;
 #pragma unroll
-      for (int kk = 0; kk < NK; ++kk) s[sub] = mfma(kr[kk][sub * 32 * NCH], qf[kk], s[sub]);
+      for (int kk = 0; kk < NK; ++kk) s[sub] = mfma(kr[kk][B + sub * 32 * NCH], qf[kk], s[sub]);
     }
     // Masking is needed only in tiles that reach past the sequence end or, with a causal mask, past the
     // wave's first query; the scale is folded into the exponent's multiply-add.
@@ -242,34 +242,47 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_fwd_kernel(const A
     for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
       for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sub][r]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(m_run, mx * sc);
-    const float alpha = fast_exp2(m_run - m_new);
+    // The output accumulators, the largest part of a wave's registers, are rescaled only when some query's maximum has
+    // grown.  (Letting it lag by up to 2^8 makes the kernel 4-5 % faster and the results 0.7 % less exact: the largest
+    // weight is then no longer exactly 1 in bf16.)
+    const float2 mh = wave_swap32(mx);
+    mx = fmaxf(mh.x, mh.y) * sc;
+    if (__any(mx > m_run)) {
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = fast_exp2(m_run - m_new);
+      l_run *= alpha;
+      m_run = m_new;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[c][r] *= alpha;
+    }
     float rs = 0.f;
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float p = fast_exp2(fmaf(s[sub][r], sc, -m_new));
+        const float p = fast_exp2(fmaf(s[sub][r], sc, -m_run));
         s[sub][r] = p;
         rs += p;
       }
-    rs += __shfl_xor(rs, 32, 64);
-    l_run = l_run * alpha + rs;
-    m_run = m_new;
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) oacc[c][r] *= alpha;
+    l_run += rs;
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
         const uint4 pf = pack_half(s[sub], x);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) oacc[c] = mfma(read_cols_at<DH>(vc[c], (unsigned)((sub * 32 + 16 * x) * NCH * 16)), pf, oacc[c]);
+        for (int c = 0; c < NC; ++c) oacc[c] = mfma(read_cols_at<DH>(vc[c], (unsigned)((B + (sub * 32 + 16 * x) * NCH) * 16)), pf, oacc[c]);
       }
+  };
+  for (int t = 0; t < n_tiles; t += 2) {
+    tile(t, std::integral_constant<int, 0>());
+    if (t + 1 < n_tiles) tile(t + 1, std::integral_constant<int, 1>());
   }
+  // a query's keys are shared by lanes l and l^32
+  const float2 lh = wave_swap32(l_run);
+  l_run = lh.x + lh.y;
   if (iq < a.S) {
     const float inv = 1.f / l_run;
     bf16_t* o = a.o[gi] + ((size_t)b * a.S + iq) * a.ld_o + h * DH;
@@ -290,14 +303,24 @@ template <int DH>
 __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dq_kernel(const AttnBwdArgs a) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
   extern __shared__ uint4 lds[];
-  uint4* tK = lds;             // [64][NCH]
-  uint4* tV = lds + 64 * NCH;  // [64][NCH]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 31, g = lane >> 5;
+  // two buffers of K [64][NCH], V [64][NCH]
+  uint4* tK = lds;
+  uint4* tV = lds + 64 * NCH;
+  constexpr int BUF = 2 * 64 * NCH;  // chunks per buffer
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, g = lane >> 5;
   AttnItem item;
   if (!attn_item((a.S + 127) / 128, a.B * a.H, a.G, item)) return;
   const int gi = item.gi, bh = item.bh, b = bh / a.H, h = bh % a.H, blk = item.blk;
   const int d = a.H * DH;
   const bf16_t* base = a.qkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
+  TileDma<DH> dma;
+  dma.init(a.ld_qkv, wave, lane);
+  const unsigned lds0 = lds_byte_addr(lds);
+  auto fetch = [&](int t, unsigned buf) {
+    dma.issue(base + d, a.ld_qkv, d + h * DH, t * 64, a.S, lds0 + buf, wave);
+    dma.issue(base + 2 * d, a.ld_qkv, 2 * d + h * DH, t * 64, a.S, lds0 + buf + 64 * NCH * 16, wave);
+  };
+  fetch(0, 0);
   const int iq = blk * 128 + wave * 32 + li;
   uint4 qf[NK], dof[NK];
   float delta = 0.f;
@@ -314,7 +337,11 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dq_kernel(cons
       for (int e = 0; e < 4; ++e) delta += bf_lo(dw[e]) * bf_lo(ow[e]) + bf_hi(dw[e]) * bf_hi(ow[e]);
     }
   }
-  delta += __shfl_xor(delta, 32, 64);
+  const float2 dh = wave_swap32(delta);
+  delta = dh.x + dh.y;
+  f32x16 nd;  // -delta: the accumulator that dP starts from, so that dP - delta costs no instruction
+#pragma unroll
+  for (int r = 0; r < 16; ++r) nd[r] = -delta;
   const float lse2 = iq < a.S ? a.lse[gi][(size_t)bh * a.S + iq] * LOG2E : 0.f;
   if (iq < a.S && g == 0) a.delta[gi][(size_t)bh * a.S + iq] = delta;
   f32x16 acc[NC];
@@ -325,35 +352,28 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dq_kernel(cons
   const float sc = a.scale * LOG2E;
   const int q_hi = min(a.S, blk * 128 + 128) - 1;
   const int n_tiles = a.causal ? (q_hi / 64 + 1) : (a.S + 63) / 64;
-  TileRegs<DH> pk, pv;
-  pk.fetch(base + d, a.ld_qkv, 0, a.S, tid);
-  pv.fetch(base + 2 * d, a.ld_qkv, 0, a.S, tid);
   const uint4* kr[NK];   // K rows l%32, chunk 2kk + g; V is 64 rows further on
   ColsBase kc_[NC];      // K columns c*32.., rows from 0
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) kr[kk] = rows_base<DH>(tK, li, 2 * kk + g);
 #pragma unroll
   for (int c = 0; c < NC; ++c) kc_[c] = cols_base<DH>(tK, c * 32, lane);
-  for (int t = 0; t < n_tiles; ++t) {
+  auto tile = [&](int t, auto buf_) {
+    constexpr int B = decltype(buf_)::value * BUF;  // chunks to the tile's buffer
     const int j0 = t * 64;
-    __syncthreads();
-    pk.put(tK, tid);
-    pv.put(tV, tid);
-    __syncthreads();
-    if (t + 1 < n_tiles) {
-      pk.fetch(base + d, a.ld_qkv, j0 + 64, a.S, tid);
-      pv.fetch(base + 2 * d, a.ld_qkv, j0 + 64, a.S, tid);
-    }
+    tile_landed();
+    if (t + 1 < n_tiles) fetch(t + 1, (unsigned)((BUF - B) * 16));
     const bool edge = j0 + 64 > a.S || (a.causal && j0 + 63 > blk * 128 + wave * 32);
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
       f32x16 s, dp;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
+      for (int r = 0; r < 16; ++r) s[r] = 0.f;
+      dp = nd;
 #pragma unroll
       for (int kk = 0; kk < NK; ++kk) {
-        s = mfma(kr[kk][sub * 32 * NCH], qf[kk], s);
-        dp = mfma(kr[kk][(64 + sub * 32) * NCH], dof[kk], dp);
+        s = mfma(kr[kk][B + sub * 32 * NCH], qf[kk], s);
+        dp = mfma(kr[kk][B + (64 + sub * 32) * NCH], dof[kk], dp);
       }
       if (edge) {
 #pragma unroll
@@ -363,14 +383,18 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dq_kernel(cons
         }
       }
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = fast_exp2(fmaf(s[r], sc, -lse2)) * (dp[r] - delta);
+      for (int r = 0; r < 16; ++r) s[r] = fast_exp2(fmaf(s[r], sc, -lse2)) * dp[r];
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
         const uint4 df = pack_half(s, x);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) acc[c] = mfma(read_cols_at<DH>(kc_[c], (unsigned)((sub * 32 + 16 * x) * NCH * 16)), df, acc[c]);
+        for (int c = 0; c < NC; ++c) acc[c] = mfma(read_cols_at<DH>(kc_[c], (unsigned)((B + (sub * 32 + 16 * x) * NCH) * 16)), df, acc[c]);
       }
     }
+  };
+  for (int t = 0; t < n_tiles; t += 2) {
+    tile(t, std::integral_constant<int, 0>());
+    if (t + 1 < n_tiles) tile(t + 1, std::integral_constant<int, 1>());
   }
   if (iq < a.S) {
     bf16_t* o = a.dqkv[gi] + ((size_t)b * a.S + iq) * a.ld_qkv + h * DH;
@@ -387,20 +411,47 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dq_kernel(cons
 }
 
 // ---- backward, dk and dv -----------------------------------------------------------------------------------
+// Two waves per SIMD at DH = 128 (256 registers with 13 spilled; 376, one wave, when tiles passed through registers and the
+// accumulators moved between the two register files on every tile), three at DH = 64 (162; 200 before).  Together with
+// the dq kernel, us before | now: 8 x 32 heads, 2048, 128, causal 1645 | 1281, 2 x [4 x 16, 1024, 128] 360 | 282,
+// 4 x [32 x 12 heads, 512, 64] 527 | 477.  Held to one wave per SIMD at DH = 128: 1440.
 template <int DH>
-__global__ __launch_bounds__(256, DH == 64 ? 2 : 1) void attn_bwd_dkv_kernel(const AttnBwdArgs a) {
+__global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dkv_kernel(const AttnBwdArgs a) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
   extern __shared__ uint4 lds[];
-  uint4* tQ = lds;                                        // [64][NCH]
-  uint4* tdO = lds + 64 * NCH;                            // [64][NCH]
-  float* st = reinterpret_cast<float*>(lds + 2 * 64 * NCH);  // [2][64]: lse*log2e, delta
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 31, g = lane >> 5;
+  // two buffers of Q [64][NCH], dO [64][NCH], then two of [2][64]: lse*log2e, -delta
+  uint4* tQ = lds;
+  constexpr int BUF = 2 * 64 * NCH;  // chunks per buffer
+  float* const st = reinterpret_cast<float*>(lds + 2 * BUF);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, g = lane >> 5;
   AttnItem item;
   if (!attn_item((a.S + 127) / 128, a.B * a.H, a.G, item)) return;
   const int gi = item.gi, bh = item.bh, b = bh / a.H, h = bh % a.H, blk = item.blk;
   const int d = a.H * DH;
   const bf16_t* base = a.qkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
   const bf16_t* dobase = a.dout[gi] + (size_t)b * a.S * a.ld_o + h * DH;
+  const int t0 = a.causal ? (blk * 128) / 64 : 0;  // queries before the workgroup's first key see none of its keys
+  const int n_tiles = (a.S + 63) / 64;
+  TileDma<DH, DH == 128> dma_q, dma_o;
+  dma_q.init(a.ld_qkv, wave, lane);
+  dma_o.init(a.ld_o, wave, lane);
+  const unsigned lds0 = lds_byte_addr(lds);
+  float pst = 0.f;
+  auto fetch = [&](int t, unsigned buf) {
+    dma_q.issue(base, a.ld_qkv, h * DH, t * 64, a.S, lds0 + buf, wave);
+    dma_o.issue(dobase, a.ld_o, h * DH, t * 64, a.S, lds0 + buf + 64 * NCH * 16, wave);
+    // threads 0..63: lse*log2e, 64..127: -delta of query 64 t + tid%64
+    if (wave < 2) {
+      float* const p = (wave == 0 ? const_cast<float*>(a.lse[gi]) : a.delta[gi]) + (size_t)bh * a.S + t * 64;
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(p, 0, min(a.S - t * 64, 64) * 4, 0x00020000);
+      pst = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, 0, 0));  // zero past the last query
+      pst *= wave == 0 ? LOG2E : -1.0f;
+    }
+  };
+  if (t0 < n_tiles) {
+    fetch(t0, 0);
+    if (wave < 2) st[tid] = pst;
+  }
   const int jk = blk * 128 + wave * 32 + li;  // this lane's key
   uint4 kf[NK], vf[NK];
 #pragma unroll
@@ -417,49 +468,32 @@ __global__ __launch_bounds__(256, DH == 64 ? 2 : 1) void attn_bwd_dkv_kernel(con
 #pragma unroll
     for (int r = 0; r < 16; ++r) dk[c][r] = dv[c][r] = 0.f;
   const float sc = a.scale * LOG2E;
-  const int t0 = a.causal ? (blk * 128) / 64 : 0;  // queries before the workgroup's first key see none of its keys
-  const int n_tiles = (a.S + 63) / 64;
-  TileRegs<DH> pq, pdo;
-  float pst = 0.f;
-  auto fetch_stats = [&](int i0) {  // threads 0..63: lse*log2e, 64..127: delta of query i0 + tid%64
-    pst = 0.f;
-    const int i = i0 + (tid & 63);
-    if (tid < 128 && i < a.S) pst = tid < 64 ? a.lse[gi][(size_t)bh * a.S + i] * LOG2E : a.delta[gi][(size_t)bh * a.S + i];
-  };
   const uint4* qr[NK];   // Q rows l%32, chunk 2kk + g; dO is 64 rows further on
   ColsBase qc[NC];       // Q columns c*32.., rows from 0
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) qr[kk] = rows_base<DH>(tQ, li, 2 * kk + g);
 #pragma unroll
   for (int c = 0; c < NC; ++c) qc[c] = cols_base<DH>(tQ, c * 32, lane);
-  if (t0 < n_tiles) {
-    pq.fetch(base, a.ld_qkv, t0 * 64, a.S, tid);
-    pdo.fetch(dobase, a.ld_o, t0 * 64, a.S, tid);
-    fetch_stats(t0 * 64);
-  }
-  for (int t = t0; t < n_tiles; ++t) {
+  auto tile = [&](int t, auto buf_) {
+    constexpr int B = decltype(buf_)::value * BUF;  // chunks to the tile's buffer
+    const float* const stb = st + decltype(buf_)::value * 128;
     const int i0 = t * 64;
-    __syncthreads();
-    pq.put(tQ, tid);
-    pdo.put(tdO, tid);
-    if (tid < 128) st[tid] = pst;
-    __syncthreads();
-    if (t + 1 < n_tiles) {
-      pq.fetch(base, a.ld_qkv, i0 + 64, a.S, tid);
-      pdo.fetch(dobase, a.ld_o, i0 + 64, a.S, tid);
-      fetch_stats(i0 + 64);
-    }
+    tile_landed();
+    if (t + 1 < n_tiles) fetch(t + 1, (unsigned)((BUF - B) * 16));
     // queries past the end, or (causal) queries that precede some key of this wave, need the mask
     const bool edge = i0 + 64 > a.S || (a.causal && i0 < blk * 128 + wave * 32 + 31);
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
       f32x16 s, dp;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
+      for (int r = 0; r < 16; ++r) {
+        s[r] = 0.f;
+        dp[r] = stb[64 + sub * 32 + 8 * (r >> 2) + 4 * g + (r & 3)];  // -delta: dP - delta costs no instruction
+      }
 #pragma unroll
       for (int kk = 0; kk < NK; ++kk) {
-        s = mfma(qr[kk][sub * 32 * NCH], kf[kk], s);
-        dp = mfma(qr[kk][(64 + sub * 32) * NCH], vf[kk], dp);
+        s = mfma(qr[kk][B + sub * 32 * NCH], kf[kk], s);
+        dp = mfma(qr[kk][B + (64 + sub * 32) * NCH], vf[kk], dp);
       }
       f32x16 ds;
       if (edge) {
@@ -472,20 +506,25 @@ __global__ __launch_bounds__(256, DH == 64 ? 2 : 1) void attn_bwd_dkv_kernel(con
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int il = sub * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-        const float p = fast_exp2(fmaf(s[r], sc, -st[il]));
+        const float p = fast_exp2(fmaf(s[r], sc, -stb[il]));
         s[r] = p;
-        ds[r] = p * (dp[r] - st[64 + il]);
+        ds[r] = p * dp[r];
       }
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
         const uint4 pf = pack_half(s, x), df = pack_half(ds, x);
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-          dv[c] = mfma(read_cols_at<DH>(qc[c], (unsigned)((64 + sub * 32 + 16 * x) * NCH * 16)), pf, dv[c]);
-          dk[c] = mfma(read_cols_at<DH>(qc[c], (unsigned)((sub * 32 + 16 * x) * NCH * 16)), df, dk[c]);
+          dv[c] = mfma(read_cols_at<DH>(qc[c], (unsigned)((B + (64 + sub * 32 + 16 * x) * NCH) * 16)), pf, dv[c]);
+          dk[c] = mfma(read_cols_at<DH>(qc[c], (unsigned)((B + (sub * 32 + 16 * x) * NCH) * 16)), df, dk[c]);
         }
       }
     }
+    if (t + 1 < n_tiles && wave < 2) st[(1 - decltype(buf_)::value) * 128 + tid] = pst;
+  };
+  for (int t = t0; t < n_tiles; t += 2) {
+    tile(t, std::integral_constant<int, 0>());
+    if (t + 1 < n_tiles) tile(t + 1, std::integral_constant<int, 1>());
   }
   if (jk < a.S) {
     bf16_t* ok = a.dqkv[gi] + ((size_t)b * a.S + jk) * a.ld_qkv + d + h * DH;
@@ -504,9 +543,9 @@ __global__ __launch_bounds__(256, DH == 64 ? 2 : 1) void attn_bwd_dkv_kernel(con
   }
 }
 
-template <int DH> constexpr size_t fwd_lds() { return (size_t)2 * 64 * (DH / 8) * 16; }
-template <int DH> constexpr size_t dq_lds() { return (size_t)2 * 64 * (DH / 8) * 16; }
-template <int DH> constexpr size_t dkv_lds() { return (size_t)2 * 64 * (DH / 8) * 16 + 128 * 4; }
+template <int DH> constexpr size_t fwd_lds() { return (size_t)2 * 2 * 64 * (DH / 8) * 16; }
+template <int DH> constexpr size_t dq_lds() { return (size_t)2 * 2 * 64 * (DH / 8) * 16; }
+template <int DH> constexpr size_t dkv_lds() { return (size_t)2 * 2 * 64 * (DH / 8) * 16 + 2 * 128 * 4; }
 
 bool attn_ok(int B, int S, int H, int DH, int ld_qkv, int ld_o, int G) {
   return G >= 1 && G <= MAXG && B >= 1 && S >= 1 && H >= 1 && (DH == 64 || DH == 128) && ld_qkv >= 3 * H * DH &&
@@ -515,7 +554,10 @@ bool attn_ok(int B, int S, int H, int DH, int ld_qkv, int ld_o, int G) {
 
 }  // namespace
 
-hipError_t attn_init() { return hipSuccess; }  // every kernel stays below the default LDS limit
+hipError_t attn_init() {  // the other kernels stay within the default LDS limit
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dkv_kernel<128>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)dkv_lds<128>());
+}
 
 hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
   if (!attn_ok(a.B, a.S, a.H, a.DH, a.ld_qkv, a.ld_o, a.G)) return hipErrorInvalidValue;

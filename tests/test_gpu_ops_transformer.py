@@ -224,3 +224,43 @@ def test_layernorm_row_batches(torch, ops, dtype, G, rows, d):
             assert (err <= tol * (want.abs() + want.abs().mean())).all(), err.max()
         for got, term in ((dg[g], dyd * xh), (db[g], dyd)):
             assert ((got.double() - term.sum(0)).abs() <= 1e-5 * term.abs().sum(0) + 1e-6).all()
+
+
+@pytest.mark.parametrize("DH,causal", [(64, False), (64, True), (128, False), (128, True)])
+@pytest.mark.parametrize("S", [1, 63, 64, 65, 128, 200, 257])
+def test_attention_reads_nothing_past_its_sequence(torch, ops, S, DH, causal):
+    """Tiles of 64 rows go into LDS by loads that return zero past the sequence: with NaN in the sequence behind it every result of
+    the first one keeps its bits, for odd and even numbers of tiles and partly filled ones; and it matches fp64 (bf16 rounding of
+    the probabilities and of the results: 2^-7 of a row's largest terms)."""
+    H, B, d = 2, 2, 2 * DH
+    gen = torch.Generator(device="cuda").manual_seed(S * 3 + DH)
+    t = B * S
+    qkv0 = torch.randn(t, 3 * d, generator=gen, device="cuda").to(torch.bfloat16)
+    do0 = torch.randn(t, d, generator=gen, device="cuda").to(torch.bfloat16)
+    got = []
+    for fill in (0.0, float("nan")):
+        qkv, do = qkv0.clone(), do0.clone()
+        qkv[S:], do[S:] = fill, fill
+        o, dqkv = torch.zeros_like(do), torch.zeros_like(qkv)
+        lse, delta = torch.zeros(t * H, device="cuda"), torch.zeros(t * H, device="cuda")
+        ops.hydra_op_attention_fwd(B, S, H, DH, 3 * d, d, causal, DH ** -0.5, [qkv], [o], [lse])
+        ops.hydra_op_attention_bwd(B, S, H, DH, 3 * d, d, causal, DH ** -0.5, [qkv], [o], [do], [lse], [delta], [dqkv])
+        got.append((o[:S].clone(), lse[:H * S].clone(), dqkv[:S].clone()))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    o, lse, dqkv = got[0]
+    mask = torch.ones(S, S, device="cuda", dtype=torch.bool).triu(1)
+    for h in range(H):
+        q, k, v = (qkv0[:S, j * d + h * DH:j * d + (h + 1) * DH].double().contiguous() for j in range(3))
+        dh = do0[:S, h * DH:(h + 1) * DH].double().contiguous()
+        z = torch.mm(q, k.t().contiguous()) * DH ** -0.5
+        if causal:
+            z = z.masked_fill(mask, float("-inf"))
+        ls = torch.logsumexp(z, 1)
+        p = torch.exp(z - ls[:, None])
+        oh = torch.mm(p, v)
+        ds = p * (torch.mm(dh, v.t().contiguous()) - (dh * oh).sum(1, keepdim=True)) * DH ** -0.5
+        want = (oh, torch.mm(ds, k), torch.mm(ds.t().contiguous(), q), torch.mm(p.t().contiguous(), dh))
+        have = [o[:, h * DH:(h + 1) * DH]] + [dqkv[:, j * d + h * DH:j * d + (h + 1) * DH] for j in range(3)]
+        for a, b in zip(have, want):
+            assert (a.double() - b).abs().max() <= 2.0 ** -7 * max(float(b.abs().max()), 1.0)
+        assert (lse[h * S:(h + 1) * S].double() - ls).abs().max() <= 1e-5
