@@ -15,9 +15,10 @@ EPI_NONE, EPI_RELU, EPI_GELU = 0, 1, 2
 
 
 class hydra_gemm_desc(C.Structure):
+    # the tables' addresses are passed as plain pointers: casting a ctypes array to a typed pointer costs more than the call
     _fields_ = [(n, C.c_int) for n in ("dtype", "M", "N", "K", "x_kmajor", "w_kmajor", "ldx", "ldw", "ldo", "ldg", "ldr",
                                        "act", "out_f32", "tile", "G")] + \
-               [(n, C.POINTER(C.c_void_p)) for n in ("X", "W", "bias", "out", "pre", "gate", "resid", "rowsum", "ws")] + \
+               [(n, C.c_void_p) for n in ("X", "W", "bias", "out", "pre", "gate", "resid", "rowsum", "ws")] + \
                [("ws_bytes", C.c_size_t)]
 
 
@@ -59,14 +60,31 @@ def _L():
 
 
 def _stream():
+    """torch's current stream on the current device (the raw handle: building a Stream object costs several us)."""
     import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
+_tab_types: dict = {}  # array type by length (making one anew per call is the larger part of a small call)
 
 
 def _tab(ts: Optional[Sequence]):
     if ts is None:
         return None
-    return (C.c_void_p * len(ts))(*[t.data_ptr() for t in ts])
+    n = len(ts)
+    t = _tab_types.get(n)
+    if t is None:
+        t = _tab_types[n] = C.c_void_p * n
+    return t(*[x.data_ptr() for x in ts])
+
+
+def _addr(tab):
+    """Address of a table (None for none); the caller keeps the table alive over the call."""
+    return None if tab is None else C.addressof(tab)
+
+
+def _nbytes(ws):
+    return 0 if ws is None else min(t.numel() * t.element_size() for t in ws)
 
 
 def _check(st: int):
@@ -77,14 +95,9 @@ def _check(st: int):
 def hydra_op_gemm(dtype, M, N, K, X, W, out, *, x_kmajor, w_kmajor, ldx, ldw, ldo, bias=None, pre=None, gate=None,
                   resid=None, ldg=0, ldr=0, act=EPI_NONE, out_f32=False, tile=0, rowsum=None, ws=None):
     """ws: optional per-problem scratch tensors (uint8, hydra_op_gemm_split_ws_bytes bytes) that allow a split sum over k."""
-    d = hydra_gemm_desc()
-    d.dtype, d.M, d.N, d.K, d.x_kmajor, d.w_kmajor = dtype, M, N, K, int(x_kmajor), int(w_kmajor)
-    d.ldx, d.ldw, d.ldo, d.ldg, d.ldr, d.act, d.out_f32, d.tile, d.G = ldx, ldw, ldo, ldg, ldr, act, int(out_f32), tile, len(X)
     tabs = [_tab(t) for t in (X, W, bias, out, pre, gate, resid, rowsum, ws)]
-    for name, t in zip(("X", "W", "bias", "out", "pre", "gate", "resid", "rowsum", "ws"), tabs):
-        if t is not None:
-            setattr(d, name, C.cast(t, C.POINTER(C.c_void_p)))
-    d.ws_bytes = 0 if ws is None else min(int(t.numel() * t.element_size()) for t in ws)
+    d = hydra_gemm_desc(dtype, M, N, K, int(x_kmajor), int(w_kmajor), ldx, ldw, ldo, ldg, ldr, act, int(out_f32), tile, len(X),
+                        *[_addr(t) for t in tabs], _nbytes(ws))
     _check(_L().hydra_op_gemm(C.byref(d), _stream()))
 
 
@@ -99,14 +112,10 @@ def hydra_op_gemm_split_ws_bytes(M, N, K, ldo) -> int:
 def hydra_op_gemm_update(dtype, M, N, K, X, W, opt, p, m, v, w16, hp_rows, *, ldx, ldw, ldo, out=None, tile=0, rowsum=None,
                          ws=None):
     """Weight gradient dW[M,N] = sum_k X(k,m) W(k,n) with the optimizer step of hydra_op_optim in its epilogue."""
-    d = hydra_gemm_desc()
-    d.dtype, d.M, d.N, d.K, d.x_kmajor, d.w_kmajor = dtype, M, N, K, 0, 0
-    d.ldx, d.ldw, d.ldo, d.ldg, d.ldr, d.act, d.out_f32, d.tile, d.G = ldx, ldw, ldo, 0, 0, EPI_NONE, 1, tile, len(X)
     tabs = [_tab(t) for t in (X, W, out, rowsum, ws)]
-    for name, t in zip(("X", "W", "out", "rowsum", "ws"), tabs):
-        if t is not None:
-            setattr(d, name, C.cast(t, C.POINTER(C.c_void_p)))
-    d.ws_bytes = 0 if ws is None else min(int(t.numel() * t.element_size()) for t in ws)
+    tx, tw, to, tr, ts = [_addr(t) for t in tabs]
+    d = hydra_gemm_desc(dtype, M, N, K, 0, 0, ldx, ldw, ldo, 0, 0, EPI_NONE, 1, tile, len(X), tx, tw, None, to, None, None, None, tr, ts,
+                        _nbytes(ws))
     flat = (C.c_double * (6 * len(p)))(*[float(x) for row in hp_rows for x in row])
     _check(_L().hydra_op_gemm_update(C.byref(d), opt, _tab(p), _tab(m), _tab(v), _tab(w16), flat, _stream()))
 

@@ -344,3 +344,21 @@ def test_small_fp32_models_at_every_split_of_the_batch_rows(H, batch):
         assert np.array_equal(seq[k][0], got[k][0])
         for a, b in zip(seq[k][1], got[k][1]):
             assert np.array_equal(a, b)
+
+
+def test_reading_all_tensors_equals_reading_each():
+    """Small neighbouring tensors leave the device as one copy, larger ones by themselves: the same values as one by one, with tensors
+    of odd sizes (padded in the block), around the 1 MB limit and beyond it."""
+    import hydra_workloads.configs as W
+    from paper_2107_06469_amd import hydra as H
+    for layers, d_in, d, out in ((3, 40, 24, 7), (2, 512, 520, 11), (2, 504, 512, 1000), (1, 8, 8, 1)):
+        ctx = H.hydra_create()
+        try:
+            a = W.mlp_arch(layers, d_in, d, out, W.ACT_RELU, W.DTYPE_F32)
+            H.hydra_define_models(ctx, [a] * 2, [W.hparams(W.OPT_SGD, 0.1)] * 2, 5)
+            for k in range(2):
+                whole = H.hydra_read_params(ctx, k)
+                for j, t in enumerate(whole):
+                    assert np.array_equal(t.reshape(-1), H.hydra_read_params(ctx, k, j)), (d, k, j)
+        finally:
+            H.hydra_destroy(ctx)
