@@ -272,6 +272,139 @@ __global__ __launch_bounds__(NW * 64) void ln_bwd_kernel(const LnBwdArgs a) {
   }
 }
 
+// Small launches: one kernel instead of two.  The row statistics are inputs here, so the column sums need nothing from the
+// rows' own pass: workgroups past the row blocks add up 32 columns each over all rows, straight from x and dy (which
+// the row blocks read at the same time), instead of partial sums that a second launch collects.  Row blocks: 16 waves,
+// one row each.  Column blocks: thread (row group, chunk of 8 columns) adds every 256th row in ascending order, the row
+// groups of a wave are added by a butterfly and the 16 waves in wave order.
+// Two launches | this one, us: 4 x [1024, 256] bf16 8.9 + 2.8 | 7.0, 4 x [152, 256] 8.4 + 2.8 | 4.5, 4 x [1024, 768] 14.6 + 3.9 |
+// 11.0, fp32 4 x [1024, 256] 9.2 + 2.8 | 7.9, and a launch gap less.  A column block reads its columns of all rows through one
+// compute unit, which sets the limit: 4 x [2048, 256] 9.4 + 2.8 | 10.7, 8 x [2048, 512] 13.8 + 3.9 | 25.6.
+constexpr int LN_SMALL_ROWS = 1280, LN_SMALL_COLS = 32;
+template <typename T, int LN_MAXC>
+__global__ __launch_bounds__(1024) void ln_bwd_small_kernel(const LnBwdArgs a, int row_blocks) {
+  __shared__ float red[16][2][LN_SMALL_COLS];
+  const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int RW = sizeof(T) == 2 ? 1 : 2;  // 16-byte pieces per 8 elements
+  const T* X = static_cast<const T*>(a.x[g]);
+  const T* DY = static_cast<const T*>(a.dy[g]);
+  const float* mean = a.mean[g];
+  const float* rs = a.rstd[g];
+  if ((int)blockIdx.x < row_blocks) {
+    const int row = blockIdx.x * 16 + wave;
+    if (row >= a.rows) return;
+    const T* ADD = static_cast<const T*>(a.add[g]);
+    const float* gamma = a.gamma[g];
+    const int nch = a.d >> 3;
+    const size_t o = (size_t)row * a.ld;
+    uint4 rx[LN_MAXC][RW], rdy[LN_MAXC][RW], radd[LN_MAXC][RW];
+    float ga[LN_MAXC][8];
+    const float mu = mean[row], rstd = rs[row];
+#pragma unroll
+    for (int i = 0; i < LN_MAXC; ++i) {
+      const int c = lane + 64 * i;
+      if (c < nch) {
+#pragma unroll
+        for (int q = 0; q < RW; ++q) {
+          rx[i][q] = reinterpret_cast<const uint4*>(X + o)[c * RW + q];
+          rdy[i][q] = reinterpret_cast<const uint4*>(DY + o)[c * RW + q];
+          if (ADD) radd[i][q] = reinterpret_cast<const uint4*>(ADD + o)[c * RW + q];
+        }
+        ld8<float>(gamma + 8 * c, ga[i]);
+      }
+    }
+    float xh[LN_MAXC][8], gg[LN_MAXC][8];
+    float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int i = 0; i < LN_MAXC; ++i)
+      if (lane + 64 * i < nch) {
+        float xv[8], dv[8];
+        unpack8<T>(rx[i], xv);
+        unpack8<T>(rdy[i], dv);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          xh[i][e] = (xv[e] - mu) * rstd;
+          gg[i][e] = dv[e] * ga[i][e];
+          s1 += gg[i][e];
+          s2 += gg[i][e] * xh[i][e];
+        }
+      }
+    const float c1 = wave_sum(s1) / (float)a.d, c2 = wave_sum(s2) / (float)a.d;
+#pragma unroll
+    for (int i = 0; i < LN_MAXC; ++i) {
+      const int c = lane + 64 * i;
+      if (c < nch) {
+        float out[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) out[e] = rstd * (gg[i][e] - c1 - xh[i][e] * c2);
+        if (ADD) {
+          float av[8];
+          unpack8<T>(radd[i], av);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) out[e] += av[e];
+        }
+        st8<T>(static_cast<T*>(a.dx[g]) + o + 8 * c, out);
+      }
+    }
+    return;
+  }
+  const int col0 = ((int)blockIdx.x - row_blocks) * LN_SMALL_COLS, c = col0 / 8 + (tid & 3);  // chunk of 8 columns
+  const bool live = 8 * c < a.d;
+  float sg[8], sb[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) sg[e] = sb[e] = 0.f;
+  constexpr int NB = 4;  // rows whose loads are in flight together
+  for (int r0 = tid >> 2; r0 < a.rows; r0 += 256 * NB) {
+    uint4 rx[NB][RW], rdy[NB][RW];
+    float mu[NB], rstd[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int row = r0 + 256 * b;
+      mu[b] = rstd[b] = 0.f;
+#pragma unroll
+      for (int q = 0; q < RW; ++q) rx[b][q] = rdy[b][q] = make_uint4(0, 0, 0, 0);
+      if (row < a.rows && live) {
+        mu[b] = mean[row];
+        rstd[b] = rs[row];
+#pragma unroll
+        for (int q = 0; q < RW; ++q) {
+          rx[b][q] = reinterpret_cast<const uint4*>(X + (size_t)row * a.ld)[c * RW + q];
+          rdy[b][q] = reinterpret_cast<const uint4*>(DY + (size_t)row * a.ld)[c * RW + q];
+        }
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      if (r0 + 256 * b >= a.rows) break;
+      float xv[8], dv[8];
+      unpack8<T>(rx[b], xv);
+      unpack8<T>(rdy[b], dv);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        sg[e] += dv[e] * ((xv[e] - mu[b]) * rstd[b]);
+        sb[e] += dv[e];
+      }
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    sg[e] = wave_sum_mod4(sg[e]);
+    sb[e] = wave_sum_mod4(sb[e]);
+  }
+  if (lane < 4) {
+    st8<float>(&red[wave][0][8 * lane], sg);
+    st8<float>(&red[wave][1][8 * lane], sb);
+  }
+  __syncthreads();
+  if (tid < 2 * LN_SMALL_COLS) {
+    const int which = tid / LN_SMALL_COLS, col = tid % LN_SMALL_COLS;
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) t += red[w][which][col];
+    if (col0 + col < a.d) (which ? a.dbeta[g] : a.dgamma[g])[col0 + col] = t;
+  }
+}
+
 // Rows of more than 1024 elements: a wave per row would need 32 or 64 values of x-hat and g per lane (one or two waves
 // per SIMD, and up to 128 KB of LDS for the cross-wave column sums).  Here the four waves of a workgroup share each
 // row: thread t owns chunks t, t + 256 (MAXW of them), the two row sums cross the waves through LDS (added in wave
@@ -460,8 +593,20 @@ static hipError_t ln_bwd_pick(const LnBwdArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <typename T>
+static hipError_t ln_bwd_small_run(const LnBwdArgs& a, hipStream_t s) {
+  const int row_blocks = (a.rows + 15) / 16;
+  const dim3 grid(row_blocks + (a.d + LN_SMALL_COLS - 1) / LN_SMALL_COLS, a.G);
+  if (a.d <= 512) hipLaunchKernelGGL((ln_bwd_small_kernel<T, 1>), grid, dim3(1024), 0, s, a, row_blocks);
+  else hipLaunchKernelGGL((ln_bwd_small_kernel<T, 2>), grid, dim3(1024), 0, s, a, row_blocks);
+  return hipGetLastError();
+}
+
 hipError_t launch_ln_bwd(const LnBwdArgs& a, hipStream_t s) {
   if (!ln_shape_ok(a.G, a.rows, a.d, a.ld)) return hipErrorInvalidValue;
+  // by the shape of one problem alone: the order of the column sums must not depend on the group
+  if (a.rows <= LN_SMALL_ROWS && a.d <= LN_WAVE_ROW_MAX)
+    return a.dtype == GEMM_F32 ? ln_bwd_small_run<float>(a, s) : ln_bwd_small_run<bf16_t>(a, s);
   hipError_t e = a.dtype == GEMM_F32 ? ln_bwd_pick<float>(a, s) : ln_bwd_pick<bf16_t>(a, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(ln_reduce_kernel, dim3((2 * a.d + 15) / 16, a.G), dim3(256), 0, s, a, ln_bwd_blocks(a.rows, a.d));
