@@ -21,7 +21,7 @@
 // the products of tile t; one barrier per tile.  Softmax statistics
 // of a query live in the two lanes l and l^32 and are combined with one cross-lane exchange.  A wavefront owns 32
 // queries (or 32 keys) and loops over tiles of 64 keys (queries) shared through LDS by the four wavefronts of the
-// workgroup.  All sums run in a fixed order; dq and dk/dv are separate kernels so that no atomics are needed.
+// workgroup.  All sums run in a fixed order; dq and dk/dv are separate workgroups so that no atomics are needed.
 #include <type_traits>
 
 #include "kernels.h"
@@ -64,10 +64,10 @@ __device__ __forceinline__ f32x16 mfma(const uint4& a, const uint4& b, f32x16 c)
 // blocks that read the same K/V (or Q/dO) tiles then run on one XCD and share them through its L2, instead of
 // each XCD fetching them from memory.  Returns false for the padding ids at the end of the grid.
 struct AttnItem { int blk, bh, gi; };
-__device__ __forceinline__ bool attn_item(int n_blk, int n_bh, int n_g, AttnItem& it) {
+__device__ __forceinline__ bool attn_item(int wg, int n_blk, int n_bh, int n_g, AttnItem& it) {
   const int total = n_blk * n_bh * n_g, per_xcd = (total + 7) >> 3;
-  const int id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (id >= total || (int)(blockIdx.x >> 3) >= per_xcd) return false;
+  const int id = (wg & 7) * per_xcd + (wg >> 3);
+  if (id >= total || (wg >> 3) >= per_xcd) return false;
   it.blk = id % n_blk;
   it.bh = (id / n_blk) % n_bh;
   it.gi = id / (n_blk * n_bh);
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const A
   constexpr int BUF = 2 * 64 * NCH;  // chunks per buffer
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, g = lane >> 5;
   AttnItem item;
-  if (!attn_item((a.S + 127) / 128, a.B * a.H, a.G, item)) return;
+  if (!attn_item(blockIdx.x, (a.S + 127) / 128, a.B * a.H, a.G, item)) return;
   const int gi = item.gi, bh = item.bh, b = bh / a.H, h = bh % a.H, blk = item.blk;
   const int d = a.H * DH;
   const bf16_t* base = a.qkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
@@ -299,8 +299,22 @@ __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const A
 }
 
 // ---- backward, dq (also writes delta) ------------------------------------------------------------------
+// The lane's part (chunks 2 kk + g of a row's DH columns) of delta = sum of do * o: the two bodies below that compute it take
+// the same operations in the same order.
+template <int NK>
+__device__ __forceinline__ float delta_part(const uint4 (&dof)[NK], const uint4 (&of)[NK]) {
+  float delta = 0.f;
+#pragma unroll
+  for (int kk = 0; kk < NK; ++kk) {
+    const uint32_t dw[4] = {dof[kk].x, dof[kk].y, dof[kk].z, dof[kk].w}, ow[4] = {of[kk].x, of[kk].y, of[kk].z, of[kk].w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) delta = fmaf(bf_hi(dw[e]), bf_hi(ow[e]), fmaf(bf_lo(dw[e]), bf_lo(ow[e]), delta));
+  }
+  return delta;
+}
+
 template <int DH>
-__global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dq_kernel(const AttnBwdArgs a) {
+__device__ __forceinline__ void dq_body(const AttnBwdArgs& a, int wg) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
   extern __shared__ uint4 lds[];
   // two buffers of K [64][NCH], V [64][NCH]
@@ -309,7 +323,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dq_kernel(cons
   constexpr int BUF = 2 * 64 * NCH;  // chunks per buffer
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, g = lane >> 5;
   AttnItem item;
-  if (!attn_item((a.S + 127) / 128, a.B * a.H, a.G, item)) return;
+  if (!attn_item(wg, (a.S + 127) / 128, a.B * a.H, a.G, item)) return;
   const int gi = item.gi, bh = item.bh, b = bh / a.H, h = bh % a.H, blk = item.blk;
   const int d = a.H * DH;
   const bf16_t* base = a.qkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
@@ -322,23 +336,19 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dq_kernel(cons
   };
   fetch(0, 0);
   const int iq = blk * 128 + wave * 32 + li;
-  uint4 qf[NK], dof[NK];
-  float delta = 0.f;
+  uint4 qf[NK], dof[NK], of[NK];
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) {
-    qf[kk] = dof[kk] = make_uint4(0, 0, 0, 0);
+    qf[kk] = dof[kk] = of[kk] = make_uint4(0, 0, 0, 0);
     if (iq < a.S) {
       qf[kk] = *reinterpret_cast<const uint4*>(base + (size_t)iq * a.ld_qkv + 16 * kk + 8 * g);
       const size_t off = ((size_t)b * a.S + iq) * a.ld_o + h * DH + 16 * kk + 8 * g;
       dof[kk] = *reinterpret_cast<const uint4*>(a.dout[gi] + off);
-      const uint4 of = *reinterpret_cast<const uint4*>(a.o[gi] + off);
-      const uint32_t dw[4] = {dof[kk].x, dof[kk].y, dof[kk].z, dof[kk].w}, ow[4] = {of.x, of.y, of.z, of.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) delta += bf_lo(dw[e]) * bf_lo(ow[e]) + bf_hi(dw[e]) * bf_hi(ow[e]);
+      of[kk] = *reinterpret_cast<const uint4*>(a.o[gi] + off);
     }
   }
-  const float2 dh = wave_swap32(delta);
-  delta = dh.x + dh.y;
+  const float2 dh = wave_swap32(delta_part<NK>(dof, of));
+  const float delta = dh.x + dh.y;
   f32x16 nd;  // -delta: the accumulator that dP starts from, so that dP - delta costs no instruction
 #pragma unroll
   for (int r = 0; r < 16; ++r) nd[r] = -delta;
@@ -415,8 +425,9 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dq_kernel(cons
 // accumulators moved between the two register files on every tile), three at DH = 64 (162; 200 before).  Together with
 // the dq kernel, us before | now: 8 x 32 heads, 2048, 128, causal 1645 | 1281, 2 x [4 x 16, 1024, 128] 360 | 282,
 // 4 x [32 x 12 heads, 512, 64] 527 | 477.  Held to one wave per SIMD at DH = 128: 1440.
-template <int DH>
-__global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dkv_kernel(const AttnBwdArgs a) {
+// OWN: the kernel works out delta itself instead of reading what the dq kernel left.
+template <int DH, bool OWN>
+__device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, int wg) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
   extern __shared__ uint4 lds[];
   // two buffers of Q [64][NCH], dO [64][NCH], then two of [2][64]: lse*log2e, -delta
@@ -425,7 +436,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dkv_kernel(con
   float* const st = reinterpret_cast<float*>(lds + 2 * BUF);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, g = lane >> 5;
   AttnItem item;
-  if (!attn_item((a.S + 127) / 128, a.B * a.H, a.G, item)) return;
+  if (!attn_item(wg, (a.S + 127) / 128, a.B * a.H, a.G, item)) return;
   const int gi = item.gi, bh = item.bh, b = bh / a.H, h = bh % a.H, blk = item.blk;
   const int d = a.H * DH;
   const bf16_t* base = a.qkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
@@ -437,20 +448,40 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dkv_kernel(con
   dma_o.init(a.ld_o, wave, lane);
   const unsigned lds0 = lds_byte_addr(lds);
   float pst = 0.f;
+  uint4 own_do[NK], own_o[NK];
   auto fetch = [&](int t, unsigned buf) {
     dma_q.issue(base, a.ld_qkv, h * DH, t * 64, a.S, lds0 + buf, wave);
     dma_o.issue(dobase, a.ld_o, h * DH, t * 64, a.S, lds0 + buf + 64 * NCH * 16, wave);
     // threads 0..63: lse*log2e, 64..127: -delta of query 64 t + tid%64
-    if (wave < 2) {
+    if (wave < (OWN ? 1 : 2)) {
       float* const p = (wave == 0 ? const_cast<float*>(a.lse[gi]) : a.delta[gi]) + (size_t)bh * a.S + t * 64;
       const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(p, 0, min(a.S - t * 64, 64) * 4, 0x00020000);
       pst = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, 0, 0));  // zero past the last query
       pst *= wave == 0 ? LOG2E : -1.0f;
     }
+    if (OWN && wave >= 2) {  // waves 2 and 3: 32 queries each, two lanes to a query as in the dq kernel
+      const int i = t * 64 + (wave - 2) * 32 + li;
+#pragma unroll
+      for (int kk = 0; kk < NK; ++kk) {
+        own_do[kk] = own_o[kk] = make_uint4(0, 0, 0, 0);
+        if (i < a.S) {
+          const size_t off = (size_t)i * a.ld_o + 16 * kk + 8 * g;
+          own_do[kk] = *reinterpret_cast<const uint4*>(dobase + off);
+          own_o[kk] = *reinterpret_cast<const uint4*>(a.o[gi] + (size_t)b * a.S * a.ld_o + h * DH + off);
+        }
+      }
+    }
+  };
+  auto put_stats = [&](float* stb) {
+    if (wave < (OWN ? 1 : 2)) stb[tid] = pst;
+    if (OWN && wave >= 2) {
+      const float2 dh = wave_swap32(delta_part<NK>(own_do, own_o));
+      if (g == 0) stb[64 + (wave - 2) * 32 + li] = -(dh.x + dh.y);
+    }
   };
   if (t0 < n_tiles) {
     fetch(t0, 0);
-    if (wave < 2) st[tid] = pst;
+    put_stats(st);
   }
   const int jk = blk * 128 + wave * 32 + li;  // this lane's key
   uint4 kf[NK], vf[NK];
@@ -520,7 +551,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dkv_kernel(con
         }
       }
     }
-    if (t + 1 < n_tiles && wave < 2) st[(1 - decltype(buf_)::value) * 128 + tid] = pst;
+    if (t + 1 < n_tiles) put_stats(st + (1 - decltype(buf_)::value) * 128);
   };
   for (int t = t0; t < n_tiles; t += 2) {
     tile(t, std::integral_constant<int, 0>());
@@ -543,6 +574,26 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dkv_kernel(con
   }
 }
 
+template <int DH>
+__global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dq_kernel(const AttnBwdArgs a) {
+  dq_body<DH>(a, blockIdx.x);
+}
+template <int DH>
+__global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dkv_kernel(const AttnBwdArgs a) {
+  dkv_body<DH, false>(a, blockIdx.x);
+}
+// Small launches: both halves of the backward pass side by side, dk/dv (the longer one) first.  They share nothing but delta,
+// which the dk/dv workgroups then work out themselves from rows of dO and O (same bits): a few percent more work for
+// one launch and one latency chain less.
+// Backward pass, two launches | one, us: 4 x [8 x 4 heads, 128, 64] 17.0 | 10.5, 1 x [4 x 8, 100, 128] 25.5 | 16.1, 2 x [2 x 4, 512, 64]
+// 31.6 | 20.6, 1 x [1 x 4, 2048, 128] causal 166 | 131, 4 x [8 x 4, 256, 64] (256 row blocks) 24.4 | 18.3.
+template <int DH>
+__global__ __launch_bounds__(256, DH == 64 ? 2 : 1) void attn_bwd_both_kernel(const AttnBwdArgs a) {
+  const int half = gridDim.x / 2;
+  if ((int)blockIdx.x < half) dkv_body<DH, true>(a, blockIdx.x);
+  else dq_body<DH>(a, blockIdx.x - half);
+}
+
 template <int DH> constexpr size_t fwd_lds() { return (size_t)2 * 2 * 64 * (DH / 8) * 16; }
 template <int DH> constexpr size_t dq_lds() { return (size_t)2 * 2 * 64 * (DH / 8) * 16; }
 template <int DH> constexpr size_t dkv_lds() { return (size_t)2 * 2 * 64 * (DH / 8) * 16 + 2 * 128 * 4; }
@@ -555,7 +606,10 @@ bool attn_ok(int B, int S, int H, int DH, int ld_qkv, int ld_o, int G) {
 }  // namespace
 
 hipError_t attn_init() {  // the other kernels stay within the default LDS limit
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dkv_kernel<128>), hipFuncAttributeMaxDynamicSharedMemorySize,
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dkv_kernel<128>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_lds<128>());
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_both_kernel<128>), hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)dkv_lds<128>());
 }
 
@@ -570,6 +624,12 @@ hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
 hipError_t launch_attn_bwd(const AttnBwdArgs& a, hipStream_t s) {
   if (!attn_ok(a.B, a.S, a.H, a.DH, a.ld_qkv, a.ld_o, a.G)) return hipErrorInvalidValue;
   dim3 grid(((((a.S + 127) / 128) * a.B * a.H * a.G + 7) / 8) * 8);
+  if (grid.x <= 256) {  // at most two workgroups per CU together
+    const dim3 both(2 * grid.x);
+    if (a.DH == 64) hipLaunchKernelGGL(attn_bwd_both_kernel<64>, both, dim3(256), dkv_lds<64>(), s, a);
+    else hipLaunchKernelGGL(attn_bwd_both_kernel<128>, both, dim3(256), dkv_lds<128>(), s, a);
+    return hipGetLastError();
+  }
   if (a.DH == 64) {
     hipLaunchKernelGGL(attn_bwd_dq_kernel<64>, grid, dim3(256), dq_lds<64>(), s, a);
     hipLaunchKernelGGL(attn_bwd_dkv_kernel<64>, grid, dim3(256), dkv_lds<64>(), s, a);

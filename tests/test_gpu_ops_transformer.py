@@ -265,3 +265,25 @@ def test_attention_reads_nothing_past_its_sequence(torch, ops, S, DH, causal):
         for a, b in zip(have, want):
             assert (a.double() - b).abs().max() <= 2.0 ** -7 * max(float(b.abs().max()), 1.0)
         assert (lse[h * S:(h + 1) * S].double() - ls).abs().max() <= 1e-5
+
+
+@pytest.mark.parametrize("B,S,H,DH,causal", [(1, 200, 2, 64, False), (2, 77, 3, 64, True), (1, 300, 2, 128, True), (3, 64, 1, 128, False)])
+def test_attention_backward_in_one_launch_equals_two(torch, ops, B, S, H, DH, causal):
+    """Small launches run both halves of the backward pass as one kernel; the same problem in a group too large for that must give
+    the same bits, delta included."""
+    d, t = H * DH, B * S
+    gen = torch.Generator(device="cuda").manual_seed(S + DH)
+    qkv = torch.randn(t, 3 * d, generator=gen, device="cuda").to(torch.bfloat16)
+    do = torch.randn(t, d, generator=gen, device="cuda").to(torch.bfloat16)
+    per = (S + 127) // 128 * B * H
+    for rep in (1, 256 // per + 1):  # copies of the batch: the second is past 256 row blocks
+        n = rep * B
+        q, g = qkv.repeat(rep, 1), do.repeat(rep, 1)
+        o, dqkv = torch.zeros_like(g), torch.zeros_like(q)
+        lse, delta = torch.zeros(rep * t * H, device="cuda"), torch.zeros(rep * t * H, device="cuda")
+        ops.hydra_op_attention_fwd(n, S, H, DH, 3 * d, d, causal, DH ** -0.5, [q], [o], [lse])
+        ops.hydra_op_attention_bwd(n, S, H, DH, 3 * d, d, causal, DH ** -0.5, [q], [o], [g], [lse], [delta], [dqkv])
+        if rep == 1:
+            first = dqkv.clone(), delta.clone()
+    assert torch.equal(dqkv[:t], first[0]) and torch.equal(dqkv[-t:], first[0])
+    assert torch.equal(delta[:t * H], first[1])
