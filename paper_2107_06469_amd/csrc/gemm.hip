@@ -1698,11 +1698,15 @@ struct Dma {
 };
 // 128 x 128, 4 waves (2 x 2, each 64 x 64), ring of 4 stages of 16 KB: two workgroups per CU
 typedef Dma<bf16_t, 2, 2, 2, 2, 4> DmaMid;
-// 256 x 128, 8 waves (4 x 2, each 64 x 64), ring of 3 stages of 48 KB with 64 k each: one workgroup per CU, and a load of a
-// k-contiguous X covers 128 contiguous bytes per row.  For launches that it fits into one pass over the chip while
-// 256 x 256 tiles would leave half of it idle: 4 x [2432 rows, 30522 -> 768] input gradient 502 us, 128 x 128 tiles 670,
-// 256 x 256 tiles 634; 2 x [2048, 2048 -> 2048] forward 37 | 43 | 47, input gradient 39 | 39 | 43.
-typedef Dma<bf16_t, 4, 2, 2, 2, 3, 64> DmaWide;
+// The same tile with sub-tiles of 64 k in two stages (the same LDS): half as many barriers and, for a k-contiguous operand,
+// whole cache lines per load, but only one sub-tile in flight behind the current one.  With two workgroups on a CU the
+// other one covers that; with one it does not (us, 32 x 4 | 64 x 2 stages; tiles in brackets: forward [512] K = 1024 25.6 | 21.6
+// and 24.6 | 21.9, [1024] K = 2048 87 | 73, [128] K = 2048 21.9 | 24.8; input gradient [512] 20.4 | 19.4, [456] K = 30522 670 | 488,
+// [128] K = 4096 33 | 40).  256x128 tiles with three stages of 64 k, one workgroup per CU, are 2-9 % behind it.
+typedef Dma<bf16_t, 2, 2, 2, 2, 2, 64> DmaMidDeep;
+inline bool mid_deep(const GemmArgs& a) {
+  return a.x_kmajor && (long)((a.M + 127) / 128) * ((a.N + 127) / 128) * a.G > 256;
+}
 // What the direct-to-LDS kernels address: an operand with k as the slow index is read from the tile's first element with
 // 32-bit offsets, so its K x ld bytes must stay below 2 GiB.  (A k-contiguous operand may have any K: the last chunk's
 // elements past K are cleared in LDS.)
@@ -1810,7 +1814,7 @@ int split_for(const GemmArgs& a) {
 }
 
 // Tiles that are chosen but cannot be asked for by number
-enum { TILE_SMALL = 101, TILE_SMALL_DEEP = 102, TILE_WIDE = 103 };
+enum { TILE_SMALL = 101, TILE_SMALL_DEEP = 102 };
 typedef SmallTile<bf16_t, 16, 2> SmallBf16;
 typedef SmallTile<bf16_t, 8, 4> SmallBf16Deep;
 typedef SmallTile<float, 16, 2> SmallF32;
@@ -1835,7 +1839,6 @@ int choose_tile(const GemmArgs& a) {
   // 768 tiles 16.6 | 15).  Fewer than 96 rows would leave much of a 128-row tile empty.
   if (dma && (tiles(64, 64) <= 320 || a.M < 96)) return a.K > 1024 ? TILE_SMALL_DEEP : TILE_SMALL;
   if (a.M >= 96 && mid >= 64) {
-    if (const long wide = tiles(256, 128); dma && a.x_kmajor && a.M >= 192 && wide >= 160 && wide <= 256) return TILE_WIDE;
     // Too few big tiles for 256 CUs: 128 x 128 tiles win while they fit in one pass over the chip (two
     // workgroups per CU); beyond that a partly filled pass of big tiles is still the faster choice.
     return (a.M >= 192 && big >= 128 && mid > 512) ? 1 : 2;
@@ -1863,13 +1866,14 @@ int choose_update_tile(const GemmArgs& a) {
     if (dma && (sm <= 512 || (sm <= 2048 && a.K <= 1024))) return a.K > 1024 ? TILE_SMALL_DEEP : TILE_SMALL;
   }
   const int tile = choose_tile(a);
-  if (tile == TILE_WIDE) return 2;
   if (tile == 1 && a.K < 2048) {
     // With a short k-loop the state traffic of the epilogue dominates: with two workgroups per CU one streams
-    // state while the other runs its k-loop, which the 256x256 tile (one workgroup per CU) cannot do; with at most two
-    // 256x256 tiles per CU it is ahead all the same (us, 256x256 | 128x128: 256 tiles, K = 24 84 | 95, K = 256 85 | 96; 512
-    // tiles, K = 24 157 | 173, K = 128 157 | 220; 2048 tiles, K = 128 656 | 612, K = 512 731 | 628).
-    return a.dtype != GEMM_F32 && big <= 512 ? 1 : 2;
+    // state while the other runs its k-loop, which the 256x256 tile (one workgroup per CU) cannot do.  It is ahead all the
+    // same where the sum is very short and the tiles fill one or two passes over the chip (us, 256x256 | 128x128: 256 tiles,
+    // K = 24 84 | 95, K = 256 85 | 96; 512 tiles, K = 24 157 | 173, K = 128 157 | 220), and far behind where they just miss
+    // (260 tiles, K = 810: 192 | 143 with the layer's input gradient) or there are many (2048 tiles, K = 128 656 | 612, K = 512 731 | 628).
+    const bool full = (big > 232 && big <= 256) || (big > 464 && big <= 512);
+    return a.dtype != GEMM_F32 && a.K <= 256 && full ? 1 : 2;
   }
   return tile;
 }
@@ -1902,9 +1906,8 @@ hipError_t dispatch(const GemmArgs& a, hipStream_t s) {
   if constexpr (sizeof(T) == 2) {
     if (tile == TILE_SMALL) return SmallBf16::run(a, s);
     if (tile == TILE_SMALL_DEEP) return SmallBf16Deep::run(a, s);
-    if (tile == TILE_WIDE) return DmaWide::run_x(a, s);
     if (tile == 1 && dma_eligible(a) && DmaBig::eligible(a)) return DmaBig::run(a, s);
-    if (tile == 2 && dma_eligible(a)) return DmaMid::run(a, s);
+    if (tile == 2 && dma_eligible(a)) return mid_deep(a) ? DmaMidDeep::run_x(a, s) : DmaMid::run(a, s);
   } else {
     if (tile == TILE_SMALL) return SmallF32::run(a, s);
   }
@@ -1934,7 +1937,7 @@ hipError_t gemm_init() {
   if ((e = SmallBf16::attr()) != hipSuccess) return e;
   if ((e = SmallBf16Deep::attr()) != hipSuccess) return e;
   if ((e = SmallF32::attr()) != hipSuccess) return e;
-  if ((e = DmaWide::attr_x()) != hipSuccess) return e;
+  if ((e = DmaMidDeep::attr_x()) != hipSuccess) return e;
   e = init_tiles<bf16_t>();
   return e != hipSuccess ? e : init_tiles<float>();
 }

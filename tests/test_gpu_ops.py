@@ -569,11 +569,11 @@ def test_split_weight_gradient_matches_oracle_and_ignores_tile_and_group(torch, 
 @pytest.mark.parametrize("layout", ["fwd", "dgrad", "wgrad"])
 @pytest.mark.parametrize("dtype,M,N,K,G", [
     (1, 64, 64, 64, 2), (1, 96, 320, 320, 3), (1, 70, 40, 50, 2), (1, 33, 8, 5, 1), (1, 257, 136, 2047, 2), (1, 17, 1000, 129, 2),
-    (1, 600, 3000, 77, 3), (1, 2300, 1000, 300, 2), (0, 32, 32, 64, 2), (0, 64, 784, 768, 2), (0, 70, 40, 50, 2), (0, 33, 8, 5, 1),
+    (1, 600, 3000, 77, 3), (1, 2300, 1000, 300, 2), (1, 1100, 1030, 60, 4), (1, 1100, 1032, 130, 4), (0, 32, 32, 64, 2), (0, 64, 784, 768, 2), (0, 70, 40, 50, 2), (0, 33, 8, 5, 1),
     (0, 129, 136, 1027, 2), (0, 1000, 264, 40, 3)])
 def test_chosen_tile_gives_the_bits_of_the_general_one(torch, ops, dtype, M, N, K, G, layout):
-    """Sizes at which the automatic choice takes the 64x64, 32x32 and 256x128 tiles (edges of a tile, a sum that ends inside a
-    16-byte chunk with NaN stored behind it, one stage of k and several): the same bits as the 32x128 tile, for the plain
+    """Sizes at which the automatic choice takes the 64x64 and 32x32 tiles and the two rings of the 128x128 tile (edges of a tile, a sum
+    that ends inside a 16-byte chunk with NaN stored behind it, one stage of k and several): the same bits as the 32x128 tile, for the plain
     product, the epilogues and the update, in any group."""
     td = torch.float32 if dtype == 0 else torch.bfloat16
     gen = torch.Generator(device="cuda").manual_seed(M * 7 + N * 3 + K)
