@@ -582,8 +582,10 @@ static hipError_t ln_bwd_pick(const LnBwdArgs& a, hipStream_t s) {
   const dim3 grid(ln_bwd_blocks(a.rows, a.d), a.G);
   if (a.d <= LN_WAVE_ROW_MAX) {
     // 64 rows over 16 waves (one batch each) where a lane owns at most 8 columns, over 8 waves beyond (the cross-wave sums
-    // need NW x 8 d bytes of LDS: 64 KB either way)
+    // need NW x 8 d bytes of LDS: 64 KB either way); many wide fp32 rows over 4 waves (2 x [9000, 800]
+    // 49 us, over 8 waves 52.5; bf16 3 x [14483, 616] over 8 waves 52 us, over 4 57)
     if (a.d <= 512) hipLaunchKernelGGL((ln_bwd_kernel<T, 1, 16, sizeof(T) == 2 ? 4 : 2>), grid, dim3(1024), (size_t)16 * 8 * a.d, s, a);
+    else if (sizeof(T) == 4 && a.rows > 4096) hipLaunchKernelGGL((ln_bwd_kernel<T, 2, 4, 2>), grid, dim3(256), (size_t)4 * 8 * a.d, s, a);
     else hipLaunchKernelGGL((ln_bwd_kernel<T, 2, 8, 2>), grid, dim3(512), (size_t)8 * 8 * a.d, s, a);
   } else if (a.d <= 2048) {
     hipLaunchKernelGGL((ln_bwd_wide_kernel<T, 1>), grid, dim3(256), 0, s, a);

@@ -196,7 +196,7 @@ def test_embedding_forward_and_backward(torch, ops, dtype):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("G,rows,d", [(2, 63, 512), (2, 129, 520), (1, 64, 8), (3, 65, 1024), (1, 1, 504), (4, 8193, 128), (16, 2051, 1016), (2, 1281, 264),
-                                       (2, 1280, 1024), (3, 257, 40)])
+                                       (2, 1280, 1024), (3, 257, 40), (1, 4097, 616), (2, 4096, 640)])
 def test_layernorm_row_batches(torch, ops, dtype, G, rows, d):
     """Row counts around a workgroup's 64 rows and a wave's batch, widths around the 512- and 1024-column limits, and launches large
     enough for several rows per wave in the forward pass, against fp64 (the column sums to 1e-5 of their terms' size)."""
