@@ -148,6 +148,23 @@ __device__ __forceinline__ ColsBase cols_base(const uint4* tile, int col0, int l
   b.a1 = base + (unsigned)((r1 * NCH + (kc ^ swz<DH>(r1))) * 16 + half * 8);
   return b;
 }
+// At DH = 128 a row is 256 bytes and the bits of a chunk's number in an address are XOR-ed with the row's term, so all of a lane's
+// bases follow from one of each kind: chunk 2 kk more is address ^ 32 kk; column block c is ^ 64 c, and row r0 + 8 is ^ 32 (its
+// term differs in one bit) and 8 rows.  The dk/dv kernel, which has no register to spare, works them out per 32 queries (14
+// instructions) instead of keeping 16, so that no K or V fragment goes to scratch (a reload waits for the next tile's loads).
+__device__ __forceinline__ void bases128(const uint4* (&rows)[8], ColsBase (&cols)[4]) {
+  unsigned r = lds_byte_addr(rows[0]), c0 = cols[0].a0;
+  asm("" : "+v"(r));  // not to be hoisted
+  asm("" : "+v"(c0));
+#pragma unroll
+  for (int kk = 1; kk < 8; ++kk)
+    rows[kk] = (const uint4*)(__attribute__((address_space(3))) const uint4*)(uintptr_t)(r ^ (unsigned)(kk * 32));
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    cols[c].a0 = c0 ^ (unsigned)(c * 64);
+    cols[c].a1 = (c0 ^ (unsigned)(c * 64 + 32)) + 8u * 16u * 16u;
+  }
+}
 template <int DH>
 __device__ __forceinline__ uint4 read_cols_at(const ColsBase& b, unsigned off) {
   typedef __attribute__((ext_vector_type(4))) short s16x4;
@@ -171,7 +188,7 @@ __device__ __forceinline__ uint4 pack_half(const f32x16& p, int x) {
 template <int DH>
 __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const AttnArgs a) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
-  extern __shared__ uint4 lds[];
+  extern __shared__ __attribute__((aligned(256))) uint4 lds[];
   // two buffers of K [64][NCH], V [64][NCH]
   uint4* tK = lds;
   uint4* tV = lds + 64 * NCH;
@@ -247,10 +264,10 @@ __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const A
     // weight is then no longer exactly 1 in bf16.)
     const float2 mh = wave_swap32(mx);
     mx = fmaxf(mh.x, mh.y) * sc;
+    float alpha = 1.f;
     if (__any(mx > m_run)) {
       const float m_new = fmaxf(m_run, mx);
-      const float alpha = fast_exp2(m_run - m_new);
-      l_run *= alpha;
+      alpha = fast_exp2(m_run - m_new);
       m_run = m_new;
 #pragma unroll
       for (int c = 0; c < NC; ++c)
@@ -266,7 +283,8 @@ __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const A
         s[sub][r] = p;
         rs += p;
       }
-    l_run += rs;
+    const float2 rh = wave_swap32(rs);  // a query's keys are shared by lanes l and l^32
+    l_run = fmaf(l_run, alpha, rh.x + rh.y);
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
@@ -280,9 +298,6 @@ __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const A
     tile(t, std::integral_constant<int, 0>());
     if (t + 1 < n_tiles) tile(t + 1, std::integral_constant<int, 1>());
   }
-  // a query's keys are shared by lanes l and l^32
-  const float2 lh = wave_swap32(l_run);
-  l_run = lh.x + lh.y;
   if (iq < a.S) {
     const float inv = 1.f / l_run;
     bf16_t* o = a.o[gi] + ((size_t)b * a.S + iq) * a.ld_o + h * DH;
@@ -300,15 +315,17 @@ __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const A
 
 // ---- backward, dq (also writes delta) ------------------------------------------------------------------
 // The lane's part (chunks 2 kk + g of a row's DH columns) of delta = sum of do * o: the two bodies below that compute it take
-// the same operations in the same order.
+// the same operations in the same order.  This order, the row sums' (a tile's 64 keys, then the running sum) and dP - delta
+// after the product are part of the results: tests hold them to recorded bits.
 template <int NK>
 __device__ __forceinline__ float delta_part(const uint4 (&dof)[NK], const uint4 (&of)[NK]) {
+#pragma clang fp contract(off)
   float delta = 0.f;
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) {
     const uint32_t dw[4] = {dof[kk].x, dof[kk].y, dof[kk].z, dof[kk].w}, ow[4] = {of[kk].x, of[kk].y, of[kk].z, of[kk].w};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) delta = fmaf(bf_hi(dw[e]), bf_hi(ow[e]), fmaf(bf_lo(dw[e]), bf_lo(ow[e]), delta));
+    for (int e = 0; e < 4; ++e) delta += fmaf(bf_lo(dw[e]), bf_lo(ow[e]), bf_hi(dw[e]) * bf_hi(ow[e]));
   }
   return delta;
 }
@@ -316,7 +333,7 @@ __device__ __forceinline__ float delta_part(const uint4 (&dof)[NK], const uint4 
 template <int DH>
 __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, int wg) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
-  extern __shared__ uint4 lds[];
+  extern __shared__ __attribute__((aligned(256))) uint4 lds[];
   // two buffers of K [64][NCH], V [64][NCH]
   uint4* tK = lds;
   uint4* tV = lds + 64 * NCH;
@@ -349,9 +366,6 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, int wg) {
   }
   const float2 dh = wave_swap32(delta_part<NK>(dof, of));
   const float delta = dh.x + dh.y;
-  f32x16 nd;  // -delta: the accumulator that dP starts from, so that dP - delta costs no instruction
-#pragma unroll
-  for (int r = 0; r < 16; ++r) nd[r] = -delta;
   const float lse2 = iq < a.S ? a.lse[gi][(size_t)bh * a.S + iq] * LOG2E : 0.f;
   if (iq < a.S && g == 0) a.delta[gi][(size_t)bh * a.S + iq] = delta;
   f32x16 acc[NC];
@@ -378,8 +392,7 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, int wg) {
     for (int sub = 0; sub < 2; ++sub) {
       f32x16 s, dp;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = 0.f;
-      dp = nd;
+      for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
 #pragma unroll
       for (int kk = 0; kk < NK; ++kk) {
         s = mfma(kr[kk][B + sub * 32 * NCH], qf[kk], s);
@@ -393,7 +406,7 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, int wg) {
         }
       }
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = fast_exp2(fmaf(s[r], sc, -lse2)) * dp[r];
+      for (int r = 0; r < 16; ++r) s[r] = fast_exp2(fmaf(s[r], sc, -lse2)) * (dp[r] - delta);
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
         const uint4 df = pack_half(s, x);
@@ -421,16 +434,17 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, int wg) {
 }
 
 // ---- backward, dk and dv -----------------------------------------------------------------------------------
-// Two waves per SIMD at DH = 128 (256 registers with 13 spilled; 376, one wave, when tiles passed through registers and the
-// accumulators moved between the two register files on every tile), three at DH = 64 (162; 200 before).  Together with
-// the dq kernel, us before | now: 8 x 32 heads, 2048, 128, causal 1645 | 1281, 2 x [4 x 16, 1024, 128] 360 | 282,
-// 4 x [32 x 12 heads, 512, 64] 527 | 477.  Held to one wave per SIMD at DH = 128: 1440.
+// Two waves per SIMD at DH = 128 (256 registers and 28 bytes of scratch; 376, one wave, when tiles passed through registers and the
+// accumulators moved between the two register files on every tile), three at DH = 64 (168; 200 before).  Together with
+// the dq kernel, us before | now: 8 x 32 heads, 2048, 128, causal 1645 | 1250, 2 x [4 x 16, 1024, 128] 360 | 269,
+// 4 x [32 x 12 heads, 512, 64] 527 | 480.  Held to one wave per SIMD at DH = 128: 1440; with its 16 LDS bases kept instead of
+// bases128 (64 bytes of scratch, K and V fragments among them): 1362.
 // OWN: the kernel works out delta itself instead of reading what the dq kernel left.
 template <int DH, bool OWN>
 __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, int wg) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
-  extern __shared__ uint4 lds[];
-  // two buffers of Q [64][NCH], dO [64][NCH], then two of [2][64]: lse*log2e, -delta
+  extern __shared__ __attribute__((aligned(256))) uint4 lds[];
+  // two buffers of Q [64][NCH], dO [64][NCH], then two of [2][64]: lse*log2e, delta
   uint4* tQ = lds;
   constexpr int BUF = 2 * 64 * NCH;  // chunks per buffer
   float* const st = reinterpret_cast<float*>(lds + 2 * BUF);
@@ -452,12 +466,12 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, int wg) {
   auto fetch = [&](int t, unsigned buf) {
     dma_q.issue(base, a.ld_qkv, h * DH, t * 64, a.S, lds0 + buf, wave);
     dma_o.issue(dobase, a.ld_o, h * DH, t * 64, a.S, lds0 + buf + 64 * NCH * 16, wave);
-    // threads 0..63: lse*log2e, 64..127: -delta of query 64 t + tid%64
+    // threads 0..63: lse*log2e, 64..127: delta of query 64 t + tid%64
     if (wave < (OWN ? 1 : 2)) {
       float* const p = (wave == 0 ? const_cast<float*>(a.lse[gi]) : a.delta[gi]) + (size_t)bh * a.S + t * 64;
       const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(p, 0, min(a.S - t * 64, 64) * 4, 0x00020000);
       pst = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, 0, 0));  // zero past the last query
-      pst *= wave == 0 ? LOG2E : -1.0f;
+      if (wave == 0) pst *= LOG2E;
     }
     if (OWN && wave >= 2) {  // waves 2 and 3: 32 queries each, two lanes to a query as in the dq kernel
       const int i = t * 64 + (wave - 2) * 32 + li;
@@ -476,7 +490,7 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, int wg) {
     if (wave < (OWN ? 1 : 2)) stb[tid] = pst;
     if (OWN && wave >= 2) {
       const float2 dh = wave_swap32(delta_part<NK>(own_do, own_o));
-      if (g == 0) stb[64 + (wave - 2) * 32 + li] = -(dh.x + dh.y);
+      if (g == 0) stb[64 + (wave - 2) * 32 + li] = dh.x + dh.y;
     }
   };
   if (t0 < n_tiles) {
@@ -515,12 +529,10 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, int wg) {
     const bool edge = i0 + 64 > a.S || (a.causal && i0 < blk * 128 + wave * 32 + 31);
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
+      if constexpr (DH == 128) bases128(qr, qc);
       f32x16 s, dp;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        s[r] = 0.f;
-        dp[r] = stb[64 + sub * 32 + 8 * (r >> 2) + 4 * g + (r & 3)];  // -delta: dP - delta costs no instruction
-      }
+      for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
 #pragma unroll
       for (int kk = 0; kk < NK; ++kk) {
         s = mfma(qr[kk][B + sub * 32 * NCH], kf[kk], s);
@@ -539,7 +551,7 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, int wg) {
         const int il = sub * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
         const float p = fast_exp2(fmaf(s[r], sc, -stb[il]));
         s[r] = p;
-        ds[r] = p * dp[r];
+        ds[r] = p * (dp[r] - stb[64 + il]);
       }
 #pragma unroll
       for (int x = 0; x < 2; ++x) {

@@ -2,7 +2,9 @@
 layer functions (GPU only).  bf16 inputs are rounded once on the host and the oracle gets exactly those
 values in fp64; tolerances are the bf16 output rounding (2^-8 relative) plus, for attention, the bf16
 rounding of the probabilities that feed the second matrix product."""
+import hashlib
 import math
+import os
 
 import numpy as np
 import pytest
@@ -287,3 +289,30 @@ def test_attention_backward_in_one_launch_equals_two(torch, ops, B, S, H, DH, ca
             first = dqkv.clone(), delta.clone()
     assert torch.equal(dqkv[:t], first[0]) and torch.equal(dqkv[-t:], first[0])
     assert torch.equal(delta[:t * H], first[1])
+
+
+def attention_bits(torch, ops, G, B, S, H, DH, causal):
+    """Digest of o, lse, dqkv of G problems of frozen pseudo-random inputs."""
+    d, t, r = H * DH, B * S, np.random.RandomState(S * 7 + DH)
+    mk = lambda *sh: torch.from_numpy(r.standard_normal(sh).astype(np.float32)).to(torch.bfloat16).cuda()  # noqa: E731
+    qkv, do = [mk(t, 3 * d) for _ in range(G)], [mk(t, d) for _ in range(G)]
+    o, dqkv = [torch.zeros_like(x) for x in do], [torch.zeros_like(x) for x in qkv]
+    lse, delta = ([torch.zeros(t * H, device="cuda") for _ in range(G)] for _ in range(2))
+    ops.hydra_op_attention_fwd(B, S, H, DH, 3 * d, d, causal, DH ** -0.5, qkv, o, lse)
+    ops.hydra_op_attention_bwd(B, S, H, DH, 3 * d, d, causal, DH ** -0.5, qkv, o, do, lse, delta, dqkv)
+    h = hashlib.sha256()
+    for x in o + lse + dqkv:
+        h.update(x.cpu().view(torch.uint8).numpy().tobytes())
+    return h.hexdigest()[:32]
+
+
+def _golden_lines(name):
+    with open(os.path.join(os.path.dirname(__file__), "golden", name)) as f:
+        return [ln.split() for ln in f if ln.strip() and not ln.startswith("#")]
+
+
+@pytest.mark.parametrize("line", _golden_lines("attention_bits.txt"), ids=lambda ln: "x".join(ln[:6]))
+def test_attention_keeps_its_bits(torch, ops, line):
+    """A training run repeats itself bit for bit from one version of the kernels to the next: the order of the row sums, of dO.O and of
+    dP - delta is part of the result (twenty Adam steps turn a changed last bit into 1e-3 of a parameter)."""
+    assert attention_bits(torch, ops, *[int(x) for x in line[:6]]) == line[6]
