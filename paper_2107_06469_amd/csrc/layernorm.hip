@@ -6,8 +6,10 @@
 // One wavefront owns a row (in the backward pass only up to 1024 elements; wider rows are shared by the four
 // waves of a workgroup): each lane keeps its 16-byte chunks of the row in registers, statistics are
 // butterfly reductions over the 64 lanes (wave_math.h, fixed order).  The column sums of the backward pass are
-// accumulated per workgroup over a fixed range of rows, written as partial sums, and added over
-// workgroups in index order by a second kernel: no atomics, so results do not depend on timing.
+// accumulated over blocks of 64 (wide rows: 32) rows, and the blocks' partial sums are added in a fixed order, as a rule by
+// a second kernel: no atomics, so results do not depend on timing.  Rows of up to 1024 elements: rows r, r + 4, ... of a
+// block are one chain of multiply-adds, the four chains are added in order, then the blocks in 16 ranges and the ranges.
+// Several kernels take that order, so which of them runs never changes a bit.
 #include "kernels.h"
 #include "wave_math.h"
 
@@ -157,105 +159,105 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const LnArgs a) {
   }
 }
 
-// dx and per-workgroup partial column sums, rows of up to 1024 elements.  Workgroup b owns rows [b*64, b*64+64); wave w of NW takes
-// rows b*64 + w, + NW, ...; partial sums go to part[g][b][2][d].
-// A wave takes its rows in batches of NB: all loads of a batch (x, dy, the additive term, the statistics) are issued
-// before its first row is reduced, so that the batch costs one round trip to memory.  Small launches are bound by a
-// wave's serial rows, large ones by memory; 4 waves of 16 rows, the next row's loads ahead of the current one's
-// reduction, against this form (us): 4 x [1024, 256] bf16 18.1 | 8.7, 4 x [4096, 512] 22 | 13.8, 4 x [1024, 768] 20.7 | 14.5,
-// 4 x [16384, 512] 51 | 46, 4 x [16384, 768] 87 | 86 (4.7 TB/s: a device copy's rate), fp32 165 | 161.
-template <typename T, int LN_MAXC, int NW, int NB>
-__global__ __launch_bounds__(NW * 64) void ln_bwd_kernel(const LnBwdArgs a) {
-  extern __shared__ float red[];  // [NW][2][d]
+// dx and per-workgroup partial column sums, rows of up to 1024 elements.  Workgroup b owns rows [b*64, b*64+64); wave w takes rows
+// b*64 + w, +4, +8, ... in ascending order; partial sums go to part[g][b][2][d].
+template <typename T, int C>
+struct LnRow {  // one row's operands as they lie in memory: chunks lane, lane + 64, ...
+  static constexpr int RW = sizeof(T) == 2 ? 1 : 2;  // 16-byte pieces per 8 elements
+  uint4 x[C][RW], dy[C][RW], add[C][RW];
+  float mu, rstd;
+  __device__ __forceinline__ void fetch(const LnBwdArgs& a, int g, int row, int lane, int nch) {
+    const uint4* px = reinterpret_cast<const uint4*>(static_cast<const T*>(a.x[g]) + (size_t)row * a.ld);
+    const uint4* pd = reinterpret_cast<const uint4*>(static_cast<const T*>(a.dy[g]) + (size_t)row * a.ld);
+    const uint4* pa = reinterpret_cast<const uint4*>(static_cast<const T*>(a.add[g]) + (size_t)row * a.ld);
+    mu = a.mean[g][row];
+    rstd = a.rstd[g][row];
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+      const int c = lane + 64 * i;
+      if (c < nch) {
+#pragma unroll
+        for (int q = 0; q < RW; ++q) {
+          x[i][q] = px[c * RW + q];
+          dy[i][q] = pd[c * RW + q];
+          if (a.add[g]) add[i][q] = pa[c * RW + q];
+        }
+      }
+    }
+  }
+};
+// One row: its dx is stored, its terms are added to the column sums where SUMS.  Every multiply-add is written out, so that all
+// kernels give the same bits.
+template <typename T, int C, bool SUMS>
+__device__ __forceinline__ void ln_bwd_row(const LnBwdArgs& a, int g, int row, int lane, int nch, const LnRow<T, C>& r,
+                                           const float (&ga)[C][8], float (&sg)[C][8], float (&sb)[C][8]) {
+#pragma clang fp contract(off)
+  float xh[C][8], gg[C][8];
+  float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+  for (int i = 0; i < C; ++i) {
+    if (lane + 64 * i < nch) {
+      float xv[8], dv[8];
+      unpack8<T>(r.x[i], xv);
+      unpack8<T>(r.dy[i], dv);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        xh[i][e] = (xv[e] - r.mu) * r.rstd;
+        gg[i][e] = dv[e] * ga[i][e];
+        s1 = fmaf(dv[e], ga[i][e], s1);
+        s2 = fmaf(gg[i][e], xh[i][e], s2);
+        if (SUMS) {
+          sg[i][e] = fmaf(dv[e], xh[i][e], sg[i][e]);
+          sb[i][e] += dv[e];
+        }
+      }
+    }
+  }
+  const float c1 = wave_sum(s1) / (float)a.d, c2 = wave_sum(s2) / (float)a.d;
+#pragma unroll
+  for (int i = 0; i < C; ++i) {
+    const int c = lane + 64 * i;
+    if (c < nch) {
+      float o[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = r.rstd * fmaf(-xh[i][e], c2, gg[i][e] - c1);
+      if (a.add[g]) {
+        float av[8];
+        unpack8<T>(r.add[i], av);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] += av[e];
+      }
+      st8<T>(static_cast<T*>(a.dx[g]) + (size_t)row * a.ld + 8 * c, o);
+    }
+  }
+}
+// Many rows: workgroups of 4 waves, each with its next row's loads in flight while it reduces the current one; bound by
+// memory.  us: 4 x [16384, 768] bf16 97 (4.2 TB/s), 3 x [14483, 616] 46, 2 x [16384, 1024] 53; fp32 4 x [16384, 768] 175.  With two rows in
+// flight 94 | 53 | 54 | 175, with four and no prefetch 101 | 60 | 57 | 205, over 8 waves (one workgroup per CU) 96 | 52 | 55 | 175.
+template <typename T, int C>
+__global__ __launch_bounds__(256) void ln_bwd_kernel(const LnBwdArgs a) {
+  extern __shared__ float red[];  // [4][2][d]
   const int g = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nch = a.d >> 3;
-  constexpr int RW = sizeof(T) == 2 ? 1 : 2;  // 16-byte pieces per 8 elements
-  static_assert(LN_ROWS_PER_WG % (NW * NB) == 0, "whole batches");
-  const int row0 = blockIdx.x * LN_ROWS_PER_WG + wave;
-  const T* X = static_cast<const T*>(a.x[g]);
-  const T* DY = static_cast<const T*>(a.dy[g]);
-  const T* ADD = static_cast<const T*>(a.add[g]);
-  T* DX = static_cast<T*>(a.dx[g]);
-  const float* mean = a.mean[g];
-  const float* rs = a.rstd[g];
-  const float* gamma = a.gamma[g];
-  float ga[LN_MAXC][8], sg[LN_MAXC][8], sb[LN_MAXC][8];
+  const int first = blockIdx.x * LN_ROWS_PER_WG, row0 = first + wave, end = first + min(a.rows - first, LN_ROWS_PER_WG);
+  float ga[C][8], sg[C][8], sb[C][8];
 #pragma unroll
-  for (int i = 0; i < LN_MAXC; ++i) {
+  for (int i = 0; i < C; ++i) {
     const int c = lane + 64 * i;
 #pragma unroll
     for (int e = 0; e < 8; ++e) sg[i][e] = sb[i][e] = ga[i][e] = 0.f;
-    if (c < nch) ld8<float>(gamma + 8 * c, ga[i]);
+    if (c < nch) ld8<float>(a.gamma[g] + 8 * c, ga[i]);
   }
-  for (int r0 = 0; r0 < LN_ROWS_PER_WG; r0 += NW * NB) {
-    if (row0 + r0 >= a.rows) break;
-    uint4 rx[NB][LN_MAXC][RW], rdy[NB][LN_MAXC][RW], radd[NB][LN_MAXC][RW];
-    float mu[NB], rstd[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int row = row0 + r0 + b * NW;
-      const bool live = row < a.rows;
-      const size_t o = (size_t)(live ? row : row0) * a.ld;
-      mu[b] = live ? mean[row] : 0.f;
-      rstd[b] = live ? rs[row] : 0.f;
-#pragma unroll
-      for (int i = 0; i < LN_MAXC; ++i) {
-        const int c = lane + 64 * i;
-        if (live && c < nch) {
-#pragma unroll
-          for (int q = 0; q < RW; ++q) {
-            rx[b][i][q] = reinterpret_cast<const uint4*>(X + o)[c * RW + q];
-            rdy[b][i][q] = reinterpret_cast<const uint4*>(DY + o)[c * RW + q];
-            if (ADD) radd[b][i][q] = reinterpret_cast<const uint4*>(ADD + o)[c * RW + q];
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int row = row0 + r0 + b * NW;
-      if (row >= a.rows) break;
-      float xh[LN_MAXC][8], gg[LN_MAXC][8];
-      float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-      for (int i = 0; i < LN_MAXC; ++i) {
-        if (lane + 64 * i < nch) {
-          float xv[8], dv[8];
-          unpack8<T>(rx[b][i], xv);
-          unpack8<T>(rdy[b][i], dv);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            xh[i][e] = (xv[e] - mu[b]) * rstd[b];
-            gg[i][e] = dv[e] * ga[i][e];
-            s1 += gg[i][e];
-            s2 += gg[i][e] * xh[i][e];
-            sg[i][e] += dv[e] * xh[i][e];
-            sb[i][e] += dv[e];
-          }
-        }
-      }
-      const float c1 = wave_sum(s1) / (float)a.d, c2 = wave_sum(s2) / (float)a.d;
-#pragma unroll
-      for (int i = 0; i < LN_MAXC; ++i) {
-        const int c = lane + 64 * i;
-        if (c < nch) {
-          float o[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] = rstd[b] * (gg[i][e] - c1 - xh[i][e] * c2);
-          if (ADD) {
-            float av[8];
-            unpack8<T>(radd[b][i], av);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] += av[e];
-          }
-          st8<T>(DX + (size_t)row * a.ld + 8 * c, o);
-        }
-      }
-    }
+  LnRow<T, C> cur, nxt;
+  if (row0 < end) nxt.fetch(a, g, row0, lane, nch);
+  for (int row = row0; row < end; row += 4) {
+    cur = nxt;
+    if (row + 4 < end) nxt.fetch(a, g, row + 4, lane, nch);
+    ln_bwd_row<T, C, true>(a, g, row, lane, nch, cur, ga, sg, sb);
   }
   // the waves' partial sums are added in wave order
 #pragma unroll
-  for (int i = 0; i < LN_MAXC; ++i) {
+  for (int i = 0; i < C; ++i) {
     const int c = lane + 64 * i;
     if (c < nch) {
       st8<float>(&red[(wave * 2 + 0) * a.d + 8 * c], sg[i]);
@@ -264,144 +266,187 @@ __global__ __launch_bounds__(NW * 64) void ln_bwd_kernel(const LnBwdArgs a) {
   }
   __syncthreads();
   float* part = a.part[g] + (size_t)blockIdx.x * 2 * a.d;
-  for (int j = threadIdx.x; j < 2 * a.d; j += NW * 64) {  // red is [wave][2 d]
+  for (int j = threadIdx.x; j < 2 * a.d; j += 256) {  // red is [wave][2 d]
     float t = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) t += red[w * 2 * a.d + j];
+    for (int w = 0; w < 4; ++w) t += red[w * 2 * a.d + j];
     part[j] = t;
   }
 }
 
-// Small launches: one kernel instead of two.  The row statistics are inputs here, so the column sums need nothing from the
-// rows' own pass: workgroups past the row blocks add up 32 columns each over all rows, straight from x and dy (which
-// the row blocks read at the same time), instead of partial sums that a second launch collects.  Row blocks: 16 waves,
-// one row each.  Column blocks: thread (row group, chunk of 8 columns) adds every 256th row in ascending order, the row
-// groups of a wave are added by a butterfly and the 16 waves in wave order.
-// Two launches | this one, us: 4 x [1024, 256] bf16 8.9 + 2.8 | 7.0, 4 x [152, 256] 8.4 + 2.8 | 4.5, 4 x [1024, 768] 14.6 + 3.9 |
-// 11.0, fp32 4 x [1024, 256] 9.2 + 2.8 | 7.9, and a launch gap less.  A column block reads its columns of all rows through one
-// compute unit, which sets the limit: 4 x [2048, 256] 9.4 + 2.8 | 10.7, 8 x [2048, 512] 13.8 + 3.9 | 25.6.
-constexpr int LN_SMALL_ROWS = 1280, LN_SMALL_COLS = 32;
-template <typename T, int LN_MAXC>
-__global__ __launch_bounds__(1024) void ln_bwd_small_kernel(const LnBwdArgs a, int row_blocks) {
-  __shared__ float red[16][2][LN_SMALL_COLS];
-  const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  constexpr int RW = sizeof(T) == 2 ? 1 : 2;  // 16-byte pieces per 8 elements
-  const T* X = static_cast<const T*>(a.x[g]);
-  const T* DY = static_cast<const T*>(a.dy[g]);
-  const float* mean = a.mean[g];
-  const float* rs = a.rstd[g];
-  if ((int)blockIdx.x < row_blocks) {
-    const int row = blockIdx.x * 16 + wave;
-    if (row >= a.rows) return;
-    const T* ADD = static_cast<const T*>(a.add[g]);
-    const float* gamma = a.gamma[g];
-    const int nch = a.d >> 3;
-    const size_t o = (size_t)row * a.ld;
-    uint4 rx[LN_MAXC][RW], rdy[LN_MAXC][RW], radd[LN_MAXC][RW];
-    float ga[LN_MAXC][8];
-    const float mu = mean[row], rstd = rs[row];
+// Up to a workgroup per CU and d <= 512: 16 waves per 64 rows, four rows each, so that a block is a quarter as long.  The row sums
+// need no order among rows; the column sums keep the order of ln_bwd_kernel: waves w, 4 + w, 8 + w, 12 + w hold the rows of its
+// wave w in turn and hand the sums on through LDS.  us, this | 4 waves of 16 rows: 4 x [2048, 256] bf16 12.0 | 17.5, 4 x [4096, 512]
+// (256 blocks) 17.9 | 20.2, 16 x [2048, 512] (512) 30 | 25.5; fp32 2 x [4096, 512] (128) 18.9 | 20.6, 4 x [4096, 512] 26.7 | 25.4.
+template <typename T>
+__global__ __launch_bounds__(1024) void ln_bwd_chain_kernel(const LnBwdArgs a) {
+  __shared__ float4 red[4][4][64];  // [chain][sums of dgamma: columns 0-3, 4-7 of the lane's chunk; of dbeta][lane]
+  const int g = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, w = wave & 3, quarter = wave >> 2;
+  const int nch = a.d >> 3, row0 = blockIdx.x * LN_ROWS_PER_WG + w + 16 * quarter;
+  float ga[1][8], none[1][8], xh[4][8], dv[4][8];
+  LnRow<T, 1> r[4];
 #pragma unroll
-    for (int i = 0; i < LN_MAXC; ++i) {
-      const int c = lane + 64 * i;
-      if (c < nch) {
+  for (int b0 = 0; b0 < 4; b0 += 2) {  // two rows in flight: four spill with fp32
 #pragma unroll
-        for (int q = 0; q < RW; ++q) {
-          rx[i][q] = reinterpret_cast<const uint4*>(X + o)[c * RW + q];
-          rdy[i][q] = reinterpret_cast<const uint4*>(DY + o)[c * RW + q];
-          if (ADD) radd[i][q] = reinterpret_cast<const uint4*>(ADD + o)[c * RW + q];
-        }
-        ld8<float>(gamma + 8 * c, ga[i]);
-      }
-    }
-    float xh[LN_MAXC][8], gg[LN_MAXC][8];
-    float s1 = 0.f, s2 = 0.f;
+    for (int b = b0; b < b0 + 2; ++b)
+      if (row0 + 4 * b < a.rows) r[b].fetch(a, g, row0 + 4 * b, lane, nch);
+    if (b0 == 0 && lane < nch) ld8<float>(a.gamma[g] + 8 * lane, ga[0]);
 #pragma unroll
-    for (int i = 0; i < LN_MAXC; ++i)
-      if (lane + 64 * i < nch) {
-        float xv[8], dv[8];
-        unpack8<T>(rx[i], xv);
-        unpack8<T>(rdy[i], dv);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          xh[i][e] = (xv[e] - mu) * rstd;
-          gg[i][e] = dv[e] * ga[i][e];
-          s1 += gg[i][e];
-          s2 += gg[i][e] * xh[i][e];
-        }
-      }
-    const float c1 = wave_sum(s1) / (float)a.d, c2 = wave_sum(s2) / (float)a.d;
-#pragma unroll
-    for (int i = 0; i < LN_MAXC; ++i) {
-      const int c = lane + 64 * i;
-      if (c < nch) {
-        float out[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) out[e] = rstd * (gg[i][e] - c1 - xh[i][e] * c2);
-        if (ADD) {
-          float av[8];
-          unpack8<T>(radd[i], av);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) out[e] += av[e];
-        }
-        st8<T>(static_cast<T*>(a.dx[g]) + o + 8 * c, out);
-      }
-    }
-    return;
-  }
-  const int col0 = ((int)blockIdx.x - row_blocks) * LN_SMALL_COLS, c = col0 / 8 + (tid & 3);  // chunk of 8 columns
-  const bool live = 8 * c < a.d;
-  float sg[8], sb[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) sg[e] = sb[e] = 0.f;
-  constexpr int NB = 4;  // rows whose loads are in flight together
-  for (int r0 = tid >> 2; r0 < a.rows; r0 += 256 * NB) {
-    uint4 rx[NB][RW], rdy[NB][RW];
-    float mu[NB], rstd[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int row = r0 + 256 * b;
-      mu[b] = rstd[b] = 0.f;
-#pragma unroll
-      for (int q = 0; q < RW; ++q) rx[b][q] = rdy[b][q] = make_uint4(0, 0, 0, 0);
-      if (row < a.rows && live) {
-        mu[b] = mean[row];
-        rstd[b] = rs[row];
-#pragma unroll
-        for (int q = 0; q < RW; ++q) {
-          rx[b][q] = reinterpret_cast<const uint4*>(X + (size_t)row * a.ld)[c * RW + q];
-          rdy[b][q] = reinterpret_cast<const uint4*>(DY + (size_t)row * a.ld)[c * RW + q];
-        }
-      }
-    }
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      if (r0 + 256 * b >= a.rows) break;
-      float xv[8], dv[8];
-      unpack8<T>(rx[b], xv);
-      unpack8<T>(rdy[b], dv);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        sg[e] += dv[e] * ((xv[e] - mu[b]) * rstd[b]);
-        sb[e] += dv[e];
-      }
-    }
+    for (int b = b0; b < b0 + 2; ++b)
+      if (row0 + 4 * b < a.rows) ln_bwd_row<T, 1, false>(a, g, row0 + 4 * b, lane, nch, r[b], ga, none, none);
   }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    sg[e] = wave_sum_mod4(sg[e]);
-    sb[e] = wave_sum_mod4(sb[e]);
+  for (int b = 0; b < 4; ++b)
+    if (row0 + 4 * b < a.rows && lane < nch) {
+      float xv[8];
+      unpack8<T>(r[b].x[0], xv);
+      unpack8<T>(r[b].dy[0], dv[b]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) xh[b][e] = (xv[e] - r[b].mu) * r[b].rstd;
+    }
+  for (int p = 0; p < 4; ++p) {
+    if (quarter == p) {
+#pragma clang fp contract(off)
+      float sg[8], sb[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sg[e] = sb[e] = 0.f;
+      if (p > 0) {
+        const float4 t[4] = {red[w][0][lane], red[w][1][lane], red[w][2][lane], red[w][3][lane]};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          sg[4 * h] = t[h].x; sg[4 * h + 1] = t[h].y; sg[4 * h + 2] = t[h].z; sg[4 * h + 3] = t[h].w;
+          sb[4 * h] = t[2 + h].x; sb[4 * h + 1] = t[2 + h].y; sb[4 * h + 2] = t[2 + h].z; sb[4 * h + 3] = t[2 + h].w;
+        }
+      }
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        if (row0 + 4 * b < a.rows && lane < nch) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            sg[e] = fmaf(dv[b][e], xh[b][e], sg[e]);
+            sb[e] += dv[b][e];
+          }
+        }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        red[w][h][lane] = make_float4(sg[4 * h], sg[4 * h + 1], sg[4 * h + 2], sg[4 * h + 3]);
+        red[w][2 + h][lane] = make_float4(sb[4 * h], sb[4 * h + 1], sb[4 * h + 2], sb[4 * h + 3]);
+      }
+    }
+    __syncthreads();
   }
-  if (lane < 4) {
-    st8<float>(&red[wave][0][8 * lane], sg);
-    st8<float>(&red[wave][1][8 * lane], sb);
-  }
-  __syncthreads();
-  if (tid < 2 * LN_SMALL_COLS) {
-    const int which = tid / LN_SMALL_COLS, col = tid % LN_SMALL_COLS;
+  const int which = threadIdx.x >> 9, col = threadIdx.x & 511;
+  if (col < a.d) {
     float t = 0.f;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) t += red[w][which][col];
-    if (col0 + col < a.d) (which ? a.dbeta[g] : a.dgamma[g])[col0 + col] = t;
+    for (int c = 0; c < 4; ++c) t += reinterpret_cast<const float*>(&red[c][2 * which + ((col >> 2) & 1)][col >> 3])[col & 3];
+    a.part[g][((size_t)blockIdx.x * 2 + which) * a.d + col] = t;
+  }
+}
+
+template <typename T> struct LnQuad { typedef uint4 type; };
+template <> struct LnQuad<bf16_t> { typedef uint2 type; };
+__device__ __forceinline__ void unpack4(const uint4& r, float (&v)[4]) {
+  v[0] = __uint_as_float(r.x); v[1] = __uint_as_float(r.y); v[2] = __uint_as_float(r.z); v[3] = __uint_as_float(r.w);
+}
+__device__ __forceinline__ void unpack4(const uint2& r, float (&v)[4]) {
+  v[0] = __uint_as_float(r.x << 16); v[1] = __uint_as_float(r.x & 0xffff0000u); v[2] = __uint_as_float(r.y << 16); v[3] = __uint_as_float(r.y & 0xffff0000u);
+}
+// Launches that do not fill the chip: every row gets a wave of its own, and the column sums, which need nothing from the rows' own
+// pass (the row statistics are inputs), are added up by workgroups of their own straight from x and dy, which the row
+// workgroups read at the same time.  The order is that of ln_bwd_kernel and ln_reduce_kernel, so the bits are the same: thread
+// (chain, 4 columns) adds the 16 rows that a wave of ln_bwd_kernel would, four chains make a block's partial sum.  A column
+// workgroup takes 20 blocks of 64 rows; where those are all (FINAL), it adds the partial sums up as ln_reduce_kernel does and
+// there is no second launch.  dx must not overlap x or dy.
+// us, this | ln_bwd_chain_kernel (d <= 512) or ln_bwd_kernel: 4 x [1024, 256] bf16 6.9 | 11.3, 4 x [1024, 768] 11.8 | 23.2, 1 x [4096, 1024]
+// 15.3 | 25.1; x and dy are read twice, which sets the limit: 16 x [1024, 256] 18.1 | 14.1, 16 x [1024, 1024] 32.6 | 27.4.
+// Eight columns per thread: 2 us more of dependent instructions at 1 x [1280, 1024]; all 16 rows' loads in flight: 9.8 | 16.1.
+constexpr int LN_SPLIT_BLOCKS = 20, LN_SPLIT_COLS = 32, LN_SPLIT_NT = LN_SPLIT_BLOCKS * 4 * LN_SPLIT_COLS / 4;
+template <typename T, int C, bool FINAL>
+__global__ __launch_bounds__(LN_SPLIT_NT) void ln_bwd_split_kernel(const LnBwdArgs a, int col_wgs) {
+  constexpr int NV = 2 * LN_SPLIT_COLS;
+  __shared__ float red[4 * LN_SPLIT_BLOCKS][NV], sum[FINAL ? LN_SPLIT_BLOCKS : 1][NV];
+  const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if ((int)blockIdx.x >= col_wgs) {
+    const int row = ((int)blockIdx.x - col_wgs) * (LN_SPLIT_NT / 64) + wave, nch = a.d >> 3;
+    if (row >= a.rows) return;
+    float ga[C][8], none[C][8];
+    LnRow<T, C> r;
+    r.fetch(a, g, row, lane, nch);
+#pragma unroll
+    for (int i = 0; i < C; ++i)
+      if (lane + 64 * i < nch) ld8<float>(a.gamma[g] + 8 * (lane + 64 * i), ga[i]);
+    ln_bwd_row<T, C, false>(a, g, row, lane, nch, r, ga, none, none);
+    return;
+  }
+  typedef typename LnQuad<T>::type Q;
+  constexpr int NB = 4;  // rows whose loads are in flight together
+  const int nblk = (a.rows + LN_ROWS_PER_WG - 1) / LN_ROWS_PER_WG, ncol = (a.d + LN_SPLIT_COLS - 1) / LN_SPLIT_COLS;
+  const int blk0 = FINAL ? 0 : (int)blockIdx.x / ncol * LN_SPLIT_BLOCKS, nb = min(nblk - blk0, LN_SPLIT_BLOCKS);
+  // workgroups 8 apart, which run on one XCD, take neighbouring columns: 32 columns of 16 bits are half a cache line
+  int ci = FINAL ? (int)blockIdx.x : (int)blockIdx.x % ncol;
+  if (ci < ncol / 16 * 16) ci = ci / 16 * 16 + (ci % 8) * 2 + (ci / 8) % 2;
+  const int col0 = ci * LN_SPLIT_COLS, c = col0 / 4 + (tid & 7);  // 4 columns
+  const int chain = tid >> 3;  // rows (blk0 + chain/4) * 64 + chain%4, + 4, ...
+  if (chain < 4 * nb) {
+#pragma clang fp contract(off)
+    const bool live = 4 * c < a.d;
+    const int first = (blk0 + (chain >> 2)) * LN_ROWS_PER_WG, row0 = first + (chain & 3), end = first + min(a.rows - first, LN_ROWS_PER_WG);
+    const T* X = static_cast<const T*>(a.x[g]);
+    const T* DY = static_cast<const T*>(a.dy[g]);
+    float sg[4] = {0.f, 0.f, 0.f, 0.f}, sb[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int r0 = row0; r0 < end; r0 += 4 * NB) {
+      Q rx[NB], rdy[NB];
+      float mu[NB], rstd[NB];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const int row = r0 + 4 * b;
+        if (row < end && live) {
+          mu[b] = a.mean[g][row];
+          rstd[b] = a.rstd[g][row];
+          rx[b] = reinterpret_cast<const Q*>(X + (size_t)row * a.ld)[c];
+          rdy[b] = reinterpret_cast<const Q*>(DY + (size_t)row * a.ld)[c];
+        }
+      }
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        if (r0 + 4 * b >= end || !live) break;
+        float xv[4], dv[4];
+        unpack4(rx[b], xv);
+        unpack4(rdy[b], dv);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          sg[e] = fmaf(dv[e], (xv[e] - mu[b]) * rstd[b], sg[e]);
+          sb[e] += dv[e];
+        }
+      }
+    }
+    *reinterpret_cast<float4*>(&red[chain][4 * (tid & 7)]) = make_float4(sg[0], sg[1], sg[2], sg[3]);
+    *reinterpret_cast<float4*>(&red[chain][LN_SPLIT_COLS + 4 * (tid & 7)]) = make_float4(sb[0], sb[1], sb[2], sb[3]);
+  }
+  __syncthreads();
+  for (int i = tid; i < nb * NV; i += LN_SPLIT_NT) {
+    const int b = i / NV, j = i % NV, col = col0 + j % LN_SPLIT_COLS;
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) t += red[4 * b + w][j];
+    if (FINAL) sum[b][j] = t;
+    else if (col < a.d) a.part[g][(size_t)(blk0 + b) * 2 * a.d + (j / LN_SPLIT_COLS) * a.d + col] = t;
+  }
+  if (!FINAL) return;
+  __syncthreads();
+  if (tid < NV) {  // 16 ranges of partial sums, as in ln_reduce_kernel
+    const int per = (nb + 15) / 16;
+    float t[16], s = 0.f;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      t[w] = w * per < nb ? sum[w * per][tid] : 0.f;
+      if (per == 2) t[w] += 2 * w + 1 < nb ? sum[2 * w + 1][tid] : 0.f;
+    }
+#pragma unroll
+    for (int w = 0; w < 16; ++w) s += t[w];
+    const int col = col0 + tid % LN_SPLIT_COLS;
+    if (col < a.d) (tid / LN_SPLIT_COLS ? a.dbeta[g] : a.dgamma[g])[col] = s;
   }
 }
 
@@ -580,42 +625,55 @@ hipError_t launch_ln_fwd(const LnArgs& a, hipStream_t s) {
 template <typename T>
 static hipError_t ln_bwd_pick(const LnBwdArgs& a, hipStream_t s) {
   const dim3 grid(ln_bwd_blocks(a.rows, a.d), a.G);
-  if (a.d <= LN_WAVE_ROW_MAX) {
-    // 64 rows over 16 waves (one batch each) where a lane owns at most 8 columns, over 8 waves beyond (the cross-wave sums
-    // need NW x 8 d bytes of LDS: 64 KB either way); many wide fp32 rows over 4 waves (2 x [9000, 800]
-    // 49 us, over 8 waves 52.5; bf16 3 x [14483, 616] over 8 waves 52 us, over 4 57)
-    if (a.d <= 512) hipLaunchKernelGGL((ln_bwd_kernel<T, 1, 16, sizeof(T) == 2 ? 4 : 2>), grid, dim3(1024), (size_t)16 * 8 * a.d, s, a);
-    else if (sizeof(T) == 4 && a.rows > 4096) hipLaunchKernelGGL((ln_bwd_kernel<T, 2, 4, 2>), grid, dim3(256), (size_t)4 * 8 * a.d, s, a);
-    else hipLaunchKernelGGL((ln_bwd_kernel<T, 2, 8, 2>), grid, dim3(512), (size_t)8 * 8 * a.d, s, a);
-  } else if (a.d <= 2048) {
-    hipLaunchKernelGGL((ln_bwd_wide_kernel<T, 1>), grid, dim3(256), 0, s, a);
-  } else {
-    hipLaunchKernelGGL((ln_bwd_wide_kernel<T, 2>), grid, dim3(256), 0, s, a);
-  }
+  const size_t lds = (size_t)4 * 8 * a.d;
+  // one 16-wave workgroup per CU; fp32 rows take as long in one as in four waves when every CU has one
+  const long chain_max = sizeof(T) == 2 ? 256 : 192;
+  if (a.d <= 512 && (long)grid.x * a.G <= chain_max) hipLaunchKernelGGL((ln_bwd_chain_kernel<T>), grid, dim3(1024), 0, s, a);
+  else if (a.d <= 512) hipLaunchKernelGGL((ln_bwd_kernel<T, 1>), grid, dim3(256), lds, s, a);
+  else if (a.d <= LN_WAVE_ROW_MAX) hipLaunchKernelGGL((ln_bwd_kernel<T, 2>), grid, dim3(256), lds, s, a);
+  else if (a.d <= 2048) hipLaunchKernelGGL((ln_bwd_wide_kernel<T, 1>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((ln_bwd_wide_kernel<T, 2>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
-template <typename T>
-static hipError_t ln_bwd_small_run(const LnBwdArgs& a, hipStream_t s) {
-  const int row_blocks = (a.rows + 15) / 16;
-  const dim3 grid(row_blocks + (a.d + LN_SMALL_COLS - 1) / LN_SMALL_COLS, a.G);
-  if (a.d <= 512) hipLaunchKernelGGL((ln_bwd_small_kernel<T, 1>), grid, dim3(1024), 0, s, a, row_blocks);
-  else hipLaunchKernelGGL((ln_bwd_small_kernel<T, 2>), grid, dim3(1024), 0, s, a, row_blocks);
+template <typename T, int C>
+static hipError_t ln_bwd_split_run(const LnBwdArgs& a, hipStream_t s) {
+  const int nblk = ln_bwd_blocks(a.rows, a.d), ranges = (nblk + LN_SPLIT_BLOCKS - 1) / LN_SPLIT_BLOCKS;
+  const int col_wgs = (a.d + LN_SPLIT_COLS - 1) / LN_SPLIT_COLS * ranges;
+  const dim3 grid(col_wgs + (a.rows + LN_SPLIT_NT / 64 - 1) / (LN_SPLIT_NT / 64), a.G);
+  if (ranges == 1) hipLaunchKernelGGL((ln_bwd_split_kernel<T, C, true>), grid, dim3(LN_SPLIT_NT), 0, s, a, col_wgs);
+  else hipLaunchKernelGGL((ln_bwd_split_kernel<T, C, false>), grid, dim3(LN_SPLIT_NT), 0, s, a, col_wgs);
   return hipGetLastError();
+}
+
+// Whether row and column workgroups side by side are the faster form (a choice never changes a bit of the result, so it may look
+// at the group).  d <= 512: up to 3 M elements in one launch (2.1 M 14 | 16 us for ln_bwd_chain_kernel with fp32, 4.2 M 14.1 | 13.9 and
+// 18.1 | 14.1), half of that in two (1.3 M 10.7 | 11.6, 2.1 M 13.7 | 12.0).  Wider: up to 20 MB (bf16 17 MB 21.2 | 26.0, 25 MB 32 | 26;
+// fp32 21 MB 25 | 28, 33 MB 34 | 30).
+static bool ln_bwd_split(const LnBwdArgs& a) {
+  if (a.d > LN_WAVE_ROW_MAX) return false;
+  const long n = (long)a.G * a.rows * a.d;
+  if (a.d > 512) return n * (a.dtype == GEMM_F32 ? 4 : 2) <= 20L << 20;
+  return n <= (a.rows <= LN_SPLIT_BLOCKS * LN_ROWS_PER_WG ? 3L << 20 : 3L << 19);
 }
 
 hipError_t launch_ln_bwd(const LnBwdArgs& a, hipStream_t s) {
   if (!ln_shape_ok(a.G, a.rows, a.d, a.ld)) return hipErrorInvalidValue;
-  // by the shape of one problem alone: the order of the column sums must not depend on the group
-  if (a.rows <= LN_SMALL_ROWS && a.d <= LN_WAVE_ROW_MAX)
-    return a.dtype == GEMM_F32 ? ln_bwd_small_run<float>(a, s) : ln_bwd_small_run<bf16_t>(a, s);
-  hipError_t e = a.dtype == GEMM_F32 ? ln_bwd_pick<float>(a, s) : ln_bwd_pick<bf16_t>(a, s);
+  const bool f32 = a.dtype == GEMM_F32;
+  hipError_t e;
+  if (ln_bwd_split(a)) {
+    if (a.d <= 512) e = f32 ? ln_bwd_split_run<float, 1>(a, s) : ln_bwd_split_run<bf16_t, 1>(a, s);
+    else e = f32 ? ln_bwd_split_run<float, 2>(a, s) : ln_bwd_split_run<bf16_t, 2>(a, s);
+    if (a.rows <= LN_SPLIT_BLOCKS * LN_ROWS_PER_WG) return e;
+  } else {
+    e = f32 ? ln_bwd_pick<float>(a, s) : ln_bwd_pick<bf16_t>(a, s);
+  }
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(ln_reduce_kernel, dim3((2 * a.d + 15) / 16, a.G), dim3(256), 0, s, a, ln_bwd_blocks(a.rows, a.d));
   return hipGetLastError();
 }
 
-// nothing to set up: the wave-per-row kernel needs at most 64 KB of LDS
+// nothing to set up: the wave-per-row kernel needs at most 32 KB of LDS
 hipError_t ln_init() { return hipSuccess; }
 
 }  // namespace hydra

@@ -316,3 +316,54 @@ def test_attention_keeps_its_bits(torch, ops, line):
     """A training run repeats itself bit for bit from one version of the kernels to the next: the order of the row sums, of dO.O and of
     dP - delta is part of the result (twenty Adam steps turn a changed last bit into 1e-3 of a parameter)."""
     assert attention_bits(torch, ops, *[int(x) for x in line[:6]]) == line[6]
+
+
+def _column_sums(dv, xh, rows):
+    """dgamma, dbeta in fp32 in the order the kernels add them: rows r, r + 4, ... of a block of 64 are a chain of fused multiply-adds,
+    four chains make the block's partial sum, the blocks are added in 16 ranges.  (64-bit mantissas hold the products; the fused
+    rounding is taken from them.)"""
+    nb, d = -(-rows // 64), dv.shape[1]
+    f, pad = np.float32, lambda a: np.concatenate([a, np.zeros((nb * 64 - rows, d), np.float32)]).reshape(nb, 16, 4, d)  # noqa: E731
+    v, h = pad(dv), pad(xh)
+    sg, sb = np.zeros((nb, 4, d), f), np.zeros((nb, 4, d), f)
+    for i in range(16):
+        sg = (v[:, i].astype(np.longdouble) * h[:, i] + sg).astype(f)
+        sb = sb + v[:, i]
+    per, out = (nb + 15) // 16, []
+    for chains in (sg, sb):
+        part, s = np.zeros((nb, d), f), np.zeros(d, f)
+        for w in range(4):
+            part = part + chains[:, w]
+        for w in range(16):
+            t = np.zeros(d, f)
+            for b in range(w * per, min(nb, (w + 1) * per)):
+                t = t + part[b]
+            s = s + t
+        out.append(s)
+    return out
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("G,rows,d", [(1, 1, 8), (2, 67, 64), (4, 1024, 256), (1, 1100, 200), (1, 1280, 512), (1, 1281, 264), (1, 2000, 768), (3, 1000, 1000),
+                                       (2, 2100, 512), (4, 6000, 40), (1, 16500, 160), (1, 16500, 512), (2, 5300, 1000), (1, 1024, 1024)])
+def test_layernorm_column_sums_keep_their_order(torch, ops, dtype, G, rows, d):
+    """Every kernel the backward pass may take (one launch or two, few rows or many) adds dgamma and dbeta in one order, which is part of
+    the result: the sums of the first and last problem bit for bit."""
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(rows + d)
+    mk = lambda *sh: torch.randn(*sh, generator=gen, device="cuda")  # noqa: E731
+    x, dy = ([mk(rows, d).to(t) for _ in range(G)] for _ in range(2))
+    gamma, beta = [1 + 0.1 * mk(d) for _ in range(G)], [0.1 * mk(d) for _ in range(G)]
+    y, dx = ([torch.zeros_like(u) for u in x] for _ in range(2))
+    mean, rstd = ([torch.zeros(rows, device="cuda") for _ in range(G)] for _ in range(2))
+    dg, db = ([torch.zeros(d, device="cuda") for _ in range(G)] for _ in range(2))
+    part = [torch.zeros(ops.hydra_op_layernorm_part_floats(rows, d), device="cuda") for _ in range(G)]
+    D = ops.BF16 if dtype == "bf16" else ops.F32
+    ops.hydra_op_layernorm_fwd(D, rows, d, d, 1e-5, x, y, gamma, beta, mean, rstd)
+    ops.hydra_op_layernorm_bwd(D, rows, d, d, x, dy, None, dx, gamma, mean, rstd, part, dg, db)
+    for g in {0, G - 1}:
+        dv = dy[g].float().cpu().numpy()
+        xh = (x[g].float() - mean[g][:, None]) * rstd[g][:, None]
+        want = _column_sums(dv, xh.cpu().numpy(), rows)
+        for got, w in zip((dg[g], db[g]), want):
+            assert np.array_equal(got.cpu().numpy(), w)

@@ -2,6 +2,9 @@
 causal decoder) with the CPU oracle, through the C boundary (GPU only).  bf16 tolerances as in
 test_gpu_train.py: loss and parameter norms within 2e-2, plus first-step gradients (rel-L2 / cosine)
 and bitwise identity across schedules and cuts."""
+import hashlib
+import os
+
 import numpy as np
 import pytest
 
@@ -241,3 +244,24 @@ def test_config3_full_width_first_step_gradients_and_update_against_oracle(H):
     one of depth 12."""
     w = workload(3)
     _first_step_against_oracle(H, w, k=w.extra["depths"].index(12), batch=4)
+
+
+def training_bits(H, i):
+    """Digest of the losses and trained parameters of all models of scaled workload i."""
+    w = scaled_workload(i)
+    got, _ = H.train_workload(w, make_data(w), H.SCHED_SHARD_PARALLEL)
+    h = hashlib.sha256()
+    for losses, params in (got[k] for k in range(w.K)):
+        h.update(np.ascontiguousarray(losses).tobytes())
+        for p in params:
+            h.update(np.ascontiguousarray(p).tobytes())
+    return h.hexdigest()[:32]
+
+
+@pytest.mark.parametrize("i", [2, 3, 4])
+def test_training_keeps_its_bits(H, i):
+    """A training run gives the same parameters, bit for bit, whatever version of the kernels runs it (digests recorded on an MI355X
+    before attention and the LayerNorm backward pass were rewritten).  A change of rounding that is meant needs new digests."""
+    with open(os.path.join(os.path.dirname(__file__), "golden", "training_bits.txt")) as f:
+        want = dict(ln.split() for ln in f if not ln.startswith("#"))
+    assert training_bits(H, i) == want[str(i)]
