@@ -116,7 +116,8 @@ int hydra_op_layernorm_fwd(int dtype, int rows, int d, int ld, float eps, int G,
                            const float* const* gamma, const float* const* beta, float* const* mean,
                            float* const* rstd, void* stream);
 /* Adjoint: dx = rstd*(g - mean(g) - xhat*mean(g*xhat)) + add, g = dy*gamma (add optional: NULL table);
- * dgamma = sum_rows dy*xhat; dbeta = sum_rows dy.  part_g: scratch of hydra_op_layernorm_part_floats(rows, d) floats. */
+ * dgamma = sum_rows dy*xhat; dbeta = sum_rows dy.  part_g: scratch of hydra_op_layernorm_part_floats(rows, d) floats.
+ * dx_g may be x_g, dy_g or add_g itself (the same bits as with a buffer of its own); it may not overlap them otherwise. */
 int hydra_op_layernorm_bwd(int dtype, int rows, int d, int ld, int G, const void* const* x, const void* const* dy,
                            const void* const* add, void* const* dx, const float* const* gamma,
                            const float* const* mean, const float* const* rstd, float* const* part,

@@ -197,6 +197,7 @@ struct LnArgs {
 hipError_t launch_ln_fwd(const LnArgs& a, hipStream_t s);
 // dx = rstd*(g - mean(g) - xhat*mean(g*xhat)) + add (add optional), g = dy*gamma;
 // dgamma = sum_rows dy*xhat, dbeta = sum_rows dy.  part: scratch of ln_bwd_blocks(rows, d)*2*d floats.
+// dx may be x, dy or add.
 struct LnBwdArgs {
   int dtype, rows, d, ld, G;
   const void* x[MAXG];

@@ -650,8 +650,18 @@ static hipError_t ln_bwd_split_run(const LnBwdArgs& a, hipStream_t s) {
 // at the group).  d <= 512: up to 3 M elements in one launch (2.1 M 14 | 16 us for ln_bwd_chain_kernel with fp32, 4.2 M 14.1 | 13.9 and
 // 18.1 | 14.1), half of that in two (1.3 M 10.7 | 11.6, 2.1 M 13.7 | 12.0).  Wider: up to 20 MB (bf16 17 MB 21.2 | 26.0, 25 MB 32 | 26;
 // fp32 21 MB 25 | 28, 33 MB 34 | 30).
+// Not where a problem's dx lies over its x or dy: the column workgroups read those while the row workgroups store dx, where the
+// other kernels have read a row before they store it.
+static bool ln_bwd_in_place(const LnBwdArgs& a) {
+  const uintptr_t n = ((size_t)(a.rows - 1) * a.ld + a.d) * (a.dtype == GEMM_F32 ? 4 : 2);
+  for (int g = 0; g < a.G; ++g) {
+    const uintptr_t o = (uintptr_t)a.dx[g], x = (uintptr_t)a.x[g], dy = (uintptr_t)a.dy[g];
+    if ((o < x + n && x < o + n) || (o < dy + n && dy < o + n)) return true;
+  }
+  return false;
+}
 static bool ln_bwd_split(const LnBwdArgs& a) {
-  if (a.d > LN_WAVE_ROW_MAX) return false;
+  if (a.d > LN_WAVE_ROW_MAX || ln_bwd_in_place(a)) return false;
   const long n = (long)a.G * a.rows * a.d;
   if (a.d > 512) return n * (a.dtype == GEMM_F32 ? 4 : 2) <= 20L << 20;
   return n <= (a.rows <= LN_SPLIT_BLOCKS * LN_ROWS_PER_WG ? 3L << 20 : 3L << 19);

@@ -367,3 +367,27 @@ def test_layernorm_column_sums_keep_their_order(torch, ops, dtype, G, rows, d):
         want = _column_sums(dv, xh.cpu().numpy(), rows)
         for got, w in zip((dg[g], db[g]), want):
             assert np.array_equal(got.cpu().numpy(), w)
+
+
+@pytest.mark.parametrize("over", ["x", "dy", "add"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("G,rows,d", [(2, 256, 256), (1, 1200, 1000), (1, 2000, 768), (2, 5000, 512), (3, 90, 1536)])
+def test_layernorm_backward_in_place(torch, ops, dtype, over, G, rows, d):
+    """dx written over x, dy or the additive term: the bits of the same call with a buffer of its own (column sums included: they are
+    made from x and dy, which the rows' own pass is overwriting)."""
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(rows + d)
+    mk = lambda *sh: torch.randn(*sh, generator=gen, device="cuda")  # noqa: E731
+    src = {n: [mk(rows, d).to(t) for _ in range(G)] for n in ("x", "dy", "add")}
+    gamma = [1 + 0.1 * mk(d) for _ in range(G)]
+    mean, rstd = [u.float().mean(1) for u in src["x"]], [u.float().var(1, unbiased=False).add(1e-5).rsqrt() for u in src["x"]]
+    got = []
+    for in_place in (False, True):
+        s = {n: [u.clone() for u in us] for n, us in src.items()}
+        dx = s[over] if in_place else [torch.zeros_like(u) for u in s["x"]]
+        dg, db = ([torch.zeros(d, device="cuda") for _ in range(G)] for _ in range(2))
+        part = [torch.zeros(ops.hydra_op_layernorm_part_floats(rows, d), device="cuda") for _ in range(G)]
+        ops.hydra_op_layernorm_bwd(ops.BF16 if dtype == "bf16" else ops.F32, rows, d, d, s["x"], s["dy"], s["add"], dx, gamma, mean, rstd,
+                                   part, dg, db)
+        got.append(dx + dg + db)
+    assert all(torch.equal(a, b) for a, b in zip(*got))
