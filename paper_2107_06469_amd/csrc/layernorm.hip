@@ -82,10 +82,12 @@ __device__ __forceinline__ void st8<bf16_t>(bf16_t* p, const float (&v)[8]) {
 }
 
 // R = rows per wave.  Their loads are all issued before the first is reduced, and gamma and beta (fp32: four times the bytes of a
-// 16-bit row) are read once for the R rows.  A row's result does not depend on R.  Four rows (two of fp32) where that still
-// leaves every SIMD eight waves: 4 x [16384, 768] bf16 49 -> 34 us (5.9 TB/s); fewer rows stay one to a wave.
+// 16-bit row) are read once for the R rows.  A row's result does not depend on R: its multiply-adds are written out, not left to
+// the compiler.  Four rows (two of fp32) where that still leaves every SIMD eight waves: 4 x [16384, 768] bf16 49 -> 34 us (5.9
+// TB/s); fewer rows stay one to a wave.
 template <typename T, int LN_MAXC, int R>
 __global__ __launch_bounds__(256) void ln_fwd_kernel(const LnArgs a) {
+#pragma clang fp contract(off)
   const int g = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row0 = (blockIdx.x * 4 + wave) * R;
   if (row0 >= a.rows) return;
@@ -138,7 +140,12 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const LnArgs a) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const float t = v[i][e] - mu;
-          q += t * t;
+          if (i == 0 && e == 0) {  // the first two: t0 t0 + (t1 t1, rounded)
+            const float t1 = v[0][1] - mu;
+            q = fmaf(t, t, t1 * t1);
+          } else if (i > 0 || e > 1) {
+            q = fmaf(t, t, q);
+          }
         }
       }
     const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)a.d + a.eps);
@@ -148,7 +155,7 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const LnArgs a) {
       if (c < nch) {
         float o[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = (v[i][e] - mu) * rstd * ga[i][e] + be[i][e];
+        for (int e = 0; e < 8; ++e) o[e] = fmaf((v[i][e] - mu) * rstd, ga[i][e], be[i][e]);
         st8<T>(y + (size_t)r * a.ld + 8 * c, o);
       }
     }

@@ -391,3 +391,20 @@ def test_layernorm_backward_in_place(torch, ops, dtype, over, G, rows, d):
                                    part, dg, db)
         got.append(dx + dg + db)
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("rows,d", [(8195, 256), (8193, 904), (8194, 1024)])
+def test_layernorm_forward_bits_do_not_depend_on_the_group(torch, ops, dtype, rows, d):
+    """A group of four is large enough for several rows per wave, one problem alone is not: the same bits."""
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(rows + d)
+    mk = lambda *sh: torch.randn(*sh, generator=gen, device="cuda")  # noqa: E731
+    x, gamma, beta = [mk(rows, d).to(t) for _ in range(4)], [1 + 0.1 * mk(d) for _ in range(4)], [0.1 * mk(d) for _ in range(4)]
+    got = []
+    for n in (4, 1):
+        y = [torch.zeros_like(u) for u in x[:n]]
+        mean, rstd = ([torch.zeros(rows, device="cuda") for _ in range(n)] for _ in range(2))
+        ops.hydra_op_layernorm_fwd(ops.BF16 if dtype == "bf16" else ops.F32, rows, d, d, 1e-5, x[:n], y, gamma[:n], beta[:n], mean, rstd)
+        got.append((y[0], mean[0], rstd[0]))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
