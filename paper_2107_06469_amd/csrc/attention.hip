@@ -636,7 +636,10 @@ hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
 hipError_t launch_attn_bwd(const AttnBwdArgs& a, hipStream_t s) {
   if (!attn_ok(a.B, a.S, a.H, a.DH, a.ld_qkv, a.ld_o, a.G)) return hipErrorInvalidValue;
   dim3 grid(((((a.S + 127) / 128) * a.B * a.H * a.G + 7) / 8) * 8);
-  if (grid.x <= 256) {  // at most two workgroups per CU together
+  // The halves' workgroups fit the chip together: two per CU at DH = 64, one at DH = 128 (490 registers), where a second round of
+  // the shorter dq workgroups still pays a little past that.  us, two launches | one: DH = 64, 256 row blocks 53.4 | 43.0;
+  // DH = 128, 128 blocks 89.1 | 72.9, 160 56.5 | 46.2, 192 57.7 | 63.5 and 94.9 | 109 (causal 163 | 138), 256 98.9 | 114.
+  if (grid.x <= (a.DH == 64 ? 256 : 160)) {
     const dim3 both(2 * grid.x);
     if (a.DH == 64) hipLaunchKernelGGL(attn_bwd_both_kernel<64>, both, dim3(256), dkv_lds<64>(), s, a);
     else hipLaunchKernelGGL(attn_bwd_both_kernel<128>, both, dim3(256), dkv_lds<128>(), s, a);
