@@ -614,6 +614,12 @@ bool attn_ok(int B, int S, int H, int DH, int ld_qkv, int ld_o, int G) {
   return G >= 1 && G <= MAXG && B >= 1 && S >= 1 && H >= 1 && (DH == 64 || DH == 128) && ld_qkv >= 3 * H * DH &&
          !(ld_qkv & 7) && ld_o >= H * DH && !(ld_o & 7);
 }
+// Loads into LDS move 16 bytes of one row: the matrices whose tiles they bring have to start on such a boundary (their rows then do).
+bool tiles_ok(const bf16_t* const* m, int G) {
+  uintptr_t bits = 0;
+  for (int g = 0; g < G; ++g) bits |= (uintptr_t)m[g];
+  return (bits & 15) == 0;
+}
 
 }  // namespace
 
@@ -626,7 +632,7 @@ hipError_t attn_init() {  // the other kernels stay within the default LDS limit
 }
 
 hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
-  if (!attn_ok(a.B, a.S, a.H, a.DH, a.ld_qkv, a.ld_o, a.G)) return hipErrorInvalidValue;
+  if (!attn_ok(a.B, a.S, a.H, a.DH, a.ld_qkv, a.ld_o, a.G) || !tiles_ok(a.qkv, a.G)) return hipErrorInvalidValue;
   dim3 grid(((((a.S + 127) / 128) * a.B * a.H * a.G + 7) / 8) * 8);
   if (a.DH == 64) hipLaunchKernelGGL(attn_fwd_kernel<64>, grid, dim3(256), fwd_lds<64>(), s, a);
   else hipLaunchKernelGGL(attn_fwd_kernel<128>, grid, dim3(256), fwd_lds<128>(), s, a);
@@ -634,7 +640,8 @@ hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_attn_bwd(const AttnBwdArgs& a, hipStream_t s) {
-  if (!attn_ok(a.B, a.S, a.H, a.DH, a.ld_qkv, a.ld_o, a.G)) return hipErrorInvalidValue;
+  if (!attn_ok(a.B, a.S, a.H, a.DH, a.ld_qkv, a.ld_o, a.G) || !tiles_ok(a.qkv, a.G) || !tiles_ok(a.dout, a.G))
+    return hipErrorInvalidValue;
   dim3 grid(((((a.S + 127) / 128) * a.B * a.H * a.G + 7) / 8) * 8);
   // The halves' workgroups fit the chip together: two per CU at DH = 64, one at DH = 128 (490 registers), where a second round of
   // the shorter dq workgroups still pays a little past that.  us, two launches | one: DH = 64, 256 row blocks 53.4 | 43.0;

@@ -408,3 +408,17 @@ def test_layernorm_forward_bits_do_not_depend_on_the_group(torch, ops, dtype, ro
         ops.hydra_op_layernorm_fwd(ops.BF16 if dtype == "bf16" else ops.F32, rows, d, d, 1e-5, x[:n], y, gamma[:n], beta[:n], mean, rstd)
         got.append((y[0], mean[0], rstd[0]))
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+def test_attention_refuses_misaligned_tiles(torch, ops):
+    """The matrices whose tiles are loaded straight into LDS must start on 16 bytes: an argument error, not a launch, otherwise."""
+    S, H, DH = 64, 2, 64
+    d = H * DH
+    mk = lambda n, off: torch.zeros(S * n + 8, device="cuda", dtype=torch.bfloat16)[off:off + S * n].view(S, n)  # noqa: E731
+    o, lse, delta, dqkv = mk(d, 0), torch.zeros(S * H, device="cuda"), torch.zeros(S * H, device="cuda"), mk(3 * d, 0)
+    fwd = lambda q: ops.hydra_op_attention_fwd(1, S, H, DH, 3 * d, d, False, 0.125, [q], [o], [lse])  # noqa: E731
+    bwd = lambda q, g: ops.hydra_op_attention_bwd(1, S, H, DH, 3 * d, d, False, 0.125, [q], [o], [g], [lse], [delta], [dqkv])  # noqa: E731
+    fwd(mk(3 * d, 0)), bwd(mk(3 * d, 0), mk(d, 0))
+    for call in (lambda: fwd(mk(3 * d, 4)), lambda: bwd(mk(3 * d, 4), mk(d, 0)), lambda: bwd(mk(3 * d, 0), mk(d, 4))):
+        with pytest.raises(Exception, match="attention"):
+            call()
