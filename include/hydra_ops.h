@@ -127,7 +127,7 @@ size_t hydra_op_layernorm_part_floats(int rows, int d);
 /* Attention, bf16, head width DH in {64,128}.  qkv_g [B*S, ld_qkv]: q of head h at columns [h*DH,(h+1)*DH),
  * k at H*DH + the same, v at 2*H*DH + the same.  o_g [B*S, ld_o].  P = softmax(q k^T * scale (+ causal mask)),
  * o = P v, lse_g [B*H*S] = log-sum-exp of the scaled scores.  qkv_g (and dout_g below) 16-byte aligned, ld_qkv and ld_o
- * multiples of 8. */
+ * multiples of 8, 64 rows (or S, if fewer) of either below 2 GiB. */
 int hydra_op_attention_fwd(int B, int S, int H, int DH, int ld_qkv, int ld_o, int causal, float scale, int G,
                            const void* const* qkv, void* const* o, float* const* lse, void* stream);
 /* Adjoint given dout_g [B*S, ld_o] (gradient w.r.t. o): dqkv_g in the layout of qkv; delta_g [B*H*S] scratch. */

@@ -22,6 +22,7 @@
 // of a query live in the two lanes l and l^32 and are combined with one cross-lane exchange.  A wavefront owns 32
 // queries (or 32 keys) and loops over tiles of 64 keys (queries) shared through LDS by the four wavefronts of the
 // workgroup.  All sums run in a fixed order; dq and dk/dv are separate workgroups so that no atomics are needed.
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.h"
@@ -612,7 +613,8 @@ template <int DH> constexpr size_t dkv_lds() { return (size_t)2 * 2 * 64 * (DH /
 
 bool attn_ok(int B, int S, int H, int DH, int ld_qkv, int ld_o, int G) {
   return G >= 1 && G <= MAXG && B >= 1 && S >= 1 && H >= 1 && (DH == 64 || DH == 128) && ld_qkv >= 3 * H * DH &&
-         !(ld_qkv & 7) && ld_o >= H * DH && !(ld_o & 7);
+         !(ld_qkv & 7) && ld_o >= H * DH && !(ld_o & 7) &&
+         (long)std::min(S, 64) * std::max(ld_qkv, ld_o) * 2 <= 0x7fffffffL;  // the rows of a tile: 31 bits from the first
 }
 // Loads into LDS move 16 bytes of one row: the matrices whose tiles they bring have to start on such a boundary (their rows then do).
 bool tiles_ok(const bf16_t* const* m, int G) {

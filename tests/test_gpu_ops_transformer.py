@@ -410,8 +410,9 @@ def test_layernorm_forward_bits_do_not_depend_on_the_group(torch, ops, dtype, ro
     assert all(torch.equal(a, b) for a, b in zip(*got))
 
 
-def test_attention_refuses_misaligned_tiles(torch, ops):
-    """The matrices whose tiles are loaded straight into LDS must start on 16 bytes: an argument error, not a launch, otherwise."""
+def test_attention_refuses_tiles_it_cannot_load(torch, ops):
+    """The matrices whose tiles are loaded straight into LDS must start on 16 bytes, and 64 of their rows must lie within 2 GiB: an
+    argument error, not a launch, otherwise."""
     S, H, DH = 64, 2, 64
     d = H * DH
     mk = lambda n, off: torch.zeros(S * n + 8, device="cuda", dtype=torch.bfloat16)[off:off + S * n].view(S, n)  # noqa: E731
@@ -419,6 +420,7 @@ def test_attention_refuses_misaligned_tiles(torch, ops):
     fwd = lambda q: ops.hydra_op_attention_fwd(1, S, H, DH, 3 * d, d, False, 0.125, [q], [o], [lse])  # noqa: E731
     bwd = lambda q, g: ops.hydra_op_attention_bwd(1, S, H, DH, 3 * d, d, False, 0.125, [q], [o], [g], [lse], [delta], [dqkv])  # noqa: E731
     fwd(mk(3 * d, 0)), bwd(mk(3 * d, 0), mk(d, 0))
-    for call in (lambda: fwd(mk(3 * d, 4)), lambda: bwd(mk(3 * d, 4), mk(d, 0)), lambda: bwd(mk(3 * d, 0), mk(d, 4))):
+    far = lambda: ops.hydra_op_attention_fwd(1, S, H, DH, 1 << 24, d, False, 0.125, [mk(3 * d, 0)], [o], [lse])  # noqa: E731
+    for call in (far, lambda: fwd(mk(3 * d, 4)), lambda: bwd(mk(3 * d, 4), mk(d, 0)), lambda: bwd(mk(3 * d, 0), mk(d, 4))):
         with pytest.raises(Exception, match="attention"):
             call()
