@@ -1819,6 +1819,16 @@ typedef SmallTile<bf16_t, 16, 2> SmallBf16;
 typedef SmallTile<bf16_t, 8, 4> SmallBf16Deep;
 typedef SmallTile<float, 16, 2> SmallF32;
 
+// What the few-tile kernels can launch and address: tile columns are the grid's y, and the rows of a k-contiguous operand's tile
+// lie within 31 bits of its first (the 32x128 tile takes half as many rows of X).
+inline bool small_eligible(const GemmArgs& a) {
+  const long bt = a.dtype == GEMM_F32 ? SmallF32::BT : SmallBf16::BT, sz = a.dtype == GEMM_F32 ? 4 : 2;
+  if ((a.N + bt - 1) / bt > 65535) return false;
+  if (a.x_kmajor && std::min<long>(a.M, bt) * a.ldx * sz > 0x7fffffffL) return false;
+  if (a.w_kmajor && std::min<long>(a.N, bt) * a.ldw * sz > 0x7fffffffL) return false;
+  return dma_eligible(a);
+}
+
 // A choice never changes a result (every tile sums in the same order), only the time.  Measured in kernel time with the
 // tiles of every kind side by side; figures are us, small | 128x128 (| 32x128 for fp32).
 int choose_tile(const GemmArgs& a) {
@@ -1826,18 +1836,18 @@ int choose_tile(const GemmArgs& a) {
   auto tiles = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.G; };
   const long big = tiles(256, 256), mid = tiles(128, 128);
   if (a.M >= 192 && big >= 192) return 1;  // the big tile fills the chip
-  const bool dma = dma_eligible(a);
+  const bool small = small_eligible(a);
   if (a.dtype == GEMM_F32) {
     // three 32x32 tiles per CU are as fast as 32x128 ones (800 tiles: 24.5-27.5 | 61 | 25.6-27.0; 256 tiles: 15 | 76 | 30;
     // 1024 tiles: 22.5 | 45 | 20)
-    if (dma && tiles(32, 32) <= 768) return TILE_SMALL;
+    if (small && tiles(32, 32) <= 768) return TILE_SMALL;
     // 128x128 tiles need one for every CU (224 tiles: 67 against 57 for 32x128; 256 tiles: 85 | 86 and 87 | 90)
     return a.M >= 96 && mid >= 256 ? 2 : 3;
   }
   // About one 64x64 tile per CU: ahead of 128x128 tiles by a third up to there (256 tiles: K = 1024 9.4 | 13.4,
   // K = 4096 26 | 35), level at 330 tiles (19-17.4 | 22.8-16.7), behind beyond (512 tiles, K = 2048: 26 | 21-24;
   // 768 tiles 16.6 | 15).  Fewer than 96 rows would leave much of a 128-row tile empty.
-  if (dma && (tiles(64, 64) <= 320 || a.M < 96)) return a.K > 1024 ? TILE_SMALL_DEEP : TILE_SMALL;
+  if (small && (tiles(64, 64) <= 320 || a.M < 96)) return a.K > 1024 ? TILE_SMALL_DEEP : TILE_SMALL;
   if (a.M >= 96 && mid >= 64) {
     // Too few big tiles for 256 CUs: 128 x 128 tiles win while they fit in one pass over the chip (two
     // workgroups per CU); beyond that a partly filled pass of big tiles is still the faster choice.
@@ -1851,19 +1861,19 @@ int choose_update_tile(const GemmArgs& a) {
   if (a.tile) return a.tile;
   auto tiles = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.G; };
   const long big = tiles(256, 256);
-  const bool dma = dma_eligible(a);
+  const bool small = small_eligible(a);
   if (a.dtype == GEMM_F32) {
     // 32x32 tiles are ahead until the sums get short against the number of tiles (us, 32x32 | 128x128 | 32x128: 2400 tiles,
     // K = 256 25 | 41 | 32; 2048 tiles, K = 2048 89 | 161 | 106; K = 64 14.6 | 25 | 14.5; 4096 tiles, K = 24 27 | 28 | 22)
     const long sm = tiles(32, 32);
-    if (dma && (sm <= 1024 || (sm <= 4096 && a.K >= 64))) return TILE_SMALL;
+    if (small && (sm <= 1024 || (sm <= 4096 && a.K >= 64))) return TILE_SMALL;
     if (big < 192) return 3;
   } else {
     // 64x64 tiles: the state of a tile is small enough to hide behind the other workgroups' k-loops (us, 64x64 | 128x128:
     // 256 tiles, K = 1024 13 | 22; K = 4096 31 | 46; 600 tiles, K = 700 24 | 25; 2048 tiles, K = 1024 60-65 | 57-69), but
     // a long sum wants the 128x128 tile's reuse (1024 tiles, K = 8192 119 | 104; 2048 tiles, K = 2048 84 | 77)
     const long sm = tiles(64, 64);
-    if (dma && (sm <= 512 || (sm <= 2048 && a.K <= 1024))) return a.K > 1024 ? TILE_SMALL_DEEP : TILE_SMALL;
+    if (small && (sm <= 512 || (sm <= 2048 && a.K <= 1024))) return a.K > 1024 ? TILE_SMALL_DEEP : TILE_SMALL;
   }
   const int tile = choose_tile(a);
   if (tile == 1 && a.K < 2048) {
