@@ -1819,11 +1819,10 @@ typedef SmallTile<bf16_t, 16, 2> SmallBf16;
 typedef SmallTile<bf16_t, 8, 4> SmallBf16Deep;
 typedef SmallTile<float, 16, 2> SmallF32;
 
-// What the few-tile kernels can launch and address: tile columns are the grid's y, and the rows of a k-contiguous operand's tile
-// lie within 31 bits of its first (the 32x128 tile takes half as many rows of X).
+// What the few-tile kernels can address: the rows of a k-contiguous operand's tile lie within 31 bits of its first (the 32x128
+// tile takes half as many rows of X).
 inline bool small_eligible(const GemmArgs& a) {
   const long bt = a.dtype == GEMM_F32 ? SmallF32::BT : SmallBf16::BT, sz = a.dtype == GEMM_F32 ? 4 : 2;
-  if ((a.N + bt - 1) / bt > 65535) return false;
   if (a.x_kmajor && std::min<long>(a.M, bt) * a.ldx * sz > 0x7fffffffL) return false;
   if (a.w_kmajor && std::min<long>(a.N, bt) * a.ldw * sz > 0x7fffffffL) return false;
   return dma_eligible(a);

@@ -630,19 +630,6 @@ def test_unknown_tile_numbers_are_refused(torch, ops):
             ops.hydra_op_gemm(0, 64, 64, 64, [x], [x], [torch.zeros_like(x)], x_kmajor=1, w_kmajor=1, ldx=64, ldw=64, ldo=64, tile=tile)
 
 
-def test_few_rows_by_very_many_columns(torch, ops):
-    """More tile columns than a grid's y dimension holds: the choice goes to a kernel with a flat grid, which gives the bits of the
-    32x128 tile."""
-    M, N, K = 24, 64 * 65536 + 8, 8
-    gen = torch.Generator(device="cuda").manual_seed(3)
-    x, w = (torch.randn(n, K, generator=gen, device="cuda").to(torch.bfloat16) for n in (M, N))
-    out = [torch.zeros(M, N, device="cuda", dtype=torch.bfloat16) for _ in range(2)]
-    for tile, o in zip((0, 3), out):
-        ops.hydra_op_gemm(1, M, N, K, [x], [w], [o], x_kmajor=1, w_kmajor=1, ldx=K, ldw=K, ldo=N, tile=tile)
-    assert torch.equal(*out)
-    assert torch.allclose(out[0][:, -64:].float(), x.float() @ w[-64:].float().t().contiguous(), rtol=2 ** -7, atol=1e-2)
-
-
 def test_rows_of_a_tile_past_two_gigabytes(torch, ops):
     """64 rows of a k-contiguous operand that span more than 2 GiB: the last rows' products are not lost."""
     M, N, K = 64, 8, (1 << 24) + 4096
