@@ -639,3 +639,33 @@ def test_rows_of_a_tile_past_two_gigabytes(torch, ops):
     out = torch.zeros(M, N, device="cuda")
     ops.hydra_op_gemm(1, M, N, K, [x], [w], [out], x_kmajor=1, w_kmajor=0, ldx=K, ldw=N, ldo=N, out_f32=True)
     assert torch.equal(out, (torch.arange(M, device="cuda") + 0.5)[:, None].expand(M, N))
+
+
+@pytest.mark.parametrize("M,N,K,G,tile", [(256, 256, 5, 2, 1), (300, 264, 29, 2, 1), (257, 520, 33, 1, 1), (512, 256, 61, 2, 1), (256, 72, 127, 1, 1),
+                                          (300, 300, 1027, 2, 1), (260, 256, 1850, 1, 1), (2048, 1536, 1003, 4, 0)])
+def test_input_gradient_whose_sum_ends_inside_a_chunk(torch, ops, M, N, K, G, tile):
+    """The 256x256 tile clears the tail of the last 16-byte chunk in LDS (K inside the first, a middle or the last chunk of a sub-tile
+    of 32, one sub-tile or many, fewer than the ring has stages; NaN stored behind K): the bits of the tiles that stage operands
+    through registers, with every epilogue of an input gradient.  The last shape is one that the automatic choice sends there."""
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+
+    def mat(rows, cols):
+        x = torch.randn(rows, _ld(cols), generator=gen, device="cuda").to(torch.bfloat16)
+        x[:, cols:] = float("nan")
+        return x
+
+    X, W = [mat(M, K) for _ in range(G)], [mat(K, N) for _ in range(G)]
+    side = dict(gate=[mat(M, N) for _ in range(G)], resid=[mat(M, N) for _ in range(G)])
+    for combo in ((), ("gate",), ("resid",), ("gate", "resid")):
+        kw = {n: side[n] for n in combo}
+        if "gate" in combo:
+            kw.update(ldg=_ld(N), act=ops.EPI_GELU)
+        if "resid" in combo:
+            kw.update(ldr=_ld(N))
+        got = []
+        for t in (tile, 3, 4):
+            out = [torch.zeros(M, _ld(N), device="cuda", dtype=torch.bfloat16) for _ in range(G)]
+            ops.hydra_op_gemm(1, M, N, K, X, W, out, x_kmajor=1, w_kmajor=0, ldx=_ld(K), ldw=_ld(N), ldo=_ld(N), tile=t, **kw)
+            got.append(torch.stack([o[:, :N] for o in out]))
+        assert not torch.isnan(got[0]).any()
+        assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2]), combo
