@@ -1877,12 +1877,13 @@ int choose_update_tile(const GemmArgs& a) {
   const int tile = choose_tile(a);
   if (tile == 1 && a.K < 2048) {
     // With a short k-loop the state traffic of the epilogue dominates: with two workgroups per CU one streams
-    // state while the other runs its k-loop, which the 256x256 tile (one workgroup per CU) cannot do.  It is ahead all the
-    // same where the sum is very short and the tiles fill one or two passes over the chip (us, 256x256 | 128x128: 256 tiles,
-    // K = 24 84 | 95, K = 256 85 | 96; 512 tiles, K = 24 157 | 173, K = 128 157 | 220), and far behind where they just miss
-    // (260 tiles, K = 810: 192 | 143 with the layer's input gradient) or there are many (2048 tiles, K = 128 656 | 612, K = 512 731 | 628).
-    const bool full = (big > 232 && big <= 256) || (big > 464 && big <= 512);
-    return a.dtype != GEMM_F32 && a.K <= 256 && full ? 1 : 2;
+    // state while the other runs its k-loop, which the 256x256 tile (one workgroup per CU) cannot do.  us, 256x256 | 128x128:
+    // 256 tiles of rows 4 KB apart, K = 64 85 | 86, K = 256 103 | 88; 384 tiles, 16 KB 140 | 120 and 141 | 119; 504 tiles, 9 KB 179 | 165
+    // and 186 | 167; 1024 tiles, 16 KB 402 | 296 and 377 | 299; 512 tiles, 32 KB 161 | 161 and 170 | 166.  Rows of the state exactly
+    // 8 KB apart are the exception: there the half as long row pieces of the 128x128 tile are the slower ones until the sum covers
+    // them (256 tiles, K = 64 79 | 90, K = 256 87 | 118, K = 1024 106 | 109; 512 tiles 167 | 172, 177 | 220, 210 | 211; 1024 tiles 310 | 326,
+    // 318 | 375, 395 | 366; K = 512, 512 tiles 177 | 202, 768 263 | 273).
+    return a.dtype != GEMM_F32 && a.K <= 512 && a.ldo * 4 == 8192 ? 1 : 2;
   }
   return tile;
 }

@@ -669,3 +669,21 @@ def test_input_gradient_whose_sum_ends_inside_a_chunk(torch, ops, M, N, K, G, ti
             got.append(torch.stack([o[:, :N] for o in out]))
         assert not torch.isnan(got[0]).any()
         assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2]), combo
+
+
+@pytest.mark.parametrize("K", [40, 512, 520])
+def test_update_of_rows_8_kb_apart(torch, ops, K):
+    """Parameter rows exactly 8 KB apart and a short sum: the automatic choice takes the 256x256 tile (up to K = 512) or the 128x128
+    one, and either gives the bits of the 32x128 tile."""
+    M, N = 6144, 2048
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    X, W = (torch.randn(K, n, generator=gen, device="cuda").to(torch.bfloat16) for n in (M, N))
+    st = [torch.rand(M, N, generator=gen, device="cuda") for _ in range(3)]
+    got = []
+    for tile in (0, 3):
+        p, m, v = (t.clone() for t in st)
+        w16 = torch.zeros(M, N, device="cuda", dtype=torch.bfloat16)
+        ops.hydra_op_gemm_update(1, M, N, K, [X], [W], 1, [p], [m], [v], [w16], [(1e-3, 0.9, 0.999, 1e-8, 1.5, 1.2)], tile=tile, ldx=M,
+                                 ldw=N, ldo=N)
+        got.append((p, m, v, w16))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
