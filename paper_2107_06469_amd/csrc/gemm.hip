@@ -920,12 +920,11 @@ __device__ __forceinline__ int swz8(int row) { return ((row >> 1) & 3) | (((row 
 
 // One operand tile of ROWS rows in the ring: what a lane contributes to the direct loads of a sub-tile and where it
 // reads its MFMA fragments.  NW = waves of the workgroup; load i of wave w fills slots [(i*NW + w)*64, +64).
-// BKW = k per sub-tile: four 16-byte chunks per k-contiguous row (32 bf16, 16 fp32), or for bf16 eight (64: a row is
-// then 128 contiguous bytes per load, a whole cache line).
-// fp32, k as the slow index: k-rows of ROWS elements as for bf16; a fragment is four 4-byte reads (k..k+3 of one tile
-// row).  The two halves of a wave read k-rows 4 apart, which the XOR with ((k>>2)&1)<<3 sends to different halves of
-// the banks.  A k-row of 64 bf16 is half of the banks, so k-rows of equal parity share them and only (k>>1)&1 may move
-// its chunks.
+// BKW = k per sub-tile: four 16-byte chunks per k-contiguous row (32 bf16), eight (64 bf16: a row is then 128 contiguous bytes
+// per load, a whole cache line) or sixteen (the few-tile kernels: 128 bf16, 64 fp32).
+// k as the slow index: a k-row of 64 bf16 is half of the banks, so k-rows of equal parity share them and only (k>>1)&1 may move its
+// chunks (by 4).  fp32 (gemm_small_f32_kernel, which reads its fragments itself, two 4-byte reads each): k-rows of 32 elements; the
+// lane groups of a wave read k-rows 4 apart, which ((k>>2)&1)<<2 sends to different halves of a k-row.
 template <typename T, bool KMAJ, int ROWS, int NW, int BKW>
 struct RingOperand {
   static constexpr int E = Elem<T>::E;
@@ -985,6 +984,7 @@ struct RingOperand {
     return (k * RC + (rc ^ kswz(k))) * 16 + (j & 1) * 8;
   }
   static __device__ __forceinline__ uint4 read_frag(const char* stage_part, int off) {
+    static_assert(KMAJ || sizeof(T) == 2, "the transposing reads move 16-bit elements");
     if (KMAJ) return *reinterpret_cast<const uint4*>(stage_part + off);
     typedef __attribute__((ext_vector_type(4))) short s16x4;
     typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
@@ -1014,6 +1014,7 @@ template <typename T, int WM, int WN, int FM, int FN, int NS, bool X_KMAJ, bool 
           int BK = 4 * Elem<T>::E, bool RAGK = false>
 __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a, const typename UpdSel<UPD>::type upd) {
   static_assert(!SPLITK || !UPD, "partial sums are stored plainly");
+  static_assert(sizeof(T) == 2, "bf16: fp32 launches take gemm_small_f32_kernel or gemm_kernel");
   constexpr int CPR = BK / Elem<T>::E;               // 16-byte chunks of k per sub-tile: 4, or 8 (bf16)
   constexpr int BM = WM * FM * 32, BN = WN * FN * 32, NW = WM * WN;
   constexpr int XPART = BM * CPR * 16;          // bytes of the X part of a stage
@@ -1469,7 +1470,6 @@ template <typename T, int CPR, int NS>
 struct SmallTile {
   static constexpr int BT = sizeof(T) == 2 ? 64 : 32;
   static constexpr size_t LDS = (size_t)NS * 2 * BT * CPR * 16;
-  static long tiles(const GemmArgs& a) { return (long)((a.M + BT - 1) / BT) * ((a.N + BT - 1) / BT) * a.G; }
   template <bool XK, bool WK, bool UPD>
   static constexpr auto kernel() {
     if constexpr (sizeof(T) == 2) return &gemm_small_kernel<CPR, NS, XK, WK, UPD>;
