@@ -10,6 +10,8 @@
 // a second kernel: no atomics, so results do not depend on timing.  Rows of up to 1024 elements: rows r, r + 4, ... of a
 // block are one chain of multiply-adds, the four chains are added in order, then the blocks in 16 ranges and the ranges.
 // Several kernels take that order, so which of them runs never changes a bit.
+#include <type_traits>
+
 #include "kernels.h"
 #include "wave_math.h"
 
@@ -365,9 +367,11 @@ __device__ __forceinline__ void unpack4(const uint2& r, float (&v)[4]) {
 // (chain, 4 columns) adds the 16 rows that a wave of ln_bwd_kernel would, four chains make a block's partial sum.  A column
 // workgroup takes 20 blocks of 64 rows; where those are all (FINAL), it adds the partial sums up as ln_reduce_kernel does and
 // there is no second launch.  dx must not overlap x or dy.
-// us, this | ln_bwd_chain_kernel (d <= 512) or ln_bwd_kernel: 4 x [1024, 256] bf16 6.9 | 11.3, 4 x [1024, 768] 11.8 | 23.2, 1 x [4096, 1024]
-// 15.3 | 25.1; x and dy are read twice, which sets the limit: 16 x [1024, 256] 18.1 | 14.1, 16 x [1024, 1024] 32.6 | 27.4.
-// Eight columns per thread: 2 us more of dependent instructions at 1 x [1280, 1024]; all 16 rows' loads in flight: 9.8 | 16.1.
+// us, this | ln_bwd_chain_kernel (d <= 512) or ln_bwd_kernel: 4 x [1024, 256] bf16 6.3 | 11.4, 4 x [1024, 768] 11.2 | 22.9, 1 x [4096, 1024]
+// 14.8 | 25.1; x and dy are read twice, which sets the limit: 16 x [1024, 256] 16.3 | 14.2, 16 x [1024, 1024] 32.2 | 27.3.
+// What bounds the small ones is a thread's own instruction stream.  With eight columns per thread 1 x [64, 64] takes 5.8 us, with a
+// test around every load 5.3, as it is 3.7 (a launch: 2.4); eight rows in flight instead of four are level there and cost
+// occupancy elsewhere (4 x [1280, 1024] 16.3 | 13.3).
 constexpr int LN_SPLIT_BLOCKS = 20, LN_SPLIT_COLS = 32, LN_SPLIT_NT = LN_SPLIT_BLOCKS * 4 * LN_SPLIT_COLS / 4;
 template <typename T, int C, bool FINAL>
 __global__ __launch_bounds__(LN_SPLIT_NT) void ln_bwd_split_kernel(const LnBwdArgs a, int col_wgs) {
@@ -397,37 +401,46 @@ __global__ __launch_bounds__(LN_SPLIT_NT) void ln_bwd_split_kernel(const LnBwdAr
   const int chain = tid >> 3;  // rows (blk0 + chain/4) * 64 + chain%4, + 4, ...
   if (chain < 4 * nb) {
 #pragma clang fp contract(off)
-    const bool live = 4 * c < a.d;
+    // columns past the matrix are read as its first ones, and rows past the block as its last: no branch around a load
     const int first = (blk0 + (chain >> 2)) * LN_ROWS_PER_WG, row0 = first + (chain & 3), end = first + min(a.rows - first, LN_ROWS_PER_WG);
-    const T* X = static_cast<const T*>(a.x[g]);
-    const T* DY = static_cast<const T*>(a.dy[g]);
+    const size_t col = 4 * c < a.d ? 4 * c : 0;
+    const T* X = static_cast<const T*>(a.x[g]) + col;
+    const T* DY = static_cast<const T*>(a.dy[g]) + col;
+    const float* mean = a.mean[g];
+    const float* rs = a.rstd[g];
     float sg[4] = {0.f, 0.f, 0.f, 0.f}, sb[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int r0 = row0; r0 < end; r0 += 4 * NB) {
-      Q rx[NB], rdy[NB];
-      float mu[NB], rstd[NB];
+    auto add_rows = [&](auto full) {
+      constexpr bool FULL = decltype(full)::value;
+#pragma unroll 1
+      for (int i0 = 0; i0 < 16; i0 += NB) {
+        Q rx[NB], rdy[NB];
+        float mu[NB], rstd[NB];
+        const int rb = row0 + 4 * i0;
 #pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const int row = r0 + 4 * b;
-        if (row < end && live) {
-          mu[b] = a.mean[g][row];
-          rstd[b] = a.rstd[g][row];
-          rx[b] = reinterpret_cast<const Q*>(X + (size_t)row * a.ld)[c];
-          rdy[b] = reinterpret_cast<const Q*>(DY + (size_t)row * a.ld)[c];
+        for (int b = 0; b < NB; ++b) {
+          const int row = FULL ? rb + 4 * b : min(rb + 4 * b, end - 1);
+          mu[b] = mean[row];
+          rstd[b] = rs[row];
+          rx[b] = *reinterpret_cast<const Q*>(X + (size_t)row * a.ld);
+          rdy[b] = *reinterpret_cast<const Q*>(DY + (size_t)row * a.ld);
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          float xv[4], dv[4];
+          unpack4(rx[b], xv);
+          unpack4(rdy[b], dv);
+          const bool in = FULL || rb + 4 * b < end;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float tg = fmaf(dv[e], (xv[e] - mu[b]) * rstd[b], sg[e]), tb = sb[e] + dv[e];
+            sg[e] = in ? tg : sg[e];
+            sb[e] = in ? tb : sb[e];
+          }
         }
       }
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        if (r0 + 4 * b >= end || !live) break;
-        float xv[4], dv[4];
-        unpack4(rx[b], xv);
-        unpack4(rdy[b], dv);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          sg[e] = fmaf(dv[e], (xv[e] - mu[b]) * rstd[b], sg[e]);
-          sb[e] += dv[e];
-        }
-      }
-    }
+    };
+    if (__all(end - first == LN_ROWS_PER_WG)) add_rows(std::true_type());
+    else add_rows(std::false_type());
     *reinterpret_cast<float4*>(&red[chain][4 * (tid & 7)]) = make_float4(sg[0], sg[1], sg[2], sg[3]);
     *reinterpret_cast<float4*>(&red[chain][LN_SPLIT_COLS + 4 * (tid & 7)]) = make_float4(sb[0], sb[1], sb[2], sb[3]);
   }
@@ -653,12 +666,8 @@ static hipError_t ln_bwd_split_run(const LnBwdArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Whether row and column workgroups side by side are the faster form (a choice never changes a bit of the result, so it may look
-// at the group).  d <= 512: up to 3 M elements in one launch (2.1 M 14 | 16 us for ln_bwd_chain_kernel with fp32, 4.2 M 14.1 | 13.9 and
-// 18.1 | 14.1), half of that in two (1.3 M 10.7 | 11.6, 2.1 M 13.7 | 12.0).  Wider: up to 20 MB (bf16 17 MB 21.2 | 26.0, 25 MB 32 | 26;
-// fp32 21 MB 25 | 28, 33 MB 34 | 30).
-// Not where a problem's dx lies over its x or dy: the column workgroups read those while the row workgroups store dx, where the
-// other kernels have read a row before they store it.
+// dx of some problem over its x or dy: the column workgroups of ln_bwd_split_kernel would read those while the row workgroups store
+// dx, where the other kernels have read a row before they store it.
 static bool ln_bwd_in_place(const LnBwdArgs& a) {
   const uintptr_t n = ((size_t)(a.rows - 1) * a.ld + a.d) * (a.dtype == GEMM_F32 ? 4 : 2);
   for (int g = 0; g < a.G; ++g) {
@@ -667,6 +676,10 @@ static bool ln_bwd_in_place(const LnBwdArgs& a) {
   }
   return false;
 }
+// Whether row and column workgroups side by side are the faster form (a choice never changes a bit of the result, so it may look
+// at the group).  us, this | the other form.  d <= 512: up to 3 M elements in one launch (2 M fp32 12.1 | 16.1, 4 M bf16 13.1 | 13.9 and
+// 16.3 | 14.2), half of that in two (1.3 M 9.2 | 11.7, 2 M 12.2 | 12.1 and 11.7 | 13.3, fp32 17.4 | 14.4).  Wider: up to 20 MB (bf16 16 MB
+// 21.5 | 26.7, 24 MB 31.5 | 26.5; fp32 20 MB 24.4 | 28.7, 31 MB 33.0 | 30.7).
 static bool ln_bwd_split(const LnBwdArgs& a) {
   if (a.d > LN_WAVE_ROW_MAX || ln_bwd_in_place(a)) return false;
   const long n = (long)a.G * a.rows * a.d;
