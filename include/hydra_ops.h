@@ -130,7 +130,8 @@ size_t hydra_op_layernorm_part_floats(int rows, int d);
  * multiples of 8, 64 rows (or S, if fewer) of either below 2 GiB. */
 int hydra_op_attention_fwd(int B, int S, int H, int DH, int ld_qkv, int ld_o, int causal, float scale, int G,
                            const void* const* qkv, void* const* o, float* const* lse, void* stream);
-/* Adjoint given dout_g [B*S, ld_o] (gradient w.r.t. o): dqkv_g in the layout of qkv; delta_g [B*H*S] scratch. */
+/* Adjoint given dout_g [B*S, ld_o] (gradient w.r.t. o): dqkv_g in the layout of qkv; delta_g [B*H*S] scratch.
+ * o_g may lie in the query columns of dqkv_g, which then overwrites it; nothing else may overlap dqkv_g or delta_g. */
 int hydra_op_attention_bwd(int B, int S, int H, int DH, int ld_qkv, int ld_o, int causal, float scale, int G,
                            const void* const* qkv, const void* const* o, const void* const* dout,
                            const float* const* lse, float* const* delta, void* const* dqkv, void* stream);

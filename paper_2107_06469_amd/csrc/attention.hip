@@ -623,6 +623,17 @@ bool tiles_ok(const bf16_t* const* m, int G) {
   return (bits & 15) == 0;
 }
 
+// o of some problem inside the buffer that dqkv is written to.  The dq kernel alone reads o, a row before it stores that row of dq;
+// side by side the dk/dv workgroups would read o while dq is stored.
+bool o_in_dqkv(const AttnBwdArgs& a) {
+  const uintptr_t rows = (uintptr_t)a.B * a.S;
+  for (int g = 0; g < a.G; ++g) {
+    const uintptr_t o = (uintptr_t)a.o[g], q = (uintptr_t)a.dqkv[g];
+    if (o < q + rows * a.ld_qkv * 2 && q < o + rows * a.ld_o * 2) return true;
+  }
+  return false;
+}
+
 }  // namespace
 
 hipError_t attn_init() {  // the other kernels stay within the default LDS limit
@@ -648,7 +659,7 @@ hipError_t launch_attn_bwd(const AttnBwdArgs& a, hipStream_t s) {
   // The halves' workgroups fit the chip together: two per CU at DH = 64, one at DH = 128 (490 registers), where a second round of
   // the shorter dq workgroups still pays a little past that.  us, two launches | one: DH = 64, 256 row blocks 53.4 | 43.0;
   // DH = 128, 128 blocks 89.1 | 72.9, 160 56.5 | 46.2, 192 57.7 | 63.5 and 94.9 | 109 (causal 163 | 138), 256 98.9 | 114.
-  if (grid.x <= (a.DH == 64 ? 256 : 160)) {
+  if (grid.x <= (a.DH == 64 ? 256 : 160) && !o_in_dqkv(a)) {
     const dim3 both(2 * grid.x);
     if (a.DH == 64) hipLaunchKernelGGL(attn_bwd_both_kernel<64>, both, dim3(256), dkv_lds<64>(), s, a);
     else hipLaunchKernelGGL(attn_bwd_both_kernel<128>, both, dim3(256), dkv_lds<128>(), s, a);

@@ -424,3 +424,22 @@ def test_attention_refuses_tiles_it_cannot_load(torch, ops):
     for call in (far, lambda: fwd(mk(3 * d, 4)), lambda: bwd(mk(3 * d, 4), mk(d, 0)), lambda: bwd(mk(3 * d, 0), mk(d, 4))):
         with pytest.raises(Exception, match="attention"):
             call()
+
+
+@pytest.mark.parametrize("B,S,H,DH,causal", [(2, 200, 2, 64, False), (1, 300, 2, 128, True), (8, 512, 16, 64, False)])
+def test_attention_backward_over_its_output(torch, ops, B, S, H, DH, causal):
+    """o kept in the query columns of the buffer that dqkv overwrites: the bits of the same call with a buffer of its own, for few row
+    blocks and many."""
+    d, t = H * DH, B * S
+    gen = torch.Generator(device="cuda").manual_seed(S)
+    qkv, do = (torch.randn(t, n * d, generator=gen, device="cuda").to(torch.bfloat16) for n in (3, 1))
+    do3, got = torch.zeros_like(qkv), []
+    do3[:, :d] = do
+    for own in (True, False):
+        o, dqkv = torch.zeros_like(qkv), torch.zeros_like(qkv)
+        lse, delta = torch.zeros(t * H, device="cuda"), torch.zeros(t * H, device="cuda")
+        ops.hydra_op_attention_fwd(B, S, H, DH, 3 * d, 3 * d, causal, DH ** -0.5, [qkv], [o], [lse])
+        dst = dqkv if own else o
+        ops.hydra_op_attention_bwd(B, S, H, DH, 3 * d, 3 * d, causal, DH ** -0.5, [qkv], [o], [do3], [lse], [delta], [dst])
+        got.append((dst, delta))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
