@@ -285,14 +285,16 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const LnBwdArgs a) {
 
 // Up to a workgroup per CU and d <= 512: 16 waves per 64 rows, four rows each, so that a block is a quarter as long.  The row sums
 // need no order among rows; the column sums keep the order of ln_bwd_kernel: waves w, 4 + w, 8 + w, 12 + w hold the rows of its
-// wave w in turn and hand the sums on through LDS.  us, this | 4 waves of 16 rows: 4 x [2048, 256] bf16 12.0 | 17.5, 4 x [4096, 512]
-// (256 blocks) 17.9 | 20.2, 16 x [2048, 512] (512) 30 | 25.5; fp32 2 x [4096, 512] (128) 18.9 | 20.6, 4 x [4096, 512] 26.7 | 25.4.
+// wave w in turn and hand the sums on through LDS.  us, this | 4 waves of 16 rows: 4 x [2048, 256] bf16 12.1 | 17.5, 4 x [4096, 512]
+// (256 blocks) 17.7 | 20.2, 8 x [3094, 224] (392) 22.9 | 22.0, 16 x [2048, 512] (512) 30 | 25.5; fp32 2 x [4096, 512] (128) 19.0 | 20.6,
+// 4 x [4096, 256] (256) 16.6 | 20.2, 4 x [3300, 384] (208) 19.5 | 21.4, 4 x [4096, 512] 26.8 | 25.4.  Held to 64 registers, so that two
+// workgroups fit a CU, it spills: 27-33 at 8 x [3094, 224].
 template <typename T>
 __global__ __launch_bounds__(1024) void ln_bwd_chain_kernel(const LnBwdArgs a) {
   __shared__ float4 red[4][4][64];  // [chain][sums of dgamma: columns 0-3, 4-7 of the lane's chunk; of dbeta][lane]
   const int g = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, w = wave & 3, quarter = wave >> 2;
   const int nch = a.d >> 3, row0 = blockIdx.x * LN_ROWS_PER_WG + w + 16 * quarter;
-  float ga[1][8], none[1][8], xh[4][8], dv[4][8];
+  float ga[1][8], none[1][8];
   LnRow<T, 1> r[4];
 #pragma unroll
   for (int b0 = 0; b0 < 4; b0 += 2) {  // two rows in flight: four spill with fp32
@@ -304,15 +306,6 @@ __global__ __launch_bounds__(1024) void ln_bwd_chain_kernel(const LnBwdArgs a) {
     for (int b = b0; b < b0 + 2; ++b)
       if (row0 + 4 * b < a.rows) ln_bwd_row<T, 1, false>(a, g, row0 + 4 * b, lane, nch, r[b], ga, none, none);
   }
-#pragma unroll
-  for (int b = 0; b < 4; ++b)
-    if (row0 + 4 * b < a.rows && lane < nch) {
-      float xv[8];
-      unpack8<T>(r[b].x[0], xv);
-      unpack8<T>(r[b].dy[0], dv[b]);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) xh[b][e] = (xv[e] - r[b].mu) * r[b].rstd;
-    }
   for (int p = 0; p < 4; ++p) {
     if (quarter == p) {
 #pragma clang fp contract(off)
@@ -330,10 +323,13 @@ __global__ __launch_bounds__(1024) void ln_bwd_chain_kernel(const LnBwdArgs a) {
 #pragma unroll
       for (int b = 0; b < 4; ++b)
         if (row0 + 4 * b < a.rows && lane < nch) {
+          float xv[8], dv[8];
+          unpack8<T>(r[b].x[0], xv);
+          unpack8<T>(r[b].dy[0], dv);
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            sg[e] = fmaf(dv[b][e], xh[b][e], sg[e]);
-            sb[e] += dv[b][e];
+            sg[e] = fmaf(dv[e], (xv[e] - r[b].mu) * r[b].rstd, sg[e]);
+            sb[e] += dv[e];
           }
         }
 #pragma unroll
@@ -646,9 +642,10 @@ template <typename T>
 static hipError_t ln_bwd_pick(const LnBwdArgs& a, hipStream_t s) {
   const dim3 grid(ln_bwd_blocks(a.rows, a.d), a.G);
   const size_t lds = (size_t)4 * 8 * a.d;
-  // one 16-wave workgroup per CU; fp32 rows take as long in one as in four waves when every CU has one
-  const long chain_max = sizeof(T) == 2 ? 256 : 192;
-  if (a.d <= 512 && (long)grid.x * a.G <= chain_max) hipLaunchKernelGGL((ln_bwd_chain_kernel<T>), grid, dim3(1024), 0, s, a);
+  // at most one 16-wave workgroup per CU; wide fp32 rows gain nothing when every CU has one
+  const long blocks = (long)grid.x * a.G;
+  const bool chain = a.d <= 512 && blocks <= 256 && (sizeof(T) == 2 || blocks * a.d <= 96 * 1024);
+  if (chain) hipLaunchKernelGGL((ln_bwd_chain_kernel<T>), grid, dim3(1024), 0, s, a);
   else if (a.d <= 512) hipLaunchKernelGGL((ln_bwd_kernel<T, 1>), grid, dim3(256), lds, s, a);
   else if (a.d <= LN_WAVE_ROW_MAX) hipLaunchKernelGGL((ln_bwd_kernel<T, 2>), grid, dim3(256), lds, s, a);
   else if (a.d <= 2048) hipLaunchKernelGGL((ln_bwd_wide_kernel<T, 1>), grid, dim3(256), 0, s, a);
