@@ -64,15 +64,34 @@ __device__ __forceinline__ f32x16 mfma(const uint4& a, const uint4& b, f32x16 c)
 // that each XCD gets a contiguous run of them, and the 128-row blocks of one (batch, head) are consecutive items: the
 // blocks that read the same K/V (or Q/dO) tiles then run on one XCD and share them through its L2, instead of
 // each XCD fetching them from memory.  Returns false for the padding ids at the end of the grid.
-struct AttnItem { int blk, bh, gi; };
-__device__ __forceinline__ bool attn_item(int wg, int n_blk, int n_bh, int n_g, AttnItem& it) {
-  const int total = n_blk * n_bh * n_g, per_xcd = (total + 7) >> 3;
-  const int id = (wg & 7) * per_xcd + (wg >> 3);
-  if (id >= total || (wg >> 3) >= per_xcd) return false;
-  it.blk = id % n_blk;
-  it.bh = (id / n_blk) % n_bh;
-  it.gi = id / (n_blk * n_bh);
+// What a workgroup does before its first tile has landed is a third of its life at 8 tiles, so that part is kept short in all kernels:
+// three multiplications instead of four integer divisions, every pointer read at once, rows read without branches (rows_from), and
+// nothing that waits for one load before the next is issued.  us, before | now: forward 4 x [32 x 12 heads, 512, 64] 172 | 161,
+// 8 x 32 heads, 2048, 128, causal 411 | 385; backward 490 | 453, 1239 | 1187, 4 x [8 x 16, 384, 64] 102 | 96.6.
+struct AttnGrid { unsigned n_blk, n_bh, n_h, total, per_xcd, r_blk, r_bh, r_h; };  // counts of items, reciprocals (attn_grid)
+struct AttnItem { int blk, bh, gi, b, h; };
+// n / d for the divisor whose reciprocal the host worked out, floor(2^32 / d) (2^32 - 1 for d = 1): one too small at most
+__device__ __forceinline__ unsigned div_by(unsigned n, unsigned d, unsigned rcp) {
+  const unsigned q = __umulhi(n, rcp);
+  return n - q * d >= d ? q + 1 : q;
+}
+__device__ __forceinline__ bool attn_item(unsigned wg, const AttnGrid& gr, AttnItem& it) {
+  const unsigned id = (wg & 7) * gr.per_xcd + (wg >> 3);
+  if (id >= gr.total || (wg >> 3) >= gr.per_xcd) return false;
+  const unsigned u = div_by(id, gr.n_blk, gr.r_blk), gi = div_by(u, gr.n_bh, gr.r_bh), bh = u - gi * gr.n_bh;
+  const unsigned b = div_by(bh, gr.n_h, gr.r_h);
+  it = {(int)(id - u * gr.n_blk), (int)bh, (int)gi, (int)b, (int)(bh - b * gr.n_h)};
   return true;
+}
+// Rows row0.. of a matrix for loads of the lanes' own: rows at or past nrows read as zero, without a branch around the load
+// (between branches every load fetched its pointer anew and waited for it).  src: row 0, which starts col elements into a row of ld.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_from(const bf16_t* src, int ld, int col, int row0, int nrows) {
+  long left = ((long)(nrows - row0) * ld - col) * 2;
+  left = left < 0 ? 0 : left > 0x7fffffffL ? 0x7fffffffL : left;
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(src) + (left ? (long)row0 * ld : 0), 0, (int)left, 0x00020000);
+}
+__device__ __forceinline__ uint4 row_chunk(__amdgpu_buffer_rsrc_t rs, unsigned voff) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, 0, 0));
 }
 
 // XOR term of a row's chunk index.  Two access patterns must each spread over all 64 banks: a 128-bit row read
@@ -113,9 +132,11 @@ struct TileDma {
                        lds_addr + (unsigned)((4 * i + wave) * 64 * 16), voff[ONE ? 0 : i]);
   }
 };
-// every load of this wave has landed, then every wave's
+// every load of this wave has landed, then every wave's.  (A wait written in inline asm the compiler does not count: it waited
+// again, inside the loop, for the fragments loaded before it, and with them for the next tile's loads.)
 __device__ __forceinline__ void tile_landed() {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xf70);  // vmcnt(0)
+  asm volatile("" ::: "memory");
   __syncthreads();
 }
 __device__ __forceinline__ unsigned lds_byte_addr(const void* p) {
@@ -187,7 +208,7 @@ __device__ __forceinline__ uint4 pack_half(const f32x16& p, int x) {
 // registers (four waves per SIMD; 153 when tiles passed through registers); us before | now: 4 x [32 x 12 heads, 512, 64]
 // 179 | 172, 8 x 32 heads, 2048, 128, causal 410 | 405, 2 x [4 x 16, 1024, 128] 90 | 85.
 template <int DH>
-__global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const AttnArgs a) {
+__global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const AttnArgs a, const AttnGrid gr) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
   extern __shared__ __attribute__((aligned(256))) uint4 lds[];
   // two buffers of K [64][NCH], V [64][NCH]
@@ -196,8 +217,8 @@ __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const A
   constexpr int BUF = 2 * 64 * NCH;  // chunks per buffer
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, g = lane >> 5;
   AttnItem item;
-  if (!attn_item(blockIdx.x, (a.S + 127) / 128, a.B * a.H, a.G, item)) return;
-  const int gi = item.gi, bh = item.bh, b = bh / a.H, h = bh % a.H, blk = item.blk;
+  if (!attn_item(blockIdx.x, gr, item)) return;
+  const int gi = item.gi, bh = item.bh, b = item.b, h = item.h, blk = item.blk;
   const int d = a.H * DH;
   const bf16_t* base = a.qkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
   TileDma<DH> dma;
@@ -210,11 +231,9 @@ __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const A
   fetch(0, 0);
   const int iq = blk * 128 + wave * 32 + li;  // this lane's query
   uint4 qf[NK];
+  const __amdgpu_buffer_rsrc_t q_rows = rows_from(base, a.ld_qkv, h * DH, blk * 128 + wave * 32, a.S);
 #pragma unroll
-  for (int kk = 0; kk < NK; ++kk) {
-    qf[kk] = make_uint4(0, 0, 0, 0);
-    if (iq < a.S) qf[kk] = *reinterpret_cast<const uint4*>(base + (size_t)iq * a.ld_qkv + 16 * kk + 8 * g);
-  }
+  for (int kk = 0; kk < NK; ++kk) qf[kk] = row_chunk(q_rows, (unsigned)li * (unsigned)a.ld_qkv * 2u + 32u * kk + 16u * g);
   f32x16 oacc[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c)
@@ -332,7 +351,7 @@ __device__ __forceinline__ float delta_part(const uint4 (&dof)[NK], const uint4 
 }
 
 template <int DH>
-__device__ __forceinline__ void dq_body(const AttnBwdArgs& a, int wg) {
+__device__ __forceinline__ void dq_body(const AttnBwdArgs& a, const AttnGrid& gr, int wg) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
   extern __shared__ __attribute__((aligned(256))) uint4 lds[];
   // two buffers of K [64][NCH], V [64][NCH]
@@ -341,10 +360,16 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, int wg) {
   constexpr int BUF = 2 * 64 * NCH;  // chunks per buffer
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, g = lane >> 5;
   AttnItem item;
-  if (!attn_item(wg, (a.S + 127) / 128, a.B * a.H, a.G, item)) return;
-  const int gi = item.gi, bh = item.bh, b = bh / a.H, h = bh % a.H, blk = item.blk;
+  if (!attn_item(wg, gr, item)) return;
+  const int gi = item.gi, bh = item.bh, b = item.b, h = item.h, blk = item.blk;
   const int d = a.H * DH;
-  const bf16_t* base = a.qkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
+  // every pointer at once, so that their loads are one wait
+  const bf16_t* const base = a.qkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
+  const bf16_t* const dobase = a.dout[gi] + (size_t)b * a.S * a.ld_o + h * DH;
+  const bf16_t* const obase = a.o[gi] + (size_t)b * a.S * a.ld_o + h * DH;
+  const float* const lse = a.lse[gi] + (size_t)bh * a.S;
+  float* const delta_out = a.delta[gi] + (size_t)bh * a.S;
+  bf16_t* const dqbase = a.dqkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
   TileDma<DH> dma;
   dma.init(a.ld_qkv, wave, lane);
   const unsigned lds0 = lds_byte_addr(lds);
@@ -355,20 +380,21 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, int wg) {
   fetch(0, 0);
   const int iq = blk * 128 + wave * 32 + li;
   uint4 qf[NK], dof[NK], of[NK];
+  const int row0 = blk * 128 + wave * 32;
+  const __amdgpu_buffer_rsrc_t q_rows = rows_from(base, a.ld_qkv, h * DH, row0, a.S);
+  const __amdgpu_buffer_rsrc_t do_rows = rows_from(dobase, a.ld_o, h * DH, row0, a.S);
+  const bf16_t* const orow = obase + (size_t)min(iq, a.S - 1) * a.ld_o + 8 * g;  // past the end: a row whose products nobody stores
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) {
-    qf[kk] = dof[kk] = of[kk] = make_uint4(0, 0, 0, 0);
-    if (iq < a.S) {
-      qf[kk] = *reinterpret_cast<const uint4*>(base + (size_t)iq * a.ld_qkv + 16 * kk + 8 * g);
-      const size_t off = ((size_t)b * a.S + iq) * a.ld_o + h * DH + 16 * kk + 8 * g;
-      dof[kk] = *reinterpret_cast<const uint4*>(a.dout[gi] + off);
-      of[kk] = *reinterpret_cast<const uint4*>(a.o[gi] + off);
-    }
+    qf[kk] = row_chunk(q_rows, (unsigned)li * (unsigned)a.ld_qkv * 2u + 32u * kk + 16u * g);
+    dof[kk] = row_chunk(do_rows, (unsigned)li * (unsigned)a.ld_o * 2u + 32u * kk + 16u * g);
+    of[kk] = *reinterpret_cast<const uint4*>(orow + 16 * kk);
   }
+  const __amdgpu_buffer_rsrc_t lse_rows =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(lse), 0, __builtin_amdgcn_readfirstlane(min(a.S, 0x1fffffff) * 4), 0x00020000);
+  const float lse2 = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(lse_rows, iq * 4, 0, 0)) * LOG2E;
   const float2 dh = wave_swap32(delta_part<NK>(dof, of));
   const float delta = dh.x + dh.y;
-  const float lse2 = iq < a.S ? a.lse[gi][(size_t)bh * a.S + iq] * LOG2E : 0.f;
-  if (iq < a.S && g == 0) a.delta[gi][(size_t)bh * a.S + iq] = delta;
   f32x16 acc[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c)
@@ -421,7 +447,8 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, int wg) {
     if (t + 1 < n_tiles) tile(t + 1, std::integral_constant<int, 1>());
   }
   if (iq < a.S) {
-    bf16_t* o = a.dqkv[gi] + ((size_t)b * a.S + iq) * a.ld_qkv + h * DH;
+    if (g == 0) delta_out[iq] = delta;
+    bf16_t* o = dqbase + (size_t)iq * a.ld_qkv;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -442,7 +469,7 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, int wg) {
 // bases128 (64 bytes of scratch, K and V fragments among them): 1362.
 // OWN: the kernel works out delta itself instead of reading what the dq kernel left.
 template <int DH, bool OWN>
-__device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, int wg) {
+__device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, const AttnGrid& gr, int wg) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
   extern __shared__ __attribute__((aligned(256))) uint4 lds[];
   // two buffers of Q [64][NCH], dO [64][NCH], then two of [2][64]: lse*log2e, delta
@@ -451,11 +478,15 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, int wg) {
   float* const st = reinterpret_cast<float*>(lds + 2 * BUF);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, g = lane >> 5;
   AttnItem item;
-  if (!attn_item(wg, (a.S + 127) / 128, a.B * a.H, a.G, item)) return;
-  const int gi = item.gi, bh = item.bh, b = bh / a.H, h = bh % a.H, blk = item.blk;
+  if (!attn_item(wg, gr, item)) return;
+  const int gi = item.gi, bh = item.bh, b = item.b, h = item.h, blk = item.blk;
   const int d = a.H * DH;
-  const bf16_t* base = a.qkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
-  const bf16_t* dobase = a.dout[gi] + (size_t)b * a.S * a.ld_o + h * DH;
+  const bf16_t* const base = a.qkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
+  const bf16_t* const dobase = a.dout[gi] + (size_t)b * a.S * a.ld_o + h * DH;
+  const bf16_t* const obase = OWN ? a.o[gi] + (size_t)b * a.S * a.ld_o + h * DH : nullptr;
+  const float* const lse = a.lse[gi] + (size_t)bh * a.S;
+  float* const delta = a.delta[gi] + (size_t)bh * a.S;
+  bf16_t* const dkbase = a.dqkv[gi] + (size_t)b * a.S * a.ld_qkv + d + h * DH;
   const int t0 = a.causal ? (blk * 128) / 64 : 0;  // queries before the workgroup's first key see none of its keys
   const int n_tiles = (a.S + 63) / 64;
   TileDma<DH, DH == 128> dma_q, dma_o;
@@ -469,10 +500,9 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, int wg) {
     dma_o.issue(dobase, a.ld_o, h * DH, t * 64, a.S, lds0 + buf + 64 * NCH * 16, wave);
     // threads 0..63: lse*log2e, 64..127: delta of query 64 t + tid%64
     if (wave < (OWN ? 1 : 2)) {
-      float* const p = (wave == 0 ? const_cast<float*>(a.lse[gi]) : a.delta[gi]) + (size_t)bh * a.S + t * 64;
+      float* const p = (wave == 0 ? const_cast<float*>(lse) : delta) + t * 64;
       const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(p, 0, min(a.S - t * 64, 64) * 4, 0x00020000);
       pst = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, 0, 0));  // zero past the last query
-      if (wave == 0) pst *= LOG2E;
     }
     if (OWN && wave >= 2) {  // waves 2 and 3: 32 queries each, two lanes to a query as in the dq kernel
       const int i = t * 64 + (wave - 2) * 32 + li;
@@ -482,32 +512,30 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, int wg) {
         if (i < a.S) {
           const size_t off = (size_t)i * a.ld_o + 16 * kk + 8 * g;
           own_do[kk] = *reinterpret_cast<const uint4*>(dobase + off);
-          own_o[kk] = *reinterpret_cast<const uint4*>(a.o[gi] + (size_t)b * a.S * a.ld_o + h * DH + off);
+          own_o[kk] = *reinterpret_cast<const uint4*>(obase + off);
         }
       }
     }
   };
   auto put_stats = [&](float* stb) {
-    if (wave < (OWN ? 1 : 2)) stb[tid] = pst;
+    if (wave < (OWN ? 1 : 2)) stb[tid] = wave == 0 ? pst * LOG2E : pst;
     if (OWN && wave >= 2) {
       const float2 dh = wave_swap32(delta_part<NK>(own_do, own_o));
       if (g == 0) stb[64 + (wave - 2) * 32 + li] = dh.x + dh.y;
     }
   };
-  if (t0 < n_tiles) {
-    fetch(t0, 0);
-    put_stats(st);
-  }
+  if (t0 < n_tiles) fetch(t0, 0);
   const int jk = blk * 128 + wave * 32 + li;  // this lane's key
   uint4 kf[NK], vf[NK];
+  const __amdgpu_buffer_rsrc_t k_rows = rows_from(base + d, a.ld_qkv, d + h * DH, blk * 128 + wave * 32, a.S);
+  const __amdgpu_buffer_rsrc_t v_rows = rows_from(base + 2 * d, a.ld_qkv, 2 * d + h * DH, blk * 128 + wave * 32, a.S);
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) {
-    kf[kk] = vf[kk] = make_uint4(0, 0, 0, 0);
-    if (jk < a.S) {
-      kf[kk] = *reinterpret_cast<const uint4*>(base + d + (size_t)jk * a.ld_qkv + 16 * kk + 8 * g);
-      vf[kk] = *reinterpret_cast<const uint4*>(base + 2 * d + (size_t)jk * a.ld_qkv + 16 * kk + 8 * g);
-    }
+    const unsigned vo = (unsigned)li * (unsigned)a.ld_qkv * 2u + 32u * kk + 16u * g;
+    kf[kk] = row_chunk(k_rows, vo);
+    vf[kk] = row_chunk(v_rows, vo);
   }
+  if (t0 < n_tiles) put_stats(st);
   f32x16 dk[NC], dv[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c)
@@ -571,7 +599,7 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, int wg) {
     if (t + 1 < n_tiles) tile(t + 1, std::integral_constant<int, 1>());
   }
   if (jk < a.S) {
-    bf16_t* ok = a.dqkv[gi] + ((size_t)b * a.S + jk) * a.ld_qkv + d + h * DH;
+    bf16_t* ok = dkbase + (size_t)jk * a.ld_qkv;
     bf16_t* ov = ok + d;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
@@ -588,12 +616,12 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, int wg) {
 }
 
 template <int DH>
-__global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dq_kernel(const AttnBwdArgs a) {
-  dq_body<DH>(a, blockIdx.x);
+__global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dq_kernel(const AttnBwdArgs a, const AttnGrid gr) {
+  dq_body<DH>(a, gr, blockIdx.x);
 }
 template <int DH>
-__global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dkv_kernel(const AttnBwdArgs a) {
-  dkv_body<DH, false>(a, blockIdx.x);
+__global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dkv_kernel(const AttnBwdArgs a, const AttnGrid gr) {
+  dkv_body<DH, false>(a, gr, blockIdx.x);
 }
 // Small launches: both halves of the backward pass side by side, dk/dv (the longer one) first.  They share nothing but delta,
 // which the dk/dv workgroups then work out themselves from rows of dO and O (same bits): a few percent more work for
@@ -601,10 +629,10 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dkv_kernel(con
 // Backward pass, two launches | one, us: 4 x [8 x 4 heads, 128, 64] 17.0 | 10.5, 1 x [4 x 8, 100, 128] 25.5 | 16.1, 2 x [2 x 4, 512, 64]
 // 31.6 | 20.6, 1 x [1 x 4, 2048, 128] causal 166 | 131, 4 x [8 x 4, 256, 64] (256 row blocks) 24.4 | 18.3.
 template <int DH>
-__global__ __launch_bounds__(256, DH == 64 ? 2 : 1) void attn_bwd_both_kernel(const AttnBwdArgs a) {
+__global__ __launch_bounds__(256, DH == 64 ? 2 : 1) void attn_bwd_both_kernel(const AttnBwdArgs a, const AttnGrid gr) {
   const int half = gridDim.x / 2;
-  if ((int)blockIdx.x < half) dkv_body<DH, true>(a, blockIdx.x);
-  else dq_body<DH>(a, blockIdx.x - half);
+  if ((int)blockIdx.x < half) dkv_body<DH, true>(a, gr, blockIdx.x);
+  else dq_body<DH>(a, gr, blockIdx.x - half);
 }
 
 template <int DH> constexpr size_t fwd_lds() { return (size_t)2 * 2 * 64 * (DH / 8) * 16; }
@@ -634,6 +662,20 @@ bool o_in_dqkv(const AttnBwdArgs& a) {
   return false;
 }
 
+// Work items of a launch: 128-row blocks of every (batch, head) of every problem
+dim3 attn_grid(int B, int S, int H, int G, AttnGrid& gr) {
+  auto rcp = [](unsigned d) { return d == 1 ? 0xffffffffu : (unsigned)((1ull << 32) / d); };
+  gr.n_blk = ((unsigned)S + 127) / 128;
+  gr.n_bh = (unsigned)B * H;
+  gr.n_h = H;
+  gr.total = gr.n_blk * gr.n_bh * G;
+  gr.per_xcd = (gr.total + 7) / 8;
+  gr.r_blk = rcp(gr.n_blk);
+  gr.r_bh = rcp(gr.n_bh);
+  gr.r_h = rcp(gr.n_h);
+  return dim3(gr.per_xcd * 8);
+}
+
 }  // namespace
 
 hipError_t attn_init() {  // the other kernels stay within the default LDS limit
@@ -646,31 +688,33 @@ hipError_t attn_init() {  // the other kernels stay within the default LDS limit
 
 hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
   if (!attn_ok(a.B, a.S, a.H, a.DH, a.ld_qkv, a.ld_o, a.G) || !tiles_ok(a.qkv, a.G)) return hipErrorInvalidValue;
-  dim3 grid(((((a.S + 127) / 128) * a.B * a.H * a.G + 7) / 8) * 8);
-  if (a.DH == 64) hipLaunchKernelGGL(attn_fwd_kernel<64>, grid, dim3(256), fwd_lds<64>(), s, a);
-  else hipLaunchKernelGGL(attn_fwd_kernel<128>, grid, dim3(256), fwd_lds<128>(), s, a);
+  AttnGrid gr;
+  const dim3 grid = attn_grid(a.B, a.S, a.H, a.G, gr);
+  if (a.DH == 64) hipLaunchKernelGGL(attn_fwd_kernel<64>, grid, dim3(256), fwd_lds<64>(), s, a, gr);
+  else hipLaunchKernelGGL(attn_fwd_kernel<128>, grid, dim3(256), fwd_lds<128>(), s, a, gr);
   return hipGetLastError();
 }
 
 hipError_t launch_attn_bwd(const AttnBwdArgs& a, hipStream_t s) {
   if (!attn_ok(a.B, a.S, a.H, a.DH, a.ld_qkv, a.ld_o, a.G) || !tiles_ok(a.qkv, a.G) || !tiles_ok(a.dout, a.G))
     return hipErrorInvalidValue;
-  dim3 grid(((((a.S + 127) / 128) * a.B * a.H * a.G + 7) / 8) * 8);
+  AttnGrid gr;
+  const dim3 grid = attn_grid(a.B, a.S, a.H, a.G, gr);
   // The halves' workgroups fit the chip together: two per CU at DH = 64, one at DH = 128 (490 registers), where a second round of
   // the shorter dq workgroups still pays a little past that.  us, two launches | one: DH = 64, 256 row blocks 53.4 | 43.0;
   // DH = 128, 128 blocks 89.1 | 72.9, 160 56.5 | 46.2, 192 57.7 | 63.5 and 94.9 | 109 (causal 163 | 138), 256 98.9 | 114.
   if (grid.x <= (a.DH == 64 ? 256 : 160) && !o_in_dqkv(a)) {
     const dim3 both(2 * grid.x);
-    if (a.DH == 64) hipLaunchKernelGGL(attn_bwd_both_kernel<64>, both, dim3(256), dkv_lds<64>(), s, a);
-    else hipLaunchKernelGGL(attn_bwd_both_kernel<128>, both, dim3(256), dkv_lds<128>(), s, a);
+    if (a.DH == 64) hipLaunchKernelGGL(attn_bwd_both_kernel<64>, both, dim3(256), dkv_lds<64>(), s, a, gr);
+    else hipLaunchKernelGGL(attn_bwd_both_kernel<128>, both, dim3(256), dkv_lds<128>(), s, a, gr);
     return hipGetLastError();
   }
   if (a.DH == 64) {
-    hipLaunchKernelGGL(attn_bwd_dq_kernel<64>, grid, dim3(256), dq_lds<64>(), s, a);
-    hipLaunchKernelGGL(attn_bwd_dkv_kernel<64>, grid, dim3(256), dkv_lds<64>(), s, a);
+    hipLaunchKernelGGL(attn_bwd_dq_kernel<64>, grid, dim3(256), dq_lds<64>(), s, a, gr);
+    hipLaunchKernelGGL(attn_bwd_dkv_kernel<64>, grid, dim3(256), dkv_lds<64>(), s, a, gr);
   } else {
-    hipLaunchKernelGGL(attn_bwd_dq_kernel<128>, grid, dim3(256), dq_lds<128>(), s, a);
-    hipLaunchKernelGGL(attn_bwd_dkv_kernel<128>, grid, dim3(256), dkv_lds<128>(), s, a);
+    hipLaunchKernelGGL(attn_bwd_dq_kernel<128>, grid, dim3(256), dq_lds<128>(), s, a, gr);
+    hipLaunchKernelGGL(attn_bwd_dkv_kernel<128>, grid, dim3(256), dkv_lds<128>(), s, a, gr);
   }
   return hipGetLastError();
 }

@@ -318,6 +318,31 @@ def test_attention_keeps_its_bits(torch, ops, line):
     assert attention_bits(torch, ops, *[int(x) for x in line[:6]]) == line[6]
 
 
+@pytest.mark.parametrize("G,B,S,H,DH,causal", [(1, 1, 1, 1, 64, False), (3, 2, 129, 1, 64, True), (2, 3, 127, 5, 128, False), (2, 5, 257, 3, 64, False),
+                                                (5, 7, 300, 7, 64, True), (1, 2, 385, 3, 128, True)])
+def test_attention_of_a_group_equals_its_parts(torch, ops, G, B, S, H, DH, causal):
+    """A workgroup finds its problem, batch row, head and row block by multiplications with reciprocals: every (problem, batch row) of a
+    launch gives the bits it gives alone, at counts of one and at ones that divide nothing."""
+    d, gen = H * DH, torch.Generator(device="cuda").manual_seed(S * 31 + H)
+    mk = lambda n: torch.randn(n, generator=gen, device="cuda").to(torch.bfloat16)  # noqa: E731
+    qkv, do = [mk(B * S * 3 * d).view(B * S, 3 * d) for _ in range(G)], [mk(B * S * d).view(B * S, d) for _ in range(G)]
+
+    def run(qs, gs, b):
+        o, dq = [torch.full_like(x, 7.0) for x in gs], [torch.full_like(x, 7.0) for x in qs]
+        lse, delta = ([torch.full((b * H * S,), 7.0, device="cuda") for _ in qs] for _ in range(2))
+        ops.hydra_op_attention_fwd(b, S, H, DH, 3 * d, d, causal, DH ** -0.5, qs, o, lse)
+        ops.hydra_op_attention_bwd(b, S, H, DH, 3 * d, d, causal, DH ** -0.5, qs, o, gs, lse, delta, dq)
+        return o, lse, delta, dq
+
+    whole = run(qkv, do, B)
+    for g in range(G):
+        for b in range(B):
+            r, hs = slice(b * S, (b + 1) * S), slice(b * H * S, (b + 1) * H * S)
+            part = run([qkv[g][r].contiguous()], [do[g][r].contiguous()], 1)
+            for w, p, sl in zip(whole, part, (r, hs, hs, r)):
+                assert torch.equal(w[g][sl], p[0]), (g, b)
+
+
 def _column_sums(dv, xh, rows):
     """dgamma, dbeta in fp32 in the order the kernels add them: rows r, r + 4, ... of a block of 64 are a chain of fused multiply-adds,
     four chains make the block's partial sum, the blocks are added in 16 ranges.  (64-bit mantissas hold the products; the fused
