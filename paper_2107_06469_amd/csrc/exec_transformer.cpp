@@ -50,6 +50,11 @@ struct Ctx {
   int G, Tk, NT, d, F, V, H, DH, ldv;
   const hydra_arch& a;
   Idx ix;
+  // A weight gradient with its update that was held back for the next input gradient (wgrad, dgrad below)
+  bool held = false;
+  GemmArgs hw{};
+  GemmUpdate hu{};
+  double h_flops = 0.0, h_bytes = 0.0;
   Ctx(hydra_ctx* c_, const Bucket& b_, hipStream_t s_)
       : c(c_), b(b_), s(s_), a(c_->models[b_.members[0].first].arch), ix(a) {
     G = (int)b.members.size();
@@ -214,9 +219,25 @@ static hydra_status tr_forward(Ctx& x, int batch, int step) {
   return HYDRA_OK;
 }
 
+#define TRY(expr)                      \
+  do {                                 \
+    hydra_status st_ = (expr);         \
+    if (st_ != HYDRA_OK) return st_;   \
+  } while (0)
+
+static hydra_status flush_held(Ctx& x) {
+  if (!x.held) return HYDRA_OK;
+  x.held = false;
+  HYDRA_LAUNCH(x.c, HYDRA_K_WGRAD_UPDATE, x.s, x.h_flops, x.h_bytes, launch_gemm_update(x.hw, x.hu, x.s));
+  return HYDRA_OK;
+}
+
 // weight gradient dW[N_out, K_in] = dy[rows, N_out]^T x_in[rows, K_in] of tensor jw[i] of member i, plus the
 // bias gradient = column sums of dy (computed by the same launch from the dy fragments it loads).  In fused-update mode the GEMM's epilogue applies the update of
-// the weight, so every reader of the old weight (the matching dgrad) must have been issued before.
+// the weight, so every reader of the old weight (the matching dgrad) must have been issued before.  A small one is held back for
+// the next input gradient, which it then shares a launch with: between the two the pass writes neither dy nor x_in of any of its
+// products (a block's gradients have buffers of their own, and the next use of each lies behind that input gradient), and nothing
+// reads the weight before the end of the pass, where the last one is let go.
 static hydra_status wgrad(Ctx& x, int step, int rows, int n_out, int k_in, int ld_dy, int ld_x, const void* const* dy,
                           const void* const* xin, const int* jw, float* const* db) {
   hydra_ctx* c = x.c;
@@ -238,8 +259,17 @@ static hydra_status wgrad(Ctx& x, int step, int rows, int n_out, int k_in, int l
       up.w16[i] = sh.w16 + o;
       up.hp[i] = step_hparams(x.model(i), step);
     }
-    HYDRA_LAUNCH(c, HYDRA_K_WGRAD_UPDATE, x.s, 2.0 * w.M * w.N * w.K * x.G,
-                 (fused_update_bytes(up.opt, true) * w.M * w.N + 2.0 * w.K * (w.M + w.N)) * x.G, launch_gemm_update(w, up, x.s));
+    TRY(flush_held(x));
+    const double bytes = (fused_update_bytes(up.opt, true) * w.M * w.N + 2.0 * w.K * (w.M + w.N)) * x.G;
+    if (gemm_pair_waits(w)) {
+      x.held = true;
+      x.hw = w;
+      x.hu = up;
+      x.h_flops = 2.0 * w.M * w.N * w.K * x.G;
+      x.h_bytes = bytes;
+      return HYDRA_OK;
+    }
+    HYDRA_LAUNCH(c, HYDRA_K_WGRAD_UPDATE, x.s, 2.0 * w.M * w.N * w.K * x.G, bytes, launch_gemm_update(w, up, x.s));
   } else {
     HYDRA_LAUNCH(c, HYDRA_K_GEMM_WGRAD, x.s, 2.0 * w.M * w.N * w.K * x.G, 0.0, launch_gemm(w, x.s));
   }
@@ -258,15 +288,16 @@ static hydra_status dgrad(Ctx& x, int rows, int n_out, int k_in, int ld_dy, cons
     g.gate[i] = gate ? gate[i] : nullptr;
     g.resid[i] = resid ? resid[i] : nullptr;
   }
+  if (x.held && gemm_pair_ok(g, x.hw)) {
+    x.held = false;
+    HYDRA_LAUNCH2(c, HYDRA_K_GEMM_DGRAD, HYDRA_K_WGRAD_UPDATE, x.s, 2.0 * g.M * g.N * g.K * x.G, x.h_flops, 0.0,
+                  launch_gemm_pair(g, x.hw, x.hu, x.s));
+    return HYDRA_OK;
+  }
+  TRY(flush_held(x));
   HYDRA_LAUNCH(c, HYDRA_K_GEMM_DGRAD, x.s, 2.0 * g.M * g.N * g.K * x.G, 0.0, launch_gemm(g, x.s));
   return HYDRA_OK;
 }
-
-#define TRY(expr)                      \
-  do {                                 \
-    hydra_status st_ = (expr);         \
-    if (st_ != HYDRA_OK) return st_;   \
-  } while (0)
 
 static hydra_status tr_backward(Ctx& x, int batch, int step) {
   hydra_ctx* c = x.c;
@@ -401,7 +432,7 @@ static hydra_status tr_backward(Ctx& x, int batch, int step) {
     HYDRA_LAUNCH(c, HYDRA_K_EMBED, x.s, 0.0, (double)G * ((double)Tk * d * 2 + ((double)x.V + x.a.max_seq) * d * 4),
                  launch_embed_bwd(e, x.s));
   }
-  return HYDRA_OK;
+  return flush_held(x);
 }
 
 hydra_status tr_run(hydra_ctx* c, const Bucket& b, int batch, int step, hipStream_t s) {

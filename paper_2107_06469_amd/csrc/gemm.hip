@@ -1200,7 +1200,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
 // instead of one: 2 x [300 rows, 8192 -> 512] 47 -> 40 us, 1 x 1024 x 1024 weight gradient over 4096 tokens 28.6 -> 24.3;
 // at K = 1024 it is 3-10 % behind).
 template <int CPR, int NS, bool X_KMAJ, bool W_KMAJ, bool UPD>
-__global__ __launch_bounds__(256) void gemm_small_kernel(const GemmArgs a, const typename UpdSel<UPD>::type upd) {
+__device__ __forceinline__ void small_body(const GemmArgs& a, const typename UpdSel<UPD>::type& upd, int tm, int tn, int g) {
   typedef bf16_t T;
   constexpr int E = Elem<T>::E, BK = CPR * E, NSTEP = CPR / 2;
   constexpr int BM = 64, BN = 64;
@@ -1211,7 +1211,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const GemmArgs a, const
   extern __shared__ uint4 lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int g = blockIdx.z, m0 = blockIdx.x * BM, n0 = blockIdx.y * BN, K = a.K;
+  const int m0 = tm * BM, n0 = tn * BN, K = a.K;
   RX ox;
   RW ow;
   ox.init(static_cast<const T*>(a.X[g]), a.ldx, m0, a.M, K, wave, lane);
@@ -1286,6 +1286,31 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const GemmArgs a, const
   constexpr int SP = 36;
   float* patch = reinterpret_cast<float*>(lds) + wave * (32 * SP);
   tile_epilogue<T, 1, 1, UPD, UPD ? 0 : (!X_KMAJ ? 0 : (W_KMAJ ? 1 : 2))>(acc, patch, a, upd, g, m0 + wm * 32, n0 + wn * 32, lane);
+}
+
+template <int CPR, int NS, bool X_KMAJ, bool W_KMAJ, bool UPD>
+__global__ __launch_bounds__(256) void gemm_small_kernel(const GemmArgs a, const typename UpdSel<UPD>::type upd) {
+  small_body<CPR, NS, X_KMAJ, W_KMAJ, UPD>(a, upd, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+
+// Two products of different layers side by side: an input gradient, which the backward pass waits for, and a weight gradient with its
+// update, which nothing in the pass waits for.  Each alone is bound by the latency of its tiles, so the second costs little.
+// The weight gradient's tiles come first, the longer ones.  r_*: floor(2^32 / d) of the divisor beside it (2^32 - 1 for d = 1).
+struct PairGrid { unsigned n_w, w_tm, w_tn, r_wtm, r_wtn, d_tm, d_tn, r_dtm, r_dtn; };
+template <int WCPR, int WNS>
+__global__ __launch_bounds__(256) void gemm_small_pair_kernel(const GemmArgs d, const GemmArgs w, const GemmUpdate u, const PairGrid gr) {
+  auto div = [](unsigned n, unsigned by, unsigned rcp) {  // the estimate is one too small at most
+    const unsigned q = __umulhi(n, rcp);
+    return n - q * by >= by ? q + 1 : q;
+  };
+  const unsigned id = blockIdx.x;
+  if (id < gr.n_w) {
+    const unsigned t = div(id, gr.w_tm, gr.r_wtm), g = div(t, gr.w_tn, gr.r_wtn);
+    small_body<WCPR, WNS, false, false, true>(w, u, (int)(id - t * gr.w_tm), (int)(t - g * gr.w_tn), (int)g);
+  } else {
+    const unsigned e = id - gr.n_w, t = div(e, gr.d_tm, gr.r_dtm), g = div(t, gr.d_tn, gr.r_dtn);
+    small_body<16, 2, true, false, false>(d, NoUpdate(), (int)(e - t * gr.d_tm), (int)(t - g * gr.d_tn), (int)g);
+  }
 }
 
 // fp32.  A 32x32 accumulator costs 64 cycles of one SIMD per 2 k (10 us for K = 768, which nothing can hide where a launch
@@ -1930,6 +1955,22 @@ hipError_t dispatch(const GemmArgs& a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+int pair_side(const GemmArgs& a) { return ((a.M + 63) / 64) * ((a.N + 63) / 64) * a.G; }
+hipError_t run_pair(const GemmArgs& d, const GemmArgs& w, const GemmUpdate& u, hipStream_t s) {
+  auto rcp = [](unsigned v) { return v == 1 ? 0xffffffffu : (unsigned)((1ull << 32) / v); };
+  PairGrid gr;
+  gr.n_w = (unsigned)pair_side(w);
+  gr.w_tm = (w.M + 63) / 64; gr.w_tn = (w.N + 63) / 64; gr.r_wtm = rcp(gr.w_tm); gr.r_wtn = rcp(gr.w_tn);
+  gr.d_tm = (d.M + 63) / 64; gr.d_tn = (d.N + 63) / 64; gr.r_dtm = rcp(gr.d_tm); gr.r_dtn = rcp(gr.d_tn);
+  const dim3 grid(gr.n_w + (unsigned)pair_side(d));
+  static_assert(SmallBf16::LDS == SmallBf16Deep::LDS, "one LDS size for both sides");
+  if (choose_update_tile(w) == TILE_SMALL)
+    hipLaunchKernelGGL((gemm_small_pair_kernel<16, 2>), grid, dim3(256), SmallBf16::LDS, s, d, w, u, gr);
+  else
+    hipLaunchKernelGGL((gemm_small_pair_kernel<8, 4>), grid, dim3(256), SmallBf16::LDS, s, d, w, u, gr);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t init_tiles() {
   hipError_t e;
@@ -1947,6 +1988,12 @@ hipError_t gemm_init() {
   if ((e = SmallBf16::attr()) != hipSuccess) return e;
   if ((e = SmallBf16Deep::attr()) != hipSuccess) return e;
   if ((e = SmallF32::attr()) != hipSuccess) return e;
+  if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_small_pair_kernel<16, 2>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)SmallBf16::LDS)) != hipSuccess)
+    return e;
+  if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_small_pair_kernel<8, 4>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)SmallBf16::LDS)) != hipSuccess)
+    return e;
   if ((e = DmaMidDeep::attr_x()) != hipSuccess) return e;
   e = init_tiles<bf16_t>();
   return e != hipSuccess ? e : init_tiles<float>();
@@ -2000,7 +2047,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   return a.dtype == GEMM_F32 ? dispatch<float>(a, s) : dispatch<bf16_t>(a, s);
 }
 
-hipError_t launch_gemm_update(const GemmArgs& a, const GemmUpdate& u, hipStream_t s) {
+static hipError_t check_update(const GemmArgs& a, const GemmUpdate& u) {
   hipError_t e = check_gemm(a, false);
   if (e != hipSuccess) return e;
   if (a.x_kmajor || a.w_kmajor || !a.out_f32 || a.act != EPI_ACT_NONE) return hipErrorInvalidValue;
@@ -2014,7 +2061,35 @@ hipError_t launch_gemm_update(const GemmArgs& a, const GemmUpdate& u, hipStream_
         ((uintptr_t)a.out[g] & 31))
       return hipErrorInvalidValue;
   }
+  return hipSuccess;
+}
+
+hipError_t launch_gemm_update(const GemmArgs& a, const GemmUpdate& u, hipStream_t s) {
+  const hipError_t e = check_update(a, u);
+  if (e != hipSuccess) return e;
   return a.dtype == GEMM_F32 ? dispatch_update<float>(a, u, s) : dispatch_update<bf16_t>(a, u, s);
+}
+
+bool gemm_pair_waits(const GemmArgs& w) {
+  if (w.dtype != GEMM_BF16 || w.tile || split_for(w) > 1) return false;
+  const int t = choose_update_tile(w);
+  return t == TILE_SMALL || t == TILE_SMALL_DEEP;
+}
+// The update takes 64x64 tiles by its own rule; the input gradient does too, or would take 128x128 ones and is small enough that
+// together they stay within five workgroups per CU.  us, one after the other | as one launch (4 models of 1024 tokens, d = 256): 1024 -> 256 with
+// the update of 256 x 1024 23 | 17, 256 -> 256 with 1024 x 256 20 | 17, 768 -> 256 with 256 x 256 20 | 13; an epoch of 20 steps of such
+// encoders 15.2 | 13.83 ms, and 13.64 with the pairs whose input gradient alone would take 128x128 tiles (256 -> 1024 with 768 x 256).
+bool gemm_pair_ok(const GemmArgs& d, const GemmArgs& w) {
+  if (!gemm_pair_waits(w) || d.dtype != GEMM_BF16 || d.tile || !d.x_kmajor || d.w_kmajor || d.K > 1024 || !small_eligible(d)) return false;
+  const int t = choose_tile(d);
+  return (t == TILE_SMALL || t == 2) && (long)pair_side(d) + pair_side(w) <= 1280;
+}
+hipError_t launch_gemm_pair(const GemmArgs& d, const GemmArgs& w, const GemmUpdate& u, hipStream_t s) {
+  hipError_t e = check_gemm(d, true);
+  if (e == hipSuccess) e = check_update(w, u);
+  if (e != hipSuccess) return e;
+  if (!gemm_pair_ok(d, w)) return hipErrorInvalidValue;
+  return run_pair(d, w, u, s);
 }
 
 }  // namespace hydra

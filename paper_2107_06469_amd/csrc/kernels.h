@@ -144,6 +144,12 @@ struct GemmUpdate {
   OptimHp hp[MAXG];
 };
 hipError_t launch_gemm_update(const GemmArgs& a, const GemmUpdate& u, hipStream_t s);
+// An input gradient d (bf16, x_kmajor = 1, w_kmajor = 0) and a weight gradient with its update w, u of another layer, neither of which
+// reads or writes what the other writes, as one launch: the same results as launch_gemm and launch_gemm_update.  gemm_pair_ok:
+// whether the two sizes are taken; gemm_pair_waits: whether w is taken with any d (then it may be worth holding back for one).
+bool gemm_pair_waits(const GemmArgs& w);
+bool gemm_pair_ok(const GemmArgs& d, const GemmArgs& w);
+hipError_t launch_gemm_pair(const GemmArgs& d, const GemmArgs& w, const GemmUpdate& u, hipStream_t s);
 
 // ---- whole shard phases of small fp32 MLPs in one launch (mlp_fused.hip) --------------------------------------
 // For models with at most 32 rows per step and layers at most 256 wide: the forward pass of a shard's units [u0, u1)

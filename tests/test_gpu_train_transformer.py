@@ -8,6 +8,7 @@ import os
 import numpy as np
 import pytest
 
+from hydra_workloads import configs as C
 from hydra_workloads import make_data, scaled_workload, workload
 from oracle import model as OM
 from oracle import optim as OO
@@ -105,6 +106,23 @@ def test_first_step_gradients_transformer(H, i):
                 bad.append(f"model {k} {nm}: rel {rel:.3e} cos {cos:.5f}")
     H.hydra_destroy(ctx)
     assert not bad, "; ".join(bad)
+
+
+@pytest.mark.parametrize("batch,seq,d,heads,ffn,vocab", [(2, 40, 64, 1, 136, 70), (8, 128, 128, 2, 512, 301), (9, 120, 128, 2, 264, 96), (3, 130, 256, 4, 1024, 64)])
+def test_paired_gradient_launches_keep_the_bits_of_separate_ones(H, batch, seq, d, heads, ffn, vocab):
+    """Small weight gradients with their update share a launch with the next input gradient (both tile shapes of the update: sums of up to
+    1024 tokens and longer ones); with gradients kept every product is a launch of its own.  Losses and parameters are the same bits, and
+    the paired run has fewer launches."""
+    archs = [C.transformer_arch(C.KIND_ENCODER, 2, d, heads, ffn, vocab, seq, 0, C.DTYPE_BF16) for _ in range(2)]
+    w = C.Workload("encoder_pairs", 2, archs, [C.hparams(C.OPT_ADAM, 1e-3), C.hparams(C.OPT_SGD, 1e-2)], [[1]] * 2, batch, seq, 5, 3, 3, 31 + seq)
+    data = make_data(w)
+    paired, ps = H.train_workload(w, data, H.SCHED_SHARD_PARALLEL)
+    apart, as_ = H.train_workload(w, data, H.SCHED_SHARD_PARALLEL, keep_grads=True)
+    assert ps[0]["launches"] < as_[0]["launches"]
+    for k in range(w.K):
+        assert np.array_equal(paired[k][0], apart[k][0])
+        for a, b in zip(paired[k][1], apart[k][1]):
+            assert np.array_equal(a, b)
 
 
 def test_data_is_validated(H):
