@@ -40,6 +40,12 @@ __global__ void fill_u32_kernel(uint32_t* dst, size_t n, uint32_t v) {
   for (; i < n; i += stride) dst[i] = v;
 }
 
+struct FillGroup { uint32_t* dst[MAXG]; };
+__global__ void fill_group_kernel(const FillGroup a, size_t n, uint32_t v) {
+  uint32_t* const dst = a.dst[blockIdx.y];
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) dst[i] = v;
+}
+
 __global__ void cast_bf16_kernel(const float* __restrict__ src, bf16_t* __restrict__ dst, size_t n) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -111,6 +117,14 @@ hipError_t launch_init_uniform(float* dst, size_t n, uint64_t key, float a, hipS
 hipError_t launch_fill_u32(uint32_t* dst, size_t n, uint32_t v, hipStream_t s) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(fill_u32_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, dst, n, v);
+  return hipGetLastError();
+}
+hipError_t launch_fill_group_u32(uint32_t* const* dst, int G, size_t n, uint32_t v, hipStream_t s) {
+  if (G < 1 || G > MAXG) return hipErrorInvalidValue;
+  if (n == 0) return hipSuccess;
+  FillGroup a{};
+  for (int g = 0; g < G; ++g) a.dst[g] = dst[g];
+  hipLaunchKernelGGL(fill_group_kernel, dim3(blocks_for(n, 256), G), dim3(256), 0, s, a, n, v);
   return hipGetLastError();
 }
 hipError_t launch_fill_f32(float* dst, size_t n, float v, hipStream_t s) {

@@ -324,8 +324,9 @@ static hydra_status tr_backward(Ctx& x, int batch, int step) {
     TRY(dgrad(x, NT, V, d, x.ldv, pa, pc, po, nullptr, nullptr));
     TRY(wgrad(x, step, NT, V, d, x.ldv, d, pa, pb, jw, pbias));
     // scatter the target rows into a zero [Tk, d] gradient of the final LayerNorm's output
-    FOR_G HYDRA_LAUNCH(c, HYDRA_K_ELEMENTWISE, x.s, 0.0, (double)Tk * d * 2,
-                       launch_fill_u32(static_cast<uint32_t*>(x.scratch(i).dxf), (size_t)Tk * d / 2, 0u, x.s));
+    uint32_t* zero[MAXG];
+    FOR_G zero[i] = static_cast<uint32_t*>(x.scratch(i).dxf);
+    HYDRA_LAUNCH(c, HYDRA_K_ELEMENTWISE, x.s, 0.0, (double)G * Tk * d * 2, launch_fill_group_u32(zero, G, (size_t)Tk * d / 2, 0u, x.s));
     RowsArgs sc{};
     sc.dtype = GEMM_BF16; sc.n = NT; sc.d = d; sc.ld_src = d; sc.ld_dst = d; sc.G = G;
     sc.rows = c->tgt_pos + (size_t)batch * NT;
@@ -428,7 +429,6 @@ static hydra_status tr_backward(Ctx& x, int batch, int step) {
     e.row_ptr = c->csr_ptr + (size_t)batch * (x.V + 1);
     e.positions = c->csr_pos + (size_t)batch * Tk;
     FOR_G { e.dx[i] = x.dxin(i, 0); e.dtok[i] = x.g32(i, 0); e.dpos[i] = x.g32(i, 1); }
-    ++c->launches;
     HYDRA_LAUNCH(c, HYDRA_K_EMBED, x.s, 0.0, (double)G * ((double)Tk * d * 2 + ((double)x.V + x.a.max_seq) * d * 4),
                  launch_embed_bwd(e, x.s));
   }

@@ -74,6 +74,7 @@ struct PtrGroup {
 hipError_t launch_init_uniform(float* dst, size_t n, uint64_t key, float a, hipStream_t s);
 hipError_t launch_fill_f32(float* dst, size_t n, float v, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* dst, size_t n, uint32_t v, hipStream_t s);
+hipError_t launch_fill_group_u32(uint32_t* const* dst, int G, size_t n, uint32_t v, hipStream_t s);  // n words of each of G blocks
 // dst[i] = bf16(src[i]) for i < n
 hipError_t launch_cast_bf16(const float* src, bf16_t* dst, size_t n, hipStream_t s);
 // rows x cols (fp32, contiguous) -> rows x ld (fp32 or bf16), padding columns untouched
