@@ -355,12 +355,22 @@ hydra_status run_epoch(hydra_ctx* c, const std::vector<Bucket>& plan, hydra_epoc
     hydra_status ps = prof_collect(c);
     if (ps != HYDRA_OK) return ps;
   }
-  // losses of this epoch
+  // losses of this epoch: every model's requested before the first is waited for
+  const size_t per = c->n_batches;
+  const StageLease lease;
+  float* const stage = !c->dry && per * c->K * 4 <= STAGE_BYTES ? lease.p : nullptr;
+  if (stage) {
+    for (int k = 0; k < c->K; ++k)
+      if (c->models[k].active)
+        HYDRA_HIP(c, hipMemcpyAsync(stage + k * per, c->models[k].loss_dev, per * 4, hipMemcpyDeviceToHost, c->streams[0]));
+    HYDRA_HIP(c, hipStreamSynchronize(c->streams[0]));
+  }
   for (int k = 0; k < c->K; ++k) {
     Model& m = c->models[k];
     if (!m.active) continue;
-    std::vector<float> l(c->n_batches, 0.f);
-    if (!c->dry) HYDRA_HIP(c, hipMemcpy(l.data(), m.loss_dev, l.size() * 4, hipMemcpyDeviceToHost));
+    std::vector<float> l(per, 0.f);
+    if (stage) l.assign(stage + k * per, stage + (k + 1) * per);
+    else if (!c->dry) HYDRA_HIP(c, hipMemcpy(l.data(), m.loss_dev, l.size() * 4, hipMemcpyDeviceToHost));
     m.losses.insert(m.losses.end(), l.begin(), l.end());
   }
   if (stats) {

@@ -381,3 +381,39 @@ def test_reading_all_tensors_equals_reading_each():
                     assert np.array_equal(t.reshape(-1), H.hydra_read_params(ctx, k, j)), (d, k, j)
         finally:
             H.hydra_destroy(ctx)
+
+
+def test_reading_large_models_from_two_threads():
+    """A range of more than 2 MB travels in pieces that several threads take apart, tensors reaching across their ends; a reader that
+    finds the pinned buffer taken copies without it.  Either way the values are those of tensors read one by one."""
+    import threading
+    from paper_2107_06469_amd import hydra as h
+    ctxs = []
+    for seed in (3, 4):
+        ctx = h.hydra_create()
+        a = C.mlp_arch(3, 776, 776, 13, C.ACT_GELU, C.DTYPE_F32)
+        h.hydra_define_models(ctx, [a, a], [C.hparams(C.OPT_SGD, 0.1)] * 2, seed)
+        for k in range(2):
+            h.hydra_shard(ctx, k, [1])
+        rng = np.random.default_rng(seed)
+        h.hydra_set_data(ctx, rng.standard_normal((1, 8, 776), dtype=np.float32), None, rng.integers(0, 13, (1, 8), dtype=np.int32))
+        h.hydra_train_epoch(ctx)
+        ctxs.append(ctx)
+    try:
+        ref = [[np.concatenate([h.hydra_read_params(ctx, k, j) for j in range(8)]) for k in range(2)] for ctx in ctxs]
+        bad = []
+
+        def read(i):
+            for _ in range(6):
+                for k in range(2):
+                    got = np.concatenate([t.reshape(-1) for t in h.hydra_read_params(ctxs[i], k)])
+                    if not np.array_equal(got, ref[i][k]):
+                        bad.append((i, k))
+
+        ts = [threading.Thread(target=read, args=(i,)) for i in range(2)]
+        [t.start() for t in ts]
+        [t.join() for t in ts]
+        assert not bad
+    finally:
+        for ctx in ctxs:
+            h.hydra_destroy(ctx)
