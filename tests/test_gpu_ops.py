@@ -687,3 +687,31 @@ def test_update_of_rows_8_kb_apart(torch, ops, K):
                                  ldw=N, ldo=N)
         got.append((p, m, v, w16))
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("C", [1, 5, 1020, 1023, 1024, 1025, 8188, 8192, 8193, 16384, 30522, 32765, 32768])
+@pytest.mark.parametrize("f32", [False, True])
+def test_softmax_rows_at_the_ends_of_register_groups(torch, ops, C, f32):
+    """Rows that end inside a group of four, at a whole number of groups per thread and one beside it; labels in the first and the last
+    group; logits of -inf.  Against float64: the sums carry fp32 rounding (a few 1e-7 of the row's largest weight), the gradient its own."""
+    M, ld = 6, (C + 7) // 8 * 8
+    gen = torch.Generator(device="cuda").manual_seed(C)
+    z = torch.full((M, ld), float("nan"), device="cuda")                 # what lies behind a row is not read as part of it
+    z[:, :C] = 3.0 * torch.randn(M, C, generator=gen, device="cuda")
+    if C > 4:
+        z[1, 2] = z[3, C - 1] = float("-inf")
+    y = torch.tensor([0, C - 1, C // 2, min(3, C - 1), max(C - 5, 0), C - 1], dtype=torch.int32, device="cuda")
+    y[3] = 0
+    dz = torch.full((M, ld), 7.0, device="cuda", dtype=torch.float32 if f32 else torch.bfloat16)
+    rl, loss = torch.zeros(M, device="cuda"), torch.zeros(1, device="cuda")
+    ops.hydra_op_softmax_ce(ops.F32 if f32 else ops.BF16, M, C, ld, ld, 1.0 / M, [z], y, [dz], [rl], [loss])
+    zd = z[:, :C].double()
+    lp = torch.log_softmax(zd, 1)
+    want = torch.exp(lp)
+    want[torch.arange(M), y.long()] -= 1.0
+    want /= M
+    nll = -lp[torch.arange(M), y.long()]
+    assert torch.allclose(rl.double(), nll, rtol=2e-6, atol=2e-6) and abs(float(loss) - float(nll.mean())) <= 2e-6 * max(1.0, float(nll.mean()))
+    # half a unit in the last place of 8 significant bits is 2^-8 of the value
+    tol = 2e-6 / M if f32 else 2.0 ** -8 * want.abs() + 2e-6 / M
+    assert bool(((dz[:, :C].double() - want).abs() <= tol).all()) and not bool(dz[:, C:].any())
