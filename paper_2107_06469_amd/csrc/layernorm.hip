@@ -195,25 +195,42 @@ struct LnRow {  // one row's operands as they lie in memory: chunks lane, lane +
     }
   }
 };
+// A lane's gamma: in registers, or (AGAIN) read from LDS where it is used, dy * gamma being worked out twice: 24 registers less for
+// the kernel whose occupancy they cost.
+template <int C>
+struct GammaRegs {
+  static constexpr bool AGAIN = false;
+  const float (&v)[C][8];
+  __device__ __forceinline__ void get(int i, int, float (&o)[8]) const {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = v[i][e];
+  }
+};
+struct GammaLds {
+  static constexpr bool AGAIN = true;
+  const float* p;
+  __device__ __forceinline__ void get(int, int c, float (&o)[8]) const { ld8<float>(p + 8 * c, o); }
+};
 // One row: its dx is stored, its terms are added to the column sums where SUMS.  Every multiply-add is written out, so that all
 // kernels give the same bits.
-template <typename T, int C, bool SUMS>
+template <typename T, int C, bool SUMS, typename GA>
 __device__ __forceinline__ void ln_bwd_row(const LnBwdArgs& a, int g, int row, int lane, int nch, const LnRow<T, C>& r,
-                                           const float (&ga)[C][8], float (&sg)[C][8], float (&sb)[C][8]) {
+                                           const GA& gam, float (&sg)[C][8], float (&sb)[C][8]) {
 #pragma clang fp contract(off)
   float xh[C][8], gg[C][8];
   float s1 = 0.f, s2 = 0.f;
 #pragma unroll
   for (int i = 0; i < C; ++i) {
     if (lane + 64 * i < nch) {
-      float xv[8], dv[8];
+      float xv[8], dv[8], ga[8];
       unpack8<T>(r.x[i], xv);
       unpack8<T>(r.dy[i], dv);
+      gam.get(i, lane + 64 * i, ga);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         xh[i][e] = (xv[e] - r.mu) * r.rstd;
-        gg[i][e] = dv[e] * ga[i][e];
-        s1 = fmaf(dv[e], ga[i][e], s1);
+        gg[i][e] = dv[e] * ga[e];
+        s1 = fmaf(dv[e], ga[e], s1);
         s2 = fmaf(gg[i][e], xh[i][e], s2);
         if (SUMS) {
           sg[i][e] = fmaf(dv[e], xh[i][e], sg[i][e]);
@@ -228,6 +245,13 @@ __device__ __forceinline__ void ln_bwd_row(const LnBwdArgs& a, int g, int row, i
     const int c = lane + 64 * i;
     if (c < nch) {
       float o[8];
+      if constexpr (GA::AGAIN) {
+        float dv[8], ga[8];
+        unpack8<T>(r.dy[i], dv);
+        gam.get(i, c, ga);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) gg[i][e] = dv[e] * ga[e];
+      }
 #pragma unroll
       for (int e = 0; e < 8; ++e) o[e] = r.rstd * fmaf(-xh[i][e], c2, gg[i][e] - c1);
       if (a.add[g]) {
@@ -243,26 +267,34 @@ __device__ __forceinline__ void ln_bwd_row(const LnBwdArgs& a, int g, int row, i
 // Many rows: workgroups of 4 waves, each with its next row's loads in flight while it reduces the current one; bound by
 // memory.  us: 4 x [16384, 768] bf16 97 (4.2 TB/s), 3 x [14483, 616] 46, 2 x [16384, 1024] 53; fp32 4 x [16384, 768] 175.  With two rows in
 // flight 94 | 53 | 54 | 175, with four and no prefetch 101 | 60 | 57 | 205, over 8 waves (one workgroup per CU) 96 | 52 | 55 | 175.
-template <typename T, int C>
-__global__ __launch_bounds__(256) void ln_bwd_kernel(const LnBwdArgs a) {
-  extern __shared__ float red[];  // [4][2][d]
+// FOUR (bf16 rows wider than 512): gamma in LDS, 128 registers instead of 146, so that four workgroups share a CU and not three;
+// ahead where there are more than three per CU: 4 x [16384, 768] (1024 workgroups) 95.7 | 91.1, up to there 1 to 2 % behind.
+template <typename T, int C, bool FOUR = false>
+__global__ __launch_bounds__(256, FOUR ? 4 : 1) void ln_bwd_kernel(const LnBwdArgs a) {
+  extern __shared__ float red[];  // [4][2][d], FOUR: gamma [d]
+  float* const gl = red + 8 * a.d;
   const int g = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nch = a.d >> 3;
   const int first = blockIdx.x * LN_ROWS_PER_WG, row0 = first + wave, end = first + min(a.rows - first, LN_ROWS_PER_WG);
   float ga[C][8], sg[C][8], sb[C][8];
+  LnRow<T, C> cur, nxt;
+  if (FOUR && row0 < end) nxt.fetch(a, g, row0, lane, nch);
+  if constexpr (FOUR)
+    for (int j = 4 * threadIdx.x; j < a.d; j += 1024) *reinterpret_cast<float4*>(gl + j) = *reinterpret_cast<const float4*>(a.gamma[g] + j);
 #pragma unroll
   for (int i = 0; i < C; ++i) {
     const int c = lane + 64 * i;
 #pragma unroll
     for (int e = 0; e < 8; ++e) sg[i][e] = sb[i][e] = ga[i][e] = 0.f;
-    if (c < nch) ld8<float>(a.gamma[g] + 8 * c, ga[i]);
+    if (!FOUR && c < nch) ld8<float>(a.gamma[g] + 8 * c, ga[i]);
   }
-  LnRow<T, C> cur, nxt;
-  if (row0 < end) nxt.fetch(a, g, row0, lane, nch);
+  if constexpr (FOUR) __syncthreads();
+  else if (row0 < end) nxt.fetch(a, g, row0, lane, nch);
   for (int row = row0; row < end; row += 4) {
     cur = nxt;
     if (row + 4 < end) nxt.fetch(a, g, row + 4, lane, nch);
-    ln_bwd_row<T, C, true>(a, g, row, lane, nch, cur, ga, sg, sb);
+    if constexpr (FOUR) ln_bwd_row<T, C, true>(a, g, row, lane, nch, cur, GammaLds{gl}, sg, sb);
+    else ln_bwd_row<T, C, true>(a, g, row, lane, nch, cur, GammaRegs<C>{ga}, sg, sb);
   }
   // the waves' partial sums are added in wave order
 #pragma unroll
@@ -304,7 +336,7 @@ __global__ __launch_bounds__(1024) void ln_bwd_chain_kernel(const LnBwdArgs a) {
     if (b0 == 0 && lane < nch) ld8<float>(a.gamma[g] + 8 * lane, ga[0]);
 #pragma unroll
     for (int b = b0; b < b0 + 2; ++b)
-      if (row0 + 4 * b < a.rows) ln_bwd_row<T, 1, false>(a, g, row0 + 4 * b, lane, nch, r[b], ga, none, none);
+      if (row0 + 4 * b < a.rows) ln_bwd_row<T, 1, false>(a, g, row0 + 4 * b, lane, nch, r[b], GammaRegs<1>{ga}, none, none);
   }
   for (int p = 0; p < 4; ++p) {
     if (quarter == p) {
@@ -383,7 +415,7 @@ __global__ __launch_bounds__(LN_SPLIT_NT) void ln_bwd_split_kernel(const LnBwdAr
 #pragma unroll
     for (int i = 0; i < C; ++i)
       if (lane + 64 * i < nch) ld8<float>(a.gamma[g] + 8 * (lane + 64 * i), ga[i]);
-    ln_bwd_row<T, C, false>(a, g, row, lane, nch, r, ga, none, none);
+    ln_bwd_row<T, C, false>(a, g, row, lane, nch, r, GammaRegs<C>{ga}, none, none);
     return;
   }
   typedef typename LnQuad<T>::type Q;
@@ -647,6 +679,8 @@ static hipError_t ln_bwd_pick(const LnBwdArgs& a, hipStream_t s) {
   const bool chain = a.d <= 512 && blocks <= 256 && (sizeof(T) == 2 || blocks * a.d <= 96 * 1024);
   if (chain) hipLaunchKernelGGL((ln_bwd_chain_kernel<T>), grid, dim3(1024), 0, s, a);
   else if (a.d <= 512) hipLaunchKernelGGL((ln_bwd_kernel<T, 1>), grid, dim3(256), lds, s, a);
+  else if (sizeof(T) == 2 && a.d <= LN_WAVE_ROW_MAX && blocks > 768)
+    hipLaunchKernelGGL((ln_bwd_kernel<bf16_t, 2, true>), grid, dim3(256), lds + 4 * a.d, s, a);
   else if (a.d <= LN_WAVE_ROW_MAX) hipLaunchKernelGGL((ln_bwd_kernel<T, 2>), grid, dim3(256), lds, s, a);
   else if (a.d <= 2048) hipLaunchKernelGGL((ln_bwd_wide_kernel<T, 1>), grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL((ln_bwd_wide_kernel<T, 2>), grid, dim3(256), 0, s, a);

@@ -394,6 +394,12 @@ def test_layernorm_column_sums_keep_their_order(torch, ops, dtype, G, rows, d):
             assert np.array_equal(got.cpu().numpy(), w)
 
 
+@pytest.mark.parametrize("G,rows,d", [(3, 16500, 520), (4, 12321, 1024), (7, 7041, 1000)])
+def test_layernorm_column_sums_with_four_workgroups_to_a_cu(torch, ops, G, rows, d):
+    """More than three blocks of 64 rows per compute unit, rows wider than 512: the kernel that reads gamma from LDS keeps the order, too."""
+    test_layernorm_column_sums_keep_their_order(torch, ops, "bf16", G, rows, d)
+
+
 @pytest.mark.parametrize("over", ["x", "dy", "add"])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("G,rows,d", [(2, 256, 256), (1, 1200, 1000), (1, 2000, 768), (2, 5000, 512), (3, 90, 1536)])
