@@ -76,6 +76,8 @@ __device__ __forceinline__ unsigned div_by(unsigned n, unsigned d, unsigned rcp)
   return n - q * d >= d ? q + 1 : q;
 }
 __device__ __forceinline__ bool attn_item(unsigned wg, const AttnGrid& gr, AttnItem& it) {
+  // all of the grid's fields by one scalar load, not those behind the test by another
+  asm volatile("" ::"s"(gr.total), "s"(gr.per_xcd), "s"(gr.n_blk), "s"(gr.n_bh), "s"(gr.n_h), "s"(gr.r_blk), "s"(gr.r_bh), "s"(gr.r_h));
   const unsigned id = (wg & 7) * gr.per_xcd + (wg >> 3);
   if (id >= gr.total || (wg >> 3) >= gr.per_xcd) return false;
   const unsigned u = div_by(id, gr.n_blk, gr.r_blk), gi = div_by(u, gr.n_bh, gr.r_bh), bh = u - gi * gr.n_bh;

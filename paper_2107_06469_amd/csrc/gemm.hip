@@ -1886,13 +1886,23 @@ inline bool small_eligible(const GemmArgs& a) {
   return dma_eligible(a);
 }
 
+// Percent of the passes of one 256x256 tile per CU that hold a tile
+inline long pass_fill(long big) { return big * 100 / ((big + 255) / 256 * 256); }
+
 // A choice never changes a result (every tile sums in the same order), only the time.  Measured in kernel time with the
 // tiles of every kind side by side; figures are us, small | 128x128 (| 32x128 for fp32).
 int choose_tile(const GemmArgs& a) {
   if (a.tile) return a.tile;
   auto tiles = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.G; };
   const long big = tiles(256, 256), mid = tiles(128, 128);
-  if (a.M >= 192 && big >= 192) return 1;  // the big tile fills the chip
+  if (a.M >= 192 && big >= 192) {  // the big tile fills the chip
+    // ... unless its last pass over the 256 CUs is nearly empty: then two 128x128 workgroups per CU, whose passes are half as
+    // long, are ahead.  us, 256x256 | 128x128, K = 768 and 3072: 288 tiles forward with GeLU 61 | 46 and 153 | 133, 320 input gradient with
+    // gate 61 | 50 and 161 | 139, 384 bias only 48 | 44 and 145 | 142, 576 plain input gradient 73 | 68 and 224 | 220; 640 tiles 94 | 84 but
+    // 252 | 258, 448 62 | 62 and 164 | 181; one pass that is not full stays (192 tiles: 30 | 31 and 76 | 84).
+    if (a.dtype != GEMM_F32 && big > 256 && pass_fill(big) <= (a.K <= 768 ? 84 : 76)) return 2;
+    return 1;
+  }
   const bool small = small_eligible(a);
   if (a.dtype == GEMM_F32) {
     // three 32x32 tiles per CU are as fast as 32x128 ones (800 tiles: 24.5-27.5 | 61 | 25.6-27.0; 256 tiles: 15 | 76 | 30;
@@ -1932,7 +1942,7 @@ int choose_update_tile(const GemmArgs& a) {
     const long sm = tiles(64, 64);
     if (small && (sm <= 512 || (sm <= 2048 && a.K <= 1024))) return a.K > 1024 ? TILE_SMALL_DEEP : TILE_SMALL;
   }
-  const int tile = choose_tile(a);
+  const int tile = a.M >= 192 && big >= 192 ? 1 : choose_tile(a);
   if (tile == 1 && a.K < 2048) {
     // With a short k-loop the state traffic of the epilogue dominates: with two workgroups per CU one streams
     // state while the other runs its k-loop, which the 256x256 tile (one workgroup per CU) cannot do.  us, 256x256 | 128x128:
@@ -1941,8 +1951,15 @@ int choose_update_tile(const GemmArgs& a) {
     // 8 KB apart are the exception: there the half as long row pieces of the 128x128 tile are the slower ones until the sum covers
     // them (256 tiles, K = 64 79 | 90, K = 256 87 | 118, K = 1024 106 | 109; 512 tiles 167 | 172, 177 | 220, 210 | 211; 1024 tiles 310 | 326,
     // 318 | 375, 395 | 366; K = 512, 512 tiles 177 | 202, 768 263 | 273).
-    return a.dtype != GEMM_F32 && a.K <= 512 && a.ldo * 4 == 8192 ? 1 : 2;
+    // A last pass that is nearly empty outweighs that (320 tiles, K = 256 129 | 106; 384 K = 256 134 | 147, K = 512 155 | 145).
+    const bool thin = big > 256 && pass_fill(big) <= (a.K <= 256 ? 70 : 76);
+    return a.dtype != GEMM_F32 && a.K <= 512 && a.ldo * 4 == 8192 && !thin ? 1 : 2;
   }
+  // Longer sums, passes that are a quarter empty or more: they cost more here, the state's part included (us, 256x256 | 128x128: 288 tiles
+  // Adam, K = 3072 264 | 189, K = 8192 522 | 391; 320 238 | 187 and SGD 159 | 121; 384 230 | 183; 144, in one pass, K = 2048 108 | 97, K = 8192
+  // 254 | 236 but K = 16384 442 | 490).  In full passes the 128x128 tile gains 2 to 6 % on one update repeated (256 tiles, Adam, K = 2048 to
+  // 4096) and nothing, or 1 % less, behind the input gradient that it follows in a layer's backward pass; SGD's is 2 to 11 % slower.
+  if (tile == 1 && a.dtype != GEMM_F32 && pass_fill(big) <= 76) return big > 256 || a.K <= 8192 ? 2 : 1;
   return tile;
 }
 

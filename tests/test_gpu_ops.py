@@ -715,3 +715,25 @@ def test_softmax_rows_at_the_ends_of_register_groups(torch, ops, C, f32):
     # half a unit in the last place of 8 significant bits is 2^-8 of the value
     tol = 2e-6 / M if f32 else 2.0 ** -8 * want.abs() + 2e-6 / M
     assert bool(((dz[:, :C].double() - want).abs() <= tol).all()) and not bool(dz[:, C:].any())
+
+
+@pytest.mark.parametrize("G,M,N,K", [(3, 2048, 3072, 72), (5, 2048, 2048, 256), (3, 2048, 3072, 2056), (9, 2040, 2048, 520), (2, 4608, 2048, 2048)])
+def test_tiles_of_a_thin_last_pass_give_the_same_bits(torch, ops, G, M, N, K):
+    """Launches whose last pass of 256x256 tiles would be nearly empty take 128x128 ones: forward, input gradient and update as with
+    the 256x256 tile asked for, bit for bit."""
+    gen = torch.Generator(device="cuda").manual_seed(M + K)
+    mk = lambda *s: torch.randn(*s, generator=gen, device="cuda").to(torch.bfloat16)  # noqa: E731
+    x, w, wt, xk = [mk(M, K) for _ in range(G)], [mk(N, K) for _ in range(G)], [mk(K, N) for _ in range(G)], [mk(K, M) for _ in range(G)]
+    b, gate = [torch.randn(N, generator=gen, device="cuda") for _ in range(G)], [mk(M, N) for _ in range(G)]
+    hp = [(1e-3, 0.9, 0.999, 1e-8, 1.5, 10.0)] * G
+    got = []
+    for tile in (0, 1):
+        o, pre, dx = ([torch.zeros(M, N, device="cuda", dtype=torch.bfloat16) for _ in range(G)] for _ in range(3))
+        ops.hydra_op_gemm(ops.BF16, M, N, K, x, w, o, x_kmajor=True, w_kmajor=True, ldx=K, ldw=K, ldo=N, bias=b, pre=pre, act=ops.EPI_GELU, tile=tile)
+        ops.hydra_op_gemm(ops.BF16, M, N, K, x, wt, dx, x_kmajor=True, w_kmajor=False, ldx=K, ldw=N, ldo=N, gate=gate, ldg=N, act=ops.EPI_GELU, tile=tile)
+        p = [torch.full((M, N), 0.5, device="cuda") for _ in range(G)]
+        m, v = ([torch.full((M, N), 0.25, device="cuda") for _ in range(G)] for _ in range(2))
+        rs = [torch.zeros(M, device="cuda") for _ in range(G)]
+        ops.hydra_op_gemm_update(ops.BF16, M, N, K, xk, wt, 1, p, m, v, None, hp, ldx=M, ldw=N, ldo=N, rowsum=rs, tile=tile)
+        got.append(o + pre + dx + p + m + v + rs)
+    assert all(torch.equal(a, c) for a, c in zip(*got))
