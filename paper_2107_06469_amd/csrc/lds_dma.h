@@ -22,9 +22,14 @@ __device__ __forceinline__ rsrc_u32x4 rsrc_words(const void* base, long first, l
 }
 // One wave-wide load of 16 bytes per lane from a buffer into LDS: lane l's bytes land at lds_addr + 16 l (lds_addr is
 // a byte address inside the workgroup's LDS, uniform over the wave).  The compiler does not see the LDS write:
-// callers order it against LDS reads with an explicit vmcnt wait and a barrier.
+// callers order it against LDS reads with an explicit vmcnt wait and a barrier.  A load into LDS must not issue right behind the write
+// of its M0: one wait state stands between them on gfx9, which the compiler puts in for its own loads but not inside an asm block.
 __device__ __forceinline__ void load_to_lds_b128(rsrc_u32x4 rs, unsigned lds_addr, unsigned voff) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voff), "s"(rs) : "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voff), "s"(rs) : "m0");
+}
+// The same with 4 bytes per lane: lane l's at lds_addr + 4 l
+__device__ __forceinline__ void load_to_lds_b32(rsrc_u32x4 rs, unsigned lds_addr, unsigned voff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voff), "s"(rs) : "m0");
 }
 
 }  // namespace hydra

@@ -129,10 +129,6 @@ __device__ __forceinline__ void lds_reads_done() {
 __device__ __forceinline__ unsigned lds_addr_of(const void* p) {
   return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)reinterpret_cast<const char*>(p);
 }
-// 4 bytes per lane into LDS: lane l's at lds_addr + 4 l
-__device__ __forceinline__ void load_to_lds_b32(rsrc_u32x4 rs, unsigned lds_addr, unsigned voff) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds_addr), "v"(voff), "s"(rs) : "m0");
-}
 // chunks of a unit whose sum runs over K (an even number: the register sets alternate)
 __device__ __forceinline__ int chunks_of(int K) { return (K + 63) / 64 * 2; }
 

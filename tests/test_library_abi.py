@@ -2,6 +2,8 @@
 logic (argument checks, call order, shard cutting, schedule validation, planning) behaves."""
 import os
 import re
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -412,3 +414,39 @@ def test_optimizer_state_calls_check_their_arguments():
         assert st == 2 and "dry-run" in H.lib().hydra_last_error(ctx.handle).decode()   # nothing to size, no values to give
     finally:
         H.hydra_destroy(ctx)
+
+
+def _device_code(tmp_path):
+    """Disassembly of the kernels that the library was built with, a list of instructions per kernel."""
+    llvm = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
+    if not os.path.exists(llvm):
+        pytest.skip("no llvm-objdump")
+    lib = shutil.copy(H.lib()._name, tmp_path)
+    subprocess.run([llvm, "--offloading", lib], check=True, capture_output=True, cwd=tmp_path)
+    kernels = {}
+    for f in sorted(os.listdir(tmp_path)):
+        if "amdgcn" not in f:
+            continue
+        out = subprocess.run([llvm, "-d", "--no-show-raw-insn", os.path.join(tmp_path, f)], check=True, capture_output=True, text=True).stdout
+        name = None
+        for ln in out.splitlines():
+            label = re.match(r"[0-9a-f]+ <(\w+)>:", ln)
+            if label:
+                name = label.group(1)
+                kernels[name] = []
+            elif name and ln.startswith("\t"):
+                kernels[name].append(ln.split("//")[0].strip())
+    return kernels
+
+
+def test_loads_into_lds_stand_a_wait_state_behind_the_write_of_their_m0(tmp_path):
+    """A scalar write of M0 and a load into LDS, which takes its address from there, must not issue back to back on gfx9: one wait state lies
+    between.  The compiler sees to that for instructions of its own, not for those inside an asm block."""
+    seen, bad = 0, []
+    for name, code in _device_code(tmp_path).items():
+        for before, ins in zip(code, code[1:]):
+            if ins.startswith("buffer_load") and ins.split()[-1] == "lds":
+                seen += 1
+                if re.match(r"s_\w+ m0\b", before):
+                    bad.append((name, before, ins))
+    assert seen > 0 and not bad, f"{len(bad)} of {seen}: {bad[:3]}"
