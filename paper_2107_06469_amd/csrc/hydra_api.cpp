@@ -14,28 +14,16 @@ using namespace hydra;
 
 static std::string g_create_error;
 
-static std::mutex g_stage_mutex;  // guards the two below and, while leased, the buffer's bytes
-static void* g_stage = nullptr;
-static int g_stage_users = 0;
-void hydra::stage_attach(hydra_ctx* c) {
-  std::lock_guard<std::mutex> l(g_stage_mutex);
-  if (!c->stage_user) ++g_stage_users;
-  c->stage_user = true;
-  if (!g_stage && hipHostMalloc(&g_stage, STAGE_BYTES, hipHostMallocPortable) != hipSuccess) {
-    (void)hipGetLastError();
-    g_stage = nullptr;
-  }
-}
-void hydra::stage_detach(hydra_ctx* c) {
-  if (!c->stage_user) return;
-  std::lock_guard<std::mutex> l(g_stage_mutex);
-  if (--g_stage_users == 0 && g_stage) {
-    (void)hipHostFree(g_stage);
-    g_stage = nullptr;
-  }
-}
-hydra::StageLease::StageLease() : lock(g_stage_mutex, std::try_to_lock) {
-  if (lock.owns_lock()) p = static_cast<float*>(g_stage);
+Stage& hydra::result_stage() {
+  static Stage s(
+      [](size_t n) -> void* {
+        void* p = nullptr;
+        if (hipHostMalloc(&p, n, hipHostMallocPortable) == hipSuccess) return p;
+        (void)hipGetLastError();
+        return nullptr;
+      },
+      [](void* p) { (void)hipHostFree(p); });
+  return s;
 }
 
 #define HYDRA_TRY try {
@@ -111,7 +99,7 @@ hydra_status hydra_destroy(hydra_ctx* c) {
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
     for (hipEvent_t e : c->prof_pool) (void)hipEventDestroy(e);
     if (c->prof_origin) (void)hipEventDestroy(c->prof_origin);
-    stage_detach(c);
+    if (c->stage_user) result_stage().detach();
     spill_release_all(c);
     ctx_free_all(c);
     if (c->own_streams)
@@ -210,7 +198,10 @@ hydra_status hydra_define_models(hydra_ctx* c, int K, const hydra_arch* archs, i
       sh.g = m.g ? m.g + sh.off : nullptr;
       sh.w16 = m.w16 ? m.w16 + sh.off : nullptr;
     }
-  if (!c->dry) stage_attach(c);
+  if (!c->dry && !c->stage_user) {
+    result_stage().attach();
+    c->stage_user = true;
+  }
   c->state = ST_DEFINED;
   return HYDRA_OK;
   HYDRA_CATCH(c)
@@ -466,7 +457,7 @@ static hipError_t copy_tensors_out(hydra_ctx* c, const Model& m, int tensor, con
     to += m.tensors[j].n;
   }
   if (ps.empty()) return hipSuccess;
-  const StageLease lease;
+  const StageLease lease(result_stage());
   float* const stage = rising ? lease.p : nullptr;
   if (!stage) {  // runs of tensors that fit 1 MB as one copy (some 10 us each whatever its size), larger ones straight to their place
     constexpr size_t RUN = (size_t)1 << 18;  // floats
@@ -487,7 +478,7 @@ static hipError_t copy_tensors_out(hydra_ctx* c, const Model& m, int tensor, con
   }
   const size_t first = ps.front().off, total = ps.back().off + ps.back().n - first;
   const unsigned T = total * 4 >= ((size_t)2 << 20) ? std::max(1u, std::min(4u, std::thread::hardware_concurrency())) : 1;
-  const size_t part = STAGE_BYTES / 4 / T;
+  const size_t part = Stage::BYTES / 4 / T;
   int dev = 0;
   if (const hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
   std::atomic<size_t> next{0};

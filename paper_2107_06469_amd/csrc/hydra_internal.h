@@ -6,13 +6,13 @@
 #include <cstdarg>
 #include <cstdio>
 #include <map>
-#include <mutex>
 #include <string>
 #include <utility>
 #include <vector>
 
 #include "../../include/hydra.h"
 #include "kernels.h"
+#include "result_copy.h"
 
 namespace hydra {
 
@@ -205,7 +205,7 @@ struct hydra_ctx {
   std::vector<Slot> slots;
   size_t slot_elems = 0, next_slot = 0;
   size_t state_bytes = 0;  // resident parameter bytes (working weights, vectors) counted against the budget
-  bool stage_user = false;  // holds a share of the pinned result buffer (stage_attach)
+  bool stage_user = false;  // attached to result_stage()
   hipStream_t copy_in = nullptr, copy_out = nullptr;
   std::vector<void*> host_allocs;
   size_t host_bytes = 0, peak_host_bytes = 0;
@@ -250,18 +250,7 @@ void ctx_free_all(hydra_ctx* c);
 // spill.cpp
 size_t resident_state_bytes(const hydra_ctx* c);
 hydra_status spill_alloc_models(hydra_ctx* c);
-// One pinned buffer of the process for results on their way to a caller's memory: made when the first context defines models, given back with
-// the last such context (making one takes 0.4 ms, as long as an epoch of small models).  One reader at a time: p is null while
-// another holds it, or when there is no pinned memory to be had, and the reader copies without it.
-constexpr size_t STAGE_BYTES = (size_t)4 << 20;
-void stage_attach(hydra_ctx* c);
-void stage_detach(hydra_ctx* c);
-struct StageLease {
-  std::unique_lock<std::mutex> lock;
-  float* p = nullptr;
-  StageLease();
-};
-
+Stage& result_stage();  // pinned memory; hydra_define_models attaches a context, hydra_destroy detaches it
 hydra_status spill_prepare(hydra_ctx* c);
 int spill_max_group(const hydra_ctx* c);
 hydra_status spill_acquire(hydra_ctx* c, int k, int s, hipStream_t compute, bool synchronous);

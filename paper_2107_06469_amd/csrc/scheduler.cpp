@@ -357,8 +357,8 @@ hydra_status run_epoch(hydra_ctx* c, const std::vector<Bucket>& plan, hydra_epoc
   }
   // losses of this epoch: every model's requested before the first is waited for
   const size_t per = c->n_batches;
-  const StageLease lease;
-  float* const stage = !c->dry && per * c->K * 4 <= STAGE_BYTES ? lease.p : nullptr;
+  const StageLease lease(result_stage());
+  float* const stage = !c->dry && per * c->K * 4 <= Stage::BYTES ? lease.p : nullptr;
   if (stage) {
     for (int k = 0; k < c->K; ++k)
       if (c->models[k].active)

@@ -1,0 +1,73 @@
+"""The host side of copying results out (csrc/result_copy.h) by itself: it calls no HIP, so small programs around it run on the CPU, with
+memory copies in the place of the device's."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def _run(tmp_path, body, top=""):
+    """Compiles and runs int main() { body }; CHECK(condition) ends it with the line's number."""
+    if not shutil.which("g++"):
+        pytest.skip("no g++")
+    src, exe = tmp_path / "t.cpp", tmp_path / "t"
+    src.write_text("#include <chrono>\n#include <cstdio>\n#include <cstdlib>\n#include <cstring>\n#include <future>\n#include <new>\n"
+                   '#include <thread>\n#include <vector>\n#include "result_copy.h"\n'
+                   "#define CHECK(x) do { if (!(x)) { std::printf(\"line %d: %s\\n\", __LINE__, #x); std::fflush(stdout); std::_Exit(1); } } while (0)\n"
+                   "using namespace hydra;\n" + top + "\nint main() {\n" + body + "\n  return 0;\n}\n")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", os.path.join(ROOT, "paper_2107_06469_amd", "csrc"), str(src), "-o", str(exe)],
+                   check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, (r.returncode, r.stdout, r.stderr)
+
+
+STAGE = """
+static int made = 0, given = 0;
+static bool none = false;
+static Stage st([](size_t n) -> void* { if (none) return nullptr; ++made; return std::malloc(n); },
+                [](void* p) { ++given; std::free(p); });
+"""
+
+
+def test_contexts_come_and_go_while_another_reads(tmp_path):
+    """A reader keeps the buffer for the length of its copies, seconds for large models: contexts of other threads attach and detach
+    meanwhile."""
+    _run(tmp_path, """
+  st.attach();
+  StageLease held(st);
+  CHECK(held.p);
+  auto other = std::async(std::launch::async, [] { st.attach(); { StageLease l(st); CHECK(!l.p); } st.detach(); });
+  CHECK(other.wait_for(std::chrono::seconds(10)) == std::future_status::ready);
+  CHECK(made == 1 && given == 0);
+""", STAGE)
+
+
+def test_the_buffer_has_one_reader_and_goes_with_the_last_context(tmp_path):
+    _run(tmp_path, """
+  { StageLease l(st); CHECK(!l.p); }
+  st.attach();
+  st.attach();
+  { StageLease a(st); StageLease b(st); CHECK(a.p && !b.p); }
+  { StageLease a(st); CHECK(a.p); }
+  st.detach();
+  CHECK(made == 1 && given == 0);
+  {
+    StageLease a(st);
+    st.detach();
+    CHECK(given == 0);
+    a.p[0] = 1.f;
+  }
+  CHECK(given == 1);
+  none = true;
+  st.attach();
+  { StageLease l(st); CHECK(!l.p); }
+  none = false;
+  st.attach();
+  { StageLease l(st); CHECK(l.p); }
+  st.detach();
+  st.detach();
+  CHECK(made == 2 && given == 2);
+""", STAGE)
