@@ -4,7 +4,6 @@
 #include <atomic>
 #include <cstring>
 #include <new>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -500,14 +499,7 @@ static hipError_t copy_tensors_out(hydra_ctx* c, const Model& m, int tensor, con
     }
     if (e != hipSuccess) err.store((int)e);
   };
-  std::vector<std::thread> helpers;
-  helpers.reserve(T);
-  try {
-    for (unsigned k = 1; k < T; ++k) helpers.emplace_back(work, k);
-  } catch (const std::system_error&) {  // no more threads: those there are do the work
-  }
-  work(0);
-  for (std::thread& t : helpers) t.join();
+  on_threads(T, work);
   return (hipError_t)err.load();
 }
 

@@ -3,6 +3,8 @@
 #pragma once
 #include <cstddef>
 #include <mutex>
+#include <thread>
+#include <vector>
 
 namespace hydra {
 
@@ -63,5 +65,19 @@ class StageLease {
  private:
   Stage& s_;
 };
+
+// work(0) on this thread and work(1) ... work(T - 1) on threads of their own, which have ended when it returns.  Where the system gives
+// no more threads, or no memory for one, those there are do without it: work takes its share from a common counter, not from k.
+template <typename W>
+void on_threads(unsigned T, const W& work) {
+  std::vector<std::thread> helpers;
+  try {
+    helpers.reserve(T);
+    for (unsigned k = 1; k < T; ++k) helpers.emplace_back([&work, k] { work(k); });
+  } catch (...) {
+  }
+  work(0);
+  for (std::thread& t : helpers) t.join();
+}
 
 }  // namespace hydra

@@ -71,3 +71,31 @@ def test_the_buffer_has_one_reader_and_goes_with_the_last_context(tmp_path):
   st.detach();
   CHECK(made == 2 && given == 2);
 """, STAGE)
+
+
+@pytest.mark.parametrize("left", [0, 1, 2, 3, 5])
+def test_threads_that_cannot_be_made_leave_their_work_to_the_others(tmp_path, left):
+    """Memory for a thread's state runs out after `left` allocations: the threads made so far are waited for, no exception leaves."""
+    _run(tmp_path, f"""
+  std::atomic<int> next{{0}}, done{{0}};
+  auto work = [&](unsigned) {{
+    while (next.fetch_add(1) < 100) {{
+      std::this_thread::sleep_for(std::chrono::microseconds(200));
+      ++done;
+    }}
+  }};
+  left = {left};
+  on_threads(4, work);
+  left = -1;
+  CHECK(done == 100);
+""", """
+#include <atomic>
+static std::atomic<int> left{-1};  // allocations that still succeed; negative: all do
+void* operator new(std::size_t n) {
+  if (left >= 0 && left-- == 0) { left = 0; throw std::bad_alloc(); }
+  if (void* p = std::malloc(n)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, std::size_t) noexcept { std::free(p); }
+""")
