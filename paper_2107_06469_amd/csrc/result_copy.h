@@ -66,6 +66,16 @@ class StageLease {
   Stage& s_;
 };
 
+// Requests parts 0 .. n - 1 of a copy into a leased buffer and waits for them: also where one could not be requested, since those before it
+// are on their way and the buffer is another reader's once the lease ends.  The first error, 0 if there was none.
+template <typename R, typename W>
+int request_all(int n, const R& request, const W& wait) {
+  int e = 0;
+  for (int i = 0; i < n && !e; ++i) e = (int)request(i);
+  const int w = (int)wait();
+  return e ? e : w;
+}
+
 // work(0) on this thread and work(1) ... work(T - 1) on threads of their own, which have ended when it returns.  Where the system gives
 // no more threads, or no memory for one, those there are do without it: work takes its share from a common counter, not from k.
 template <typename W>

@@ -360,10 +360,12 @@ hydra_status run_epoch(hydra_ctx* c, const std::vector<Bucket>& plan, hydra_epoc
   const StageLease lease(result_stage());
   float* const stage = !c->dry && per * c->K * 4 <= Stage::BYTES ? lease.p : nullptr;
   if (stage) {
-    for (int k = 0; k < c->K; ++k)
-      if (c->models[k].active)
-        HYDRA_HIP(c, hipMemcpyAsync(stage + k * per, c->models[k].loss_dev, per * 4, hipMemcpyDeviceToHost, c->streams[0]));
-    HYDRA_HIP(c, hipStreamSynchronize(c->streams[0]));
+    auto request = [&](int k) {
+      if (!c->models[k].active) return hipSuccess;
+      return hipMemcpyAsync(stage + k * per, c->models[k].loss_dev, per * 4, hipMemcpyDeviceToHost, c->streams[0]);
+    };
+    const hipError_t losses_copied = (hipError_t)request_all(c->K, request, [&] { return hipStreamSynchronize(c->streams[0]); });
+    HYDRA_HIP(c, losses_copied);
   }
   for (int k = 0; k < c->K; ++k) {
     Model& m = c->models[k];

@@ -99,3 +99,15 @@ void* operator new(std::size_t n) {
 void operator delete(void* p) noexcept { std::free(p); }
 void operator delete(void* p, std::size_t) noexcept { std::free(p); }
 """)
+
+
+def test_copies_under_way_are_waited_for_where_one_could_not_be_requested(tmp_path):
+    """The third of five copies into the leased buffer fails to start: the first two have landed before the lease can end."""
+    _run(tmp_path, """
+  int asked = 0, waits = 0;
+  CHECK(request_all(5, [&](int i) { ++asked; return i == 2 ? 7 : 0; }, [&] { ++waits; return 0; }) == 7);
+  CHECK(asked == 3 && waits == 1);
+  CHECK(request_all(5, [&](int i) { return 0; }, [&] { ++waits; return 9; }) == 9);
+  CHECK(request_all(5, [&](int i) { return i == 4 ? 3 : 0; }, [&] { ++waits; return 9; }) == 3);
+  CHECK(request_all(0, [&](int i) { return 1; }, [&] { ++waits; return 0; }) == 0 && waits == 4);
+""")
