@@ -102,7 +102,7 @@ static hydra_status mlp_forward(hydra_ctx* c, const Bucket& b, int batch, int st
       // gradients with the update
       const hydra_arch& a0 = m0.arch;
       HYDRA_LAUNCH2(c, HYDRA_K_GEMM_FWD, HYDRA_K_GEMM_DGRAD, s, unit_flops(c, a0, f.u0, f.u1) * f.G,
-                    unit_flops(c, a0, 1, f.u1) * f.G, 0.0, launch_mlp_fwd_chain(f, s));
+                    unit_flops(c, a0, 1, f.u1) * f.G, 0.0, 0.0, launch_mlp_fwd_chain(f, s));
       return mlp_fused_gradients(c, b, f, s);
     }
     HYDRA_LAUNCH(c, HYDRA_K_GEMM_FWD, s, unit_flops(c, m0.arch, f.u0, f.u1) * f.G, 0.0, launch_mlp_fwd_fused(f, s));

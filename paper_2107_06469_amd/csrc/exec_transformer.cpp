@@ -290,7 +290,7 @@ static hydra_status dgrad(Ctx& x, int rows, int n_out, int k_in, int ld_dy, cons
   }
   if (x.held && gemm_pair_ok(g, x.hw)) {
     x.held = false;
-    HYDRA_LAUNCH2(c, HYDRA_K_GEMM_DGRAD, HYDRA_K_WGRAD_UPDATE, x.s, 2.0 * g.M * g.N * g.K * x.G, x.h_flops, 0.0,
+    HYDRA_LAUNCH2(c, HYDRA_K_GEMM_DGRAD, HYDRA_K_WGRAD_UPDATE, x.s, 2.0 * g.M * g.N * g.K * x.G, x.h_flops, 0.0, x.h_bytes,
                   launch_gemm_pair(g, x.hw, x.hu, x.s));
     return HYDRA_OK;
   }

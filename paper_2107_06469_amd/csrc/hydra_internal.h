@@ -214,7 +214,7 @@ struct hydra_ctx {
   // optional per-launch timing (hydra_profile_enable): event pairs on the launching stream
   bool profiling = false;
   // cls2 >= 0: the launch also does flops2 of work of a second class; its time is split in proportion to the flops
-  struct ProfRec { int cls; hipEvent_t a, b; double flops, bytes; int cls2; double flops2; };
+  struct ProfRec { int cls; hipEvent_t a, b; double flops, bytes; int cls2; double flops2, bytes2; };
   std::vector<ProfRec> prof_recs;
   std::vector<hipEvent_t> prof_pool;
   size_t prof_used = 0;
@@ -289,21 +289,21 @@ inline double fused_update_bytes(int opt, bool bf16) { return (opt == 1 ? 24.0 :
 hipError_t prof_epoch_begin(hydra_ctx* c);  // records the time origin of a profiled epoch on stream 0
 hipError_t prof_begin(hydra_ctx* c, hipStream_t s, hipEvent_t* a);
 hipError_t prof_end(hydra_ctx* c, hipStream_t s, hipEvent_t a, int cls, double flops, double bytes, int cls2 = -1,
-                    double flops2 = 0.0);
+                    double flops2 = 0.0, double bytes2 = 0.0);
 hydra_status prof_collect(hydra_ctx* c);  // after the streams have drained
 
 // a kernel launch of class `cls` on stream `s` doing `flops` / moving `bytes` of algorithmic work:
 // counted always, executed unless the context is a dry run, timed when profiling is on
-#define HYDRA_LAUNCH(c, cls, s, flops, bytes, expr) HYDRA_LAUNCH2(c, cls, -1, s, flops, 0.0, bytes, expr)
+#define HYDRA_LAUNCH(c, cls, s, flops, bytes, expr) HYDRA_LAUNCH2(c, cls, -1, s, flops, 0.0, bytes, 0.0, expr)
 // ... of two classes (one kernel that does, say, a forward and an input-gradient pass)
-#define HYDRA_LAUNCH2(c, cls, cls2, s, flops, flops2, bytes, expr)                                      \
+#define HYDRA_LAUNCH2(c, cls, cls2, s, flops, flops2, bytes, bytes2, expr)                              \
   do {                                                                                                  \
     ++(c)->launches;                                                                                    \
     if (!(c)->dry) {                                                                                    \
       hipEvent_t pa_ = nullptr;                                                                         \
       hipError_t e_ = (c)->profiling ? prof_begin(c, s, &pa_) : hipSuccess;                             \
       if (e_ == hipSuccess) e_ = (expr);                                                                \
-      if (e_ == hipSuccess && (c)->profiling) e_ = prof_end(c, s, pa_, cls, flops, bytes, cls2, flops2); \
+      if (e_ == hipSuccess && (c)->profiling) e_ = prof_end(c, s, pa_, cls, flops, bytes, cls2, flops2, bytes2); \
       if (e_ != hipSuccess) return (c)->fail(HYDRA_ERR_DEVICE, "%s: %s", #expr, hipGetErrorString(e_)); \
     }                                                                                                   \
   } while (0)

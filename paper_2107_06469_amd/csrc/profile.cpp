@@ -27,13 +27,14 @@ hipError_t prof_begin(hydra_ctx* c, hipStream_t s, hipEvent_t* a) {
   return r != hipSuccess ? r : hipEventRecord(*a, s);
 }
 
-hipError_t prof_end(hydra_ctx* c, hipStream_t s, hipEvent_t a, int cls, double flops, double bytes, int cls2, double flops2) {
+hipError_t prof_end(hydra_ctx* c, hipStream_t s, hipEvent_t a, int cls, double flops, double bytes, int cls2, double flops2,
+                    double bytes2) {
   hipEvent_t b;
   hipError_t r = next_event(c, &b);
   if (r != hipSuccess) return r;
   r = hipEventRecord(b, s);
   if (r != hipSuccess) return r;
-  c->prof_recs.push_back({cls, a, b, flops, bytes, cls2, flops2});
+  c->prof_recs.push_back({cls, a, b, flops, bytes, cls2, flops2, bytes2});
   return hipSuccess;
 }
 
@@ -77,6 +78,7 @@ hydra_status prof_collect(hydra_ctx* c) {
       ++s2.launches;
       s2.ms += ms * share2;
       s2.flops += r.flops2;
+      s2.bytes += r.bytes2;
     }
   }
   // time during which at least one kernel was running: launches on different streams overlap, so the sum of their

@@ -241,7 +241,8 @@ def test_profile_accounts_the_algorithmic_work_of_an_epoch(H):
 def test_profile_accounts_the_products_of_transformer_blocks(H, i):
     """Encoders (workload 2's layers) and gated causal decoders (workload 4's) at reduced size: every weight matrix
     is booked once per pass with 2·rows·in·out, the attention products with 4 (forward) + 10 (backward) ·B·S²·d,
-    halved under the causal mask."""
+    halved under the causal mask; every weight's update with the state's bytes and its product's operands, also where it shares a
+    launch with an input gradient."""
     w = scaled_workload(i, K=2, depths=[2, 4], steps=2)
     data = make_data(w)
     ctx = H.hydra_create(n_streams=2)
@@ -254,15 +255,19 @@ def test_profile_accounts_the_products_of_transformer_blocks(H, i):
         steps = H.hydra_train_epoch(ctx, H.SCHED_SHARD_PARALLEL, None)["steps"]
         prof = H.hydra_profile_read(ctx)
         T, NT = w.batch * w.seq, w.batch * w.n_targets
-        gemm = att = 0.0
+        gemm = att = upd = 0.0
         for a in w.archs:
             d, F, V, L = a["d_model"], a["d_ffn"], a["n_out"], a["n_layers"]
+            # fused Adam update: p, m, v read and written, the bf16 copy written (26 B); the product's two bf16 operands
+            mats = [(3 * d, d), (d, d), (F, d), (d, F)] + [(F, d)] * a["ffn_gated"]
+            upd += sum(26.0 * o * i + 2.0 * T * (o + i) for o, i in mats) * L + 26.0 * V * d + 2.0 * NT * (V + d)
             gemm += 2.0 * T * L * (3 * d * d + d * d + (3 if a["ffn_gated"] else 2) * d * F) + 2.0 * NT * d * V
             att += w.batch * float(w.seq) ** 2 * d * L * (0.5 if a["causal"] else 1.0)
         assert prof["gemm_fwd"]["flops"] == pytest.approx(gemm * steps, rel=1e-12)
         assert prof["gemm_dgrad"]["flops"] == pytest.approx(gemm * steps, rel=1e-12)
         wg = sum(prof[c]["flops"] for c in ("gemm_wgrad", "wgrad_update") if c in prof)
         assert wg == pytest.approx(gemm * steps, rel=1e-12)
+        assert prof["wgrad_update"]["bytes"] == pytest.approx(upd * steps, rel=1e-12)
         assert prof["attention"]["flops"] == pytest.approx(14.0 * att * steps, rel=1e-12)
     finally:
         H.hydra_destroy(ctx)
