@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "act_math.h"
+#include "gemm_rules.h"
 #include "kernels.h"
 #include "lds_dma.h"
 #include "optim_math.h"
@@ -1886,9 +1887,6 @@ inline bool small_eligible(const GemmArgs& a) {
   return dma_eligible(a);
 }
 
-// Percent of the passes of one 256x256 tile per CU that hold a tile
-inline long pass_fill(long big) { return big * 100 / ((big + 255) / 256 * 256); }
-
 // A choice never changes a result (every tile sums in the same order), only the time.  Measured in kernel time with the
 // tiles of every kind side by side; figures are us, small | 128x128 (| 32x128 for fp32).
 int choose_tile(const GemmArgs& a) {
@@ -1896,11 +1894,8 @@ int choose_tile(const GemmArgs& a) {
   auto tiles = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.G; };
   const long big = tiles(256, 256), mid = tiles(128, 128);
   if (a.M >= 192 && big >= 192) {  // the big tile fills the chip
-    // ... unless its last pass over the 256 CUs is nearly empty: then two 128x128 workgroups per CU, whose passes are half as
-    // long, are ahead.  us, 256x256 | 128x128, K = 768 and 3072: 288 tiles forward with GeLU 61 | 46 and 153 | 133, 320 input gradient with
-    // gate 61 | 50 and 161 | 139, 384 bias only 48 | 44 and 145 | 142, 576 plain input gradient 73 | 68 and 224 | 220; 640 tiles 94 | 84 but
-    // 252 | 258, 448 62 | 62 and 164 | 181; one pass that is not full stays (192 tiles: 30 | 31 and 76 | 84).
-    if (a.dtype != GEMM_F32 && big > 256 && pass_fill(big) <= (a.K <= 768 ? 84 : 76)) return 2;
+    // ... unless its last pass over the 256 CUs is nearly empty
+    if (a.dtype != GEMM_F32 && mid_tiles_for_product(big, mid, a.K, a.pre[0] || a.gate[0])) return 2;
     return 1;
   }
   const bool small = small_eligible(a);

@@ -1,0 +1,31 @@
+// Rules of the tile choice for large bf16 launches, by counts alone: a choice never changes a result (every tile sums in the same order), only
+// the time.  Nothing here calls HIP.
+#pragma once
+
+namespace hydra {
+
+// A launch of `big` 256x256 tiles runs in passes of one tile per CU (256), the same launch as `mid` 128x128 tiles with two workgroups per CU.
+inline long tile_passes(long big) { return (big + 255) / 256; }
+// percent of the passes of 256x256 tiles that hold a tile
+inline long pass_fill(long big) { return big * 100 / (tile_passes(big) * 256); }
+// How many 128x128 tiles the fullest CU has beyond three to a pass.  A pass of 256x256 tiles takes as long as three or four of them: three are
+// ahead, a fourth is behind unless the epilogue is long against the sum.
+inline long rounds_over(long big, long mid) { return (mid + 255) / 256 - 3 * tile_passes(big); }
+
+// Products of two passes or more whose passes are a sixth (K <= 768) or a quarter empty.  wide: the epilogue reads a gate or stores the
+// pre-activation beside the output.  us, 256x256 | 128x128, K = 768 and 3072:
+//   three to a pass   288 tiles GeLU 61 | 46 and 153 | 133, 320 gate 61 | 50 and 161 | 139, 384 plain 50 | 45 and 147 | 143, 576 73 | 68 and 222 | 217
+//   one more, 2 passes   390 GeLU 60 | 60 and 153 | 174, gate 63 | 64 and 160 | 178, bias 49 | 51 and 143 | 165, plain 47 | 50 and 143 | 166; 400,
+//     K = 512 GeLU 49 | 47, gate 53 | 52, bias 37 | 39, plain 37 | 40
+//   one more, 3 and 4 passes   640 GeLU 94 | 86 and 243 | 241, plain 75 | 74 and 227 | 236; 832 GeLU 124 | 110, plain 98 | 96
+//   two more, 4 passes   860 GeLU 122 | 114, gate 128 | 125, plain 97 | 102
+// One pass that is not full stays with 256x256 tiles (192 tiles: 30 | 31 and 76 | 84).
+inline bool mid_tiles_for_product(long big, long mid, int K, bool wide) {
+  const long passes = tile_passes(big), over = rounds_over(big, mid);
+  if (passes < 2 || pass_fill(big) > (K <= 768 ? 84 : 76)) return false;
+  if (over <= 0) return true;
+  if (wide) return K <= (passes >= 3 ? 768 : 512);
+  return passes >= 3 && over == 1 && K <= 768;
+}
+
+}  // namespace hydra

@@ -1,0 +1,34 @@
+"""The rules that choose a tile for large launches (csrc/gemm_rules.h) at counts where both tiles were measured: what was slower is not chosen.
+The rules are host code without HIP: a small program around them runs on the CPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def _chosen(tmp_path, calls):
+    """Values of the calls, expressions in C++."""
+    if not shutil.which("g++"):
+        pytest.skip("no g++")
+    src, exe = tmp_path / "t.cpp", tmp_path / "t"
+    src.write_text('#include <cstdio>\n#include "gemm_rules.h"\nusing namespace hydra;\nint main() {\n'
+                   + "".join(f'  std::printf("%d\\n", (int)({c}));\n' for c in calls) + "}\n")
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2107_06469_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    return [int(x) for x in subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split()]
+
+
+def test_products_with_a_thin_last_pass(tmp_path):
+    # (256x256 tiles, 128x128 tiles, K, gate or pre-activation, 128x128 tiles are ahead)
+    cases = [(288, 1152, 768, 1, 1), (288, 1152, 3072, 1, 1), (320, 1280, 3072, 1, 1), (384, 1536, 768, 0, 1), (384, 1536, 3072, 0, 1),
+             (377, 1450, 3072, 0, 1), (576, 2304, 3072, 0, 1), (640, 2560, 768, 0, 1), (640, 2560, 768, 1, 1), (832, 3328, 768, 0, 1),
+             (800, 3200, 512, 1, 1), (860, 3440, 768, 1, 1), (1050, 4200, 768, 1, 1), (400, 1600, 512, 1, 1), (414, 1656, 256, 1, 1),
+             # a fourth 128x128 tile to a pass: behind
+             (390, 1560, 768, 0, 0), (390, 1560, 3072, 0, 0), (390, 1560, 3072, 1, 0), (390, 1560, 1024, 0, 0), (400, 1600, 768, 0, 0),
+             (400, 1600, 512, 0, 0), (416, 1664, 768, 1, 0), (430, 1720, 768, 0, 0), (430, 1720, 3072, 1, 0), (585, 2340, 3072, 0, 0),
+             (585, 2340, 3072, 1, 0), (640, 2560, 3072, 0, 0), (860, 3440, 768, 0, 0), (1050, 4200, 512, 0, 0), (1000, 4000, 768, 1, 0),
+             (192, 768, 768, 0, 0), (192, 768, 3072, 0, 0), (512, 2048, 768, 0, 0)]
+    got = _chosen(tmp_path, [f"mid_tiles_for_product({b}, {m}, {k}, {'true' if w else 'false'})" for b, m, k, w, _ in cases])
+    assert [c for c, g in zip(cases, got) if g != c[4]] == []
