@@ -1895,7 +1895,7 @@ int choose_tile(const GemmArgs& a) {
   const long big = tiles(256, 256), mid = tiles(128, 128);
   if (a.M >= 192 && big >= 192) {  // the big tile fills the chip
     // ... unless its last pass over the 256 CUs is nearly empty
-    if (a.dtype != GEMM_F32 && mid_tiles_for_product(big, mid, a.K, a.pre[0] || a.gate[0])) return 2;
+    if (a.dtype != GEMM_F32 && mid_tiles_for_product(big, mid, a.K, a.pre[0] || a.gate[0], dma_eligible(a))) return 2;
     return 1;
   }
   const bool small = small_eligible(a);

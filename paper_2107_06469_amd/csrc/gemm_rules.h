@@ -19,10 +19,11 @@ inline long rounds_over(long big, long mid) { return (mid + 255) / 256 - 3 * til
 //     K = 512 GeLU 49 | 47, gate 53 | 52, bias 37 | 39, plain 37 | 40
 //   one more, 3 and 4 passes   640 GeLU 94 | 86 and 243 | 241, plain 75 | 74 and 227 | 236; 832 GeLU 124 | 110, plain 98 | 96
 //   two more, 4 passes   860 GeLU 122 | 114, gate 128 | 125, plain 97 | 102
-// One pass that is not full stays with 256x256 tiles (192 tiles: 30 | 31 and 76 | 84).
-inline bool mid_tiles_for_product(long big, long mid, int K, bool wide) {
+// One pass that is not full stays with 256x256 tiles (192 tiles: 30 | 31 and 76 | 84), and so do operands that the direct-to-LDS kernels
+// do not reach (!direct): of the register-staged ones the smaller tile is behind (288 tiles plain, K = 131136, 7250 | 8371).
+inline bool mid_tiles_for_product(long big, long mid, int K, bool wide, bool direct) {
   const long passes = tile_passes(big), over = rounds_over(big, mid);
-  if (passes < 2 || pass_fill(big) > (K <= 768 ? 84 : 76)) return false;
+  if (!direct || passes < 2 || pass_fill(big) > (K <= 768 ? 84 : 76)) return false;
   if (over <= 0) return true;
   if (wide) return K <= (passes >= 3 ? 768 : 512);
   return passes >= 3 && over == 1 && K <= 768;

@@ -30,5 +30,7 @@ def test_products_with_a_thin_last_pass(tmp_path):
              (400, 1600, 512, 0, 0), (416, 1664, 768, 1, 0), (430, 1720, 768, 0, 0), (430, 1720, 3072, 1, 0), (585, 2340, 3072, 0, 0),
              (585, 2340, 3072, 1, 0), (640, 2560, 3072, 0, 0), (860, 3440, 768, 0, 0), (1050, 4200, 512, 0, 0), (1000, 4000, 768, 1, 0),
              (192, 768, 768, 0, 0), (192, 768, 3072, 0, 0), (512, 2048, 768, 0, 0)]
-    got = _chosen(tmp_path, [f"mid_tiles_for_product({b}, {m}, {k}, {'true' if w else 'false'})" for b, m, k, w, _ in cases])
+    got = _chosen(tmp_path, [f"mid_tiles_for_product({b}, {m}, {k}, {w}, true)" for b, m, k, w, _ in cases])
     assert [c for c, g in zip(cases, got) if g != c[4]] == []
+    # operands of 2 GiB and more, which the direct-to-LDS kernels do not take
+    assert _chosen(tmp_path, ["mid_tiles_for_product(288, 1152, 131136, 0, true)", "mid_tiles_for_product(288, 1152, 131136, 0, false)"]) == [1, 0]
