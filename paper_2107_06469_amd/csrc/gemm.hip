@@ -1950,11 +1950,7 @@ int choose_update_tile(const GemmArgs& a) {
     const bool thin = big > 256 && pass_fill(big) <= (a.K <= 256 ? 70 : 76);
     return a.dtype != GEMM_F32 && a.K <= 512 && a.ldo * 4 == 8192 && !thin ? 1 : 2;
   }
-  // Longer sums, passes that are a quarter empty or more: they cost more here, the state's part included (us, 256x256 | 128x128: 288 tiles
-  // Adam, K = 3072 264 | 189, K = 8192 522 | 391; 320 238 | 187 and SGD 159 | 121; 384 230 | 183; 144, in one pass, K = 2048 108 | 97, K = 8192
-  // 254 | 236 but K = 16384 442 | 490).  In full passes the 128x128 tile gains 2 to 6 % on one update repeated (256 tiles, Adam, K = 2048 to
-  // 4096) and nothing, or 1 % less, behind the input gradient that it follows in a layer's backward pass; SGD's is 2 to 11 % slower.
-  if (tile == 1 && a.dtype != GEMM_F32 && pass_fill(big) <= 76) return big > 256 || a.K <= 8192 ? 2 : 1;
+  if (tile == 1 && a.dtype != GEMM_F32 && mid_tiles_for_long_update(big, tiles(128, 128), a.K)) return 2;
   return tile;
 }
 

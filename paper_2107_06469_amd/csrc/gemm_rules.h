@@ -29,4 +29,18 @@ inline bool mid_tiles_for_product(long big, long mid, int K, bool wide, bool dir
   return passes >= 3 && over == 1 && K <= 768;
 }
 
+// Updates over K >= 2048, whose thin passes cost the state's part of the epilogue, too.  us, 256x256 | 128x128, Adam, K = 2048, 8192, 16384:
+//   one pass, three to it   144 tiles 105 | 95, 255 | 231, 442 | 490; 192 125 | 108, 284 | 253 (rows 8 KB apart 115 | 112, 278 | 259; SGD 80 | 72,
+//     241 | 224); 12 x [1024 x 1024] 126 | 104, 291 | 266, at K = 12288 401 | 396 and SGD 360 | 365
+//   one pass, a fourth   195 120 | 120, 277 | 295; 198 117 | 119, 273 | 291; SGD 195 82 | 84, 237 | 262
+//   more passes, three to each   288 215 | 170, 526 | 394, 916 | 750; 384 238 | 204, 561 | 497, 977 | 917; 576 364 | 283, 827 | 742, 1465 | 1447
+//   more passes, a fourth to each   390 242 | 206, 563 | 537, 968 | 1014; 585 367 | 294, 839 | 783, 1462 | 1486; SGD 390 160 | 144, 475 | 474, 898 | 943
+// In full passes the 128x128 tile gains 2 to 6 % on one update repeated (256 tiles, Adam, K = 2048 to 4096) and nothing, or 1 % less, behind the
+// input gradient that it follows in a layer's backward pass; SGD's is 2 to 11 % slower.
+inline bool mid_tiles_for_long_update(long big, long mid, int K) {
+  if (pass_fill(big) > 76) return false;
+  if (rounds_over(big, mid) <= 0) return tile_passes(big) > 1 || K <= 8192;
+  return tile_passes(big) > 1 && K <= 8192;
+}
+
 }  // namespace hydra

@@ -34,3 +34,16 @@ def test_products_with_a_thin_last_pass(tmp_path):
     assert [c for c, g in zip(cases, got) if g != c[4]] == []
     # operands of 2 GiB and more, which the direct-to-LDS kernels do not take
     assert _chosen(tmp_path, ["mid_tiles_for_product(288, 1152, 131136, 0, true)", "mid_tiles_for_product(288, 1152, 131136, 0, false)"]) == [1, 0]
+
+
+def test_updates_over_long_sums_with_a_thin_last_pass(tmp_path):
+    # (256x256 tiles, 128x128 tiles, K, 128x128 tiles are ahead)
+    cases = [(144, 576, 2048, 1), (144, 576, 8192, 1), (192, 768, 2048, 1), (192, 768, 8192, 1), (187, 748, 6144, 1), (288, 1152, 2048, 1),
+             (288, 1152, 16384, 1), (320, 1280, 12288, 1), (384, 1536, 16384, 1), (576, 2304, 16384, 1), (390, 1560, 2048, 1),
+             (390, 1560, 8192, 1), (585, 2340, 8192, 1),
+             # behind
+             (144, 576, 16384, 0), (195, 780, 2048, 0), (195, 780, 4096, 0), (195, 780, 8192, 0), (196, 784, 3072, 0), (198, 792, 2048, 0),
+             (216, 864, 4096, 0), (390, 1560, 12288, 0), (390, 1560, 16384, 0), (585, 2340, 16384, 0), (800, 3200, 12288, 0),
+             (256, 1024, 2048, 0), (512, 2048, 4096, 0)]
+    got = _chosen(tmp_path, [f"mid_tiles_for_long_update({b}, {m}, {k})" for b, m, k, _ in cases])
+    assert [c for c, g in zip(cases, got) if g != c[3]] == []
