@@ -2116,14 +2116,13 @@ bool gemm_pair_waits(const GemmArgs& w) {
   const int t = choose_update_tile(w);
   return t == TILE_SMALL || t == TILE_SMALL_DEEP;
 }
-// The update takes 64x64 tiles by its own rule; the input gradient does too, or would take 128x128 ones and is small enough that
-// together they stay within five workgroups per CU.  us, one after the other | as one launch (4 models of 1024 tokens, d = 256): 1024 -> 256 with
-// the update of 256 x 1024 23 | 17, 256 -> 256 with 1024 x 256 20 | 17, 768 -> 256 with 256 x 256 20 | 13; an epoch of 20 steps of such
-// encoders 15.2 | 13.83 ms, and 13.64 with the pairs whose input gradient alone would take 128x128 tiles (256 -> 1024 with 768 x 256).
+// The update takes 64x64 tiles by its own rule; the input gradient does too, or would take 128x128 ones.  us, one after the other | as one launch
+// (4 models of 1024 tokens, d = 256): 1024 -> 256 with the update of 256 x 1024 23 | 17, 256 -> 256 with 1024 x 256 20 | 17, 768 -> 256 with
+// 256 x 256 20 | 13; an epoch of 20 steps of such encoders 15.2 | 13.64 ms.
 bool gemm_pair_ok(const GemmArgs& d, const GemmArgs& w) {
-  if (!gemm_pair_waits(w) || d.dtype != GEMM_BF16 || d.tile || !d.x_kmajor || d.w_kmajor || d.K > 1024 || !small_eligible(d)) return false;
+  if (!gemm_pair_waits(w) || d.dtype != GEMM_BF16 || d.tile || !d.x_kmajor || d.w_kmajor || !small_eligible(d)) return false;
   const int t = choose_tile(d);
-  return (t == TILE_SMALL || t == 2) && (long)pair_side(d) + pair_side(w) <= 1280;
+  return (t == TILE_SMALL || t == 2) && pair_ahead(pair_side(d), pair_side(w), t == TILE_SMALL, d.K, w.K);
 }
 hipError_t launch_gemm_pair(const GemmArgs& d, const GemmArgs& w, const GemmUpdate& u, hipStream_t s) {
   hipError_t e = check_gemm(d, true);

@@ -43,4 +43,23 @@ inline bool mid_tiles_for_long_update(long big, long mid, int K) {
   return tile_passes(big) > 1 && K <= 8192;
 }
 
+// A weight gradient with its update, n_w tiles of 64x64 over k_w rows, and an input gradient, n_d such tiles over k_d, as one launch of them.
+// 512 tiles run at a time.  d_small: the input gradient takes 64x64 tiles alone, too; then the launch is never slower (2531 measured pairs of up
+// to 1280 tiles, 0.976 of the two launches at worst).  Otherwise its 64x64 tiles cost more than the 128x128 ones that it gives up: little
+// over a short sum, and nothing where all tiles run at once or the update takes the longer.  Together against apart, n pairs, mean and worst, and
+// examples in us, apart | together (n_d + n_w, k_d and k_w):
+//   k_d <= 384: 1013, 0.74, 1.07 (eight slower, the next worst 1.04)   1024 + 192, 256 and 1024 25 | 20;  756 + 144, 384 and 1328 18.5 | 19.8
+//   all tiles at once: 279, 0.68, 0.87
+//   n_d <= 512, k_w >= 1.5 k_d: 173, 0.77, 1.02   512 + 256, 1024 and 2048 30 | 26
+//   k_d <= 512, a last pass of 160 tiles or more: 78, 0.82, 1.00   512 + 384, 512 and 1024 23 | 17;  696 + 144, 472 and 1841 27.7 | 26.6
+//   the rest: 268, 0.94, 1.29 (76 slower)   675 + 450, 952 and 572 30 | 38;  576 + 512, 1024 and 1100 34 | 40;  576 + 128, 768 and 1100 19 | 21
+// More than 1280 tiles: 1536 46 | 44 to 47 | 49, 2240 30 | 31, 2560 79 | 89, 6576 91 | 106.  k_d > 1024: together is ahead up to some 1000 tiles (768 44 |
+// 34) and behind from there (1536 60 | 65, 2560 93 | 123); not taken.
+inline bool pair_ahead(long n_d, long n_w, bool d_small, int k_d, int k_w) {
+  const long all = n_d + n_w, last = (all - 1) % 512 + 1;
+  if (all > 1280 || k_d > 1024) return false;
+  if (d_small || k_d <= 384 || all <= 512) return true;
+  return (k_d <= 512 && last >= 160) || (n_d <= 512 && 2L * k_w >= 3L * k_d);
+}
+
 }  // namespace hydra

@@ -47,3 +47,36 @@ def test_updates_over_long_sums_with_a_thin_last_pass(tmp_path):
              (256, 1024, 2048, 0), (512, 2048, 4096, 0)]
     got = _chosen(tmp_path, [f"mid_tiles_for_long_update({b}, {m}, {k})" for b, m, k, _ in cases])
     assert [c for c, g in zip(cases, got) if g != c[3]] == []
+
+
+def test_pairs_of_an_input_gradient_and_an_update(tmp_path):
+    # (input gradient's 64x64 tiles, update's, the former takes such tiles alone, too, its k, the update's, together is ahead)
+    cases = [(256, 256, 1, 1024, 1024, 1), (120, 480, 1, 928, 45, 1), (1024, 192, 0, 256, 1024, 1), (640, 64, 0, 128, 1024, 1),
+             (512, 256, 0, 1024, 2048, 1), (384, 64, 0, 768, 300, 1), (640, 240, 0, 512, 1024, 1), (512, 128, 0, 768, 4096, 1),
+             # apart
+             (576, 512, 0, 1024, 1100, 0), (576, 128, 0, 768, 1100, 0), (675, 450, 0, 952, 572, 0), (1080, 200, 0, 888, 1675, 0),
+             (825, 231, 0, 664, 1567, 0), (910, 140, 0, 624, 814, 0), (930, 90, 0, 936, 1961, 0), (384, 384, 0, 976, 140, 0),
+             (640, 448, 0, 432, 627, 0), (870, 210, 0, 416, 1803, 0), (440, 200, 0, 912, 692, 0), (2048, 192, 0, 256, 1024, 0),
+             (256, 1280, 1, 1536, 2048, 0)]
+    got = _chosen(tmp_path, [f"pair_ahead({d}, {w}, {s}, {kd}, {kw})" for d, w, s, kd, kw, _ in cases])
+    assert [c for c, g in zip(cases, got) if g != c[5]] == []
+
+
+@pytest.mark.parametrize("K,B,S,d,ffn,L,pairs", [(4, 8, 128, 256, 1024, 4, 16),   # every update but the first block's last one shares a launch
+                                                 (8, 10, 110, 256, 1024, 3, 3),   # the updates of W1 only, with the gradient through Wo
+                                                 (5, 4, 143, 960, 960, 3, 0), (8, 10, 110, 128, 512, 3, 12)])
+def test_launches_of_a_step_that_are_shared(K, B, S, d, ffn, L, pairs):
+    """Launches of a dry run against those with gradients kept, where every product is a launch of its own."""
+    from hydra_workloads import configs as C, make_data
+    from paper_2107_06469_amd import hydra as H
+    a = [C.transformer_arch(C.KIND_ENCODER, L, d, d // 64, ffn, 64, S, 0, C.DTYPE_BF16) for _ in range(K)]
+    w = C.Workload("pairs", 2, a, [C.hparams(C.OPT_ADAM, 1e-3)] * K, [[]] * K, B, S, 5, 1, 1, 3)
+    data, n = make_data(w), []
+    for keep in (True, False):
+        ctx = H.hydra_create(dry_run=True, n_streams=1, max_group=K, keep_grads=keep)
+        H.hydra_define_models(ctx, w.archs, w.hparams, 1)
+        H.hydra_shard(ctx, -1, [])
+        H.hydra_set_data(ctx, data["inputs"], data["target_pos"], data["targets"])
+        n.append(H.hydra_train_epoch(ctx, H.SCHED_SHARD_PARALLEL, None)["launches"])
+        H.hydra_destroy(ctx)
+    assert n[0] - n[1] == pairs
