@@ -360,23 +360,39 @@ __device__ __forceinline__ void wave_lds_sync() {
 // argument block once, so that the passes are straight-line code.
 // The optimizer state of a wave's 32x32 block, requested ahead of the products (few-tile bf16 kernels, which have the registers; the fp32
 // ones gained nothing).  us, requested behind them | ahead, Adam: 4 x [256 x 1024] over 1024 tokens 13.9 | 13.2, 1 x [1000 x 1000] over 600
-// 11.9 | 10.6, 8 x [512 x 512] over 900 22.6 | 21.3; an epoch of 20 small encoder steps 13.53 -> 12.95 ms.
+// 11.9 | 10.6, 8 x [512 x 512] over 900 22.6 | 21.3; an epoch of 20 small encoder steps 13.53 -> 12.95 ms.  161 launches of 40 to 2048 tiles and
+// random sizes, ten sets of buffers in turn: 0.92 of the time requested behind, 0.77 to 1.014.  The first products do not wait for it (the
+// kernel's waits count its loads): where they did, and each load had a test and a pointer of its own, the smallest launches took up to 1.14.
 struct NoState {};
 struct StateAhead {
+  static constexpr int ADAM_LOADS = 12, SGD_LOADS = 4;  // of a wave
   f32x4 p[2][2], m[2][2], v[2][2];
-  __device__ __forceinline__ void request(const GemmArgs& a, const GemmUpdate& u, int g, int mrow0, int ncol0, int lane) {
+  const float *P, *Mo, *Vo;
+  bool adam;
+  __device__ __forceinline__ void pointers(const GemmUpdate& u, int g) {  // ahead of everything: one wait for all of the arguments
+    P = u.p[g];
+    Mo = u.m[g];
+    Vo = u.v[g];
+    adam = u.opt == 1;
+    asm volatile("" ::"s"(P), "s"(Mo), "s"(Vo));
+  }
+  // Elements past the matrix read its last ones, which nobody uses.
+  __device__ __forceinline__ void request(const GemmArgs& a, int mrow0, int ncol0, int lane) {
+    size_t ix[2][2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {  // N is a multiple of 8: full vectors only
+        ix[q][hf] = (size_t)min(mrow0 + q * 16 + hf * 8 + lane / 8, a.M - 1) * a.ldo + min(ncol0 + (lane % 8) * 4, a.N - 4);
+        p[q][hf] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(P + ix[q][hf]));
+      }
+    if (!adam) return;
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf) {
-        const int r = mrow0 + q * 16 + hf * 8 + lane / 8, n = ncol0 + (lane % 8) * 4;
-        if (r >= a.M || n >= a.N) continue;  // N is a multiple of 8: full vectors only
-        const size_t ix = (size_t)r * a.ldo + n;
-        p[q][hf] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(u.p[g] + ix));
-        if (u.opt == 1) {
-          m[q][hf] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(u.m[g] + ix));
-          v[q][hf] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(u.v[g] + ix));
-        }
+        m[q][hf] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(Mo + ix[q][hf]));
+        v[q][hf] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(Vo + ix[q][hf]));
       }
   }
 };
@@ -1244,6 +1260,8 @@ __device__ __forceinline__ void small_body(const GemmArgs& a, const typename Upd
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int m0 = tm * BM, n0 = tn * BN, K = a.K;
+  typename std::conditional<UPD, StateAhead, NoState>::type state;
+  if constexpr (UPD) state.pointers(upd, g);
   RX ox;
   RW ow;
   ox.init(static_cast<const T*>(a.X[g]), a.ldx, m0, a.M, K, wave, lane);
@@ -1260,8 +1278,12 @@ __device__ __forceinline__ void small_body(const GemmArgs& a, const typename Upd
   };
 #pragma unroll
   for (int t = 0; t < NS; ++t) load(t);
-  typename std::conditional<UPD, StateAhead, NoState>::type state;
-  if constexpr (UPD) state.request(a, upd, g, m0 + wm * 32, n0 + wn * 32, lane);
+  if constexpr (UPD) {
+    // behind the stages' loads and ahead of everything else: the waits below count on where the state's loads stand
+    asm volatile("" ::: "memory");
+    state.request(a, m0 + wm * 32, n0 + wn * 32, lane);
+    asm volatile("" ::: "memory");
+  }
   int fx[NSTEP], fw[NSTEP];
 #pragma unroll
   for (int s = 0; s < NSTEP; ++s) {
@@ -1291,8 +1313,21 @@ __device__ __forceinline__ void small_body(const GemmArgs& a, const typename Upd
       w[s] = RW::read_frag(st, fw[s]);
     }
   };
+  // all but the newest N loads, and the state's where they were requested after the stage that is waited for
+  auto stage_landed = [&](auto n, auto lds_too, bool state_newer) {
+    constexpr int N = decltype(n)::value, L = decltype(lds_too)::value ? 15 << 8 : 0;
+    if constexpr (UPD) {
+      constexpr int NA = N + StateAhead::ADAM_LOADS, NG = N + StateAhead::SGD_LOADS;
+      static_assert(NA < 64, "vmcnt field");
+      if (state_newer && state.adam) __builtin_amdgcn_s_waitcnt((NA & 15) | ((NA >> 4) << 14) | (7 << 4) | L);
+      else if (state_newer) __builtin_amdgcn_s_waitcnt((NG & 15) | ((NG >> 4) << 14) | (7 << 4) | L);
+      else __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | L);
+    } else {
+      __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | L);
+    }
+  };
   auto body = [&](int t, uint4 (&xc)[NSTEP], uint4 (&wc)[NSTEP], uint4 (&xn)[NSTEP], uint4 (&wn_)[NSTEP]) {
-    __builtin_amdgcn_s_waitcnt((AL & 15) | ((AL >> 4) << 14) | (7 << 4));  // vmcnt(AL) lgkmcnt(0)
+    stage_landed(std::integral_constant<int, AL>(), std::false_type(), t < NS - 1);
     __builtin_amdgcn_s_barrier();
     load(t + NS);
     take(t + 1, xn, wn_);
@@ -1302,7 +1337,7 @@ __device__ __forceinline__ void small_body(const GemmArgs& a, const typename Upd
       if (RS) rs = chunk_sum<T>(xc[s], rs);
     }
   };
-  __builtin_amdgcn_s_waitcnt((AL0 & 15) | ((AL0 >> 4) << 14) | (7 << 4) | (15 << 8));
+  stage_landed(std::integral_constant<int, AL0>(), std::true_type(), true);
   __builtin_amdgcn_s_barrier();
   take(0, x0, w0);
   for (int t = 0; t < nk; t += 2) {

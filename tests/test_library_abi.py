@@ -450,3 +450,23 @@ def test_loads_into_lds_stand_a_wait_state_behind_the_write_of_their_m0(tmp_path
                 if re.match(r"s_\w+ m0\b", before):
                     bad.append((name, before, ins))
     assert seen > 0 and not bad, f"{len(bad)} of {seen}: {bad[:3]}"
+
+
+def test_state_loads_of_the_small_updates_stand_where_their_waits_count_on(tmp_path):
+    """The few-tile bf16 updates request the optimizer state behind the first stages' loads into LDS, and wait for a stage by the number of
+    loads that are newer, the state's 12 (Adam) or 4 (SGD) among them: up to the first barrier a wave issues exactly those, in that order,
+    and waits for all but the newer stages' and the state's."""
+    seen = 0
+    for name, code in _device_code(tmp_path).items():
+        small = re.search(r"gemm_small_kernelILi(\d+)ELi(\d+)ELb0ELb0ELb1E", name)
+        if not small:
+            continue
+        seen += 1
+        head = code[:next(i for i, c in enumerate(code) if c.startswith("s_barrier"))]
+        mem = [c.split()[0] + (" lds" if c.endswith(" lds") else "") for c in head if c.startswith(("buffer_", "global_", "flat_", "scratch_"))]
+        per_stage = 64 * int(small.group(1)) * 2 // 256                # 16-byte chunks of 64 + 64 rows over 256 threads
+        stages = int(small.group(2))
+        assert mem == ["buffer_load_dwordx4 lds"] * (per_stage * stages) + ["global_load_dwordx4"] * 12, (name, mem)
+        waits = sorted(int(m.group(1)) for m in (re.search(r"vmcnt\((\d+)\)", c) for c in head if c.startswith("s_waitcnt")) if m)
+        assert waits == [per_stage * (stages - 1) + 4, per_stage * (stages - 1) + 12], (name, waits)
+    assert seen == 2
