@@ -30,7 +30,7 @@
 #include <type_traits>
 
 #include "act_math.h"
-#include "gemm_rules.h"
+#include "launch_rules.h"
 #include "kernels.h"
 #include "lds_dma.h"
 #include "optim_math.h"

@@ -1,9 +1,10 @@
-// Rules of the tile choice for large bf16 launches, by counts alone: a choice never changes a result (every tile sums in the same order), only
-// the time.  Nothing here calls HIP.
+// Which of two forms of a launch is ahead, by counts alone: the forms give the same bits, so a choice changes nothing but the time.  Nothing
+// here calls HIP.
 #pragma once
 
 namespace hydra {
 
+// ---- bf16 products: 256x256 tiles or 128x128 ones -------------------------------------------------------------------------------
 // A launch of `big` 256x256 tiles runs in passes of one tile per CU (256), the same launch as `mid` 128x128 tiles with two workgroups per CU.
 inline long tile_passes(long big) { return (big + 255) / 256; }
 // percent of the passes of 256x256 tiles that hold a tile
@@ -43,6 +44,7 @@ inline bool mid_tiles_for_long_update(long big, long mid, int K) {
   return tile_passes(big) > 1 && K <= 8192;
 }
 
+// ---- launches that two products share ---------------------------------------------------------------------------------------------
 // A weight gradient with its update, n_w tiles of 64x64 over k_w rows, and an input gradient, n_d such tiles over k_d, as one launch of them.
 // 512 tiles run at a time.  d_small: the input gradient takes 64x64 tiles alone, too; then the launch is never slower (2531 measured pairs of up
 // to 1280 tiles, 0.976 of the two launches at worst).  Otherwise its 64x64 tiles cost more than the 128x128 ones that it gives up: little
@@ -61,5 +63,11 @@ inline bool pair_ahead(long n_d, long n_w, bool d_small, int k_d, int k_w) {
   if (d_small || k_d <= 384 || all <= 512) return true;
   return (k_d <= 512 && last >= 160) || (n_d <= 512 && 2L * k_w >= 3L * k_d);
 }
+
+// ---- LayerNorm backward of bf16 rows wider than 512: four workgroups to a CU or three ------------------------------------------------
+// Four take the blocks in one pass where three would begin a second one.  us, three | four: 768 blocks 69.6 | 70.0, 826 64.8 | 58.2, 924 95.2 |
+// 87.4, 959 119 | 110, 1024 95.7 | 91.1;  beyond that the passes run into one another and four are behind: 1115 82.2 | 84.1, 1444 138 | 141, 1965
+// 205 | 208, 2340 level.
+inline bool ln_four_to_a_cu(long blocks) { return blocks > 768 && blocks <= 1024; }
 
 }  // namespace hydra

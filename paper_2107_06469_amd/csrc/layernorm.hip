@@ -13,6 +13,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "launch_rules.h"
 #include "wave_math.h"
 
 namespace hydra {
@@ -268,7 +269,7 @@ __device__ __forceinline__ void ln_bwd_row(const LnBwdArgs& a, int g, int row, i
 // memory.  us: 4 x [16384, 768] bf16 97 (4.2 TB/s), 3 x [14483, 616] 46, 2 x [16384, 1024] 53; fp32 4 x [16384, 768] 175.  With two rows in
 // flight 94 | 53 | 54 | 175, with four and no prefetch 101 | 60 | 57 | 205, over 8 waves (one workgroup per CU) 96 | 52 | 55 | 175.
 // FOUR (bf16 rows wider than 512): gamma in LDS, 128 registers instead of 146, so that four workgroups share a CU and not three;
-// ahead where there are more than three per CU: 4 x [16384, 768] (1024 workgroups) 95.7 | 91.1, up to there 1 to 2 % behind.
+// ahead where they are one pass that way and two the other: 4 x [16384, 768] (1024 workgroups) 95.7 | 91.1 us.
 template <typename T, int C, bool FOUR = false>
 __global__ __launch_bounds__(256, FOUR ? 4 : 1) void ln_bwd_kernel(const LnBwdArgs a) {
   extern __shared__ float red[];  // [4][2][d], FOUR: gamma [d]
@@ -679,7 +680,7 @@ static hipError_t ln_bwd_pick(const LnBwdArgs& a, hipStream_t s) {
   const bool chain = a.d <= 512 && blocks <= 256 && (sizeof(T) == 2 || blocks * a.d <= 96 * 1024);
   if (chain) hipLaunchKernelGGL((ln_bwd_chain_kernel<T>), grid, dim3(1024), 0, s, a);
   else if (a.d <= 512) hipLaunchKernelGGL((ln_bwd_kernel<T, 1>), grid, dim3(256), lds, s, a);
-  else if (sizeof(T) == 2 && a.d <= LN_WAVE_ROW_MAX && blocks > 768)
+  else if (sizeof(T) == 2 && a.d <= LN_WAVE_ROW_MAX && ln_four_to_a_cu(blocks))
     hipLaunchKernelGGL((ln_bwd_kernel<bf16_t, 2, true>), grid, dim3(256), lds + 4 * a.d, s, a);
   else if (a.d <= LN_WAVE_ROW_MAX) hipLaunchKernelGGL((ln_bwd_kernel<T, 2>), grid, dim3(256), lds, s, a);
   else if (a.d <= 2048) hipLaunchKernelGGL((ln_bwd_wide_kernel<T, 1>), grid, dim3(256), 0, s, a);

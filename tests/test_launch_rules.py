@@ -1,4 +1,4 @@
-"""The rules that choose a tile for large launches (csrc/gemm_rules.h) at counts where both tiles were measured: what was slower is not chosen.
+"""The rules that choose between two forms of a launch (csrc/launch_rules.h) at counts where both were measured: what was slower is not chosen.
 The rules are host code without HIP: a small program around them runs on the CPU."""
 import os
 import shutil
@@ -14,7 +14,7 @@ def _chosen(tmp_path, calls):
     if not shutil.which("g++"):
         pytest.skip("no g++")
     src, exe = tmp_path / "t.cpp", tmp_path / "t"
-    src.write_text('#include <cstdio>\n#include "gemm_rules.h"\nusing namespace hydra;\nint main() {\n'
+    src.write_text('#include <cstdio>\n#include "launch_rules.h"\nusing namespace hydra;\nint main() {\n'
                    + "".join(f'  std::printf("%d\\n", (int)({c}));\n' for c in calls) + "}\n")
     subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2107_06469_amd", "csrc"), str(src), "-o", str(exe)], check=True)
     return [int(x) for x in subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split()]
@@ -60,6 +60,11 @@ def test_pairs_of_an_input_gradient_and_an_update(tmp_path):
              (256, 1280, 1, 1536, 2048, 0)]
     got = _chosen(tmp_path, [f"pair_ahead({d}, {w}, {s}, {kd}, {kw})" for d, w, s, kd, kw, _ in cases])
     assert [c for c, g in zip(cases, got) if g != c[5]] == []
+
+
+def test_layernorm_backward_takes_four_workgroups_to_a_cu_for_one_pass_of_them(tmp_path):
+    cases = [(768, 0), (769, 1), (826, 1), (959, 1), (1024, 1), (1025, 0), (1115, 0), (1444, 0), (1965, 0), (2340, 0)]
+    assert _chosen(tmp_path, [f"ln_four_to_a_cu({b})" for b, _ in cases]) == [f for _, f in cases]
 
 
 @pytest.mark.parametrize("K,B,S,d,ffn,L,pairs", [(4, 8, 128, 256, 1024, 4, 16),   # every update but the first block's last one shares a launch
