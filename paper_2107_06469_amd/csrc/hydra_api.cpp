@@ -1,7 +1,6 @@
 // The C boundary declared in include/hydra.h: argument checking, call-order checking and copies
 // between caller memory and the device.  No exception leaves these functions.
 #include <algorithm>
-#include <atomic>
 #include <cstring>
 #include <new>
 #include <thread>
@@ -445,7 +444,6 @@ hydra_status hydra_train_epoch(hydra_ctx* c, const hydra_schedule* sch, hydra_ep
 // to pageable memory runs at 7 to 11 GB/s, most of it the first touch of dst's pages by one thread; from 2 MB on four threads share the
 // pieces.  Four models of 3.4 M parameters: 4.6 to 7.6 ms before, 1.9 to 3.3 now; four of 0.26 M (one thread) 0.41 | 0.28.
 static hipError_t copy_tensors_out(hydra_ctx* c, const Model& m, int tensor, const float* src, float* dst) {
-  struct Piece { size_t off, n, to; };
   std::vector<Piece> ps;
   const int nt = (int)m.tensors.size();
   size_t to = 0;
@@ -457,50 +455,18 @@ static hipError_t copy_tensors_out(hydra_ctx* c, const Model& m, int tensor, con
   }
   if (ps.empty()) return hipSuccess;
   const StageLease lease(result_stage());
-  float* const stage = rising ? lease.p : nullptr;
-  if (!stage) {  // runs of tensors that fit 1 MB as one copy (some 10 us each whatever its size), larger ones straight to their place
-    constexpr size_t RUN = (size_t)1 << 18;  // floats
-    std::vector<float> buf;
-    for (size_t j = 0; j < ps.size();) {
-      size_t k = j + 1;
-      while (rising && k < ps.size() && ps[k].off + ps[k].n <= ps[j].off + RUN) ++k;
-      const size_t n = ps[k - 1].off + ps[k - 1].n - ps[j].off;
-      const bool run = k > j + 1;
-      if (run) buf.resize(n);
-      const hipError_t e = hipMemcpy(run ? buf.data() : dst + ps[j].to, src + ps[j].off, n * 4, hipMemcpyDeviceToHost);
-      if (e != hipSuccess) return e;
-      const size_t at = ps[j].off;
-      for (; j < k; ++j)
-        if (run) memcpy(dst + ps[j].to, buf.data() + (ps[j].off - at), ps[j].n * 4);
-    }
-    return hipSuccess;
-  }
-  const size_t first = ps.front().off, total = ps.back().off + ps.back().n - first;
+  if (!lease.p || !rising)
+    return (hipError_t)copy_direct(ps, rising, src, dst, [](float* d, const float* s, size_t n) { return hipMemcpy(d, s, n * 4, hipMemcpyDeviceToHost); });
+  const size_t total = ps.back().off + ps.back().n - ps.front().off;
   const unsigned T = total * 4 >= ((size_t)2 << 20) ? std::max(1u, std::min(4u, std::thread::hardware_concurrency())) : 1;
-  const size_t part = Stage::BYTES / 4 / T;
   int dev = 0;
   if (const hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
-  std::atomic<size_t> next{0};
-  std::atomic<int> err{(int)hipSuccess};
-  auto work = [&](unsigned k) {
-    float* const buf = stage + k * part;
+  return (hipError_t)copy_staged(ps, src, dst, lease.p, Stage::BYTES / 4, T, [&](unsigned k, float* d, const float* from, size_t n) {
     const hipStream_t s = c->streams[k % c->streams.size()];
     hipError_t e = k ? hipSetDevice(dev) : hipSuccess;
-    for (size_t b; e == hipSuccess && err.load() == (int)hipSuccess && (b = next.fetch_add(part)) < total;) {
-      const size_t lo = first + b, hi = std::min(first + total, lo + part);
-      e = hipMemcpyAsync(buf, src + lo, (hi - lo) * 4, hipMemcpyDeviceToHost, s);
-      if (e == hipSuccess) e = hipStreamSynchronize(s);
-      if (e != hipSuccess) break;
-      auto p = std::upper_bound(ps.begin(), ps.end(), lo, [](size_t v, const Piece& q) { return v < q.off + q.n; });
-      for (; p != ps.end() && p->off < hi; ++p) {
-        const size_t x = std::max(lo, p->off), y = std::min(hi, p->off + p->n);
-        memcpy(dst + p->to + (x - p->off), buf + (x - lo), (y - x) * 4);
-      }
-    }
-    if (e != hipSuccess) err.store((int)e);
-  };
-  on_threads(T, work);
-  return (hipError_t)err.load();
+    if (e == hipSuccess) e = hipMemcpyAsync(d, from, n * 4, hipMemcpyDeviceToHost, s);
+    return e == hipSuccess ? hipStreamSynchronize(s) : e;
+  });
 }
 
 static hydra_status copy_out(hydra_ctx* c, int model, int tensor, float* dst, size_t cap, size_t* n_written, bool grads) {

@@ -1,7 +1,10 @@
 // Host side of results on their way from the device to a caller's memory.  Nothing here calls HIP: what allocates and what copies
 // is handed in.
 #pragma once
+#include <algorithm>
+#include <atomic>
 #include <cstddef>
+#include <cstring>
 #include <mutex>
 #include <thread>
 #include <vector>
@@ -88,6 +91,54 @@ void on_threads(unsigned T, const W& work) {
   }
   work(0);
   for (std::thread& t : helpers) t.join();
+}
+
+// n floats at `off` of a block go to `to` of the caller's array
+struct Piece { size_t off, n, to; };
+
+// Pieces of the block at src straight to dst.  Where they rise in the block, runs that fit 1 MB travel as one copy (some 10 us each whatever
+// its size) and are taken apart here; larger pieces go to their place.  copy(to, from, floats) returns when it is done, 0 if it went well.
+template <typename C>
+int copy_direct(const std::vector<Piece>& ps, bool rising, const float* src, float* dst, const C& copy) {
+  constexpr size_t RUN = (size_t)1 << 18;  // floats
+  std::vector<float> buf;
+  for (size_t j = 0; j < ps.size();) {
+    size_t k = j + 1;
+    while (rising && k < ps.size() && ps[k].off + ps[k].n <= ps[j].off + RUN) ++k;
+    const size_t n = ps[k - 1].off + ps[k - 1].n - ps[j].off;
+    const bool run = k > j + 1;
+    if (run) buf.resize(n);
+    if (const int e = (int)copy(run ? buf.data() : dst + ps[j].to, src + ps[j].off, n)) return e;
+    const size_t at = ps[j].off;
+    for (; j < k; ++j)
+      if (run) memcpy(dst + ps[j].to, buf.data() + (ps[j].off - at), ps[j].n * 4);
+  }
+  return 0;
+}
+
+// Pieces that rise in the block, as one range in parts through a buffer of `room` floats that T threads share; thread k's copies are
+// copy(k, to, from, floats).
+template <typename C>
+int copy_staged(const std::vector<Piece>& ps, const float* src, float* dst, float* stage, size_t room, unsigned T, const C& copy) {
+  const size_t first = ps.front().off, total = ps.back().off + ps.back().n - first, part = room / T;
+  std::atomic<size_t> next{0};
+  std::atomic<int> err{0};
+  on_threads(T, [&](unsigned k) {
+    float* const buf = stage + k * part;
+    for (size_t b; err.load() == 0 && (b = next.fetch_add(part)) < total;) {
+      const size_t lo = first + b, hi = std::min(first + total, lo + part);
+      if (const int e = (int)copy(k, buf, src + lo, hi - lo)) {
+        err.store(e);
+        return;
+      }
+      auto p = std::upper_bound(ps.begin(), ps.end(), lo, [](size_t v, const Piece& q) { return v < q.off + q.n; });
+      for (; p != ps.end() && p->off < hi; ++p) {
+        const size_t x = std::max(lo, p->off), y = std::min(hi, p->off + p->n);
+        memcpy(dst + p->to + (x - p->off), buf + (x - lo), (y - x) * 4);
+      }
+    }
+  });
+  return err.load();
 }
 
 }  // namespace hydra

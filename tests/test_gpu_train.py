@@ -366,18 +366,25 @@ def test_small_fp32_models_at_ragged_widths(H, batch, d_in, d, n_out, layers):
 
 
 def test_reading_all_tensors_equals_reading_each():
-    """Small neighbouring tensors leave the device as one copy, larger ones by themselves: the same values as one by one, with tensors
-    of odd sizes (padded in the block), around the 1 MB limit and beyond it."""
+    """A model leaves the device as one range through the pinned buffer and is taken apart on the way (below 2 MB by one thread, from there on
+    by four): the values that were written tensor by tensor, as one by one, with tensors of odd sizes (padded in the block).  The way
+    without the buffer is tested on the host (test_result_copy.py)."""
     import hydra_workloads.configs as W
     from paper_2107_06469_amd import hydra as H
+    rng = np.random.default_rng(8)
     for layers, d_in, d, out in ((3, 40, 24, 7), (2, 512, 520, 11), (2, 504, 512, 1000), (1, 8, 8, 1)):
         ctx = H.hydra_create()
         try:
             a = W.mlp_arch(layers, d_in, d, out, W.ACT_RELU, W.DTYPE_F32)
             H.hydra_define_models(ctx, [a] * 2, [W.hparams(W.OPT_SGD, 0.1)] * 2, 5)
+            written = [[rng.standard_normal(s, dtype=np.float32) for s in H.hydra_tensor_shapes(ctx, k)] for k in range(2)]
+            for k in range(2):
+                for j, t in enumerate(written[k]):
+                    H.hydra_write_params(ctx, k, j, t)
             for k in range(2):
                 whole = H.hydra_read_params(ctx, k)
                 for j, t in enumerate(whole):
+                    assert np.array_equal(t.reshape(-1), written[k][j].reshape(-1)), (d, k, j)
                     assert np.array_equal(t.reshape(-1), H.hydra_read_params(ctx, k, j)), (d, k, j)
         finally:
             H.hydra_destroy(ctx)

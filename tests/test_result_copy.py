@@ -111,3 +111,61 @@ def test_copies_under_way_are_waited_for_where_one_could_not_be_requested(tmp_pa
   CHECK(request_all(5, [&](int i) { return i == 4 ? 3 : 0; }, [&] { ++waits; return 9; }) == 3);
   CHECK(request_all(0, [&](int i) { return 1; }, [&] { ++waits; return 0; }) == 0 && waits == 4);
 """)
+
+
+# Tensors of a model as they lie in its block (each padded to 64 floats): what is left out of a run, and runs on either side of 1 MB (262144
+# floats); one tensor; tensors that do not rise.
+BLOCKS = {"small": [40 * 24, 24, 24 * 24, 24, 7 * 24, 7], "around_1_mb": [512 * 512, 512, 512 * 520, 520, 130000, 131000, 1000, 11],
+          "exactly_1_mb": [262144 - 64, 64, 262144, 1, 262143, 1], "large": [776 * 776, 776] * 3 + [13 * 776, 13], "one": [5]}
+
+
+@pytest.mark.parametrize("block,first", [(b, f) for b in sorted(BLOCKS) for f in (0, 1) if f < len(BLOCKS[b])])
+def test_tensors_arrive_whole_with_and_without_the_buffer(tmp_path, block, first):
+    """Every tensor at its place and nothing beside it, straight and through the buffer by one thread and by four (a buffer of 4 MB and one of
+    a few hundred floats, so that parts end inside tensors); a copy that fails is reported; the number of direct copies is that of the runs."""
+    sizes = BLOCKS[block]
+    _run(tmp_path, """
+  const std::vector<size_t> sizes = {%s};
+  std::vector<Piece> ps;
+  size_t off = 64, to = 0;
+  for (size_t j = 0; j < sizes.size(); ++j) {
+    if (j >= %d) { ps.push_back({off, sizes[j], to}); to += sizes[j]; }
+    off += (sizes[j] + 63) / 64 * 64;
+  }
+  std::vector<float> src(off + 64), want(to);
+  for (size_t i = 0; i < src.size(); ++i) src[i] = (float)(i %% 16777213);
+  for (const Piece& p : ps) std::memcpy(&want[p.to], &src[p.off], p.n * 4);
+  auto same = [&](const std::vector<float>& got) {
+    return got.size() == to + 2 && got[0] == -1.f && got.back() == -1.f && std::memcmp(&got[1], want.data(), to * 4) == 0;
+  };
+  auto fresh = [&] { return std::vector<float>(to + 2, -1.f); };
+
+  int copies = 0;
+  auto plain = [&](float* d, const float* s, size_t n) { ++copies; std::memcpy(d, s, n * 4); return 0; };
+  std::vector<float> got = fresh();
+  CHECK(copy_direct(ps, true, src.data(), &got[1], plain) == 0 && same(got));
+  int runs = 0;
+  for (size_t j = 0; j < ps.size(); ++runs) {
+    const size_t end = ps[j].off + 262144;
+    for (++j; j < ps.size() && ps[j].off + ps[j].n <= end;) ++j;
+  }
+  CHECK(copies == runs);
+  copies = 0;
+  got = fresh();
+  CHECK(copy_direct(ps, false, src.data(), &got[1], plain) == 0 && same(got) && copies == (int)ps.size());
+  CHECK(copy_direct(ps, true, src.data(), &got[1], [](float*, const float*, size_t) { return 5; }) == 5);
+
+  for (const size_t room : {Stage::BYTES / 4, (size_t)1000}) {
+    std::vector<float> stage(room);
+    for (const unsigned T : {1u, 4u}) {
+      got = fresh();
+      auto part = [&](unsigned k, float* d, const float* s, size_t n) {
+        CHECK(k < T && n <= room / T && d == stage.data() + k * (room / T));
+        std::memcpy(d, s, n * 4);
+        return 0;
+      };
+      CHECK(copy_staged(ps, src.data(), &got[1], stage.data(), room, T, part) == 0 && same(got));
+      CHECK(copy_staged(ps, src.data(), &got[1], stage.data(), room, T, [](unsigned, float*, const float*, size_t) { return 3; }) == 3);
+    }
+  }
+""" % (", ".join(map(str, sizes)), first))
