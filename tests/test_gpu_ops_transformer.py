@@ -164,12 +164,16 @@ def test_attention_uniform_scores_closed_form(torch, ops):
 
 
 @pytest.mark.parametrize("dtype", [0, 1])
-def test_embedding_forward_and_backward(torch, ops, dtype):
+@pytest.mark.parametrize("d,B,often", [(72, 3, 5), (328, 8, 16), (328, 9, 17), (256, 17, 19), (520, 16, 33), (264, 1, 4)])
+def test_embedding_forward_and_backward(torch, ops, dtype, d, B, often):
+    """One id that `often` tokens have (16 are added at a time, what is left in fours), rows wider than the 256 columns of a workgroup, batches
+    of eight (a position's rows are added eight at a time) and what is left of them, positions past the sequence."""
     r = np.random.default_rng(5)
-    V, S_table, S, B, d = 50, 40, 33, 3, 72
+    V, S_table, S = 50, 40, 33
     mk = _bf if dtype else _f32
     ids = r.integers(0, V, size=(B, S)).astype(np.int32)
-    ids[0, :5] = 7                                           # duplicates
+    ids[ids == 7] = 8
+    ids.reshape(-1)[r.choice(B * S, size=often, replace=False)] = 7
     order = np.argsort(ids.reshape(-1), kind="stable").astype(np.int32)
     row_ptr = np.concatenate([[0], np.cumsum(np.bincount(ids.reshape(-1), minlength=V))]).astype(np.int32)
     toks, poss, xs, dxs, dtoks, dposs, refs = [], [], [], [], [], [], []
