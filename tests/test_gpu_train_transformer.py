@@ -125,6 +125,31 @@ def test_paired_gradient_launches_keep_the_bits_of_separate_ones(H, batch, seq, 
             assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("gated,recompute", [(1, False), (1, True), (0, True)])
+@pytest.mark.parametrize("batch,seq,d,heads,ffn", [(3, 48, 128, 2, 344), (9, 120, 128, 1, 264)])
+def test_paired_gradient_launches_of_gated_decoders_and_recomputed_blocks(H, gated, recompute, batch, seq, d, heads, ffn):
+    """As above where a held W1 gradient rides with the gradient through Wg, which reads and writes its own output, and where the products'
+    operands lie in workspaces that the shards' tasks share."""
+    kind = C.KIND_DECODER if gated else C.KIND_ENCODER
+    archs = [C.transformer_arch(kind, 4, d, heads, ffn, 96, seq, gated, C.DTYPE_BF16) for _ in range(2)]
+    n_targets = seq if gated else 5
+    w = C.Workload("paired", 2, archs, [C.hparams(C.OPT_ADAM, 1e-3), C.hparams(C.OPT_SGD, 1e-2)], [[2]] * 2, batch, seq, n_targets, 3, 3, 31 + seq)
+    data = make_data(w)
+    # room for one shard's workspace, or a few
+    kw = dict(activation_budget_bytes=max(3 << 20, batch * seq * 13000)) if recompute else {}
+    paired, ps = H.train_workload(w, data, H.SCHED_SHARD_PARALLEL, **kw)
+    apart, as_ = H.train_workload(w, data, H.SCHED_SHARD_PARALLEL, keep_grads=True)
+    if recompute:                                                        # the forward passes of the shards but the last run twice
+        kept, ks = H.train_workload(w, data, H.SCHED_SHARD_PARALLEL, keep_grads=True, **kw)
+        assert ks[0]["launches"] > as_[0]["launches"] and ps[0]["launches"] < ks[0]["launches"]
+    else:
+        assert ps[0]["launches"] < as_[0]["launches"]
+    for k in range(w.K):
+        assert np.array_equal(paired[k][0], apart[k][0])
+        for a, b in zip(paired[k][1], apart[k][1]):
+            assert np.array_equal(a, b)
+
+
 def test_data_is_validated(H):
     w = scaled_workload(2, K=1)
     d = make_data(w)
