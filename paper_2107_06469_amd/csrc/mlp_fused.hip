@@ -11,8 +11,9 @@
 // apply the same single-rounded operations as the tiled GEMM kernel's.  Results depend on nothing but the model: not
 // on the group, the cut points or the schedule.
 //
-// Bound by what one compute unit takes in: 256 KB of weights a layer at 36 to 40 bytes a cycle, 3 us; the products (32 dependent
-// instructions of 12 cycles per 32 k) stand beside that.  4 x (4 layers of 256, 32 rows), forward and chain in one launch: 35.8 us, of which
+// Bound by what one compute unit takes in: 256 KB of weights a layer at 36 to 40 bytes a cycle, 3 us.  The same weights go into LDS and out
+// again, 512 KB at 128 bytes a cycle, 4100 of those 6300 to 7200 cycles, and the products (32 dependent instructions of 12 cycles per 32
+// k) stand beside both.  4 x (4 layers of 256, 32 rows), forward and chain in one launch: 35.8 us, of which
 // 23 are those sums; with 16 rows a workgroup (v_mfma_f32_16x16x4_f32, weights through registers, 8 of 256 compute units) 59.4.
 // Bringing the weights into L2 beforehand changes nothing, nor does asking for the input rows ahead of them.
 #include "act_math.h"
@@ -67,10 +68,6 @@ __device__ __forceinline__ float4 gload4(const gfloat* p) {
   const f32x4v v = *(const gf32x4v*)p;
   return make_float4(v.x, v.y, v.z, v.w);
 }
-__device__ __forceinline__ void gstore4(gfloat* p, float a, float b, float c, float d) {
-  const f32x4v v = {a, b, c, d};
-  *(gf32x4v*)p = v;
-}
 
 // rows [0, rows) x columns [0, cols) of a row-major matrix into the RB LDS rows of pitch XS, 16 bytes a thread; the rest of the 256
 // columns is zero (the products run over k in groups of 16 and must not meet what an earlier kernel left in LDS)
@@ -103,12 +100,6 @@ constexpr size_t CHAIN_LDS = 2 * RB * XS * sizeof(float) + 4 * (size_t)WLDS;
 
 // the same value in every lane, told to the compiler (descriptors of buffer loads must sit in scalar registers)
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ const float* uniform(const float* p) {
-  const unsigned long long b = reinterpret_cast<unsigned long long>(p);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)b);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(b >> 32));
-  return reinterpret_cast<const float*>(((unsigned long long)hi << 32) | lo);
-}
 
 // orders a wave's own LDS writes before its later LDS reads (the hardware keeps a wave's LDS operations in order; this
 // keeps the compiler from moving them)
@@ -427,7 +418,8 @@ __global__ __launch_bounds__(256) void mlp_dgrad_chain_kernel(const MlpFusedArgs
 // Forward through all of a model's units, then straight on into the chain of input gradients: a workgroup's rows
 // need nothing from other workgroups in between (the rows' losses and the gradient of the logits are its own), so
 // the two phases of a step that the plan runs back to back are one launch.  The pre-activations that the forward phase wrote to
-// memory are read back by the wave that wrote them.
+// memory are read back by the wave that wrote them.  45 scalar registers of the weights' stream are kept in lanes of a vector register: the
+// two halves' arguments and descriptors together are more than there are (neither half alone spills any).
 __global__ __launch_bounds__(256) void mlp_fwd_chain_kernel(const MlpFusedArgs a) {
   extern __shared__ float smem[];
   const int g = blockIdx.x % a.G, tid = threadIdx.x, wave = uniform(tid >> 6);

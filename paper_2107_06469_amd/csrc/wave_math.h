@@ -33,15 +33,6 @@ __device__ __forceinline__ float wave_sum(float v) {
   v += wave_dpp<0x4e>(v);   // quad_perm [2,3,0,1]
   return v + wave_dpp<0xb1>(v);  // quad_perm [1,0,3,2]
 }
-// the sum over the 16 lanes with the same lane % 4
-__device__ __forceinline__ float wave_sum_mod4(float v) {
-  float2 p = wave_swap32(v);
-  v = p.x + p.y;
-  p = wave_swap16(v);
-  v = p.x + p.y;
-  v += wave_dpp<0x128>(v);
-  return v + wave_dpp<0x124>(v);
-}
 __device__ __forceinline__ float wave_max(float v) {
   float2 p = wave_swap32(v);
   v = fmaxf(p.x, p.y);
