@@ -57,8 +57,11 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(const SoftmaxCeArgs a) 
 // multiples of 4).  Loads and stores go through descriptors that end with the row, and only the groups past the last whole NT, and the
 // one that holds the label, are looked at element by element: with a test per element and per access the long rows took 176
 // registers, one workgroup per CU, so that nothing ran while a row was on its way.  us, before | now: 4 x [2432, 30522] bf16 445 | 329 (5.4
-// TB/s), 2 x [1000, 20000] 80 | 51, 1 x [4096, 10000] 131 | 88.
-template <typename T, int NV, int NT>
+// TB/s), 2 x [1000, 20000] 80 | 45, 1 x [4096, 10000] 131 | 68.
+// SKIP: no gradients are worked out for groups past the row's end.  The long rows' kernel then has 78 registers instead of 82 and three workgroups
+// to a CU instead of two, which rows that fill it do not want: us, without | with, 4 x [2432, 16384] 217 | 175, 1 x [88, 10280] 11.1 | 9.9, 2 x
+// [1000, 20000] 50 | 45, 4 x [1000, 24000] 112 | 112.3, 28000 132 | 134, 4 x [2432, 30522] 330 | 338.
+template <typename T, int NV, int NT, bool SKIP = true>
 __global__ __launch_bounds__(NT) void softmax_ce_row_kernel(const SoftmaxCeArgs a) {
   typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
   typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
@@ -122,7 +125,7 @@ __global__ __launch_bounds__(NT) void softmax_ce_row_kernel(const SoftmaxCeArgs 
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     const int c = 4 * (tid + NT * i);
-    if (NV == 1 ? c >= a.lddz : 4 * NT * i >= a.lddz) continue;
+    if (SKIP && (NV == 1 ? c >= a.lddz : 4 * NT * i >= a.lddz)) continue;
     float d[4];
     if (i >= whole || i == y_group) {
 #pragma unroll
@@ -175,9 +178,12 @@ hipError_t launch_softmax_ce(const SoftmaxCeArgs& a, hipStream_t s) {
     } else if (a.lddz <= 8192) {
       if (f32) hipLaunchKernelGGL((softmax_ce_row_kernel<float, 8, 256>), grid, dim3(256), 0, s, a);
       else hipLaunchKernelGGL((softmax_ce_row_kernel<bf16_t, 8, 256>), grid, dim3(256), 0, s, a);
-    } else {
+    } else if (a.lddz <= 20480) {
       if (f32) hipLaunchKernelGGL((softmax_ce_row_kernel<float, 16, 512>), grid, dim3(512), 0, s, a);
       else hipLaunchKernelGGL((softmax_ce_row_kernel<bf16_t, 16, 512>), grid, dim3(512), 0, s, a);
+    } else {
+      if (f32) hipLaunchKernelGGL((softmax_ce_row_kernel<float, 16, 512, false>), grid, dim3(512), 0, s, a);
+      else hipLaunchKernelGGL((softmax_ce_row_kernel<bf16_t, 16, 512, false>), grid, dim3(512), 0, s, a);
     }
   } else if (a.dtype == GEMM_F32) hipLaunchKernelGGL(softmax_ce_kernel<float>, grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL(softmax_ce_kernel<bf16_t>, grid, dim3(256), 0, s, a);

@@ -689,7 +689,7 @@ def test_update_of_rows_8_kb_apart(torch, ops, K):
     assert all(torch.equal(a, b) for a, b in zip(*got))
 
 
-@pytest.mark.parametrize("C", [1, 5, 1020, 1023, 1024, 1025, 8188, 8192, 8193, 16384, 30522, 32765, 32768])
+@pytest.mark.parametrize("C", [1, 5, 1020, 1023, 1024, 1025, 8188, 8192, 8193, 16384, 20480, 20481, 30522, 32765, 32768])
 @pytest.mark.parametrize("f32", [False, True])
 def test_softmax_rows_at_the_ends_of_register_groups(torch, ops, C, f32):
     """Rows that end inside a group of four, at a whole number of groups per thread and one beside it; labels in the first and the last
