@@ -20,6 +20,14 @@ __device__ __forceinline__ rsrc_u32x4 rsrc_words(const void* base, long first, l
   r.w = 0x00020000u;
   return r;
 }
+// A descriptor whose words a vector instruction (readfirstlane) may have written just before: a load may read them five wait states later on
+// gfx9, which the compiler counts for its own loads, not for those in the asm blocks below.  Where the words are worked out by the scalar
+// unit, or long before, nothing is to be waited for (in the attention kernels these states cost 0.5 to 0.8 %); a test looks at every such
+// load of the built library.
+__device__ __forceinline__ rsrc_u32x4 rsrc_settled(rsrc_u32x4 r) {
+  asm("s_nop 4" : "+s"(r));
+  return r;
+}
 // One wave-wide load of 16 bytes per lane from a buffer into LDS: lane l's bytes land at lds_addr + 16 l (lds_addr is
 // a byte address inside the workgroup's LDS, uniform over the wave).  The compiler does not see the LDS write:
 // callers order it against LDS reads with an explicit vmcnt wait and a barrier.  A load into LDS must not issue right behind the write

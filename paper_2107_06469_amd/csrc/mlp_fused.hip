@@ -145,7 +145,7 @@ struct WStream {
     k0 = 0;
     lK = uniform(FWD ? cols : rows);
     lN = uniform(FWD ? rows : cols);
-    rs = rsrc_words(P + a.w_off[live ? lu : a.u0], 0, live ? (long)lN * lK * 4 : 0);
+    rs = rsrc_settled(rsrc_words(P + a.w_off[live ? lu : a.u0], 0, live ? (long)lN * lK * 4 : 0));
     step = uniform((FWD ? 8 * lK : 4 * lN) * 4);
     place();
   }
@@ -297,7 +297,7 @@ __device__ __forceinline__ void fwd_body(const MlpFusedArgs& a, float* smem, F&&
     const int K = u == 0 ? a.d_in : a.d, N = u < a.L ? a.d : a.n_out;
     float* const xs = smem + ((u - a.u0) & 1) * RB * XS;
     float* const xn = smem + ((u - a.u0 + 1) & 1) * RB * XS;
-    load_to_lds_b32(rsrc_words(P + a.b_off[u], 0, (long)N * 4), lds_addr_of(lbias), (unsigned)n * 4u);
+    load_to_lds_b32(rsrc_settled(rsrc_words(P + a.b_off[u], 0, (long)N * 4)), lds_addr_of(lbias), (unsigned)n * 4u);
     // where the unit's outputs go: read from the table now, not between the stores at the unit's end
     const bool last = u == a.L;
     const RowStore zs(global_ptr(last ? tb->logits : tb->z[u]), a.B, last ? a.ldv : a.ldd, r0, n, N);
@@ -381,7 +381,7 @@ __device__ __forceinline__ void chain_body(const MlpFusedArgs& a, float* smem, W
     float* const dn = smem + (buf ^ 1) * RB * XS;
     // read the table now: between the stores at the unit's end a pointer read would wait for each of them
     const RowStore dzs(global_ptr(tb->dz[u - 1]), a.B, a.ldd, r0, n, Kin);
-    const rsrc_u32x4 zr = rsrc_words(tb->z[u - 1], (long)r0 * a.ldd * 4, ((long)(a.B - 1) * a.ldd + Kin) * 4);
+    const rsrc_u32x4 zr = rsrc_settled(rsrc_words(tb->z[u - 1], (long)r0 * a.ldd * 4, ((long)(a.B - 1) * a.ldd + Kin) * 4));
 #pragma unroll
     for (int r = 0; r < RB; ++r)  // z_{u-1} at the outputs this lane will hold
       load_to_lds_b32(zr, lds_addr_of(gate) + 256 * r, n < Kin ? (unsigned)(r * a.ldd + n) * 4u : 0x80000000u);

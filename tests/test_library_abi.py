@@ -416,34 +416,40 @@ def test_optimizer_state_calls_check_their_arguments():
         H.hydra_destroy(ctx)
 
 
-def _device_code(tmp_path):
-    """Disassembly of the kernels that the library was built with, a list of instructions per kernel."""
+@pytest.fixture(scope="module")
+def device_code(tmp_path_factory):
+    """Disassembly of the kernels that the library was built with: {kernel: {address: instruction}} in the order of the addresses."""
     llvm = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
     if not os.path.exists(llvm):
         pytest.skip("no llvm-objdump")
+    tmp_path = tmp_path_factory.mktemp("code")
     lib = shutil.copy(H.lib()._name, tmp_path)
     subprocess.run([llvm, "--offloading", lib], check=True, capture_output=True, cwd=tmp_path)
     kernels = {}
     for f in sorted(os.listdir(tmp_path)):
         if "amdgcn" not in f:
             continue
-        out = subprocess.run([llvm, "-d", "--no-show-raw-insn", os.path.join(tmp_path, f)], check=True, capture_output=True, text=True).stdout
+        out = subprocess.run([llvm, "-d", os.path.join(tmp_path, f)], check=True, capture_output=True, text=True).stdout
         name = None
         for ln in out.splitlines():
             label = re.match(r"[0-9a-f]+ <(\w+)>:", ln)
             if label:
                 name = label.group(1)
-                kernels[name] = []
+                kernels[name] = {}
             elif name and ln.startswith("\t"):
-                kernels[name].append(ln.split("//")[0].strip())
+                text, _, at = ln.partition("//")
+                if not at:
+                    continue
+                kernels[name][int(at.split(":")[0], 16)] = text.strip()
     return kernels
 
 
-def test_loads_into_lds_stand_a_wait_state_behind_the_write_of_their_m0(tmp_path):
+def test_loads_into_lds_stand_a_wait_state_behind_the_write_of_their_m0(device_code):
     """A scalar write of M0 and a load into LDS, which takes its address from there, must not issue back to back on gfx9: one wait state lies
     between.  The compiler sees to that for instructions of its own, not for those inside an asm block."""
     seen, bad = 0, []
-    for name, code in _device_code(tmp_path).items():
+    for name, kernel in device_code.items():
+        code = list(kernel.values())
         for before, ins in zip(code, code[1:]):
             if ins.startswith("buffer_load") and ins.split()[-1] == "lds":
                 seen += 1
@@ -452,12 +458,13 @@ def test_loads_into_lds_stand_a_wait_state_behind_the_write_of_their_m0(tmp_path
     assert seen > 0 and not bad, f"{len(bad)} of {seen}: {bad[:3]}"
 
 
-def test_state_loads_of_the_small_updates_stand_where_their_waits_count_on(tmp_path):
+def test_state_loads_of_the_small_updates_stand_where_their_waits_count_on(device_code):
     """The few-tile bf16 updates request the optimizer state behind the first stages' loads into LDS, and wait for a stage by the number of
     loads that are newer, the state's 12 (Adam) or 4 (SGD) among them: up to the first barrier a wave issues exactly those, in that order,
     and waits for all but the newer stages' and the state's."""
     seen = 0
-    for name, code in _device_code(tmp_path).items():
+    for name, kernel in device_code.items():
+        code = list(kernel.values())
         small = re.search(r"gemm_small_kernelILi(\d+)ELi(\d+)ELb0ELb0ELb1E", name)
         if not small:
             continue
@@ -470,3 +477,42 @@ def test_state_loads_of_the_small_updates_stand_where_their_waits_count_on(tmp_p
         waits = sorted(int(m.group(1)) for m in (re.search(r"vmcnt\((\d+)\)", c) for c in head if c.startswith("s_waitcnt")) if m)
         assert waits == [per_stage * (stages - 1) + 4, per_stage * (stages - 1) + 12], (name, waits)
     assert seen == 2
+
+
+def _scalar_registers(text):
+    regs = set()
+    for m in re.finditer(r"\bs\[(\d+):(\d+)\]|\bs(\d+)\b", text):
+        regs |= set(range(int(m.group(1)), int(m.group(2)) + 1)) if m.group(1) else {int(m.group(3))}
+    return regs
+
+
+def test_loads_into_lds_stand_five_wait_states_behind_the_vector_unit_s_writes_of_their_descriptor(device_code):
+    """A scalar register that a vector instruction wrote (v_readfirstlane) may be read by a memory instruction five wait states later on gfx9,
+    along every path to it.  The compiler sees to that for instructions of its own, not for those inside an asm block."""
+    seen, bad = 0, []
+    for name, kernel in device_code.items():
+        if not any(ins.endswith(" lds") for ins in kernel.values()):
+            continue
+        at = list(kernel)
+        before = {a: {p} for p, a in zip(at, at[1:]) if not kernel[p].startswith(("s_branch", "s_endpgm", "s_setpc"))}
+        for p in at:
+            if kernel[p].startswith(("s_branch", "s_cbranch")):
+                off = int(kernel[p].split()[1])
+                before.setdefault(p + 4 + 4 * (off - 65536 if off > 32767 else off), set()).add(p)
+        for a in at:
+            ins = kernel[a]
+            if not (ins.startswith("buffer_load") and ins.split()[-1] == "lds"):
+                continue
+            seen += 1
+            use, paths, done = _scalar_registers(ins), [(p, 0) for p in before.get(a, ())], {}
+            while paths:
+                p, waited = paths.pop()
+                if waited >= 5 or done.get(p, 5) <= waited:
+                    continue
+                done[p] = waited
+                op, _, rest = kernel[p].partition(" ")
+                if op.startswith("v_") and _scalar_registers(rest.split(",")[0]) & use:
+                    bad.append((name, waited, kernel[p], ins))
+                waited += int(rest, 0) + 1 if op == "s_nop" else 1
+                paths += [(q, waited) for q in before.get(p, ())]
+    assert seen > 0 and not bad, f"{len(bad)} of {seen}: {bad[:3]}"
