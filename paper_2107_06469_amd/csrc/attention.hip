@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "launch_rules.h"
 #include "lds_dma.h"
 #include "wave_math.h"
 
@@ -67,30 +68,44 @@ __device__ __forceinline__ f32x16 mfma(const uint4& a, const uint4& b, f32x16 c)
 // What a workgroup does before its first tile has landed is a third of its life at 8 tiles, so that part is kept short in all kernels:
 // three multiplications instead of four integer divisions, every pointer read at once, rows read without branches (rows_from), and
 // nothing that waits for one load before the next is issued.  us, before | now: forward 4 x [32 x 12 heads, 512, 64] 172 | 161,
-// 8 x 32 heads, 2048, 128, causal 411 | 385; backward 490 | 453, 1239 | 1187, 4 x [8 x 16, 384, 64] 102 | 96.6.
-struct AttnGrid { unsigned n_blk, n_bh, n_h, total, per_xcd, r_blk, r_bh, r_h; };  // counts of items, reciprocals (attn_grid)
-struct AttnItem { int blk, bh, gi, b, h; };
+// 8 x 32 heads, 2048, 128, causal 411 | 385; backward 490 | 453, 1239 | 1187, 4 x [8 x 16, 384, 64] 102 | 96.6.  Then descriptors of a tile by 32-bit
+// scalar arithmetic from its first row (64-bit from the matrix's before, which took all scalar registers and spilled some on
+// every tile), masks by one comparison, 16-byte stores: forward 160 | 145 and 34.3 | 30.8, backward 451 | 430 and 94 | 88.
+// Under a causal mask the row blocks of a head have one to n_blk parts of work.  Where attn_pairs says so (launch_rules.h) a workgroup takes
+// blocks i and `last` - i one after the other, the longer one first, and asks for the first tile and the fragments of the
+// second under the last tile of the first: equal workgroups, half the launch latencies, K and V of a head from one L2.  us, one block | two:
+// forward 8 x 32 heads, 2048, 128 362 | 339, backward 1110 | 1036; 2 x [4 x 16, 1024, 128] 66 | 49 and 198 | 156; 16 heads, 8 x 1024, 64 43 | 33
+// and 113 | 94.  (Chains of three or four blocks and one resident workgroup for all of its blocks: level under a mask; without one 2 to 8 %
+// behind single blocks, whose loads do not all come at once.)
+struct AttnGrid { unsigned n_blk, n_bh, n_h, total, per_xcd, r_blk, r_bh, r_h; int last; };  // counts of items, reciprocals (attn_grid); last: -1 without pairs
+struct AttnItem { int blk, then, bh, gi, b, h; };
 // n / d for the divisor whose reciprocal the host worked out, floor(2^32 / d) (2^32 - 1 for d = 1): one too small at most
 __device__ __forceinline__ unsigned div_by(unsigned n, unsigned d, unsigned rcp) {
   const unsigned q = __umulhi(n, rcp);
   return n - q * d >= d ? q + 1 : q;
 }
+// then: the second block of a pair, -1 where there is none.  HIGH_FIRST: the higher block is the longer one (more keys to a query).
+template <bool HIGH_FIRST>
 __device__ __forceinline__ bool attn_item(unsigned wg, const AttnGrid& gr, AttnItem& it) {
   // all of the grid's fields by one scalar load, not those behind the test by another
-  asm volatile("" ::"s"(gr.total), "s"(gr.per_xcd), "s"(gr.n_blk), "s"(gr.n_bh), "s"(gr.n_h), "s"(gr.r_blk), "s"(gr.r_bh), "s"(gr.r_h));
+  asm volatile("" ::"s"(gr.total), "s"(gr.per_xcd), "s"(gr.n_blk), "s"(gr.n_bh), "s"(gr.n_h), "s"(gr.r_blk), "s"(gr.r_bh), "s"(gr.r_h), "s"(gr.last));
   const unsigned id = (wg & 7) * gr.per_xcd + (wg >> 3);
   if (id >= gr.total || (wg >> 3) >= gr.per_xcd) return false;
   const unsigned u = div_by(id, gr.n_blk, gr.r_blk), gi = div_by(u, gr.n_bh, gr.r_bh), bh = u - gi * gr.n_bh;
   const unsigned b = div_by(bh, gr.n_h, gr.r_h);
-  it = {(int)(id - u * gr.n_blk), (int)bh, (int)gi, (int)b, (int)(bh - b * gr.n_h)};
+  const int low = (int)(id - u * gr.n_blk), high = gr.last - low;
+  const bool pair = gr.last >= 0;
+  it = {pair && HIGH_FIRST ? high : low, !pair ? -1 : HIGH_FIRST ? low : high, (int)bh, (int)gi, (int)b, (int)(bh - b * gr.n_h)};
   return true;
 }
-// Rows row0.. of a matrix for loads of the lanes' own: rows at or past nrows read as zero, without a branch around the load
-// (between branches every load fetched its pointer anew and waited for it).  src: row 0, which starts col elements into a row of ld.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_from(const bf16_t* src, int ld, int col, int row0, int nrows) {
-  long left = ((long)(nrows - row0) * ld - col) * 2;
-  left = left < 0 ? 0 : left > 0x7fffffffL ? 0x7fffffffL : left;
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(src) + (left ? (long)row0 * ld : 0), 0, (int)left, 0x00020000);
+// Bytes from the start of a head's columns in one row to the end of those columns in the last of `rows` rows (none: 0): what a
+// descriptor that begins there spans.  Rows behind it read as zero and are not written, without a branch around the access
+// (between branches every load fetched its pointer anew and waited for it).
+template <int DH>
+__device__ __forceinline__ int span_of(int rows, int ld) { return rows > 0 ? ((rows - 1) * ld + DH) * 2 : 0; }
+template <int DH>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_at(const bf16_t* first, int rows, int ld) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(first), 0, span_of<DH>(min(rows, 32), ld), 0x00020000);
 }
 __device__ __forceinline__ uint4 row_chunk(__amdgpu_buffer_rsrc_t rs, unsigned voff) {
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, 0, 0));
@@ -108,12 +123,12 @@ __device__ __forceinline__ int swz(int row) {
   return 4 * ((row >> 1) & 1) + ((row >> 2) & 3);
 }
 
-// A tile's way into LDS: load i of wave w fills slots [(4 i + w) 64, + 64), lane l slot + l, with the chunk that belongs there.
-// Rows at or past nrows read as zero (the descriptor ends with row nrows - 1; it is made per tile, so that the lane's
+// A tile's way into LDS: load i of wave w fills slots [(4 i + w) 64, + 64), lane l slot l, with the chunk that belongs there.
+// Rows past the last one read as zero (the descriptor ends with it; it is made per tile, so that the lane's
 // offset is the same for every tile).  ONE: the rows of load i are those of load 0 plus 16 or 32 i, which have the same XOR
 // terms, so one offset per lane serves every load and the descriptor, in scalar registers, moves on: for the kernel
 // that has no vector register to spare (the others would only spill scalar registers for it).
-template <int DH, bool ONE = false>
+template <int DH, bool ONE = false, bool SETTLE = false>
 struct TileDma {
   static constexpr int NCH = DH / 8, N = 64 * NCH / 256, STEP = 256 / NCH;  // loads per wave, rows between them
   unsigned voff[ONE ? 1 : N];
@@ -124,22 +139,27 @@ struct TileDma {
       voff[i] = ((unsigned)row * (unsigned)ld + (unsigned)((sl % NCH) ^ swz<DH>(row)) * 8u) * 2u;
     }
   }
-  // src: row 0 of the sequence at the head's columns, which start col elements into a row of ld
-  __device__ __forceinline__ void issue(const bf16_t* src, int ld, int col, int row0, int nrows, unsigned lds_addr, int wave) const {
-    const long total = ((long)nrows * ld - col) * 2;
-    const rsrc_u32x4 rs = rsrc_words(src, (long)row0 * ld * 2, total);
+  // first: the tile's first row at the head's columns; rows: how many there are from it on (at least one)
+  __device__ __forceinline__ void issue(const bf16_t* first, int rows, int ld, unsigned lds_addr, int wave) const {
 #pragma unroll
-    for (int i = 0; i < N; ++i)
-      load_to_lds_b128(ONE ? rsrc_words(src, (long)(row0 + STEP * i) * ld * 2, total) : rs,
-                       lds_addr + (unsigned)((4 * i + wave) * 64 * 16), voff[ONE ? 0 : i]);
+    for (int i = 0; i < N; ++i) {
+      const int skip = ONE ? STEP * i : 0;
+      const uint64_t p = (uint64_t)(uintptr_t)(first + (size_t)skip * ld);
+      rsrc_u32x4 rs = {(unsigned)p, (unsigned)(p >> 32) & 0xffffu, (unsigned)span_of<DH>(min(rows, 64) - skip, ld), 0x00020000u};
+      if constexpr (SETTLE) {
+        rs.x = __builtin_amdgcn_readfirstlane(rs.x), rs.y = __builtin_amdgcn_readfirstlane(rs.y), rs.z = __builtin_amdgcn_readfirstlane(rs.z);
+        rs = rsrc_settled(rs);
+      }
+      load_to_lds_b128(rs, lds_addr + (unsigned)((4 * i + wave) * 64 * 16), voff[ONE ? 0 : i]);
+    }
   }
 };
-// every load of this wave has landed, then every wave's.  (A wait written in inline asm the compiler does not count: it waited
-// again, inside the loop, for the fragments loaded before it, and with them for the next tile's loads.)
-__device__ __forceinline__ void tile_landed() {
+// Every load of this wave has landed.  (A wait written in inline asm the compiler does not count: it waited again, inside the loop, for
+// the fragments loaded before it, and with them for the next tile's loads.  For the same reason it stands at the end of every tile,
+// on all paths, and ahead of the stores of an item that ends there: their way to memory is under the next item's first tile.)
+__device__ __forceinline__ void loads_landed() {
   __builtin_amdgcn_s_waitcnt(0xf70);  // vmcnt(0)
   asm volatile("" ::: "memory");
-  __syncthreads();
 }
 __device__ __forceinline__ unsigned lds_byte_addr(const void* p) {
   return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)reinterpret_cast<const char*>(p);
@@ -204,11 +224,31 @@ __device__ __forceinline__ uint4 pack_half(const f32x16& p, int x) {
                     pack2(p[8 * x + 6], p[8 * x + 7]));
 }
 
+// An accumulator's 32 columns of 32 rows (lane l: row l%32, columns 8q + 4(l/32) + e) as bf16 to the rows that a descriptor
+// begins with; off: the lane's row and the block's first column.  The two lanes of a row trade halves so that a lane stores 8 columns
+// at once: two stores of 16 bytes (four of 8 before).  Rows past the descriptor's end are dropped.
+__device__ __forceinline__ void store_block(const f32x16& v, float f, __amdgpu_buffer_rsrc_t rs, unsigned off, int g) {
+  typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+#pragma unroll
+  for (int q = 0; q < 4; q += 2) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(pack2(v[4 * q] * f, v[4 * q + 1] * f), pack2(v[4 * q + 4] * f, v[4 * q + 5] * f), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(pack2(v[4 * q + 2] * f, v[4 * q + 3] * f), pack2(v[4 * q + 6] * f, v[4 * q + 7] * f), false, false);
+    const u32x4 w = {lo[0], hi[0], lo[1], hi[1]};
+    __builtin_amdgcn_raw_buffer_store_b128(w, rs, off + (unsigned)(8 * q + 8 * g) * 2u, 0, 0);
+  }
+}
+// One float of each of a wave's 32 rows, from the lower half of the wave
+__device__ __forceinline__ void store_stat(float v, float* first, int rows, int li, int g) {
+  const uint64_t p = (uint64_t)(uintptr_t)first;
+  const uint64_t u = (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((unsigned)(p >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((unsigned)p);
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((float*)(uintptr_t)u, 0, __builtin_amdgcn_readfirstlane(max(min(rows, 32), 0) * 4), 0x00020000);
+  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rs, g ? 0x7ffffff0 : li * 4, 0, 0);
+}
+
 // ---- forward ---------------------------------------------------------------------------------------------
 // Bound by the VALU: a score costs a multiply-add, an exponential (four times a plain instruction's cycles), an addition, half a
-// maximum, half a conversion and (where a maximum grew) a multiplication, 8 issue slots for 1.3 of MFMA at DH = 64.  128
-// registers (four waves per SIMD; 153 when tiles passed through registers); us before | now: 4 x [32 x 12 heads, 512, 64]
-// 179 | 172, 8 x 32 heads, 2048, 128, causal 410 | 405, 2 x [4 x 16, 1024, 128] 90 | 85.
+// maximum, half a conversion and (where a maximum grew) a multiplication, 8 issue slots for 1.3 of MFMA at DH = 64.  120
+// registers (four waves per SIMD; 153 when tiles passed through registers).
 template <int DH>
 __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const AttnArgs a, const AttnGrid gr) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
@@ -219,43 +259,54 @@ __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const A
   constexpr int BUF = 2 * 64 * NCH;  // chunks per buffer
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, g = lane >> 5;
   AttnItem item;
-  if (!attn_item(blockIdx.x, gr, item)) return;
-  const int gi = item.gi, bh = item.bh, b = item.b, h = item.h, blk = item.blk;
-  const int d = a.H * DH;
-  const bf16_t* base = a.qkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
-  TileDma<DH> dma;
-  dma.init(a.ld_qkv, wave, lane);
-  const unsigned lds0 = lds_byte_addr(lds);
-  auto fetch = [&](int t, unsigned buf) {
-    dma.issue(base + d, a.ld_qkv, d + h * DH, t * 64, a.S, lds0 + buf, wave);
-    dma.issue(base + 2 * d, a.ld_qkv, 2 * d + h * DH, t * 64, a.S, lds0 + buf + 64 * NCH * 16, wave);
-  };
-  fetch(0, 0);
-  const int iq = blk * 128 + wave * 32 + li;  // this lane's query
-  uint4 qf[NK];
-  const __amdgpu_buffer_rsrc_t q_rows = rows_from(base, a.ld_qkv, h * DH, blk * 128 + wave * 32, a.S);
-#pragma unroll
-  for (int kk = 0; kk < NK; ++kk) qf[kk] = row_chunk(q_rows, (unsigned)li * (unsigned)a.ld_qkv * 2u + 32u * kk + 16u * g);
-  f32x16 oacc[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) oacc[c][r] = 0.f;
-  float m_run = NEG_BIG, l_run = 0.f;
+  if (!attn_item<true>(blockIdx.x, gr, item)) return;
+  const int d = a.H * DH, ld = a.ld_qkv;
   const float sc = a.scale * LOG2E;
-  const int q_hi = min(a.S, blk * 128 + 128) - 1;          // last query of the workgroup
-  const int n_tiles = a.causal ? (q_hi / 64 + 1) : (a.S + 63) / 64;
+  TileDma<DH> dma;
+  dma.init(ld, wave, lane);
+  const unsigned lds0 = lds_byte_addr(lds), q_off = (unsigned)li * (unsigned)ld * 2u + 16u * g;
+  auto fetch = [&](const bf16_t* k, int rows, unsigned buf) {  // k: the tile's first key
+    dma.issue(k, rows, ld, lds0 + buf, wave);
+    dma.issue(k + d, rows, ld, lds0 + buf + 64 * NCH * 16, wave);
+  };
+  const bf16_t* const base = a.qkv[item.gi] + (size_t)item.b * a.S * ld + item.h * DH;
+  fetch(base + d, a.S, 0);
+  uint4 qf[NK];
+  auto load_q = [&](int blk) {
+    const int row0 = blk * 128 + wave * 32;
+    const __amdgpu_buffer_rsrc_t q_rows = rows_at<DH>(base + (size_t)row0 * ld, a.S - row0, ld);
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) qf[kk] = row_chunk(q_rows, q_off + 32u * kk);
+    asm volatile("" ::: "memory");
+  };
+  load_q(item.blk);
   const uint4* kr[NK];   // K rows l%32, chunk 2kk + g
   ColsBase vc[NC];       // V columns c*32.., rows from 0
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) kr[kk] = rows_base<DH>(tK, li, 2 * kk + g);
 #pragma unroll
   for (int c = 0; c < NC; ++c) vc[c] = cols_base<DH>(tV, c * 32, lane);
-  auto tile = [&](int t, auto buf_) {
+  f32x16 oacc[NC];
+  float m_run, l_run;
+  int t = 0, n_tiles;
+  const bf16_t* ktile = base + d;
+  auto begin = [&] {
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[c][r] = 0.f;
+    m_run = NEG_BIG, l_run = 0.f, t = 0;
+    n_tiles = (a.causal ? min(a.S, item.blk * 128 + 128) + 63 : a.S + 63) / 64;
+  };
+  begin();
+  loads_landed();
+  auto tile = [&](auto buf_) {
     constexpr int B = decltype(buf_)::value * BUF;  // chunks to the tile's buffer
-    const int j0 = t * 64;
-    tile_landed();
-    if (t + 1 < n_tiles) fetch(t + 1, (unsigned)((BUF - B) * 16));
+    const int j0 = t * 64, row0 = item.blk * 128 + wave * 32, iq = row0 + li;  // this lane's query
+    const bool last = t + 1 == n_tiles, more = !last || item.then >= 0;
+    __syncthreads();
+    ktile = last ? base + d : ktile + (size_t)64 * ld;
+    if (more) fetch(ktile, last ? a.S : a.S - j0 - 64, (unsigned)((BUF - B) * 16));
     f32x16 s[2];
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
@@ -264,18 +315,17 @@ __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const A
 #pragma unroll
       for (int kk = 0; kk < NK; ++kk) s[sub] = mfma(kr[kk][B + sub * 32 * NCH], qf[kk], s[sub]);
     }
+    if (last && more) load_q(item.then);
     // Masking is needed only in tiles that reach past the sequence end or, with a causal mask, past the
     // wave's first query; the scale is folded into the exponent's multiply-add.
-    const bool edge = j0 + 64 > a.S || (a.causal && j0 + 63 > blk * 128 + wave * 32);
+    const bool edge = j0 + 64 > a.S || (a.causal && j0 + 63 > row0);
     float mx = NEG_BIG;
     if (edge) {
+      const int keys = (a.causal ? min(a.S, iq + 1) : a.S) - j0 - 4 * g;  // keys the query sees, from the lane's first on
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = j0 + sub * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-          if (j >= a.S || (a.causal && j > iq)) s[sub][r] = NEG_BIG;
-        }
+        for (int r = 0; r < 16; ++r) s[sub][r] = sub * 32 + 8 * (r >> 2) + (r & 3) < keys ? s[sub][r] : NEG_BIG;
     }
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub)
@@ -315,23 +365,19 @@ __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const A
 #pragma unroll
         for (int c = 0; c < NC; ++c) oacc[c] = mfma(read_cols_at<DH>(vc[c], (unsigned)((B + (sub * 32 + 16 * x) * NCH) * 16)), pf, oacc[c]);
       }
-  };
-  for (int t = 0; t < n_tiles; t += 2) {
-    tile(t, std::integral_constant<int, 0>());
-    if (t + 1 < n_tiles) tile(t + 1, std::integral_constant<int, 1>());
-  }
-  if (iq < a.S) {
+    loads_landed();
+    ++t;
+    if (!last) return true;
     const float inv = 1.f / l_run;
-    bf16_t* o = a.o[gi] + ((size_t)b * a.S + iq) * a.ld_o + h * DH;
+    const __amdgpu_buffer_rsrc_t o_rows = rows_at<DH>(a.o[item.gi] + ((size_t)item.b * a.S + row0) * a.ld_o + item.h * DH, a.S - row0, a.ld_o);
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int col = c * 32 + 8 * q + 4 * g;
-        *reinterpret_cast<uint2*>(o + col) = make_uint2(pack2(oacc[c][4 * q] * inv, oacc[c][4 * q + 1] * inv),
-                                                        pack2(oacc[c][4 * q + 2] * inv, oacc[c][4 * q + 3] * inv));
-      }
-    if (g == 0) a.lse[gi][(size_t)bh * a.S + iq] = (m_run + log2f(l_run)) * LN2;
+    for (int c = 0; c < NC; ++c) store_block(oacc[c], inv, o_rows, (unsigned)li * (unsigned)a.ld_o * 2u + c * 64u, g);
+    store_stat((m_run + log2f(l_run)) * LN2, a.lse[item.gi] + (size_t)item.bh * a.S + row0, a.S - row0, li, g);
+    item.blk = item.then, item.then = -1;
+    begin();
+    return more;
+  };
+  while (tile(std::integral_constant<int, 0>()) && tile(std::integral_constant<int, 1>())) {
   }
 }
 
@@ -352,71 +398,82 @@ __device__ __forceinline__ float delta_part(const uint4 (&dof)[NK], const uint4 
   return delta;
 }
 
-template <int DH>
+template <int DH, bool ONE_ITEM>
 __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, const AttnGrid& gr, int wg) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
   extern __shared__ __attribute__((aligned(256))) uint4 lds[];
   // two buffers of K [64][NCH], V [64][NCH]
   uint4* tK = lds;
-  uint4* tV = lds + 64 * NCH;
   constexpr int BUF = 2 * 64 * NCH;  // chunks per buffer
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, g = lane >> 5;
   AttnItem item;
-  if (!attn_item(wg, gr, item)) return;
-  const int gi = item.gi, bh = item.bh, b = item.b, h = item.h, blk = item.blk;
-  const int d = a.H * DH;
-  // every pointer at once, so that their loads are one wait
-  const bf16_t* const base = a.qkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
-  const bf16_t* const dobase = a.dout[gi] + (size_t)b * a.S * a.ld_o + h * DH;
-  const bf16_t* const obase = a.o[gi] + (size_t)b * a.S * a.ld_o + h * DH;
-  const float* const lse = a.lse[gi] + (size_t)bh * a.S;
-  float* const delta_out = a.delta[gi] + (size_t)bh * a.S;
-  bf16_t* const dqbase = a.dqkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
-  TileDma<DH> dma;
-  dma.init(a.ld_qkv, wave, lane);
-  const unsigned lds0 = lds_byte_addr(lds);
-  auto fetch = [&](int t, unsigned buf) {
-    dma.issue(base + d, a.ld_qkv, d + h * DH, t * 64, a.S, lds0 + buf, wave);
-    dma.issue(base + 2 * d, a.ld_qkv, 2 * d + h * DH, t * 64, a.S, lds0 + buf + 64 * NCH * 16, wave);
-  };
-  fetch(0, 0);
-  const int iq = blk * 128 + wave * 32 + li;
-  uint4 qf[NK], dof[NK], of[NK];
-  const int row0 = blk * 128 + wave * 32;
-  const __amdgpu_buffer_rsrc_t q_rows = rows_from(base, a.ld_qkv, h * DH, row0, a.S);
-  const __amdgpu_buffer_rsrc_t do_rows = rows_from(dobase, a.ld_o, h * DH, row0, a.S);
-  const bf16_t* const orow = obase + (size_t)min(iq, a.S - 1) * a.ld_o + 8 * g;  // past the end: a row whose products nobody stores
-#pragma unroll
-  for (int kk = 0; kk < NK; ++kk) {
-    qf[kk] = row_chunk(q_rows, (unsigned)li * (unsigned)a.ld_qkv * 2u + 32u * kk + 16u * g);
-    dof[kk] = row_chunk(do_rows, (unsigned)li * (unsigned)a.ld_o * 2u + 32u * kk + 16u * g);
-    of[kk] = *reinterpret_cast<const uint4*>(orow + 16 * kk);
-  }
-  const __amdgpu_buffer_rsrc_t lse_rows =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(lse), 0, __builtin_amdgcn_readfirstlane(min(a.S, 0x1fffffff) * 4), 0x00020000);
-  const float lse2 = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(lse_rows, iq * 4, 0, 0)) * LOG2E;
-  const float2 dh = wave_swap32(delta_part<NK>(dof, of));
-  const float delta = dh.x + dh.y;
-  f32x16 acc[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
+  if (!attn_item<true>(wg, gr, item)) return;
+  const int d = a.H * DH, ld = a.ld_qkv;
   const float sc = a.scale * LOG2E;
-  const int q_hi = min(a.S, blk * 128 + 128) - 1;
-  const int n_tiles = a.causal ? (q_hi / 64 + 1) : (a.S + 63) / 64;
+  TileDma<DH, false, ONE_ITEM> dma;
+  dma.init(ld, wave, lane);
+  const unsigned lds0 = lds_byte_addr(lds);
+  // every pointer at once, so that their loads are one wait
+  const size_t seq = (size_t)item.b * a.S;
+  const bf16_t* const base = a.qkv[item.gi] + seq * ld + item.h * DH;
+  const bf16_t* const dobase = a.dout[item.gi] + seq * a.ld_o + item.h * DH;
+  const bf16_t* const obase = a.o[item.gi] + seq * a.ld_o + item.h * DH;
+  const float* const lse = a.lse[item.gi] + (size_t)item.bh * a.S;
+  float* const delta_out = a.delta[item.gi] + (size_t)item.bh * a.S;
+  bf16_t* const dqbase = a.dqkv[item.gi] + seq * ld + item.h * DH;
+  auto fetch = [&](const bf16_t* k, int rows, unsigned buf) {  // k: the tile's first key
+    dma.issue(k, rows, ld, lds0 + buf, wave);
+    dma.issue(k + d, rows, ld, lds0 + buf + 64 * NCH * 16, wave);
+  };
+  uint4 qf[NK], dof[NK], of[NK];
+  float lse_in;
+  auto load_rows = [&](int blk) {
+    const int row0 = blk * 128 + wave * 32, left = a.S - row0;
+    const __amdgpu_buffer_rsrc_t q_rows = rows_at<DH>(base + (size_t)row0 * ld, left, ld);
+    const __amdgpu_buffer_rsrc_t do_rows = rows_at<DH>(dobase + (size_t)row0 * a.ld_o, left, a.ld_o);
+    const bf16_t* const orow = obase + (size_t)min(row0 + li, a.S - 1) * a.ld_o + 8 * g;  // past the end: a row whose products nobody stores
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) {
+      qf[kk] = row_chunk(q_rows, (unsigned)li * (unsigned)ld * 2u + 32u * kk + 16u * g);
+      dof[kk] = row_chunk(do_rows, (unsigned)li * (unsigned)a.ld_o * 2u + 32u * kk + 16u * g);
+      of[kk] = *reinterpret_cast<const uint4*>(orow + 16 * kk);
+    }
+    const __amdgpu_buffer_rsrc_t lse_rows =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(lse + row0), 0, max(min(left, 32), 0) * 4, 0x00020000);
+    lse_in = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(lse_rows, li * 4, 0, 0));
+    asm volatile("" ::: "memory");
+  };
+  fetch(base + d, a.S, 0);
+  load_rows(item.blk);
   const uint4* kr[NK];   // K rows l%32, chunk 2kk + g; V is 64 rows further on
   ColsBase kc_[NC];      // K columns c*32.., rows from 0
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) kr[kk] = rows_base<DH>(tK, li, 2 * kk + g);
 #pragma unroll
   for (int c = 0; c < NC; ++c) kc_[c] = cols_base<DH>(tK, c * 32, lane);
-  auto tile = [&](int t, auto buf_) {
+  f32x16 acc[NC];
+  float lse2, delta;
+  int t = 0, n_tiles = 0;
+  const bf16_t* ktile = base + d;
+  loads_landed();
+  auto tile = [&](auto buf_) {
     constexpr int B = decltype(buf_)::value * BUF;  // chunks to the tile's buffer
-    const int j0 = t * 64;
-    tile_landed();
-    if (t + 1 < n_tiles) fetch(t + 1, (unsigned)((BUF - B) * 16));
-    const bool edge = j0 + 64 > a.S || (a.causal && j0 + 63 > blk * 128 + wave * 32);
+    __syncthreads();
+    if (t == 0) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
+      n_tiles = (a.causal ? min(a.S, item.blk * 128 + 128) + 63 : a.S + 63) / 64;
+      const float2 dh = wave_swap32(delta_part<NK>(dof, of));
+      delta = dh.x + dh.y;
+      lse2 = lse_in * LOG2E;
+    }
+    const int j0 = t * 64, row0 = item.blk * 128 + wave * 32, iq = row0 + li;
+    const bool last = t + 1 == n_tiles, more = !last || (!ONE_ITEM && item.then >= 0);
+    ktile = last ? base + d : ktile + (size_t)64 * ld;
+    if (more) fetch(ktile, last ? a.S : a.S - j0 - 64, (unsigned)((BUF - B) * 16));
+    const bool edge = j0 + 64 > a.S || (a.causal && j0 + 63 > row0);
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
       f32x16 s, dp;
@@ -428,12 +485,11 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, const AttnGrid& gr
         dp = mfma(kr[kk][B + (64 + sub * 32) * NCH], dof[kk], dp);
       }
       if (edge) {
+        const int keys = (a.causal ? min(a.S, iq + 1) : a.S) - j0 - 4 * g;  // keys the query sees, from the lane's first on
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = j0 + sub * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-          if (j >= a.S || (a.causal && j > iq)) s[r] = NEG_BIG;
-        }
+        for (int r = 0; r < 16; ++r) s[r] = sub * 32 + 8 * (r >> 2) + (r & 3) < keys ? s[r] : NEG_BIG;
       }
+      if (sub == 1 && last && more) load_rows(item.then);
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[r] = fast_exp2(fmaf(s[r], sc, -lse2)) * (dp[r] - delta);
 #pragma unroll
@@ -443,34 +499,35 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, const AttnGrid& gr
         for (int c = 0; c < NC; ++c) acc[c] = mfma(read_cols_at<DH>(kc_[c], (unsigned)((B + (sub * 32 + 16 * x) * NCH) * 16)), df, acc[c]);
       }
     }
+    loads_landed();
+    ++t;
+    if (!last) return true;
+    const __amdgpu_buffer_rsrc_t dq_rows = rows_at<DH>(dqbase + (size_t)row0 * ld, a.S - row0, ld);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) store_block(acc[c], a.scale, dq_rows, (unsigned)li * (unsigned)ld * 2u + c * 64u, g);
+    store_stat(delta, delta_out + row0, a.S - row0, li, g);
+    item.blk = item.then, item.then = -1;
+    t = 0;
+    return more;
   };
-  for (int t = 0; t < n_tiles; t += 2) {
-    tile(t, std::integral_constant<int, 0>());
-    if (t + 1 < n_tiles) tile(t + 1, std::integral_constant<int, 1>());
-  }
-  if (iq < a.S) {
-    if (g == 0) delta_out[iq] = delta;
-    bf16_t* o = dqbase + (size_t)iq * a.ld_qkv;
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int col = c * 32 + 8 * q + 4 * g;
-        *reinterpret_cast<uint2*>(o + col) =
-            make_uint2(pack2(acc[c][4 * q] * a.scale, acc[c][4 * q + 1] * a.scale),
-                       pack2(acc[c][4 * q + 2] * a.scale, acc[c][4 * q + 3] * a.scale));
-      }
+  while (tile(std::integral_constant<int, 0>()) && tile(std::integral_constant<int, 1>())) {
   }
 }
 
 // ---- backward, dk and dv -----------------------------------------------------------------------------------
-// Two waves per SIMD at DH = 128 (256 registers and 28 bytes of scratch; 376, one wave, when tiles passed through registers and the
+// Two waves per SIMD at DH = 128 (256 registers, no scratch: values that a tile needs once are worked out again from own_lane; 376, one wave, when tiles passed through registers and the
 // accumulators moved between the two register files on every tile), three at DH = 64 (168; 200 before).  Together with
 // the dq kernel, us before | now: 8 x 32 heads, 2048, 128, causal 1645 | 1250, 2 x [4 x 16, 1024, 128] 360 | 269,
 // 4 x [32 x 12 heads, 512, 64] 527 | 480.  Held to one wave per SIMD at DH = 128: 1440; with its 16 LDS bases kept instead of
 // bases128 (64 bytes of scratch, K and V fragments among them): 1362.
 // OWN: the kernel works out delta itself instead of reading what the dq kernel left.
-template <int DH, bool OWN>
+// The lane's number, worked out where it is used: kept in a register, or in scratch, it costs more than two instructions a tile
+__device__ __forceinline__ unsigned own_lane() {
+  unsigned l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
+template <int DH, bool OWN, bool ONE_ITEM = OWN>
 __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, const AttnGrid& gr, int wg) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
   extern __shared__ __attribute__((aligned(256))) uint4 lds[];
@@ -480,32 +537,30 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, const AttnGrid& g
   float* const st = reinterpret_cast<float*>(lds + 2 * BUF);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, g = lane >> 5;
   AttnItem item;
-  if (!attn_item(wg, gr, item)) return;
-  const int gi = item.gi, bh = item.bh, b = item.b, h = item.h, blk = item.blk;
-  const int d = a.H * DH;
-  const bf16_t* const base = a.qkv[gi] + (size_t)b * a.S * a.ld_qkv + h * DH;
-  const bf16_t* const dobase = a.dout[gi] + (size_t)b * a.S * a.ld_o + h * DH;
-  const bf16_t* const obase = OWN ? a.o[gi] + (size_t)b * a.S * a.ld_o + h * DH : nullptr;
-  const float* const lse = a.lse[gi] + (size_t)bh * a.S;
-  float* const delta = a.delta[gi] + (size_t)bh * a.S;
-  bf16_t* const dkbase = a.dqkv[gi] + (size_t)b * a.S * a.ld_qkv + d + h * DH;
-  const int t0 = a.causal ? (blk * 128) / 64 : 0;  // queries before the workgroup's first key see none of its keys
-  const int n_tiles = (a.S + 63) / 64;
-  TileDma<DH, DH == 128> dma_q, dma_o;
-  dma_q.init(a.ld_qkv, wave, lane);
+  if (!attn_item<false>(wg, gr, item)) return;
+  const int d = a.H * DH, ld = a.ld_qkv, n_tiles = (a.S + 63) / 64;
+  const float sc = a.scale * LOG2E;
+  TileDma<DH, DH == 128, ONE_ITEM> dma_q, dma_o;
+  dma_q.init(ld, wave, lane);
   dma_o.init(a.ld_o, wave, lane);
-  const unsigned lds0 = lds_byte_addr(lds);
+  const unsigned lds0 = lds_byte_addr(lds), row_off = (unsigned)li * (unsigned)ld * 2u + 16u * g;
+  const size_t seq = (size_t)item.b * a.S;
+  const bf16_t* const base = a.qkv[item.gi] + seq * ld + item.h * DH;
+  const bf16_t* const dobase = a.dout[item.gi] + seq * a.ld_o + item.h * DH;
+  const bf16_t* const obase = OWN ? a.o[item.gi] + seq * a.ld_o + item.h * DH : nullptr;
+  const float* const stat = (wave == 0 ? a.lse[item.gi] : a.delta[item.gi]) + (size_t)item.bh * a.S;  // wave 1 reads delta
+  bf16_t* const dkbase = a.dqkv[item.gi] + seq * ld + d + item.h * DH;
+  auto first_tile = [&](int blk) { return a.causal ? blk * 2 : 0; };  // queries before the workgroup's first key see none of its keys
   float pst = 0.f;
   uint4 own_do[NK], own_o[NK];
   auto fetch = [&](int t, unsigned buf) {
-    dma_q.issue(base, a.ld_qkv, h * DH, t * 64, a.S, lds0 + buf, wave);
-    dma_o.issue(dobase, a.ld_o, h * DH, t * 64, a.S, lds0 + buf + 64 * NCH * 16, wave);
-    // threads 0..63: lse*log2e, 64..127: delta of query 64 t + tid%64
-    if (wave < (OWN ? 1 : 2)) {
-      float* const p = (wave == 0 ? const_cast<float*>(lse) : delta) + t * 64;
-      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(p, 0, min(a.S - t * 64, 64) * 4, 0x00020000);
-      pst = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, 0, 0));  // zero past the last query
-    }
+    const int left = a.S - t * 64;
+    // threads 0..63: lse*log2e, 64..127: delta of query 64 t + tid%64 (zero past the last query); the other waves read nothing
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(stat + t * 64), 0, wave < (OWN ? 1 : 2) ? min(left, 64) * 4 : 0, 0x00020000);
+    pst = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, own_lane() * 4, 0, 0));
+    dma_q.issue(base + (size_t)t * 64 * ld, left, ld, lds0 + buf, wave);
+    dma_o.issue(dobase + (size_t)t * 64 * a.ld_o, left, a.ld_o, lds0 + buf + 64 * NCH * 16, wave);
     if (OWN && wave >= 2) {  // waves 2 and 3: 32 queries each, two lanes to a query as in the dq kernel
       const int i = t * 64 + (wave - 2) * 32 + li;
 #pragma unroll
@@ -520,44 +575,52 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, const AttnGrid& g
     }
   };
   auto put_stats = [&](float* stb) {
-    if (wave < (OWN ? 1 : 2)) stb[tid] = wave == 0 ? pst * LOG2E : pst;
+    if (wave < (OWN ? 1 : 2)) stb[wave * 64 + own_lane()] = wave == 0 ? pst * LOG2E : pst;
     if (OWN && wave >= 2) {
       const float2 dh = wave_swap32(delta_part<NK>(own_do, own_o));
       if (g == 0) stb[64 + (wave - 2) * 32 + li] = dh.x + dh.y;
     }
   };
-  if (t0 < n_tiles) fetch(t0, 0);
-  const int jk = blk * 128 + wave * 32 + li;  // this lane's key
   uint4 kf[NK], vf[NK];
-  const __amdgpu_buffer_rsrc_t k_rows = rows_from(base + d, a.ld_qkv, d + h * DH, blk * 128 + wave * 32, a.S);
-  const __amdgpu_buffer_rsrc_t v_rows = rows_from(base + 2 * d, a.ld_qkv, 2 * d + h * DH, blk * 128 + wave * 32, a.S);
+  auto load_kv = [&](int blk) {
+    const int row0 = blk * 128 + wave * 32;
+    const bf16_t* const k = base + (size_t)row0 * ld + d;
+    const __amdgpu_buffer_rsrc_t k_rows = rows_at<DH>(k, a.S - row0, ld), v_rows = rows_at<DH>(k + d, a.S - row0, ld);
 #pragma unroll
-  for (int kk = 0; kk < NK; ++kk) {
-    const unsigned vo = (unsigned)li * (unsigned)a.ld_qkv * 2u + 32u * kk + 16u * g;
-    kf[kk] = row_chunk(k_rows, vo);
-    vf[kk] = row_chunk(v_rows, vo);
-  }
-  if (t0 < n_tiles) put_stats(st);
+    for (int kk = 0; kk < NK; ++kk) {
+      kf[kk] = row_chunk(k_rows, row_off + 32u * kk);
+      vf[kk] = row_chunk(v_rows, row_off + 32u * kk);
+    }
+    asm volatile("" ::: "memory");
+  };
+  int t = first_tile(item.blk);
+  fetch(t, 0);
+  load_kv(item.blk);
+  put_stats(st);
   f32x16 dk[NC], dv[NC];
+  auto clear = [&] {
 #pragma unroll
-  for (int c = 0; c < NC; ++c)
+    for (int c = 0; c < NC; ++c)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) dk[c][r] = dv[c][r] = 0.f;
-  const float sc = a.scale * LOG2E;
+      for (int r = 0; r < 16; ++r) dk[c][r] = dv[c][r] = 0.f;
+  };
+  clear();
   const uint4* qr[NK];   // Q rows l%32, chunk 2kk + g; dO is 64 rows further on
   ColsBase qc[NC];       // Q columns c*32.., rows from 0
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) qr[kk] = rows_base<DH>(tQ, li, 2 * kk + g);
 #pragma unroll
   for (int c = 0; c < NC; ++c) qc[c] = cols_base<DH>(tQ, c * 32, lane);
-  auto tile = [&](int t, auto buf_) {
+  loads_landed();
+  auto tile = [&](auto buf_) {
     constexpr int B = decltype(buf_)::value * BUF;  // chunks to the tile's buffer
     const float* const stb = st + decltype(buf_)::value * 128;
-    const int i0 = t * 64;
-    tile_landed();
-    if (t + 1 < n_tiles) fetch(t + 1, (unsigned)((BUF - B) * 16));
+    const int i0 = t * 64, row0 = item.blk * 128 + wave * 32;  // the wave's first key
+    const bool last = t + 1 == n_tiles, more = !last || (!ONE_ITEM && item.then >= 0);
+    __syncthreads();
+    if (more) fetch(last ? first_tile(item.then) : t + 1, (unsigned)((BUF - B) * 16));
     // queries past the end, or (causal) queries that precede some key of this wave, need the mask
-    const bool edge = i0 + 64 > a.S || (a.causal && i0 < blk * 128 + wave * 32 + 31);
+    const bool edge = i0 + 64 > a.S || (a.causal && i0 < row0 + 31);
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
       if constexpr (DH == 128) bases128(qr, qc);
@@ -571,18 +634,19 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, const AttnGrid& g
       }
       f32x16 ds;
       if (edge) {
+        // queries that see the key: from `seen` on, `n` of them, both counted from the lane's first
+        const int l = own_lane(), i1 = i0 + 4 * (l >> 5), seen = a.causal ? row0 + (l & 31) - i1 : -i1, n = max(a.S - i1 - seen, 0);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int i = i0 + sub * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-          if (i >= a.S || (a.causal && jk > i)) s[r] = NEG_BIG;
-        }
+        for (int r = 0; r < 16; ++r) s[r] = (unsigned)(sub * 32 + 8 * (r >> 2) + (r & 3) - seen) < (unsigned)n ? s[r] : NEG_BIG;
       }
+      if (sub == 1 && last && more) load_kv(item.then);
+      const float* const stl = stb + 4 * (DH == 128 ? (int)(own_lane() >> 5) : g);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int il = sub * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-        const float p = fast_exp2(fmaf(s[r], sc, -stb[il]));
+        const int il = sub * 32 + 8 * (r >> 2) + (r & 3);
+        const float p = fast_exp2(fmaf(s[r], sc, -stl[il]));
         s[r] = p;
-        ds[r] = p * (dp[r] - stb[64 + il]);
+        ds[r] = p * (dp[r] - stl[64 + il]);
       }
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
@@ -594,32 +658,29 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, const AttnGrid& g
         }
       }
     }
-    if (t + 1 < n_tiles) put_stats(st + (1 - decltype(buf_)::value) * 128);
+    if (more) put_stats(st + (1 - decltype(buf_)::value) * 128);
+    loads_landed();
+    ++t;
+    if (!last) return true;
+    const bf16_t* const ok = dkbase + (size_t)row0 * ld;
+    const __amdgpu_buffer_rsrc_t dk_rows = rows_at<DH>(ok, a.S - row0, ld), dv_rows = rows_at<DH>(ok + d, a.S - row0, ld);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      store_block(dk[c], a.scale, dk_rows, (unsigned)li * (unsigned)ld * 2u + c * 64u, g);
+      store_block(dv[c], 1.f, dv_rows, (unsigned)li * (unsigned)ld * 2u + c * 64u, g);
+    }
+    item.blk = item.then, item.then = -1;
+    t = first_tile(item.blk);
+    clear();
+    return more;
   };
-  for (int t = t0; t < n_tiles; t += 2) {
-    tile(t, std::integral_constant<int, 0>());
-    if (t + 1 < n_tiles) tile(t + 1, std::integral_constant<int, 1>());
-  }
-  if (jk < a.S) {
-    bf16_t* ok = dkbase + (size_t)jk * a.ld_qkv;
-    bf16_t* ov = ok + d;
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int col = c * 32 + 8 * q + 4 * g;
-        *reinterpret_cast<uint2*>(ok + col) =
-            make_uint2(pack2(dk[c][4 * q] * a.scale, dk[c][4 * q + 1] * a.scale),
-                       pack2(dk[c][4 * q + 2] * a.scale, dk[c][4 * q + 3] * a.scale));
-        *reinterpret_cast<uint2*>(ov + col) = make_uint2(pack2(dv[c][4 * q], dv[c][4 * q + 1]),
-                                                         pack2(dv[c][4 * q + 2], dv[c][4 * q + 3]));
-      }
+  while (tile(std::integral_constant<int, 0>()) && tile(std::integral_constant<int, 1>())) {
   }
 }
 
 template <int DH>
 __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dq_kernel(const AttnBwdArgs a, const AttnGrid gr) {
-  dq_body<DH>(a, gr, blockIdx.x);
+  dq_body<DH, false>(a, gr, blockIdx.x);
 }
 template <int DH>
 __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dkv_kernel(const AttnBwdArgs a, const AttnGrid gr) {
@@ -634,7 +695,7 @@ template <int DH>
 __global__ __launch_bounds__(256, DH == 64 ? 2 : 1) void attn_bwd_both_kernel(const AttnBwdArgs a, const AttnGrid gr) {
   const int half = gridDim.x / 2;
   if ((int)blockIdx.x < half) dkv_body<DH, true>(a, gr, blockIdx.x);
-  else dq_body<DH>(a, gr, blockIdx.x - half);
+  else dq_body<DH, true>(a, gr, blockIdx.x - half);
 }
 
 template <int DH> constexpr size_t fwd_lds() { return (size_t)2 * 2 * 64 * (DH / 8) * 16; }
@@ -672,10 +733,21 @@ dim3 attn_grid(int B, int S, int H, int G, AttnGrid& gr) {
   gr.n_h = H;
   gr.total = gr.n_blk * gr.n_bh * G;
   gr.per_xcd = (gr.total + 7) / 8;
+  gr.last = -1;
   gr.r_blk = rcp(gr.n_blk);
   gr.r_bh = rcp(gr.n_bh);
   gr.r_h = rcp(gr.n_h);
   return dim3(gr.per_xcd * 8);
+}
+
+// The same with two row blocks to a workgroup where that is ahead
+dim3 attn_grid_causal(int B, int S, int H, int G, int causal, int per_cu, AttnGrid& gr) {
+  const dim3 grid = attn_grid(B, S, H, G, gr);
+  if (!causal || !attn_pairs(gr.n_blk, gr.total, per_cu)) return grid;
+  const int last = (int)gr.n_blk - 1;
+  const dim3 pairs = attn_grid(B, ((S + 127) / 128) / 2 * 128, H, G, gr);  // n_blk is even
+  gr.last = last;
+  return pairs;
 }
 
 }  // namespace
@@ -691,7 +763,7 @@ hipError_t attn_init() {  // the other kernels stay within the default LDS limit
 hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
   if (!attn_ok(a.B, a.S, a.H, a.DH, a.ld_qkv, a.ld_o, a.G) || !tiles_ok(a.qkv, a.G)) return hipErrorInvalidValue;
   AttnGrid gr;
-  const dim3 grid = attn_grid(a.B, a.S, a.H, a.G, gr);
+  const dim3 grid = attn_grid_causal(a.B, a.S, a.H, a.G, a.causal, a.DH == 64 ? 4 : 2, gr);
   if (a.DH == 64) hipLaunchKernelGGL(attn_fwd_kernel<64>, grid, dim3(256), fwd_lds<64>(), s, a, gr);
   else hipLaunchKernelGGL(attn_fwd_kernel<128>, grid, dim3(256), fwd_lds<128>(), s, a, gr);
   return hipGetLastError();
@@ -711,12 +783,13 @@ hipError_t launch_attn_bwd(const AttnBwdArgs& a, hipStream_t s) {
     else hipLaunchKernelGGL(attn_bwd_both_kernel<128>, both, dim3(256), dkv_lds<128>(), s, a, gr);
     return hipGetLastError();
   }
+  const dim3 wgs = attn_grid_causal(a.B, a.S, a.H, a.G, a.causal, a.DH == 64 ? 3 : 2, gr);
   if (a.DH == 64) {
-    hipLaunchKernelGGL(attn_bwd_dq_kernel<64>, grid, dim3(256), dq_lds<64>(), s, a, gr);
-    hipLaunchKernelGGL(attn_bwd_dkv_kernel<64>, grid, dim3(256), dkv_lds<64>(), s, a, gr);
+    hipLaunchKernelGGL(attn_bwd_dq_kernel<64>, wgs, dim3(256), dq_lds<64>(), s, a, gr);
+    hipLaunchKernelGGL(attn_bwd_dkv_kernel<64>, wgs, dim3(256), dkv_lds<64>(), s, a, gr);
   } else {
-    hipLaunchKernelGGL(attn_bwd_dq_kernel<128>, grid, dim3(256), dq_lds<128>(), s, a, gr);
-    hipLaunchKernelGGL(attn_bwd_dkv_kernel<128>, grid, dim3(256), dkv_lds<128>(), s, a, gr);
+    hipLaunchKernelGGL(attn_bwd_dq_kernel<128>, wgs, dim3(256), dq_lds<128>(), s, a, gr);
+    hipLaunchKernelGGL(attn_bwd_dkv_kernel<128>, wgs, dim3(256), dkv_lds<128>(), s, a, gr);
   }
   return hipGetLastError();
 }

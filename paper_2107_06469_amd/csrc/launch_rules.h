@@ -70,4 +70,19 @@ inline bool pair_ahead(long n_d, long n_w, bool d_small, int k_d, int k_w) {
 // 205 | 208, 2340 level.
 inline bool ln_four_to_a_cu(long blocks) { return blocks > 768 && blocks <= 1024; }
 
+// ---- attention under a causal mask: two row blocks of a head to a workgroup, or one --------------------------------------------------
+// `blocks` 128-row blocks in all, n_blk to a head; per_cu: workgroups that fit a CU.  One to a workgroup suffers most where the blocks of a
+// CU, 32 apart in an XCD's run, are blocks of the same number: n_blk a multiple of 8; then pairs are ahead as soon as there is more than one
+// block to a CU.  Otherwise they are from the point where single blocks need a second pass.  An odd block left over spoils the balance.
+// us, one | two, forward and backward, n_blk and blocks:
+//   8 and 16   dh 64: 768 34.8 | 31.9, 90 | 85; 1024 42.7 | 33.4, 113 | 94; 2048 70 | 59, 198 | 178;  dh 128: 320 35 | 31, 101 | 95; 512 38 | 32, 113 | 104;
+//     16 blocks, dh 64: 288 42 | 35, 110 | 97; 1024 78 | 56, 191 | 158; dh 128: 256 47.2 | 51.7, 142 | 158; 512 65 | 53, 187 | 163
+//   4   dh 64: 640 20.1 | 19.6, 54.8 | 56.3; 1280 31.4 | 28.9, 88 | 84; 4096 82 | 70, 261 | 237;  dh 128: 320 22.1 | 20.6, 63.7 | 64.8; 640 33 | 30, 106 | 95
+//   6   dh 64: 288 16.2 | 17.7, 42 | 47; 768 22.0 | 24.9, 62 | 68; 3072 70 | 65, 203 | 194;  dh 128: 384 25.1 | 26.4, 72 | 76; 1536 66 | 61, 205 | 200
+//   2   dh 128: 2048 52.3 | 53.8, 199 | 206
+//   3, 5, 7, 9, 11   dh 64: 3072 48 | 53, 154 | 188; 5120 105 | 104, 330 | 338; 7168 186 | 192, 552 | 586; 6912 211 | 208, 628 | 634; 4224 156 | 154, 454 | 459
+inline bool attn_pairs(unsigned n_blk, unsigned blocks, int per_cu) {
+  return n_blk >= 4 && n_blk % 2 == 0 && blocks > 256u * (n_blk % 8 == 0 ? 1 : per_cu);
+}
+
 }  // namespace hydra

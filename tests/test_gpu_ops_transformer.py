@@ -295,6 +295,50 @@ def test_attention_backward_in_one_launch_equals_two(torch, ops, B, S, H, DH, ca
     assert torch.equal(delta[:t * H], first[1])
 
 
+@pytest.mark.parametrize("B,S,H,DH", [(53, 449, 5, 64), (33, 512, 5, 128), (9, 1000, 5, 64), (9, 1024, 5, 128), (6, 1410, 10, 128), (41, 700, 5, 64),
+                                      (3, 1985, 7, 64), (2, 2048, 9, 128)])
+def test_causal_attention_in_pairs_of_row_blocks_equals_single_ones(torch, ops, B, S, H, DH):
+    """Large causal launches give a workgroup two row blocks of a head, one after the other; every batch row gives the bits it gives alone,
+    in a launch too small for that, with a last block that is full or down to one row and odd and even numbers of tiles."""
+    d, gen = H * DH, torch.Generator(device="cuda").manual_seed(S + DH)
+    qkv = torch.randn(B * S, 3 * d, generator=gen, device="cuda").to(torch.bfloat16)
+    do = torch.randn(B * S, d, generator=gen, device="cuda").to(torch.bfloat16)
+
+    def both(n, q, g):
+        o, dqkv = torch.zeros_like(g), torch.zeros_like(q)
+        lse, delta = (torch.zeros(n * S * H, device="cuda") for _ in range(2))
+        ops.hydra_op_attention_fwd(n, S, H, DH, 3 * d, d, True, DH ** -0.5, [q], [o], [lse])
+        ops.hydra_op_attention_bwd(n, S, H, DH, 3 * d, d, True, DH ** -0.5, [q], [o], [g], [lse], [delta], [dqkv])
+        return o, dqkv, lse, delta
+
+    whole = both(B, qkv, do)
+    for b in range(B):
+        rows = slice(b * S, (b + 1) * S)
+        part = both(1, qkv[rows].clone(), do[rows].clone())
+        for w, x in zip(whole, part):
+            assert torch.equal(w[b * len(x):(b + 1) * len(x)], x)
+
+
+@pytest.mark.parametrize("off", [1, 2, 4, 7])
+def test_attention_writes_to_buffers_of_any_alignment(torch, ops, off):
+    """o and dqkv need no alignment beyond an element's: the same bits, and nothing outside of them."""
+    B, S, H, DH = 2, 150, 2, 64
+    d, t, gen = H * DH, B * S, torch.Generator(device="cuda").manual_seed(off)
+    qkv = torch.randn(t, 3 * d, generator=gen, device="cuda").to(torch.bfloat16)
+    do = torch.randn(t, d, generator=gen, device="cuda").to(torch.bfloat16)
+    got = []
+    for k in (0, off):
+        o_all, dq_all = (torch.full((n + 64,), 7.0, device="cuda", dtype=torch.bfloat16) for n in (t * d, 3 * t * d))
+        o, dqkv = o_all[16 + k:16 + k + t * d].view(t, d), dq_all[16 + k:16 + k + 3 * t * d].view(t, 3 * d)
+        lse, delta = (torch.zeros(t * H, device="cuda") for _ in range(2))
+        ops.hydra_op_attention_fwd(B, S, H, DH, 3 * d, d, False, DH ** -0.5, [qkv], [o], [lse])
+        ops.hydra_op_attention_bwd(B, S, H, DH, 3 * d, d, False, DH ** -0.5, [qkv], [o], [do], [lse], [delta], [dqkv])
+        got.append((o.clone(), dqkv.clone()))
+        for x, n in ((o_all, t * d), (dq_all, 3 * t * d)):
+            assert bool((x[:16 + k] == 7.0).all()) and bool((x[16 + k + n:] == 7.0).all())
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
 def attention_bits(torch, ops, G, B, S, H, DH, causal):
     """Digest of o, lse, dqkv of G problems of frozen pseudo-random inputs."""
     d, t, r = H * DH, B * S, np.random.RandomState(S * 7 + DH)

@@ -67,6 +67,17 @@ def test_layernorm_backward_takes_four_workgroups_to_a_cu_for_one_pass_of_them(t
     assert _chosen(tmp_path, [f"ln_four_to_a_cu({b})" for b, _ in cases]) == [f for _, f in cases]
 
 
+def test_causal_attention_takes_pairs_of_row_blocks(tmp_path):
+    # (row blocks of a head, of the launch, workgroups to a CU, pairs are ahead)
+    cases = [(8, 768, 4, 1), (8, 768, 3, 1), (8, 2048, 3, 1), (8, 320, 2, 1), (16, 288, 4, 1), (16, 512, 2, 1), (32, 768, 2, 1), (4, 1280, 4, 1),
+             (4, 640, 2, 1), (6, 3072, 3, 1), (6, 1536, 2, 1), (12, 9216, 3, 1),
+             # one to a workgroup
+             (16, 256, 2, 0), (4, 640, 3, 0), (4, 320, 2, 0), (6, 768, 4, 0), (6, 768, 3, 0), (6, 384, 2, 0), (2, 2048, 2, 0), (3, 3072, 3, 0),
+             (5, 5120, 3, 0), (7, 7168, 2, 0), (1, 4096, 4, 0)]
+    got = _chosen(tmp_path, [f"attn_pairs({n}, {b}, {c})" for n, b, c, _ in cases])
+    assert [c for c, g in zip(cases, got) if g != c[3]] == []
+
+
 @pytest.mark.parametrize("K,B,S,d,ffn,L,pairs", [(4, 8, 128, 256, 1024, 4, 16),   # every update but the first block's last one shares a launch
                                                  (8, 10, 110, 256, 1024, 3, 3),   # the updates of W1 only, with the gradient through Wo
                                                  (5, 4, 143, 960, 960, 3, 0), (8, 10, 110, 128, 512, 3, 12)])
