@@ -516,3 +516,23 @@ def test_loads_into_lds_stand_five_wait_states_behind_the_vector_unit_s_writes_o
                 waited += int(rest, 0) + 1 if op == "s_nop" else 1
                 paths += [(q, waited) for q in before.get(p, ())]
     assert seen > 0 and not bad, f"{len(bad)} of {seen}: {bad[:3]}"
+
+
+def test_packed_descriptors_have_the_fields_of_hydra_gemm_desc():
+    """The Python binding packs a product's descriptor and makes its tables as one array: field by field what the C struct holds."""
+    import ctypes as C
+    from paper_2107_06469_amd import ops
+
+    class T:
+        def __init__(self, p):
+            self.p = p
+
+        def data_ptr(self):
+            return self.p
+
+    keep, a, none, b = ops._tabs([T(2 ** 47 + 16), T(3)], None, [T(5), T(7)])
+    assert none is None and list((C.c_uint64 * 2).from_address(a)) == [2 ** 47 + 16, 3] and list((C.c_uint64 * 2).from_address(b)) == [5, 7]
+    d = ops._desc(*range(1, 16), *range(2 ** 47, 2 ** 47 + 9), 2 ** 40)
+    assert len(d) == C.sizeof(ops.hydra_gemm_desc)
+    x = ops.hydra_gemm_desc.from_buffer_copy(d)
+    assert [getattr(x, n) for n, _ in x._fields_] == list(range(1, 16)) + list(range(2 ** 47, 2 ** 47 + 9)) + [2 ** 40]
