@@ -989,7 +989,7 @@ struct RingOperand {
   }
   u32x4 rs;
   unsigned voff[NLD];   // byte offset of the lane's chunk in sub-tile 0, relative to the descriptor's base
-  int kofs[NLD];        // k (inside a sub-tile) of the lane's chunk: a chunk at or past K is loaded as zeros
+  int kofs[NLD];        // k (inside a sub-tile) of the lane's chunk (k-contiguous): a chunk at or past K is loaded as zeros
   unsigned step;        // bytes from one sub-tile to the next
   // base/ld/row0/nrows: the matrix, its leading dimension, the tile's first row and the matrix's row count
   __device__ __forceinline__ void init(const T* base, int ld, int row0, int nrows, int K, int wave, int lane) {
@@ -1018,7 +1018,9 @@ struct RingOperand {
   // nd-th load of sub-tile t into the operand's part of a stage at LDS byte address st
   __device__ __forceinline__ void issue(int nd, int t, unsigned st, int K, int wave) const {
     const int i = nd < NLD ? nd : 0;
-    load_to_lds_b128(rs, st + (unsigned)((i * NW + wave) * 64 * 16), t * BKW + kofs[i] < K ? voff[i] + (unsigned)t * step : 0xfffffff0u);
+    // k-rows past K lie past the descriptor's end (dma_eligible: their offsets, too, are below 2^32)
+    const unsigned off = voff[i] + (unsigned)t * step;
+    load_to_lds_b128(rs, st + (unsigned)((i * NW + wave) * 64 * 16), !KMAJ || t * BKW + kofs[i] < K ? off : 0xfffffff0u);
   }
   // byte offset inside the operand's part of a stage of the lane's fragment of rows [rowbase, rowbase+32) for MFMA step
   // mfma_step of the sub-tile (k-contiguous: every step has its own offset because of the XOR; k-slow: 2 E k-rows each)
@@ -1153,16 +1155,19 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
 #pragma unroll
   for (int j = 0; j < FN; ++j) wa[j] = RW::read_frag(lds_c, fw[0][j]);
   // Row sums of the X operand (the bias gradient when X = dY), as in gemm_kernel: every lane adds up the chunks it
-  // feeds to the MFMAs, in ascending k
+  // feeds to the MFMAs, in ascending k.  Only the waves that store them do, in a loop of their own: 16 of the vector unit's instructions per
+  // MFMA step of a 256x256 tile, which all waves issued before, with a comparison and a selection per load of a k-slow operand.  us, before |
+  // now: weight gradient with Adam 4 x [1024 x 4096] over 3072 tokens 172 | 160, 4 x [30522 x 768] over 2432 828 | 748, 4 x [3072 x 768]
+  // over 16384 404 | 357, 2 x [4096 x 4096] over 8192 629 | 550; input gradient 4 x [2432, 30522 -> 768] 493 | 473.
   constexpr bool RS = !X_KMAJ && !W_KMAJ;
-  const bool do_rs = RS && a.rowsum[g] != nullptr && tn == 0;
+  const bool do_rs = RS && a.rowsum[g] != nullptr && tn == 0 && wn == 0;
   float rs[FM];
 #pragma unroll
   for (int i = 0; i < FM; ++i) rs[i] = 0.f;
   // One MFMA step on the fragments (xc, wc) while the fragments of the following step are read from stage sn into
   // (xn, wn) and, with tl >= 0, the loads of sub-tile tl are issued; the order is pinned so that LDS reads and
   // loads sit between the MFMAs that hide them.
-  auto step = [&](uint4(&xc)[FM], uint4(&wc)[FN], uint4(&xn)[FM], uint4(&wn_)[FN], const char* sn, int s, int tl) {
+  auto step = [&](auto sums, uint4(&xc)[FM], uint4(&wc)[FN], uint4(&xn)[FM], uint4(&wn_)[FN], const char* sn, int s, int tl) {
     constexpr int T_ = FM * FN, RPM = (FM + FN + T_ - 1) / T_;  // MFMAs per step; fragment reads ahead of each
     int nr = 0, nd = 0;
 #pragma unroll
@@ -1184,30 +1189,34 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
             ++nr;
           }
         mma<T>(acc[i][j], wc[j], xc[i]);
-        if (RS && j == 0) rs[i] = chunk_sum<T>(xc[i], rs[i]);
+        if (decltype(sums)::value && j == 0) rs[i] = chunk_sum<T>(xc[i], rs[i]);
         __builtin_amdgcn_sched_barrier(0);
       }
   };
-  for (int t = 0; t < nk; ++t) {
-    const char* st = lds_c + (t % NS) * STAGE;
-    const char* sn = lds_c + ((t + 1) % NS) * STAGE;
-    if constexpr (CPR == 4) {
-      step(xa, wa, xb, wb, st, 1, t + NS - 1);
-      __builtin_amdgcn_s_waitcnt(WAIT_VM);
-      __builtin_amdgcn_s_barrier();
-      if (tail && t + 2 == nk) mask_tail_of(t + 1);
-      step(xb, wb, xa, wa, sn, 0, -1);
-    } else {
-      step(xa, wa, xb, wb, st, 1, -1);
-      step(xb, wb, xa, wa, st, 2, -1);
-      step(xa, wa, xb, wb, st, 3, -1);
-      __builtin_amdgcn_s_waitcnt(WAIT_VM);  // sub-tile t+1 has landed; own reads of stage t are done
-      __builtin_amdgcn_s_barrier();
-      if (tail && t + 2 == nk) mask_tail_of(t + 1);
-      step(xb, wb, xa, wa, sn, 0, t + NS);   // stage t is free: sub-tile t+NS goes there
+  auto k_loop = [&](auto sums) {
+    for (int t = 0; t < nk; ++t) {
+      const char* st = lds_c + (t % NS) * STAGE;
+      const char* sn = lds_c + ((t + 1) % NS) * STAGE;
+      if constexpr (CPR == 4) {
+        step(sums, xa, wa, xb, wb, st, 1, t + NS - 1);
+        __builtin_amdgcn_s_waitcnt(WAIT_VM);
+        __builtin_amdgcn_s_barrier();
+        if (tail && t + 2 == nk) mask_tail_of(t + 1);
+        step(sums, xb, wb, xa, wa, sn, 0, -1);
+      } else {
+        step(sums, xa, wa, xb, wb, st, 1, -1);
+        step(sums, xb, wb, xa, wa, st, 2, -1);
+        step(sums, xa, wa, xb, wb, st, 3, -1);
+        __builtin_amdgcn_s_waitcnt(WAIT_VM);  // sub-tile t+1 has landed; own reads of stage t are done
+        __builtin_amdgcn_s_barrier();
+        if (tail && t + 2 == nk) mask_tail_of(t + 1);
+        step(sums, xb, wb, xa, wa, sn, 0, t + NS);   // stage t is free: sub-tile t+NS goes there
+      }
     }
-  }
-  if (do_rs && wn == 0) {
+  };
+  if (RS && do_rs) k_loop(std::integral_constant<bool, RS>());
+  else k_loop(std::false_type());
+  if (do_rs) {
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
       const float total = rs[i] + __shfl_xor(rs[i], 32, 64);  // even chunks + odd chunks
@@ -1802,13 +1811,13 @@ inline bool mid_deep(const GemmArgs& a) {
   return a.x_kmajor && (long)((a.M + 127) / 128) * ((a.N + 127) / 128) * a.G > 256;
 }
 // What the direct-to-LDS kernels address: an operand with k as the slow index is read from the tile's first element with
-// 32-bit offsets, so its K x ld bytes must stay below 2 GiB.  (A k-contiguous operand may have any K: the last chunk's
+// 32-bit offsets, so its K x ld bytes must stay below 2 GiB, and the k-rows that a ring asks for past K (512 at most), which its
+// descriptor turns into zeros, below 4 GiB.  (A k-contiguous operand may have any K: the last chunk's
 // elements past K are cleared in LDS.)
 inline bool dma_eligible(const GemmArgs& a) {
   const long sz = a.dtype == GEMM_F32 ? 4 : 2;
-  if (!a.x_kmajor && (long)a.K * a.ldx * sz >= 0x7fffffffL) return false;
-  if (!a.w_kmajor && (long)a.K * a.ldw * sz >= 0x7fffffffL) return false;
-  return true;
+  auto reached = [&](long ld) { return a.K * ld * sz < 0x7fffffffL && (a.K + 512L) * ld * sz < 0xffffffffL; };
+  return (a.x_kmajor || reached(a.ldx)) && (a.w_kmajor || reached(a.ldw));
 }
 
 template <typename T, int WM, int WN, int FM, int FN, int PFX, int PF>
