@@ -1278,15 +1278,14 @@ __device__ __forceinline__ void small_body(const GemmArgs& a, const typename Upd
   char* const lds_c = reinterpret_cast<char*>(lds);
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
   const int nk = (K + BK - 1) / BK;
-  auto load = [&](int t) {
-    const unsigned st = lds_base + (unsigned)((t % NS) * STAGE);
-#pragma unroll
-    for (int i = 0; i < RX::NLD; ++i) ox.issue(i, t, st, K, wave);
-#pragma unroll
-    for (int i = 0; i < RW::NLD; ++i) ow.issue(i, t, st + (unsigned)XPART, K, wave);
+  auto load_one = [&](int i, int t, unsigned stage) {  // i-th load of sub-tile t, into the stage that begins there
+    if (i < RX::NLD) ox.issue(i, t, lds_base + stage, K, wave);
+    else ow.issue(i - RX::NLD, t, lds_base + stage + (unsigned)XPART, K, wave);
   };
 #pragma unroll
-  for (int t = 0; t < NS; ++t) load(t);
+  for (int t = 0; t < NS; ++t)
+#pragma unroll
+    for (int i = 0; i < NL; ++i) load_one(i, t, (unsigned)(t * STAGE));
   if constexpr (UPD) {
     // behind the stages' loads and ahead of everything else: the waits below count on where the state's loads stand
     asm volatile("" ::: "memory");
@@ -1303,24 +1302,17 @@ __device__ __forceinline__ void small_body(const GemmArgs& a, const typename Upd
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.f;
   constexpr bool RS = !X_KMAJ && !W_KMAJ;
-  const bool do_rs = RS && a.rowsum[g] != nullptr && n0 == 0;
+  const bool do_rs = RS && a.rowsum[g] != nullptr && n0 == 0 && wn == 0;
   float rs = 0.f;
   const bool tail = (X_KMAJ || W_KMAJ) && K % E != 0;
   uint4 x0[NSTEP], w0[NSTEP], x1[NSTEP], w1[NSTEP];
   constexpr int AL0 = (NS - 1) * NL, AL = (NS - 2) * NL;
   static_assert(AL0 < 64, "vmcnt field");
-  auto take = [&](int t, uint4 (&x)[NSTEP], uint4 (&w)[NSTEP]) {
+  auto mask = [&](int t) {
     char* const st = lds_c + (t % NS) * STAGE;
-    if (tail && t + 1 == nk) {
-      RX::mask_k(st, K - t * BK, tid);
-      RW::mask_k(st + XPART, K - t * BK, tid);
-      __syncthreads();
-    }
-#pragma unroll
-    for (int s = 0; s < NSTEP; ++s) {
-      x[s] = RX::read_frag(st, fx[s]);
-      w[s] = RW::read_frag(st, fw[s]);
-    }
+    RX::mask_k(st, K - t * BK, tid);
+    RW::mask_k(st + XPART, K - t * BK, tid);
+    __syncthreads();
   };
   // all but the newest N loads, and the state's where they were requested after the stage that is waited for
   auto stage_landed = [&](auto n, auto lds_too, bool state_newer) {
@@ -1335,26 +1327,65 @@ __device__ __forceinline__ void small_body(const GemmArgs& a, const typename Upd
       __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | L);
     }
   };
-  auto body = [&](int t, uint4 (&xc)[NSTEP], uint4 (&wc)[NSTEP], uint4 (&xn)[NSTEP], uint4 (&wn_)[NSTEP]) {
+  // The products of stage t, whose fragments are in (xc, wc); the next stage's fragments are read and sub-tile t + NS is asked for.  cur, next:
+  // the stages' places.  Weight gradients and long sums have the reads and loads between the products: a wave that is alone on its
+  // SIMD issues an instruction every five cycles or so, and 8 loads with their addresses and 32 reads take longer than 8 products.  us, ahead of
+  // the products | between them: weight gradient with Adam 4 x [256 x 256] over 1024 rows 8.6 | 8.3; 2 x [300,
+  // 8192 -> 512] 35.8 | 34.2.  (Row sums stay out of that order, behind one test: a loop of its own for them takes 332 registers, and with them one
+  // workgroup to a CU.)  The other products wait for their loads, which start a little later between them: 4 x [1024, 1024 -> 256] 8.9 | 9.2
+  // forward and 7.9 | 8.1 backward, with K = 256 5.4 | 5.4 and 4.9 | 4.9.
+  constexpr bool BETWEEN = RS || NS == 4;
+  constexpr int READS = RS ? 1 : 2;  // fragment pairs read, beside two loads, behind a product
+  auto body = [&](int t, unsigned cur, unsigned next, uint4 (&xc)[NSTEP], uint4 (&wc)[NSTEP], uint4 (&xn)[NSTEP], uint4 (&wn_)[NSTEP]) {
     stage_landed(std::integral_constant<int, AL>(), std::false_type(), t < NS - 1);
     __builtin_amdgcn_s_barrier();
-    load(t + NS);
-    take(t + 1, xn, wn_);
+    const char* const st = lds_c + next;
+    if (!BETWEEN) {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) load_one(i, t + NS, cur);
+    }
+    if (tail && t + 2 == nk) mask(t + 1);
+    if (!BETWEEN) {
+#pragma unroll
+      for (int s = 0; s < NSTEP; ++s) {
+        xn[s] = RX::read_frag(st, fx[s]);
+        wn_[s] = RW::read_frag(st, fw[s]);
+      }
+    }
 #pragma unroll
     for (int s = 0; s < NSTEP; ++s) {
       mma<T>(acc[0][0], wc[s], xc[s]);
-      if (RS) rs = chunk_sum<T>(xc[s], rs);
+      if (BETWEEN) {
+#pragma unroll
+        for (int u = s * READS; u < NSTEP && u < (s + 1) * READS; ++u) {
+          xn[u] = RX::read_frag(st, fx[u]);
+          wn_[u] = RW::read_frag(st, fw[u]);
+        }
+#pragma unroll
+        for (int i = 2 * s; i < NL && i < 2 * s + 2; ++i) load_one(i, t + NS, cur);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (RS && do_rs) {
+#pragma unroll
+      for (int s = 0; s < NSTEP; ++s) rs = chunk_sum<T>(xc[s], rs);
     }
   };
   stage_landed(std::integral_constant<int, AL0>(), std::true_type(), true);
   __builtin_amdgcn_s_barrier();
-  take(0, x0, w0);
+  if (tail && nk == 1) mask(0);
+#pragma unroll
+  for (int s = 0; s < NSTEP; ++s) {
+    x0[s] = RX::read_frag(lds_c, fx[s]);
+    w0[s] = RW::read_frag(lds_c, fw[s]);
+  }
   for (int t = 0; t < nk; t += 2) {
-    body(t, x0, w0, x1, w1);
-    if (t + 1 < nk) body(t + 1, x1, w1, x0, w0);
+    const unsigned s0 = NS == 2 ? 0 : (unsigned)(t % NS) * STAGE, s1 = NS == 2 ? STAGE : (unsigned)((t + 1) % NS) * STAGE;
+    body(t, s0, s1, x0, w0, x1, w1);
+    if (t + 1 < nk) body(t + 1, s1, NS == 2 ? 0 : (unsigned)((t + 2) % NS) * STAGE, x1, w1, x0, w0);
   }
   const int lrow = lane & 31, lgrp = lane >> 5;
-  if (do_rs && wn == 0) {
+  if (do_rs) {
     const float total = rs + __shfl_xor(rs, 32, 64);
     const int m = m0 + wm * 32 + lrow;
     if (lgrp == 0 && m < a.M) a.rowsum[g][m] = total;
@@ -1366,8 +1397,9 @@ __device__ __forceinline__ void small_body(const GemmArgs& a, const typename Upd
   tile_epilogue<T, 1, 1, UPD, UPD ? 0 : (!X_KMAJ ? 0 : (W_KMAJ ? 1 : 2))>(acc, patch, a, upd, g, m0 + wm * 32, n0 + wn * 32, lane, 0, state);
 }
 
+// Two waves per SIMD asked for, so that accumulators stay in the vector registers: 2 to 5 % (4 x [1024, 768 -> 256] input gradient 6.6 | 6.3).
 template <int CPR, int NS, bool X_KMAJ, bool W_KMAJ, bool UPD>
-__global__ __launch_bounds__(256) void gemm_small_kernel(const GemmArgs a, const typename UpdSel<UPD>::type upd) {
+__global__ __launch_bounds__(256, 2) void gemm_small_kernel(const GemmArgs a, const typename UpdSel<UPD>::type upd) {
   small_body<CPR, NS, X_KMAJ, W_KMAJ, UPD>(a, upd, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
@@ -1376,7 +1408,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const GemmArgs a, const
 // The weight gradient's tiles come first, the longer ones.  r_*: floor(2^32 / d) of the divisor beside it (2^32 - 1 for d = 1).
 struct PairGrid { unsigned n_w, w_tm, w_tn, r_wtm, r_wtn, d_tm, d_tn, r_dtm, r_dtn; };
 template <int WCPR, int WNS>
-__global__ __launch_bounds__(256) void gemm_small_pair_kernel(const GemmArgs d, const GemmArgs w, const GemmUpdate u, const PairGrid gr) {
+__global__ __launch_bounds__(256, 2) void gemm_small_pair_kernel(const GemmArgs d, const GemmArgs w, const GemmUpdate u, const PairGrid gr) {
   auto div = [](unsigned n, unsigned by, unsigned rcp) {  // the estimate is one too small at most
     const unsigned q = __umulhi(n, rcp);
     return n - q * by >= by ? q + 1 : q;
@@ -1416,15 +1448,16 @@ __global__ __launch_bounds__(256) void gemm_small_f32_kernel(const GemmArgs a, c
   char* const lds_c = reinterpret_cast<char*>(lds);
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
   const int nk = (K + BK - 1) / BK;
-  auto load = [&](int t) {
-    const unsigned st = lds_base + (unsigned)((t % NS) * STAGE);
-#pragma unroll
-    for (int i = 0; i < RX::NLD; ++i) ox.issue(i, t, st, K, wave);
-#pragma unroll
-    for (int i = 0; i < RW::NLD; ++i) ow.issue(i, t, st + (unsigned)XPART, K, wave);
+  auto load_one = [&](int i, int t, unsigned stage) {  // i-th load of sub-tile t, into the stage that begins there
+    if (i < RX::NLD) ox.issue(i, t, lds_base + stage, K, wave);
+    else ow.issue(i - RX::NLD, t, lds_base + stage + (unsigned)XPART, K, wave);
   };
 #pragma unroll
-  for (int t = 0; t < NS; ++t) load(t);
+  for (int t = 0; t < NS; ++t)
+    if (t < nk) {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) load_one(i, t, (unsigned)(t * STAGE));
+    }
   const int xrow = wm * 16 + r16, wrow = wn * 16 + r16;
   auto frag = [&](const char* part, bool kmaj, int row, int s) {  // k = 8 s + 4 (q%2) + q/2 and that k + 2
     if (kmaj) {
@@ -1435,56 +1468,103 @@ __global__ __launch_bounds__(256) void gemm_small_f32_kernel(const GemmArgs a, c
     const float* p = reinterpret_cast<const float*>(part) + ((k * (BM / E) + ((row >> 2) ^ RX::kswz(k))) * 4 + (row & 3));
     return make_float2(p[0], p[2 * BM]);
   };
+  // One stage (K <= 64, the rows of a small batch): the state comes with the operands.  Lanes past the matrix read its last elements.
+  const int m = m0 + xrow, n = n0 + wn * 16 + 4 * q;
+  f32x4 sp = {0.f, 0.f, 0.f, 0.f}, sm = sp, sv = sp;
+  auto state = [&](size_t at) {
+    if constexpr (UPD) {
+      sp = *reinterpret_cast<const f32x4*>(upd.p[g] + at);
+      if (upd.opt == 1) {
+        sm = *reinterpret_cast<const f32x4*>(upd.m[g] + at);
+        sv = *reinterpret_cast<const f32x4*>(upd.v[g] + at);
+      }
+    }
+  };
+  if constexpr (UPD && NS == 1) state((size_t)min(m, a.M - 1) * a.ldo + min(n, a.N - 4));
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   constexpr bool RS = !X_KMAJ && !W_KMAJ;
   const bool do_rs = RS && a.rowsum[g] != nullptr && n0 == 0 && wn == 0;
   float rs = 0.f;
   const bool tail = (X_KMAJ || W_KMAJ) && K % E != 0;
   float2 x0[NSTEP], w0[NSTEP], x1[NSTEP], w1[NSTEP];
-  constexpr int AL0 = (NS - 1) * NL, AL = (NS - 2) * NL;
-  static_assert(AL0 < 64, "vmcnt field");
-  auto take = [&](int t, float2 (&x)[NSTEP], float2 (&w)[NSTEP]) {
+  auto mask = [&](int t) {
     char* const st = lds_c + (t % NS) * STAGE;
-    if (tail && t + 1 == nk) {
-      RX::mask_k(st, K - t * BK, tid);
-      RW::mask_k(st + XPART, K - t * BK, tid);
-      __syncthreads();
-    }
-#pragma unroll
-    for (int s = 0; s < NSTEP; ++s) {
-      x[s] = frag(st, X_KMAJ, xrow, s);
-      w[s] = frag(st + XPART, W_KMAJ, wrow, s);
-    }
-    if (RS && do_rs) {  // as chunk_sum in the other kernels: half (lane/16)%2 adds k = 8 s + 4 half + 0..3 in ascending k
+    RX::mask_k(st, K - t * BK, tid);
+    RW::mask_k(st + XPART, K - t * BK, tid);
+    __syncthreads();
+  };
+  auto sums_of = [&](unsigned stage) {  // as chunk_sum in the other kernels: half (lane/16)%2 adds k = 8 s + 4 half + 0..3 in ascending k
 #pragma clang fp contract(off)
+    const float* const st = reinterpret_cast<const float*>(lds_c + stage);
 #pragma unroll
-      for (int s = 0; s < NSTEP; ++s)
+    for (int s = 0; s < NSTEP; ++s)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int k = 8 * s + 4 * (q & 1) + e;
-          rs = rs + *(reinterpret_cast<const float*>(st) + ((k * (BM / E) + ((xrow >> 2) ^ RX::kswz(k))) * 4 + (xrow & 3)));
-        }
-    }
+      for (int e = 0; e < 4; ++e) {
+        const int k = 8 * s + 4 * (q & 1) + e;
+        rs = rs + *(st + ((k * (BM / E) + ((xrow >> 2) ^ RX::kswz(k))) * 4 + (xrow & 3)));
+      }
   };
-  auto body = [&](int t, float2 (&xc)[NSTEP], float2 (&wc)[NSTEP], float2 (&xn)[NSTEP], float2 (&wn_)[NSTEP]) {
-    __builtin_amdgcn_s_waitcnt((AL & 15) | ((AL >> 4) << 14) | (7 << 4));  // vmcnt(AL) lgkmcnt(0)
+  auto products = [&](int s, float2 (&x)[NSTEP], float2 (&w)[NSTEP]) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s].x, x[s].x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s].y, x[s].y, acc, 0, 0, 0);
+  };
+  // As in small_body, the next stage's reads and the loads of sub-tile t + 2 between the products of sub-tile t: ahead of them K = 768 took
+  // 18 200 of a tile's 25 000 cycles, 95 for a product of 32.  Products have them in the first half (their loads come from far), weight
+  // gradients, whose reads are twice as many instructions, all along.  us, ahead | first half | all along: 4 x [64, 784 -> 768] forward
+  // 12.6 | 10.3 | 10.4, input gradient 11.0 | 9.7 | 11.4; 2 x [200, 2000 -> 96] input gradient 21.3 | 15.6 | 16.8; 2 x [200 x 304] with Adam
+  // over 500 rows 8.8 | 8.7 | 7.9, [96 x 96] over 2000 22.5 | 22.9 | 18.8.  (Four stages: 9.4 for the second and 12.1 instead of 9.4 at
+  // [768 x 784] over 64 rows.)
+  constexpr int READS = RS ? 1 : 2, LOADS = RS ? 1 : 2;  // fragment pairs read and loads behind a step's two products
+  static_assert(NS <= 2, "a stage's place is its sub-tile's parity");
+  auto body = [&](auto loads, int t, unsigned cur, unsigned next, float2 (&xc)[NSTEP], float2 (&wc)[NSTEP], float2 (&xn)[NSTEP], float2 (&wn_)[NSTEP]) {
+    __builtin_amdgcn_s_waitcnt(7 << 4);  // vmcnt(0) lgkmcnt(0): stage t + 1 has landed, this wave's reads of stage t are done
     __builtin_amdgcn_s_barrier();
-    load(t + NS);
-    if (t + 1 < nk) take(t + 1, xn, wn_);
+    if (tail && t + 2 == nk) mask(t + 1);
 #pragma unroll
     for (int s = 0; s < NSTEP; ++s) {
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[s].x, xc[s].x, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[s].y, xc[s].y, acc, 0, 0, 0);
+      products(s, xc, wc);
+#pragma unroll
+      for (int u = s * READS; u < NSTEP && u < (s + 1) * READS; ++u) {
+        xn[u] = frag(lds_c + next, X_KMAJ, xrow, u);
+        wn_[u] = frag(lds_c + next + XPART, W_KMAJ, wrow, u);
+      }
+      if constexpr (decltype(loads)::value) {
+#pragma unroll
+        for (int i = s * LOADS; i < NL && i < (s + 1) * LOADS; ++i) load_one(i, t + NS, cur);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
+    if (RS && do_rs) sums_of(next);
   };
-  __builtin_amdgcn_s_waitcnt((AL0 & 15) | ((AL0 >> 4) << 14) | (7 << 4) | (15 << 8));
+  if (NS > 1 && nk > 1) __builtin_amdgcn_s_waitcnt((NL & 15) | (7 << 4) | (15 << 8));  // all but the second stage's loads
+  else __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
   __builtin_amdgcn_s_barrier();
-  take(0, x0, w0);
-  for (int t = 0; t < nk; t += 2) {
-    body(t, x0, w0, x1, w1);
-    if (t + 1 < nk) body(t + 1, x1, w1, x0, w0);
+  if (tail && nk == 1) mask(0);
+#pragma unroll
+  for (int s = 0; s < NSTEP; ++s) {
+    x0[s] = frag(lds_c, X_KMAJ, xrow, s);
+    w0[s] = frag(lds_c + XPART, W_KMAJ, wrow, s);
   }
-  const int m = m0 + xrow, n = n0 + wn * 16 + 4 * q;
+  if (RS && do_rs) sums_of(0);
+  if constexpr (NS == 1) {
+#pragma unroll
+    for (int s = 0; s < NSTEP; ++s) products(s, x0, w0);
+  } else {
+    int t = 0;
+    for (; t + 2 < nk; t += 2) {
+      body(std::true_type(), t, 0, STAGE, x0, w0, x1, w1);
+      body(std::true_type(), t + 1, STAGE, 0, x1, w1, x0, w0);
+    }
+    if (t + 1 < nk) {  // the last one or two sub-tiles
+      body(std::false_type(), t, 0, STAGE, x0, w0, x1, w1);
+#pragma unroll
+      for (int s = 0; s < NSTEP; ++s) products(s, x1, w1);
+    } else {
+#pragma unroll
+      for (int s = 0; s < NSTEP; ++s) products(s, x0, w0);
+      __builtin_amdgcn_s_waitcnt(0xf70);  // vmcnt(0): zeros for a stage past the last one may be on their way to LDS
+    }
+  }
   if (RS && do_rs) {
     const float total = rs + __shfl_xor(rs, 16, 64);
     if (q == 0 && m < a.M) a.rowsum[g][m] = total;
@@ -1493,12 +1573,9 @@ __global__ __launch_bounds__(256) void gemm_small_f32_kernel(const GemmArgs a, c
   if constexpr (UPD) {  // N is a multiple of 8
     const size_t ix = (size_t)m * a.ldo + n;
     const OptimHp h = upd.hp[g];
-    const f32x4 p = *reinterpret_cast<const f32x4*>(upd.p[g] + ix);
-    float pe[4] = {p.x, p.y, p.z, p.w}, me[4] = {0.f, 0.f, 0.f, 0.f}, ve[4] = {0.f, 0.f, 0.f, 0.f};
+    if (NS > 1) state(ix);
+    float pe[4] = {sp.x, sp.y, sp.z, sp.w}, me[4] = {sm.x, sm.y, sm.z, sm.w}, ve[4] = {sv.x, sv.y, sv.z, sv.w};
     if (upd.opt == 1) {
-      const f32x4 mm = *reinterpret_cast<const f32x4*>(upd.m[g] + ix), vv = *reinterpret_cast<const f32x4*>(upd.v[g] + ix);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { me[e] = mm[e]; ve[e] = vv[e]; }
 #pragma unroll
       for (int e = 0; e < 4; ++e) optim_step<1>(pe[e], me[e], ve[e], acc[e], h);
       *reinterpret_cast<f32x4*>(upd.m[g] + ix) = f32x4{me[0], me[1], me[2], me[3]};
@@ -1921,6 +1998,7 @@ enum { TILE_SMALL = 101, TILE_SMALL_DEEP = 102 };
 typedef SmallTile<bf16_t, 16, 2> SmallBf16;
 typedef SmallTile<bf16_t, 8, 4> SmallBf16Deep;
 typedef SmallTile<float, 16, 2> SmallF32;
+typedef SmallTile<float, 16, 1> SmallF32One;  // weight gradients over up to 64 rows
 
 // What the few-tile kernels can address: the rows of a k-contiguous operand's tile lie within 31 bits of its first (the 32x128
 // tile takes half as many rows of X).
@@ -1969,10 +2047,12 @@ int choose_update_tile(const GemmArgs& a) {
   const long big = tiles(256, 256);
   const bool small = small_eligible(a);
   if (a.dtype == GEMM_F32) {
-    // 32x32 tiles are ahead until the sums get short against the number of tiles (us, 32x32 | 128x128 | 32x128: 2400 tiles,
-    // K = 256 25 | 41 | 32; 2048 tiles, K = 2048 89 | 161 | 106; K = 64 14.6 | 25 | 14.5; 4096 tiles, K = 24 27 | 28 | 22)
+    // 32x32 tiles are ahead until there are many of them over a short sum (us, 32x32 | 128x128 | 32x128: 2400 tiles, K = 256 25 | 41 | 32;
+    // 2048 tiles, K = 2048 89 | 161 | 106).  Up to 64 rows the one-stage kernel is ahead of 32x128 tiles, too (SGD and Adam, 2400 tiles, K = 8
+    // 8.2 | 8.3 and 12.4 | 16.5, K = 48 8.3 | 9.9 and 12.5 | 18.8; 1200 tiles, K = 16 5.3 | 5.9; 4050 tiles 20.7 | 21.7) but where rows
+    // of the state lie 2 KB apart (2048 tiles of 512 x 512, K = 16 12.0 | 9.6, K = 32 12.6 | 12.0, K = 64 12.4 | 13.4 with two stages).
     const long sm = tiles(32, 32);
-    if (small && (sm <= 1024 || (sm <= 4096 && a.K >= 64))) return TILE_SMALL;
+    if (small && (sm <= 1024 || (sm <= 4096 && (a.K > 32 || a.ldo % 512)))) return TILE_SMALL;
     if (big < 192) return 3;
   } else {
     // 64x64 tiles: the state of a tile is small enough to hide behind the other workgroups' k-loops (us, 64x64 | 128x128:
@@ -2008,7 +2088,11 @@ hipError_t dispatch_update(const GemmArgs& a, const GemmUpdate& u, hipStream_t s
     if (tile == 1 && dma_eligible(a)) return DmaBig::run_update(a, u, s);
     if (tile == 2 && dma_eligible(a)) return DmaMid::run_update(a, u, s);
   } else {
-    if (tile == TILE_SMALL) return SmallF32::run_update(a, u, s);
+    if (tile == TILE_SMALL) {
+      // one stage where that brings more workgroups to a CU (us, two | one: 2400 tiles, K = 64 9.4 | 8.5, Adam 14.3 | 12.6; 128 tiles 4.3 | 4.7)
+      const long tiles = (long)((a.M + 31) / 32) * ((a.N + 31) / 32) * a.G;
+      return a.K <= 64 && tiles > 1024 ? SmallF32One::run_update(a, u, s) : SmallF32::run_update(a, u, s);
+    }
   }
   switch (tile) {
     case 1:

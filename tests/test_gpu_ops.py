@@ -757,3 +757,27 @@ def test_k_rows_megabytes_apart(torch, ops, ld, tile):
                           rowsum=[rs], tile=tile)
         got.append((out, rs))
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("opt", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(520, 544, 1), (545, 528, 17), (513, 552, 63), (520, 544, 64), (512, 512, 33), (512, 512, 32), (520, 544, 65)])
+def test_fp32_updates_over_a_small_batch(torch, ops, M, N, K, opt):
+    """Weight gradients of more than 1024 32x32 tiles over up to 64 rows take a kernel of one stage that reads the state ahead: the bits of the
+    32x128 tiles, at the edges of tiles and on either side of both limits."""
+    G, gen = 4, torch.Generator(device="cuda").manual_seed(M + N + K)
+    mk = lambda *sh: torch.randn(*sh, generator=gen, device="cuda")  # noqa: E731
+    ldm = (M + 7) // 8 * 8
+    dy, x = [mk(K, ldm) for _ in range(G)], [mk(K, N) for _ in range(G)]
+    state = [mk(M, N) * 0.1 for _ in range(G)], [mk(M, N) * 0.1 for _ in range(G)], [(mk(M, N) * 0.1).square() for _ in range(G)]
+    hp, got = [(1e-3 * (g + 1), 0.9, 0.999, 1e-8, 1.5, 1.2) for g in range(G)], []
+    for tile in (0, 3):
+        p, m, v = ([t.clone() for t in s] for s in state)
+        db = [torch.zeros(ldm, device="cuda") for _ in range(G)]
+        ops.hydra_op_gemm_update(ops.F32, M, N, K, dy, x, opt, p, m if opt else None, v if opt else None, None, hp, ldx=ldm, ldw=N, ldo=N,
+                                 rowsum=db, tile=tile)
+        got.append(p + m + v + db)
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    want = state[0][0].double() - hp[0][0] * (dy[0][:, :M].double().t() @ x[0].double()) if opt == 0 else None
+    if opt == 0:  # one chain of K products, its rounding and the update's: (K + 2) 2^-24 of the sum's terms
+        bound = (K + 2) * EPS32 * (hp[0][0] * (dy[0][:, :M].double().abs().t() @ x[0].double().abs()) + state[0][0].double().abs())
+        assert ((got[0][0].double() - want).abs() <= bound).all()
