@@ -1015,12 +1015,13 @@ struct RingOperand {
       }
     }
   }
-  // nd-th load of sub-tile t into the operand's part of a stage at LDS byte address st
+  // nd-th load of sub-tile t into the operand's part of a stage at LDS byte address st.  WHOLE: the sub-tile ends before K.
+  template <bool WHOLE = false>
   __device__ __forceinline__ void issue(int nd, int t, unsigned st, int K, int wave) const {
     const int i = nd < NLD ? nd : 0;
     // k-rows past K lie past the descriptor's end (dma_eligible: their offsets, too, are below 2^32)
     const unsigned off = voff[i] + (unsigned)t * step;
-    load_to_lds_b128(rs, st + (unsigned)((i * NW + wave) * 64 * 16), !KMAJ || t * BKW + kofs[i] < K ? off : 0xfffffff0u);
+    load_to_lds_b128(rs, st + (unsigned)((i * NW + wave) * 64 * 16), !KMAJ || WHOLE || t * BKW + kofs[i] < K ? off : 0xfffffff0u);
   }
   // byte offset inside the operand's part of a stage of the lane's fragment of rows [rowbase, rowbase+32) for MFMA step
   // mfma_step of the sub-tile (k-contiguous: every step has its own offset because of the XOR; k-slow: 2 E k-rows each)
@@ -1068,7 +1069,8 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
   constexpr int CPR = BK / Elem<T>::E;               // 16-byte chunks of k per sub-tile: 4, or 8 (bf16)
   constexpr int BM = WM * FM * 32, BN = WN * FN * 32, NW = WM * WN;
   constexpr int XPART = BM * CPR * 16;          // bytes of the X part of a stage
-  constexpr int STAGE = (BM + BN) * CPR * 16;   // bytes per stage: X part, then W part
+  constexpr int WPART = BN * CPR * 16;
+  constexpr int STAGE = XPART + WPART;          // bytes per stage; the X parts of all stages come first, then the W parts
   typedef RingOperand<T, X_KMAJ, BM, NW, BK> RX;
   typedef RingOperand<T, W_KMAJ, BN, NW, BK> RW;
   constexpr int NL = RX::NLD + RW::NLD;
@@ -1103,10 +1105,10 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
   const int kb = sp * nk_per;
   const int nk = max(0, min(nk_all, kb + nk_per) - kb);
   const int K_end = min(K, (kb + nk) * BK);  // chunks at or past it load as zeros
-  auto load_one = [&](int t, int nd) {  // nd-th direct load of the range's sub-tile t
-    const unsigned st = lds_base + (unsigned)((t % NS) * STAGE);
-    if (nd < RX::NLD) ox_.issue(nd, kb + t, st, K_end, wave);
-    else ow_.issue(nd - RX::NLD, kb + t, st + (unsigned)XPART, K_end, wave);
+  auto load_one = [&](auto whole, int place, int t, int nd) {  // nd-th direct load of the range's sub-tile t, into stage `place`
+    constexpr bool WHOLE = decltype(whole)::value;
+    if (nd < RX::NLD) ox_.template issue<WHOLE>(nd, kb + t, lds_base + (unsigned)(place * XPART), K_end, wave);
+    else ow_.template issue<WHOLE>(nd - RX::NLD, kb + t, lds_base + (unsigned)(NS * XPART + place * WPART), K_end, wave);
   };
 
   f32x16 acc[FM][FN];
@@ -1118,13 +1120,17 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
   const int lrow = lane & 31, lgrp = lane >> 5;
   constexpr int NSTEP = CPR / 2;   // MFMA steps per sub-tile
-  int fx[NSTEP][FM], fw[NSTEP][FN];  // fragment byte offsets inside a stage per MFMA step
+  // fragment byte offsets per MFMA step: those in stage 0, from which the other stages are constants that fit an instruction's offset
+  int fx[NSTEP][FM], fw[NSTEP][FN];
 #pragma unroll
   for (int s = 0; s < NSTEP; ++s) {
 #pragma unroll
     for (int i = 0; i < FM; ++i) fx[s][i] = RX::frag_offset((wm * FM + i) * 32, lane, s);
 #pragma unroll
-    for (int j = 0; j < FN; ++j) fw[s][j] = XPART + RW::frag_offset((wn * FN + j) * 32, lane, s);
+    for (int j = 0; j < FN; ++j) {
+      fw[s][j] = NS * XPART + RW::frag_offset((wn * FN + j) * 32, lane, s);
+      asm("" : "+v"(fw[s][j]));  // the W parts' start stays in the register
+    }
   }
   // loads of this wave that may still be in flight when the next sub-tile must have landed (eight chunks: the loads of
   // the sub-tile that replaces the current one are issued behind the barrier); in the prologue sub-tile 0 must have landed
@@ -1136,16 +1142,16 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
 #pragma unroll
   for (int t = 0; t < (CPR == 4 ? NS - 1 : NS); ++t)
 #pragma unroll
-    for (int nd = 0; nd < NL; ++nd) load_one(t, nd);
+    for (int nd = 0; nd < NL; ++nd) load_one(std::false_type(), t, t, nd);
   __builtin_amdgcn_s_waitcnt(WAIT_VM0);
   __builtin_amdgcn_s_barrier();
   // RAGK (K not a multiple of a chunk): the elements past K in a k-contiguous operand's last chunk are cleared in LDS once
   // the last sub-tile has landed.  A version of its own: a uniform branch per sub-tile costs the others 0.7 %.
   constexpr bool tail = RAGK && (X_KMAJ || W_KMAJ);
   auto mask_tail_of = [&](int t) {
-    char* const st = reinterpret_cast<char*>(lds) + (t % NS) * STAGE;
-    RX::mask_k(st, K - (kb + t) * BK, tid);
-    RW::mask_k(st + XPART, K - (kb + t) * BK, tid);
+    char* const st = reinterpret_cast<char*>(lds);
+    RX::mask_k(st + (t % NS) * XPART, K - (kb + t) * BK, tid);
+    RW::mask_k(st + NS * XPART + (t % NS) * WPART, K - (kb + t) * BK, tid);
     __syncthreads();
   };
   if (tail && nk == 1) mask_tail_of(0);
@@ -1164,11 +1170,13 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
   float rs[FM];
 #pragma unroll
   for (int i = 0; i < FM; ++i) rs[i] = 0.f;
-  // One MFMA step on the fragments (xc, wc) while the fragments of the following step are read from stage sn into
-  // (xn, wn) and, with tl >= 0, the loads of sub-tile tl are issued; the order is pinned so that LDS reads and
+  // One MFMA step on the fragments (xc, wc) while the fragments of the following step are read from stage `from` into
+  // (xn, wn) and, with LOADS, the loads of sub-tile tl are issued into stage `to`; the order is pinned so that LDS reads and
   // loads sit between the MFMAs that hide them.
-  auto step = [&](auto sums, uint4(&xc)[FM], uint4(&wc)[FN], uint4(&xn)[FM], uint4(&wn_)[FN], const char* sn, int s, int tl) {
+  auto step = [&](auto sums, auto loads, auto whole, auto from, auto to, uint4(&xc)[FM], uint4(&wc)[FN], uint4(&xn)[FM], uint4(&wn_)[FN], int s, int tl) {
     constexpr int T_ = FM * FN, RPM = (FM + FN + T_ - 1) / T_;  // MFMAs per step; fragment reads ahead of each
+    const char* const sx = lds_c + decltype(from)::value * XPART;
+    const char* const sw = lds_c + decltype(from)::value * WPART;
     int nr = 0, nd = 0;
 #pragma unroll
     for (int i = 0; i < FM; ++i)
@@ -1177,15 +1185,15 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
         const int q = i * FN + j;
 #pragma unroll
         for (int u = 0; u < NL; ++u)
-          if (tl >= 0 && nd < NL && nd * T_ <= q * NL + (NL > T_ ? NL - T_ : 0)) {
-            load_one(tl, nd);
+          if (decltype(loads)::value && nd < NL && nd * T_ <= q * NL + (NL > T_ ? NL - T_ : 0)) {
+            load_one(whole, decltype(to)::value, tl, nd);
             ++nd;
           }
 #pragma unroll
         for (int u = 0; u < RPM; ++u)
           if (nr < FM + FN) {
-            if (nr < FM) xn[nr] = RX::read_frag(sn, fx[s][nr]);
-            else wn_[nr - FM] = RW::read_frag(sn, fw[s][nr - FM]);
+            if (nr < FM) xn[nr] = RX::read_frag(sx, fx[s][nr]);
+            else wn_[nr - FM] = RW::read_frag(sw, fw[s][nr - FM]);
             ++nr;
           }
         mma<T>(acc[i][j], wc[j], xc[i]);
@@ -1193,27 +1201,65 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
         __builtin_amdgcn_sched_barrier(0);
       }
   };
+  // Sub-tile t, which lies in stage P.  Stages are constants: with a stage's address added to every read and three instructions more per
+  // load (comparison, selection, sum) the vector unit had 18 to 28 instructions per 16 MFMAs, now 5 to 9.  us, before | now: forward
+  // 4 x [16384, 768 -> 3072] with GeLU 362 | 351, 4 x [1024, 256 -> 768] 6.5 | 6.1; input gradient 4 x [3072, 1024 -> 4096] 116 | 112, 8 x [512, 4096 ->
+  // 4096] 135 | 128; weight gradient with Adam 4 x [1024 x 4096] over 3072 tokens 155.5 | 153.5, 4 x [30522 x 768] over 2432 747 | 734.
+  auto sub_tile = [&](auto sums, auto whole, auto place, int t) {
+    constexpr int P = decltype(place)::value;
+    typedef std::integral_constant<int, P> Here;
+    typedef std::integral_constant<int, (P + 1) % NS> Next;
+    typedef std::integral_constant<int, (P + NS - 1) % NS> Last;
+    const std::true_type load;
+    const std::false_type none;
+    if constexpr (CPR == 4) {
+      step(sums, load, whole, Here(), Last(), xa, wa, xb, wb, 1, t + NS - 1);
+      __builtin_amdgcn_s_waitcnt(WAIT_VM);
+      __builtin_amdgcn_s_barrier();
+      if (tail && t + 2 == nk) mask_tail_of(t + 1);
+      step(sums, none, whole, Next(), Here(), xb, wb, xa, wa, 0, 0);
+    } else {
+      step(sums, none, whole, Here(), Here(), xa, wa, xb, wb, 1, 0);
+      step(sums, none, whole, Here(), Here(), xb, wb, xa, wa, 2, 0);
+      step(sums, none, whole, Here(), Here(), xa, wa, xb, wb, 3, 0);
+      __builtin_amdgcn_s_waitcnt(WAIT_VM);  // sub-tile t+1 has landed; own reads of stage t are done
+      __builtin_amdgcn_s_barrier();
+      if (tail && t + 2 == nk) mask_tail_of(t + 1);
+      step(sums, load, whole, Next(), Here(), xb, wb, xa, wa, 0, t + NS);   // stage t is free: sub-tile t+NS goes there
+    }
+  };
+  typedef std::integral_constant<int, 0> P0;
+  typedef std::integral_constant<int, 1> P1;
+  typedef std::integral_constant<int, 2 % NS> P2;
+  typedef std::integral_constant<int, 3 % NS> P3;
   auto k_loop = [&](auto sums) {
-    for (int t = 0; t < nk; ++t) {
-      const char* st = lds_c + (t % NS) * STAGE;
-      const char* sn = lds_c + ((t + 1) % NS) * STAGE;
-      if constexpr (CPR == 4) {
-        step(sums, xa, wa, xb, wb, st, 1, t + NS - 1);
-        __builtin_amdgcn_s_waitcnt(WAIT_VM);
-        __builtin_amdgcn_s_barrier();
-        if (tail && t + 2 == nk) mask_tail_of(t + 1);
-        step(sums, xb, wb, xa, wa, sn, 0, -1);
-      } else {
-        step(sums, xa, wa, xb, wb, st, 1, -1);
-        step(sums, xb, wb, xa, wa, st, 2, -1);
-        step(sums, xa, wa, xb, wb, st, 3, -1);
-        __builtin_amdgcn_s_waitcnt(WAIT_VM);  // sub-tile t+1 has landed; own reads of stage t are done
-        __builtin_amdgcn_s_barrier();
-        if (tail && t + 2 == nk) mask_tail_of(t + 1);
-        step(sums, xb, wb, xa, wa, sn, 0, t + NS);   // stage t is free: sub-tile t+NS goes there
+    // sub-tiles in rounds of NS while every sub-tile that is asked for meanwhile ends before K; the rest one by one
+    constexpr int AHEAD = CPR == 4 ? NS - 1 : NS;
+    const int n_whole = X_KMAJ || W_KMAJ ? (K_end - kb * BK) / BK - AHEAD : nk;
+    const std::true_type whole;
+    const std::false_type part;
+    int t = 0;
+    for (; t + NS <= n_whole; t += NS) {
+      sub_tile(sums, whole, P0(), t);
+      sub_tile(sums, whole, P1(), t + 1);
+      if constexpr (NS == 4) {
+        sub_tile(sums, whole, P2(), t + 2);
+        sub_tile(sums, whole, P3(), t + 3);
+      }
+    }
+    while (t < nk) {
+      sub_tile(sums, part, P0(), t++);
+      if (t >= nk) break;
+      sub_tile(sums, part, P1(), t++);
+      if constexpr (NS == 4) {
+        if (t >= nk) break;
+        sub_tile(sums, part, P2(), t++);
+        if (t >= nk) break;
+        sub_tile(sums, part, P3(), t++);
       }
     }
   };
+  static_assert(NS == 2 || NS == 4, "rounds of the loop");
   if (RS && do_rs) k_loop(std::integral_constant<bool, RS>());
   else k_loop(std::false_type());
   if (do_rs) {
