@@ -630,8 +630,15 @@ __global__ __launch_bounds__(256) void ln_reduce_kernel(const LnBwdArgs a, int n
   const int per = (nblocks + 15) / 16, b0 = w * per, b1 = min(nblocks, b0 + per);
   const float* part = a.part[g];
   float t = 0.f;
+  // 16 partial sums requested together, past the range its last one again (one after the other, each add waits for its load)
   if (j < n2)
-    for (int b = b0; b < b1; ++b) t += part[(size_t)b * n2 + j];
+    for (int b = b0; b < b1; b += 16) {
+      float v[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[i] = part[(size_t)min(b + i, b1 - 1) * n2 + j];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) t = b + i < b1 ? t + v[i] : t;
+    }
   sh[w][cl] = t;
   __syncthreads();
   if (w == 0 && j < n2) {
