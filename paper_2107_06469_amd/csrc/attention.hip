@@ -398,7 +398,7 @@ __device__ __forceinline__ float delta_part(const uint4 (&dof)[NK], const uint4 
   return delta;
 }
 
-template <int DH, bool ONE_ITEM>
+template <int DH, bool ONE_ITEM, bool SETTLE = ONE_ITEM>
 __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, const AttnGrid& gr, int wg) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
   extern __shared__ __attribute__((aligned(256))) uint4 lds[];
@@ -410,7 +410,7 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, const AttnGrid& gr
   if (!attn_item<true>(wg, gr, item)) return;
   const int d = a.H * DH, ld = a.ld_qkv;
   const float sc = a.scale * LOG2E;
-  TileDma<DH, false, ONE_ITEM> dma;
+  TileDma<DH, false, SETTLE> dma;
   dma.init(ld, wave, lane);
   const unsigned lds0 = lds_byte_addr(lds);
   // every pointer at once, so that their loads are one wait
@@ -540,7 +540,7 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, const AttnGrid& g
   if (!attn_item<false>(wg, gr, item)) return;
   const int d = a.H * DH, ld = a.ld_qkv, n_tiles = (a.S + 63) / 64;
   const float sc = a.scale * LOG2E;
-  TileDma<DH, DH == 128, ONE_ITEM> dma_q, dma_o;
+  TileDma<DH, DH == 128, OWN> dma_q, dma_o;
   dma_q.init(ld, wave, lane);
   dma_o.init(a.ld_o, wave, lane);
   const unsigned lds0 = lds_byte_addr(lds), row_off = (unsigned)li * (unsigned)ld * 2u + 16u * g;
@@ -678,9 +678,11 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, const AttnGrid& g
   }
 }
 
-template <int DH>
-__global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dq_kernel(const AttnBwdArgs a, const AttnGrid gr) {
-  dq_body<DH, false>(a, gr, blockIdx.x);
+// Single row blocks need 128 registers at DH = 64, four waves per SIMD; pairs, with the rows of the next block on their way, 156 (us, all as
+// pairs | apart, both halves of the pass: 4 x [32 x 12 heads, 512, 64] 433 | 422, 4 x [8 x 12, 2048, 64] 1358 | 1326).
+template <int DH, bool PAIRS>
+__global__ __launch_bounds__(256, DH == 64 ? (PAIRS ? 3 : 4) : 2) void attn_bwd_dq_kernel(const AttnBwdArgs a, const AttnGrid gr) {
+  dq_body<DH, !PAIRS, false>(a, gr, blockIdx.x);
 }
 template <int DH>
 __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dkv_kernel(const AttnBwdArgs a, const AttnGrid gr) {
@@ -785,10 +787,12 @@ hipError_t launch_attn_bwd(const AttnBwdArgs& a, hipStream_t s) {
   }
   const dim3 wgs = attn_grid_causal(a.B, a.S, a.H, a.G, a.causal, a.DH == 64 ? 3 : 2, gr);
   if (a.DH == 64) {
-    hipLaunchKernelGGL(attn_bwd_dq_kernel<64>, wgs, dim3(256), dq_lds<64>(), s, a, gr);
+    if (gr.last >= 0) hipLaunchKernelGGL((attn_bwd_dq_kernel<64, true>), wgs, dim3(256), dq_lds<64>(), s, a, gr);
+    else hipLaunchKernelGGL((attn_bwd_dq_kernel<64, false>), wgs, dim3(256), dq_lds<64>(), s, a, gr);
     hipLaunchKernelGGL(attn_bwd_dkv_kernel<64>, wgs, dim3(256), dkv_lds<64>(), s, a, gr);
   } else {
-    hipLaunchKernelGGL(attn_bwd_dq_kernel<128>, wgs, dim3(256), dq_lds<128>(), s, a, gr);
+    if (gr.last >= 0) hipLaunchKernelGGL((attn_bwd_dq_kernel<128, true>), wgs, dim3(256), dq_lds<128>(), s, a, gr);
+    else hipLaunchKernelGGL((attn_bwd_dq_kernel<128, false>), wgs, dim3(256), dq_lds<128>(), s, a, gr);
     hipLaunchKernelGGL(attn_bwd_dkv_kernel<128>, wgs, dim3(256), dkv_lds<128>(), s, a, gr);
   }
   return hipGetLastError();
