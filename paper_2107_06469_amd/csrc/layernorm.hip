@@ -171,8 +171,14 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const LnArgs a) {
 
 // dx and per-workgroup partial column sums, rows of up to 1024 elements.  Workgroup b owns rows [b*64, b*64+64); wave w takes rows
 // b*64 + w, +4, +8, ... in ascending order; partial sums go to part[g][b][2][d].
-template <typename T, int C>
-struct LnRow {  // one row's operands as they lie in memory: chunks lane, lane + 64, ...
+struct LnRows {  // a problem's matrices, read from the arguments once
+  const void *x, *dy, *add;
+  void* dx;
+  const float *mean, *rstd;
+  int d, ld;
+};
+template <typename T, int C, int W = 64>
+struct LnRow {  // one row's operands as they lie in memory: chunks lane, lane + W, ...
   static constexpr int RW = sizeof(T) == 2 ? 1 : 2;  // 16-byte pieces per 8 elements
   uint4 x[C][RW], dy[C][RW], add[C][RW];
   float mu, rstd;
@@ -184,7 +190,7 @@ struct LnRow {  // one row's operands as they lie in memory: chunks lane, lane +
     rstd = a.rstd[g][row];
 #pragma unroll
     for (int i = 0; i < C; ++i) {
-      const int c = lane + 64 * i;
+      const int c = lane + W * i;
       if (c < nch) {
 #pragma unroll
         for (int q = 0; q < RW; ++q) {
@@ -194,6 +200,31 @@ struct LnRow {  // one row's operands as they lie in memory: chunks lane, lane +
         }
       }
     }
+  }
+  // The same through descriptors: nothing is conditional (past the row's end, or of a row that is not `there`, zeros), so that the
+  // compiler knows how many loads and stores stand behind these and waits for no more than them.  row: the same for the whole wave.
+  __device__ __forceinline__ void fetch(const LnRows& a, int row, bool there, int lane) {
+    typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+    const int n = there ? a.d * (int)sizeof(T) : 0;
+    auto of = [&](const void* m, int bytes) {
+      return __builtin_amdgcn_make_buffer_rsrc(static_cast<T*>(const_cast<void*>(m)) + (size_t)row * a.ld, 0, bytes, 0x00020000);
+    };
+    const __amdgpu_buffer_rsrc_t rx = of(a.x, n), rd = of(a.dy, n), ra = of(a.add, a.add ? n : 0);
+    auto one = [&](const float* m) {
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(m) + row, 0, there ? 4 : 0, 0x00020000);
+      return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, 0, 0, 0));
+    };
+    mu = one(a.mean);
+    rstd = one(a.rstd);
+#pragma unroll
+    for (int i = 0; i < C; ++i)
+#pragma unroll
+      for (int q = 0; q < RW; ++q) {
+        const int off = ((lane + W * i) * RW + q) * 16;
+        x[i][q] = __builtin_bit_cast(uint4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(rx, off, 0, 0));
+        dy[i][q] = __builtin_bit_cast(uint4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(rd, off, 0, 0));
+        add[i][q] = __builtin_bit_cast(uint4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(ra, off, 0, 0));
+      }
   }
 };
 // A lane's gamma: in registers, or (AGAIN) read from LDS where it is used, dy * gamma being worked out twice: 24 registers less for
@@ -212,17 +243,34 @@ struct GammaLds {
   const float* p;
   __device__ __forceinline__ void get(int, int c, float (&o)[8]) const { ld8<float>(p + 8 * c, o); }
 };
+// Eight elements of a row of dx, dropped where the row has none
+template <typename T>
+__device__ __forceinline__ void store8_rows(const LnRows& a, int row, int c, const float (&v)[8]) {
+  typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(static_cast<T*>(a.dx) + (size_t)row * a.ld, 0, a.d * (int)sizeof(T), 0x00020000);
+  if constexpr (sizeof(T) == 2) {
+    const u32x4 w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+    __builtin_amdgcn_raw_buffer_store_b128(w, rs, c * 16, 0, 0);
+  } else {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const u32x4 w = {__float_as_uint(v[4 * q]), __float_as_uint(v[4 * q + 1]), __float_as_uint(v[4 * q + 2]), __float_as_uint(v[4 * q + 3])};
+      __builtin_amdgcn_raw_buffer_store_b128(w, rs, (2 * c + q) * 16, 0, 0);
+    }
+  }
+}
 // One row: its dx is stored, its terms are added to the column sums where SUMS.  Every multiply-add is written out, so that all
 // kernels give the same bits.
 template <typename T, int C, bool SUMS, typename GA>
 __device__ __forceinline__ void ln_bwd_row(const LnBwdArgs& a, int g, int row, int lane, int nch, const LnRow<T, C>& r,
-                                           const GA& gam, float (&sg)[C][8], float (&sb)[C][8]) {
+                                           const GA& gam, float (&sg)[C][8], float (&sb)[C][8], const LnRows* rows = nullptr) {
 #pragma clang fp contract(off)
+  const bool desc = rows != nullptr, has_add = desc ? rows->add != nullptr : a.add[g] != nullptr;
   float xh[C][8], gg[C][8];
   float s1 = 0.f, s2 = 0.f;
 #pragma unroll
   for (int i = 0; i < C; ++i) {
-    if (lane + 64 * i < nch) {
+    if ((C == 2 && i == 0 && !GA::AGAIN) || lane + 64 * i < nch) {
       float xv[8], dv[8], ga[8];
       unpack8<T>(r.x[i], xv);
       unpack8<T>(r.dy[i], dv);
@@ -244,8 +292,8 @@ __device__ __forceinline__ void ln_bwd_row(const LnBwdArgs& a, int g, int row, i
 #pragma unroll
   for (int i = 0; i < C; ++i) {
     const int c = lane + 64 * i;
-    if (c < nch) {
-      float o[8];
+    float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if ((C == 2 && i == 0 && !GA::AGAIN) || c < nch) {
       if constexpr (GA::AGAIN) {
         float dv[8], ga[8];
         unpack8<T>(r.dy[i], dv);
@@ -255,31 +303,38 @@ __device__ __forceinline__ void ln_bwd_row(const LnBwdArgs& a, int g, int row, i
       }
 #pragma unroll
       for (int e = 0; e < 8; ++e) o[e] = r.rstd * fmaf(-xh[i][e], c2, gg[i][e] - c1);
-      if (a.add[g]) {
+      if (has_add) {
         float av[8];
         unpack8<T>(r.add[i], av);
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[e] += av[e];
       }
-      st8<T>(static_cast<T*>(a.dx[g]) + (size_t)row * a.ld + 8 * c, o);
+      if (!desc) st8<T>(static_cast<T*>(a.dx[g]) + (size_t)row * a.ld + 8 * c, o);
     }
+    if (desc) store8_rows<T>(*rows, row, c, o);
   }
 }
-// Many rows: workgroups of 4 waves, each with its next row's loads in flight while it reduces the current one; bound by
-// memory.  us: 4 x [16384, 768] bf16 97 (4.2 TB/s), 3 x [14483, 616] 46, 2 x [16384, 1024] 53; fp32 4 x [16384, 768] 175.  With two rows in
-// flight 94 | 53 | 54 | 175, with four and no prefetch 101 | 60 | 57 | 205, over 8 waves (one workgroup per CU) 96 | 52 | 55 | 175.
-// FOUR (bf16 rows wider than 512): gamma in LDS, 128 registers instead of 146, so that four workgroups share a CU and not three;
+// Many rows: workgroups of 4 waves, each with its next row's loads in flight while it reduces the current one; bound by memory.  DESC: by
+// descriptors, two rows' operands in turn.  With conditional loads and the next row's copied over the current one's, a row began when its
+// own loads and the last row's stores were through, and read its pointers anew after them.  us, before | now, forward pass with it:
+// 4 x [16384, 768] bf16 123.3 | 121.4, 2 x [12000, 640] 50.9 | 47.7, [65536, 128] 50.1 | 45.4, 4 x [16384, 512] 82.6 | 78.7; fp32 4 x [12000, 256]
+// 65.2 | 61.5, 2 x [9000, 1000] 118 | 109.  Matrices of 16-bit elements that do not start on a word keep the loop it replaces.
+// FOUR (bf16 rows wider than 512): gamma in LDS, 124 registers instead of 141, so that four workgroups share a CU and not three;
 // ahead where they are one pass that way and two the other: 4 x [16384, 768] (1024 workgroups) 95.7 | 91.1 us.
-template <typename T, int C, bool FOUR = false>
+template <typename T, int C, bool DESC, bool FOUR = false>
 __global__ __launch_bounds__(256, FOUR ? 4 : 1) void ln_bwd_kernel(const LnBwdArgs a) {
   extern __shared__ float red[];  // [4][2][d], FOUR: gamma [d]
   float* const gl = red + 8 * a.d;
-  const int g = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = blockIdx.y, lane = threadIdx.x & 63, wave = DESC ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
   const int nch = a.d >> 3;
   const int first = blockIdx.x * LN_ROWS_PER_WG, row0 = first + wave, end = first + min(a.rows - first, LN_ROWS_PER_WG);
+  const LnRows rows = {a.x[g], a.dy[g], a.add[g], a.dx[g], a.mean[g], a.rstd[g], a.d, a.ld};
   float ga[C][8], sg[C][8], sb[C][8];
   LnRow<T, C> cur, nxt;
-  if (FOUR && row0 < end) nxt.fetch(a, g, row0, lane, nch);
+  if constexpr (DESC) {
+    cur.fetch(rows, row0, row0 < end, lane);
+    nxt.fetch(rows, row0 + 4, row0 + 4 < end, lane);
+  }
   if constexpr (FOUR)
     for (int j = 4 * threadIdx.x; j < a.d; j += 1024) *reinterpret_cast<float4*>(gl + j) = *reinterpret_cast<const float4*>(a.gamma[g] + j);
 #pragma unroll
@@ -290,12 +345,28 @@ __global__ __launch_bounds__(256, FOUR ? 4 : 1) void ln_bwd_kernel(const LnBwdAr
     if (!FOUR && c < nch) ld8<float>(a.gamma[g] + 8 * c, ga[i]);
   }
   if constexpr (FOUR) __syncthreads();
-  else if (row0 < end) nxt.fetch(a, g, row0, lane, nch);
-  for (int row = row0; row < end; row += 4) {
-    cur = nxt;
-    if (row + 4 < end) nxt.fetch(a, g, row + 4, lane, nch);
-    if constexpr (FOUR) ln_bwd_row<T, C, true>(a, g, row, lane, nch, cur, GammaLds{gl}, sg, sb);
-    else ln_bwd_row<T, C, true>(a, g, row, lane, nch, cur, GammaRegs<C>{ga}, sg, sb);
+  auto add_row = [&](int row, const LnRow<T, C>& r) {
+    if constexpr (FOUR) ln_bwd_row<T, C, true>(a, g, row, lane, nch, r, GammaLds{gl}, sg, sb, &rows);
+    else ln_bwd_row<T, C, true>(a, g, row, lane, nch, r, GammaRegs<C>{ga}, sg, sb, DESC ? &rows : nullptr);
+  };
+  if constexpr (DESC) {
+    // The first row stands ahead of the loop, so that at its head the same loads and stores are on their way from either side
+    if (row0 < end) add_row(row0, cur);
+    for (int row = row0 + 4; row < end; row += 4) {
+      cur.fetch(rows, row + 4, row + 4 < end, lane);
+      add_row(row, nxt);
+      row += 4;
+      if (row >= end) break;
+      nxt.fetch(rows, row + 4, row + 4 < end, lane);
+      add_row(row, cur);
+    }
+  } else {
+    if (row0 < end) nxt.fetch(a, g, row0, lane, nch);
+    for (int row = row0; row < end; row += 4) {
+      cur = nxt;
+      if (row + 4 < end) nxt.fetch(a, g, row + 4, lane, nch);
+      add_row(row, cur);
+    }
   }
   // the waves' partial sums are added in wave order
 #pragma unroll
@@ -620,6 +691,104 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const LnBwdArgs a) {
   }
 }
 
+// The same with every row on its way while the one before it is reduced, as in ln_bwd_kernel, and the operands of two rows in turn.  us, before | now,
+// forward pass with it: 2 x [16384, 4096] bf16 350 | 335, 3 x [8000, 1536] 94.9 | 92.1, [2000, 3000] 51.7 | 39.9; fp32 2 x [16384, 4096] 668 | 629,
+// 2 x [4000, 2560] 147 | 105, 2 x [9000, 1288] 138 | 128.  ln_bwd_wide_kernel keeps bf16 matrices that do not start on a word and the fp32 ones where it is
+// ahead (ln_wide_ahead).
+template <typename T, int MAXW>
+__global__ __launch_bounds__(256) void ln_bwd_wide_ahead_kernel(const LnBwdArgs a) {
+  __shared__ float xs[2][4][2];  // [row parity][wave][s1, s2]
+  const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nch = a.d >> 3;
+  typedef LnRow<T, MAXW, 256> Row;
+  const int row0 = blockIdx.x * LN_WIDE_ROWS_PER_WG;
+  const int nrow = min(LN_WIDE_ROWS_PER_WG, a.rows - row0);  // the same for every thread: the barriers below are uniform
+  const LnRows rows = {a.x[g], a.dy[g], a.add[g], a.dx[g], a.mean[g], a.rstd[g], a.d, a.ld};
+  Row cur, nxt;
+  cur.fetch(rows, row0, true, tid);
+  nxt.fetch(rows, row0 + 1, nrow > 1, tid);
+  const float* gamma = a.gamma[g];
+  float ga[MAXW][8], sg[MAXW][8], sb[MAXW][8];
+#pragma unroll
+  for (int i = 0; i < MAXW; ++i) {
+    const int c = tid + 256 * i;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sg[i][e] = sb[i][e] = ga[i][e] = 0.f;
+    if (c < nch) ld8<float>(gamma + 8 * c, ga[i]);
+  }
+  const bool has_add = rows.add != nullptr;
+  auto add_row = [&](int r, const Row& in) {
+    float xh[MAXW][8], gg[MAXW][8];
+    float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int i = 0; i < MAXW; ++i) {
+      if ((MAXW == 2 && i == 0) || tid + 256 * i < nch) {
+        float xv[8], dv[8];
+        unpack8<T>(in.x[i], xv);
+        unpack8<T>(in.dy[i], dv);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          xh[i][e] = (xv[e] - in.mu) * in.rstd;
+          gg[i][e] = dv[e] * ga[i][e];
+          s1 += gg[i][e];
+          s2 += gg[i][e] * xh[i][e];
+          sg[i][e] += dv[e] * xh[i][e];
+          sb[i][e] += dv[e];
+        }
+      }
+    }
+    // Two LDS slots by row parity and one barrier per row: a wave can write the slot of row r + 2 only after the
+    // barrier of row r + 1, which every wave reaches after it has read the slot of row r.
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
+    if (lane == 0) {
+      xs[r & 1][wave][0] = s1;
+      xs[r & 1][wave][1] = s2;
+    }
+    __syncthreads();
+    float t1 = 0.f, t2 = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      t1 += xs[r & 1][w][0];
+      t2 += xs[r & 1][w][1];
+    }
+    const float c1 = t1 / (float)a.d, c2 = t2 / (float)a.d;
+#pragma unroll
+    for (int i = 0; i < MAXW; ++i) {
+      const int c = tid + 256 * i;
+      float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      if ((MAXW == 2 && i == 0) || c < nch) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = in.rstd * (gg[i][e] - c1 - xh[i][e] * c2);
+        if (has_add) {
+          float av[8];
+          unpack8<T>(in.add[i], av);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o[e] += av[e];
+        }
+      }
+      store8_rows<T>(rows, row0 + r, c, o);
+    }
+  };
+  add_row(0, cur);  // ahead of the loop, as in ln_bwd_kernel
+  for (int r = 1; r < nrow; ++r) {
+    cur.fetch(rows, row0 + r + 1, r + 1 < nrow, tid);
+    add_row(r, nxt);
+    if (++r >= nrow) break;
+    nxt.fetch(rows, row0 + r + 1, r + 1 < nrow, tid);
+    add_row(r, cur);
+  }
+  float* part = a.part[g] + (size_t)blockIdx.x * 2 * a.d;
+#pragma unroll
+  for (int i = 0; i < MAXW; ++i) {
+    const int c = tid + 256 * i;
+    if (c < nch) {
+      st8<float>(part + 8 * c, sg[i]);
+      st8<float>(part + a.d + 8 * c, sb[i]);
+    }
+  }
+}
+
 // dgamma[col] = sum_b part[b][0][col], dbeta[col] = sum_b part[b][1][col].  A workgroup owns 16 columns; thread
 // (w, col) adds the w-th of 16 contiguous ranges of b in ascending order and the 16 range sums are then added in
 // ascending w: a fixed order that depends on the number of row blocks only.
@@ -684,13 +853,22 @@ static hipError_t ln_bwd_pick(const LnBwdArgs& a, hipStream_t s) {
   const size_t lds = (size_t)4 * 8 * a.d;
   // at most one 16-wave workgroup per CU; wide fp32 rows gain nothing when every CU has one
   const long blocks = (long)grid.x * a.G;
+  // accesses through descriptors are of whole words
+  uintptr_t at = 0;
+  for (int g = 0; g < a.G; ++g) at |= (uintptr_t)a.x[g] | (uintptr_t)a.dy[g] | (uintptr_t)a.add[g] | (uintptr_t)a.dx[g];
+  const bool desc = (at & 3) == 0;
   const bool chain = a.d <= 512 && blocks <= 256 && (sizeof(T) == 2 || blocks * a.d <= 96 * 1024);
   if (chain) hipLaunchKernelGGL((ln_bwd_chain_kernel<T>), grid, dim3(1024), 0, s, a);
-  else if (a.d <= 512) hipLaunchKernelGGL((ln_bwd_kernel<T, 1>), grid, dim3(256), lds, s, a);
-  else if (sizeof(T) == 2 && a.d <= LN_WAVE_ROW_MAX && ln_four_to_a_cu(blocks))
-    hipLaunchKernelGGL((ln_bwd_kernel<bf16_t, 2, true>), grid, dim3(256), lds + 4 * a.d, s, a);
-  else if (a.d <= LN_WAVE_ROW_MAX) hipLaunchKernelGGL((ln_bwd_kernel<T, 2>), grid, dim3(256), lds, s, a);
+  else if (a.d <= 512 && desc) hipLaunchKernelGGL((ln_bwd_kernel<T, 1, true>), grid, dim3(256), lds, s, a);
+  else if (a.d <= 512) hipLaunchKernelGGL((ln_bwd_kernel<T, 1, false>), grid, dim3(256), lds, s, a);
+  else if (sizeof(T) == 2 && a.d <= LN_WAVE_ROW_MAX && desc && ln_four_to_a_cu(blocks))
+    hipLaunchKernelGGL((ln_bwd_kernel<bf16_t, 2, true, true>), grid, dim3(256), lds + 4 * a.d, s, a);
+  else if (a.d <= LN_WAVE_ROW_MAX && desc) hipLaunchKernelGGL((ln_bwd_kernel<T, 2, true>), grid, dim3(256), lds, s, a);
+  else if (a.d <= LN_WAVE_ROW_MAX) hipLaunchKernelGGL((ln_bwd_kernel<T, 2, false>), grid, dim3(256), lds, s, a);
+  else if (a.d <= 2048 && desc && (sizeof(T) == 2 || ln_wide_ahead(blocks, a.d)))
+    hipLaunchKernelGGL((ln_bwd_wide_ahead_kernel<T, 1>), grid, dim3(256), 0, s, a);
   else if (a.d <= 2048) hipLaunchKernelGGL((ln_bwd_wide_kernel<T, 1>), grid, dim3(256), 0, s, a);
+  else if (desc) hipLaunchKernelGGL((ln_bwd_wide_ahead_kernel<T, 2>), grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL((ln_bwd_wide_kernel<T, 2>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }

@@ -472,6 +472,35 @@ def test_layernorm_backward_in_place(torch, ops, dtype, over, G, rows, d):
     assert all(torch.equal(a, b) for a, b in zip(*got))
 
 
+@pytest.mark.parametrize("with_add", [True, False])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("rows,d,ld", [(16449, 184, 192), (16449, 512, 512), (16449, 520, 1040), (57345, 776, 776), (16449, 1016, 1024), (16449, 1800, 1800),
+                                       (22529, 2048, 2048), (99, 1032, 1040), (4129, 2056, 2064)])
+def test_layernorm_backward_from_any_address(torch, ops, dtype, with_add, rows, d, ld):
+    """Matrices that start anywhere give the bits of matrices that start on a word (bf16 ones that do not are loaded another way), a third of
+    the rows, which may be another kernel's, has the same dx, the last block of rows holds few of them, and what lies behind a row's end is
+    not written."""
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(rows + d)
+    src = [torch.randn(rows, ld, generator=gen, device="cuda").to(t) for _ in range(3)]
+    gamma = [1 + 0.1 * torch.randn(d, generator=gen, device="cuda")]
+    v = src[0][:, :d].float()
+    mean, rstd = [v.mean(1)], [v.var(1, unbiased=False).add(1e-5).rsqrt()]
+    got = []
+    for shift, n in ((0, rows), (1, rows), (0, rows // 3)):
+        x, dy, add, dx = (torch.full((rows * ld + 8,), 7.0, device="cuda", dtype=t)[shift:shift + rows * ld].view(rows, ld) for _ in range(4))
+        for to, of in zip((x, dy, add), src):
+            to.copy_(of)
+        dg, db = torch.zeros(d, device="cuda"), torch.zeros(d, device="cuda")
+        part = [torch.zeros(ops.hydra_op_layernorm_part_floats(rows, d), device="cuda")]
+        ops.hydra_op_layernorm_bwd(ops.BF16 if dtype == "bf16" else ops.F32, n, d, ld, [x], [dy], [add] if with_add else None, [dx], gamma,
+                                   mean, rstd, part, [dg], [db])
+        assert bool((dx[:, d:] == 7.0).all()) and bool((dx[n:] == 7.0).all())
+        got.append((dx[:, :d].clone(), dg, db))
+    assert all(torch.equal(a, b) for a, b in zip(*got[:2]))
+    assert torch.equal(got[0][0][:rows // 3], got[2][0][:rows // 3])
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("rows,d", [(8195, 256), (8193, 904), (8194, 1024)])
 def test_layernorm_forward_bits_do_not_depend_on_the_group(torch, ops, dtype, rows, d):

@@ -67,6 +67,12 @@ def test_layernorm_backward_takes_four_workgroups_to_a_cu_for_one_pass_of_them(t
     assert _chosen(tmp_path, [f"ln_four_to_a_cu({b})" for b, _ in cases]) == [f for _, f in cases]
 
 
+def test_layernorm_backward_of_wide_fp32_rows_asks_for_the_next_row_unless_a_few_units_hold_a_third_workgroup(tmp_path):
+    cases = [(250, 2048, 1), (512, 2048, 1), (513, 2048, 0), (564, 2048, 0), (564, 2040, 0), (626, 2048, 0), (750, 2048, 1), (1024, 2048, 1),
+             (564, 1536, 1), (564, 1288, 1)]
+    assert _chosen(tmp_path, [f"ln_wide_ahead({b}, {d})" for b, d, _ in cases]) == [f for _, _, f in cases]
+
+
 def test_causal_attention_takes_pairs_of_row_blocks(tmp_path):
     # (row blocks of a head, of the launch, workgroups to a CU, pairs are ahead)
     cases = [(8, 768, 4, 1), (8, 768, 3, 1), (8, 2048, 3, 1), (8, 320, 2, 1), (16, 288, 4, 1), (16, 512, 2, 1), (32, 768, 2, 1), (4, 1280, 4, 1),
