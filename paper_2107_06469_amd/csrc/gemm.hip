@@ -33,6 +33,7 @@
 #include "launch_rules.h"
 #include "kernels.h"
 #include "lds_dma.h"
+#include "ring_offsets.h"
 #include "optim_math.h"
 
 namespace hydra {
@@ -990,16 +991,15 @@ struct RingOperand {
   u32x4 rs;
   unsigned voff[NLD];   // byte offset of the lane's chunk in sub-tile 0, relative to the descriptor's base
   int kofs[NLD];        // k (inside a sub-tile) of the lane's chunk (k-contiguous): a chunk at or past K is loaded as zeros
-  unsigned step;        // bytes from one sub-tile to the next
+  unsigned row_bytes;   // from one k-row to the next (k as the slow index)
   // base/ld/row0/nrows: the matrix, its leading dimension, the tile's first row and the matrix's row count
   __device__ __forceinline__ void init(const T* base, int ld, int row0, int nrows, int K, int wave, int lane) {
     constexpr unsigned SZ = sizeof(T);
     if (KMAJ) {
       rs = rsrc_words(base, (long)row0 * ld * SZ, (long)nrows * ld * SZ);  // rows past the matrix read as zero
-      step = SZ * BKW;
     } else {
       rs = rsrc_words(base, (long)row0 * SZ, (long)K * ld * SZ);           // k-rows past K read as zero
-      step = SZ * BKW * (unsigned)ld;
+      row_bytes = SZ * (unsigned)ld;
     }
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
@@ -1015,13 +1015,15 @@ struct RingOperand {
       }
     }
   }
-  // nd-th load of sub-tile t into the operand's part of a stage at LDS byte address st.  WHOLE: the sub-tile ends before K.
+  // nd-th load of sub-tile t into the operand's part of a stage at LDS byte address st.  K: where the sum, or the workgroup's range of
+  // it, ends.  WHOLE: the sub-tile ends before that.
   template <bool WHOLE = false>
   __device__ __forceinline__ void issue(int nd, int t, unsigned st, int K, int wave) const {
     const int i = nd < NLD ? nd : 0;
-    // k-rows past K lie past the descriptor's end (dma_eligible: their offsets, too, are below 2^32)
-    const unsigned off = voff[i] + (unsigned)t * step;
-    load_to_lds_b128(rs, st + (unsigned)((i * NW + wave) * 64 * 16), !KMAJ || WHOLE || t * BKW + kofs[i] < K ? off : 0xfffffff0u);
+    unsigned off;
+    if (KMAJ) off = WHOLE || t * BKW + kofs[i] < K ? voff[i] + (unsigned)(t * BKW) * (unsigned)sizeof(T) : 0xfffffff0u;
+    else off = voff[i] + (WHOLE ? (unsigned)(t * BKW) * row_bytes : ring_sub_tile(t, BKW, K, row_bytes));
+    load_to_lds_b128(rs, st + (unsigned)((i * NW + wave) * 64 * 16), off);
   }
   // byte offset inside the operand's part of a stage of the lane's fragment of rows [rowbase, rowbase+32) for MFMA step
   // mfma_step of the sub-tile (k-contiguous: every step has its own offset because of the XOR; k-slow: 2 E k-rows each)
@@ -1104,7 +1106,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
   const int nk_per = SPLITK ? (nk_all + a.split_k - 1) / a.split_k : nk_all;
   const int kb = sp * nk_per;
   const int nk = max(0, min(nk_all, kb + nk_per) - kb);
-  const int K_end = min(K, (kb + nk) * BK);  // chunks at or past it load as zeros
+  const int K_end = min(K, (kb + nk) * BK);  // nothing at or past it is fetched
   auto load_one = [&](auto whole, int place, int t, int nd) {  // nd-th direct load of the range's sub-tile t, into stage `place`
     constexpr bool WHOLE = decltype(whole)::value;
     if (nd < RX::NLD) ox_.template issue<WHOLE>(nd, kb + t, lds_base + (unsigned)(place * XPART), K_end, wave);
@@ -1235,7 +1237,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
   auto k_loop = [&](auto sums) {
     // sub-tiles in rounds of NS while every sub-tile that is asked for meanwhile ends before K; the rest one by one
     constexpr int AHEAD = CPR == 4 ? NS - 1 : NS;
-    const int n_whole = X_KMAJ || W_KMAJ ? (K_end - kb * BK) / BK - AHEAD : nk;
+    const int n_whole = (K_end - kb * BK) / BK - AHEAD;
     const std::true_type whole;
     const std::false_type part;
     int t = 0;
@@ -1270,7 +1272,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
       if (lgrp == 0 && m < a.M) a.rowsum[g][(size_t)sp * a.M + m] = total;
     }
   }
-  // the trailing (all-zero) loads must have landed and every wave must be done with the ring before patches reuse it
+  // the trailing loads (of nothing but zeros) must have landed and every wave must be done with the ring before patches reuse it
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   constexpr int SP = FN * 32 + 4;
