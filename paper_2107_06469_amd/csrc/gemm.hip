@@ -992,6 +992,7 @@ struct RingOperand {
   unsigned voff[NLD];   // byte offset of the lane's chunk in sub-tile 0, relative to the descriptor's base
   int kofs[NLD];        // k (inside a sub-tile) of the lane's chunk (k-contiguous): a chunk at or past K is loaded as zeros
   unsigned row_bytes;   // from one k-row to the next (k as the slow index)
+  int k_rows;           // how many there are
   // base/ld/row0/nrows: the matrix, its leading dimension, the tile's first row and the matrix's row count
   __device__ __forceinline__ void init(const T* base, int ld, int row0, int nrows, int K, int wave, int lane) {
     constexpr unsigned SZ = sizeof(T);
@@ -1000,6 +1001,7 @@ struct RingOperand {
     } else {
       rs = rsrc_words(base, (long)row0 * SZ, (long)K * ld * SZ);           // k-rows past K read as zero
       row_bytes = SZ * (unsigned)ld;
+      k_rows = K;
     }
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
@@ -1011,7 +1013,7 @@ struct RingOperand {
       } else {
         const int k = sl / RC, rc = (sl % RC) ^ kswz(k);
         kofs[i] = k;
-        voff[i] = ((unsigned)k * (unsigned)ld + (unsigned)(rc * E)) * SZ;
+        voff[i] = ring_lane(k, K, row_bytes, (unsigned)(rc * E) * SZ);
       }
     }
   }
@@ -1022,7 +1024,7 @@ struct RingOperand {
     const int i = nd < NLD ? nd : 0;
     unsigned off;
     if (KMAJ) off = WHOLE || t * BKW + kofs[i] < K ? voff[i] + (unsigned)(t * BKW) * (unsigned)sizeof(T) : 0xfffffff0u;
-    else off = voff[i] + (WHOLE ? (unsigned)(t * BKW) * row_bytes : ring_sub_tile(t, BKW, K, row_bytes));
+    else off = voff[i] + (WHOLE ? (unsigned)(t * BKW) * row_bytes : ring_sub_tile(t, BKW, K, k_rows, row_bytes));
     load_to_lds_b128(rs, st + (unsigned)((i * NW + wave) * 64 * 16), off);
   }
   // byte offset inside the operand's part of a stage of the lane's fragment of rows [rowbase, rowbase+32) for MFMA step
@@ -1235,10 +1237,11 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const GemmArgs a,
   typedef std::integral_constant<int, 2 % NS> P2;
   typedef std::integral_constant<int, 3 % NS> P3;
   auto k_loop = [&](auto sums) {
-    // sub-tiles in rounds of NS while every sub-tile that is asked for meanwhile ends before K; the rest one by one
+    // sub-tiles in rounds of NS while every sub-tile that is asked for meanwhile ends before K (the loads of k-slow operands ask
+    // for no such thing); the rest one by one
     constexpr int AHEAD = CPR == 4 ? NS - 1 : NS;
-    const int n_whole = (K_end - kb * BK) / BK - AHEAD;
-    const std::true_type whole;
+    const int n_whole = X_KMAJ || W_KMAJ ? (K_end - kb * BK) / BK - AHEAD : nk;
+    const std::integral_constant<bool, X_KMAJ || W_KMAJ> whole;
     const std::false_type part;
     int t = 0;
     for (; t + NS <= n_whole; t += NS) {
@@ -1936,13 +1939,11 @@ inline bool mid_deep(const GemmArgs& a) {
   return a.x_kmajor && (long)((a.M + 127) / 128) * ((a.N + 127) / 128) * a.G > 256;
 }
 // What the direct-to-LDS kernels address: an operand with k as the slow index is read from the tile's first element with
-// 32-bit offsets, so its K x ld bytes must stay below 2 GiB, and the k-rows that a ring asks for past K (512 at most), which its
-// descriptor turns into zeros, below 4 GiB.  (A k-contiguous operand may have any K: the last chunk's
+// 32-bit offsets, so its K x ld bytes must stay below 2 GiB (ring_spans).  (A k-contiguous operand may have any K: the last chunk's
 // elements past K are cleared in LDS.)
 inline bool dma_eligible(const GemmArgs& a) {
   const long sz = a.dtype == GEMM_F32 ? 4 : 2;
-  auto reached = [&](long ld) { return a.K * ld * sz < 0x7fffffffL && (a.K + 512L) * ld * sz < 0xffffffffL; };
-  return (a.x_kmajor || reached(a.ldx)) && (a.w_kmajor || reached(a.ldw));
+  return (a.x_kmajor || ring_spans(a.K, a.ldx, sz)) && (a.w_kmajor || ring_spans(a.K, a.ldw, sz));
 }
 
 template <typename T, int WM, int WN, int FM, int FN, int PFX, int PF>

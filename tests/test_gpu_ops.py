@@ -739,21 +739,22 @@ def test_tiles_of_a_thin_last_pass_give_the_same_bits(torch, ops, G, M, N, K):
     assert all(torch.equal(a, c) for a, c in zip(*got))
 
 
-@pytest.mark.parametrize("tile", [0, 1, 2])
-@pytest.mark.parametrize("ld", [4067192, 4067208, 6000000])
-def test_k_rows_megabytes_apart(torch, ops, ld, tile):
-    """A ring asks for k-rows past K, whose offsets (up to 512 k-rows more) must not wrap around to rows that are there: operands with rows
-    just below and above the limit give the bits of packed ones."""
-    M, N, K = 72, 80, 13
+@pytest.mark.parametrize("dtype,K,ld,tile", [("bf16", 13, 6000000, 0), ("bf16", 13, 17200000, 0),  # sub-tiles of 128 k: row 125 comes round
+                                             ("bf16", 5, 70000000, 0), ("bf16", 5, 70000000, 1), ("bf16", 5, 70000000, 2),  # 32 k: row 31
+                                             ("f32", 5, 17200000, 0)])  # 64 k: row 63
+def test_k_rows_megabytes_apart(torch, ops, dtype, K, ld, tile):
+    """The last sub-tile's k-rows past K, whose offsets would pass 32 bits and come round to rows that are there (filled with sevens beside the
+    operand), add nothing: the bits of packed operands."""
+    M, N, t, dt = 72, 80, torch.float32 if dtype == "f32" else torch.bfloat16, ops.F32 if dtype == "f32" else ops.BF16
     gen = torch.Generator(device="cuda").manual_seed(ld + tile)
-    x, w = (torch.randn(K, n, generator=gen, device="cuda").to(torch.bfloat16) for n in (M, N))
+    x, w = (torch.randn(K, n, generator=gen, device="cuda").to(t) for n in (M, N))
     got = []
     for far in (False, True):
         lx, lw = (ld, ld) if far else (M, N)
-        xs, ws = (torch.full((K, n), 7.0, device="cuda", dtype=torch.bfloat16) for n in (lx, lw))
+        xs, ws = (torch.full((K, n), 7.0, device="cuda", dtype=t) for n in (lx, lw))
         xs[:, :M], ws[:, :N] = x, w
         out, rs = torch.zeros(M, N, device="cuda"), torch.zeros(M, device="cuda")
-        ops.hydra_op_gemm(ops.BF16, M, N, K, [xs], [ws], [out], x_kmajor=False, w_kmajor=False, ldx=lx, ldw=lw, ldo=N, out_f32=True,
+        ops.hydra_op_gemm(dt, M, N, K, [xs], [ws], [out], x_kmajor=False, w_kmajor=False, ldx=lx, ldw=lw, ldo=N, out_f32=True,
                           rowsum=[rs], tile=tile)
         got.append((out, rs))
     assert all(torch.equal(a, b) for a, b in zip(*got))

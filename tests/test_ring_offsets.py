@@ -28,8 +28,38 @@ def test_a_range_of_a_split_sum_fetches_nothing_of_the_next_one(tmp_path, K, S):
   for (int sp = 0; sp < S; ++sp) {{
     const int kb = sp * per, nk = std::max(0, std::min(nk_all, kb + per) - kb), end = std::min(K, (kb + nk) * bk);
     for (int t = kb; t < kb + nk + 3; ++t) {{
-      const unsigned got = ring_sub_tile(t, bk, end, rb);
+      const unsigned got = ring_sub_tile(t, bk, end, K, rb);
       if (t < kb + nk ? got != (unsigned)(t * bk) * rb : got < (unsigned)K * rb) {{ std::printf("range %d, sub-tile %d: %u\\n", sp, t, got); return 1; }}
+    }}
+  }}
+""")
+
+
+@pytest.mark.parametrize("bk,sz", [(32, 2), (64, 2), (128, 2), (64, 4)])
+def test_no_k_row_past_the_sum_comes_round_to_one_that_is_there(tmp_path, bk, sz):
+    """Every load that a ring issues, up to four sub-tiles past the last one, of operands from packed to the widest that it takes: rows of the sum
+    are read where they lie, the others past the operand."""
+    _program(tmp_path, f"""
+  const int bk = {bk}, sz = {sz};
+  const int Ks[] = {{1, 2, 5, 13, bk - 1, bk, bk + 1, 3 * bk - 1, 4 * bk + 7, 1000}};
+  for (int K : Ks) {{
+    const long most = (0x7ffff000L - 1) / sz / K / 8 * 8;  // the largest ld, in chunks
+    const long lds[] = {{8, 264, 4090440, 4090448, 17200000, 34500000, 70000000, 140000000, most / 2 / 8 * 8, most - 8, most}};
+    if (!ring_spans(K, most, sz) || ring_spans(K, most + 8, sz)) return 2;
+    for (long ld : lds) {{
+      if (ld < 8 || !ring_spans(K, ld, sz)) continue;
+      const unsigned rb = (unsigned)(ld * sz);
+      const int nk = (K + bk - 1) / bk;
+      for (int t = 0; t < nk + 4; ++t)
+        for (int k = 0; k < bk; ++k)
+          for (unsigned col = 0; col < 2048; col += 496) {{
+            const unsigned got = ring_lane(k, K, rb, col) + ring_sub_tile(t, bk, K, K, rb);
+            const long row = (long)t * bk + k;
+            if (row < K ? got != row * (long)rb + col : got < (unsigned long)K * rb) {{
+              std::printf("K %d, ld %ld, row %ld, column byte %u: %u\\n", K, ld, row, col, got);
+              return 1;
+            }}
+          }}
     }}
   }}
 """)
