@@ -157,13 +157,12 @@ struct LoaderT {
   static constexpr int N_LOAD = NBT * KR, N_STORE = NBT * E;
   static constexpr int OW = KR * (int)sizeof(T) / 4;            // dwords written per output row (4, 2 or 1)
   uint4 r[NBT][KR];
-  // Buffer loads: the descriptor starts at element (k0, row0) and ends after k row K-1, so k rows past K
+  // Buffer loads: the descriptor starts at element (k0, row0) and ends with k row K-1, so k rows past K
   // read as zero without a guard.  Tile rows past the matrix read whatever follows (padding or the next
-  // k row); they only feed outputs that are never stored.
+  // k row, zero behind the last one); they only feed outputs that are never stored.
   __device__ __forceinline__ void load(const T* base, int ld, int row0, int nrows, int k0, int K, int tid) {
     const long first = ((long)k0 * ld + row0) * (long)sizeof(T);
-    const __amdgpu_buffer_rsrc_t rs = tile_rsrc(base, first, (long)K * ld * (long)sizeof(T));
-    (void)nrows;
+    const __amdgpu_buffer_rsrc_t rs = tile_rsrc(base, first, k_slow_bytes(K, ld, nrows, sizeof(T)));
 #pragma unroll
     for (int i = 0; i < NBT; ++i) {
       const int u = tid + NT * i, half = (u / LO) % SPLIT, rest = u / (LO * SPLIT);
@@ -999,7 +998,7 @@ struct RingOperand {
     if (KMAJ) {
       rs = rsrc_words(base, (long)row0 * ld * SZ, (long)nrows * ld * SZ);  // rows past the matrix read as zero
     } else {
-      rs = rsrc_words(base, (long)row0 * SZ, (long)K * ld * SZ);           // k-rows past K read as zero
+      rs = rsrc_words(base, (long)row0 * SZ, k_slow_bytes(K, ld, nrows, SZ));  // k-rows past K read as zero
       row_bytes = SZ * (unsigned)ld;
       k_rows = K;
     }

@@ -1,5 +1,5 @@
-// What the direct-to-LDS ring's loads of an operand with k as the slow index add to the start of their descriptor, which ends with the
-// operand's K k-rows: loads past it bring zeros and fetch nothing.  An offset is the sum of a part that the wave shares and a lane's own, each
+// What the direct-to-LDS ring's loads of an operand with k as the slow index add to the start of their descriptor, which ends with the last
+// of the operand's K k-rows: loads past it bring zeros and fetch nothing.  An offset is the sum of a part that the wave shares and a lane's own, each
 // at most K rows, so that with K rows below 2 GiB the sum stays below 4 GiB.  Nothing here calls HIP.
 #pragma once
 
@@ -7,6 +7,11 @@ namespace hydra {
 
 // The operands that the ring takes: a page short of 2 GiB, which the bytes inside a k-row (less than 2 KB) may fill
 constexpr bool ring_spans(long K, long ld, long sz) { return K * ld * sz < 0x7ffff000L; }
+
+// Bytes of an operand with k as the slow index, from its first element to the end of the 16-byte chunk that holds the last element of its n columns
+// in its last k-row: behind that the operand's buffer may end (columns of a wider matrix, where a tile's columns past n would be read
+// behind the whole matrix).
+constexpr long k_slow_bytes(long K, long ld, long n, long sz) { return ((K - 1) * ld + (n * sz + 15) / 16 * 16 / sz) * sz; }
 
 // The shared part, of sub-tile t (bk k-rows of row_bytes).  k_end: where the sum, or the range of it that a workgroup takes, ends; sub-tiles from
 // there on begin past the operand.  Most kernels' k_end is K, and this is one minimum of the scalar unit; a comparison and a selection per

@@ -63,3 +63,17 @@ def test_no_k_row_past_the_sum_comes_round_to_one_that_is_there(tmp_path, bk, sz
     }}
   }}
 """)
+
+
+def test_columns_of_a_wider_matrix_are_not_read_behind_it(tmp_path):
+    """An operand that is the last columns of a matrix: what a descriptor spans holds all of the operand's chunks and ends inside the matrix, whose
+    rows a product wants to be whole chunks."""
+    _program(tmp_path, """
+  for (long sz : {2L, 4L})
+    for (long K : {1L, 7L, 4096L})
+      for (long n : {1L, 8L, 60L, 200L, 320L, 768L})
+        for (long first : {0L, 8L, 640L, 1536L}) {
+          const long e = 16 / sz, ld = (first + n + e - 1) / e * e, at = first * sz, got = k_slow_bytes(K, ld, n, sz);
+          if (at + got > K * ld * sz || got < ((K - 1) * ld + n) * sz || got % 16) { std::printf("%ld %ld %ld %ld: %ld\\n", sz, K, n, first, got); return 1; }
+        }
+""")
