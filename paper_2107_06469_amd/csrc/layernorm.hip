@@ -570,6 +570,29 @@ __global__ __launch_bounds__(LN_SPLIT_NT) void ln_bwd_split_kernel(const LnBwdAr
   }
 }
 
+// Eight elements of a wide row: x-hat, dy * gamma and what they add to the row's and the columns' sums, and their dx.  Every multiply-add is
+// written out, as in ln_bwd_row, and none is left to the compiler: which of the kernels below runs depends on how many problems share a
+// launch (ln_wide_ahead).  (The residual is added by the kernels: with its test in here the compiler made selections of it, and the
+// kernel without look-ahead, whose registers were then dealt out another way, waited at every row for the stores of the one before,
+// 2 x [9024, 2048] 132 | 142 us.)
+__device__ __forceinline__ void ln_wide_terms(const float (&xv)[8], const float (&dv)[8], const float (&ga)[8], float mu, float rstd, float (&xh)[8],
+                                              float (&gg)[8], float& s1, float& s2, float (&sg)[8], float (&sb)[8]) {
+#pragma clang fp contract(off)
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    xh[e] = (xv[e] - mu) * rstd;
+    gg[e] = dv[e] * ga[e];
+    s1 = fmaf(dv[e], ga[e], s1);
+    s2 = fmaf(gg[e], xh[e], s2);
+    sg[e] = fmaf(dv[e], xh[e], sg[e]);
+    sb[e] += dv[e];
+  }
+}
+__device__ __forceinline__ void ln_wide_dx(const float (&xh)[8], const float (&gg)[8], float rstd, float c1, float c2, float (&o)[8]) {
+#pragma clang fp contract(off)
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o[e] = rstd * fmaf(-xh[e], c2, gg[e] - c1);
+}
 // Rows of more than 1024 elements: a wave per row would need 32 or 64 values of x-hat and g per lane (one or two waves
 // per SIMD, and up to 128 KB of LDS for the cross-wave column sums).  Here the four waves of a workgroup share each
 // row: thread t owns chunks t, t + 256 (MAXW of them), the two row sums cross the waves through LDS (added in wave
@@ -577,6 +600,7 @@ __global__ __launch_bounds__(LN_SPLIT_NT) void ln_bwd_split_kernel(const LnBwdAr
 // rows in row order and writes them to part[g][b][2][d] itself.  16-bit rows are prefetched one row ahead.
 template <typename T, int MAXW>
 __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const LnBwdArgs a) {
+#pragma clang fp contract(off)
   __shared__ float xs[2][4][2];  // [row parity][wave][s1, s2]
   const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nch = a.d >> 3;
@@ -635,15 +659,7 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const LnBwdArgs a) {
         float xv[8], dv[8];
         unpack8<T>(cx[i], xv);
         unpack8<T>(cdy[i], dv);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          xh[i][e] = (xv[e] - mu) * rstd;
-          gg[i][e] = dv[e] * ga[i][e];
-          s1 += gg[i][e];
-          s2 += gg[i][e] * xh[i][e];
-          sg[i][e] += dv[e] * xh[i][e];
-          sb[i][e] += dv[e];
-        }
+        ln_wide_terms(xv, dv, ga[i], mu, rstd, xh[i], gg[i], s1, s2, sg[i], sb[i]);
       }
     }
     // Two LDS slots by row parity and one barrier per row: a wave can write the slot of row r + 2 only after the
@@ -668,8 +684,7 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const LnBwdArgs a) {
       const int c = tid + 256 * i;
       if (c < nch) {
         float o[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = rstd * (gg[i][e] - c1 - xh[i][e] * c2);
+        ln_wide_dx(xh[i], gg[i], rstd, c1, c2, o);
         if (has_add) {
           float av[8];
           unpack8<T>(cadd[i], av);
@@ -697,6 +712,7 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const LnBwdArgs a) {
 // ahead (ln_wide_ahead).
 template <typename T, int MAXW>
 __global__ __launch_bounds__(256) void ln_bwd_wide_ahead_kernel(const LnBwdArgs a) {
+#pragma clang fp contract(off)
   __shared__ float xs[2][4][2];  // [row parity][wave][s1, s2]
   const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nch = a.d >> 3;
@@ -726,15 +742,7 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_ahead_kernel(const LnBwdArgs 
         float xv[8], dv[8];
         unpack8<T>(in.x[i], xv);
         unpack8<T>(in.dy[i], dv);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          xh[i][e] = (xv[e] - in.mu) * in.rstd;
-          gg[i][e] = dv[e] * ga[i][e];
-          s1 += gg[i][e];
-          s2 += gg[i][e] * xh[i][e];
-          sg[i][e] += dv[e] * xh[i][e];
-          sb[i][e] += dv[e];
-        }
+        ln_wide_terms(xv, dv, ga[i], in.mu, in.rstd, xh[i], gg[i], s1, s2, sg[i], sb[i]);
       }
     }
     // Two LDS slots by row parity and one barrier per row: a wave can write the slot of row r + 2 only after the
@@ -758,8 +766,7 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_ahead_kernel(const LnBwdArgs 
       const int c = tid + 256 * i;
       float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
       if ((MAXW == 2 && i == 0) || c < nch) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = in.rstd * (gg[i][e] - c1 - xh[i][e] * c2);
+        ln_wide_dx(xh[i], gg[i], in.rstd, c1, c2, o);
         if (has_add) {
           float av[8];
           unpack8<T>(in.add[i], av);

@@ -501,6 +501,30 @@ def test_layernorm_backward_from_any_address(torch, ops, dtype, with_add, rows, 
     assert torch.equal(got[0][0][:rows // 3], got[2][0][:rows // 3])
 
 
+@pytest.mark.parametrize("with_add", [True, False])
+@pytest.mark.parametrize("rows,d", [(8225, 1800), (8500, 2048), (11233, 2040)])
+def test_layernorm_backward_bits_do_not_depend_on_the_group(torch, ops, with_add, rows, d):
+    """fp32 rows of 1800 to 2048 elements: two problems in 513 to 704 row blocks take the kernel without look-ahead, each of them alone the one with
+    it; dx, dgamma and dbeta are the same bits."""
+    gen = torch.Generator(device="cuda").manual_seed(rows + d)
+    x, dy, add = ([torch.randn(rows, d, generator=gen, device="cuda") for _ in range(2)] for _ in range(3))
+    gamma = [1 + 0.1 * torch.randn(d, generator=gen, device="cuda") for _ in range(2)]
+    mean, rstd = [v.mean(1) for v in x], [v.var(1, unbiased=False).add(1e-5).rsqrt() for v in x]
+
+    def run(which):
+        pick = lambda ts: [ts[i] for i in which]  # noqa: E731
+        dx, (dg, db) = [torch.zeros(rows, d, device="cuda") for _ in which], ([torch.zeros(d, device="cuda") for _ in which] for _ in range(2))
+        part = [torch.zeros(ops.hydra_op_layernorm_part_floats(rows, d), device="cuda") for _ in which]
+        ops.hydra_op_layernorm_bwd(ops.F32, rows, d, d, pick(x), pick(dy), pick(add) if with_add else None, dx, pick(gamma), pick(mean), pick(rstd),
+                                   part, dg, db)
+        return list(zip(dx, dg, db))
+
+    together = run((0, 1))
+    for i in (0, 1):
+        for a, b in zip(together[i], run((i,))[0]):
+            assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("rows,d", [(8195, 256), (8193, 904), (8194, 1024)])
 def test_layernorm_forward_bits_do_not_depend_on_the_group(torch, ops, dtype, rows, d):

@@ -536,3 +536,28 @@ def test_packed_descriptors_have_the_fields_of_hydra_gemm_desc():
     assert len(d) == C.sizeof(ops.hydra_gemm_desc)
     x = ops.hydra_gemm_desc.from_buffer_copy(d)
     assert [getattr(x, n) for n, _ in x._fields_] == list(range(1, 16)) + list(range(2 ** 47, 2 ** 47 + 9)) + [2 ** 40]
+
+
+def test_layernorm_s_multiply_adds_are_written_out(tmp_path):
+    """Which LayerNorm kernel runs depends on how many problems share a launch, and the bits must not: no product is left to the compiler to join
+    with a sum, so that every kernel has the same multiply-adds, products and sums whether it may join them or not."""
+    from paper_2107_06469_amd import build as B
+
+    if not os.path.exists(B.HIPCC):
+        pytest.skip("no hipcc")
+    counts = []
+    for mode in ("fast-honor-pragmas", "off"):
+        out = tmp_path / f"{mode}.s"
+        subprocess.run([B.HIPCC] + B.FLAGS + ["-ffp-contract=" + mode, "--cuda-device-only", "-S", os.path.join(B.CSRC, "layernorm.hip"), "-o", str(out)],
+                       check=True, capture_output=True)
+        kernels, name = {}, None
+        for ln in out.read_text().splitlines():
+            label = re.match(r"(\w+):", ln)
+            if label and not ln.startswith(".L"):
+                name = label.group(1)
+                kernels[name] = dict.fromkeys(("v_fma", "v_mul_f32", "v_add_f32", "v_sub"), 0)
+            elif name and ln.startswith("\t"):
+                for op in kernels[name]:
+                    kernels[name][op] += ln[1:].startswith(op)
+        counts.append({k: (c["v_fma"], c["v_mul_f32"], c["v_add_f32"] + c["v_sub"]) for k, c in kernels.items() if sum(c.values())})
+    assert len(counts[0]) >= 20 and counts[0] == counts[1]
