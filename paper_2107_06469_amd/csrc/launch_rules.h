@@ -70,7 +70,7 @@ inline bool pair_ahead(long n_d, long n_w, bool d_small, int k_d, int k_w) {
 // 205 | 208, 2340 level.
 inline bool ln_four_to_a_cu(long blocks) { return blocks > 768 && blocks <= 1024; }
 
-// fp32 rows of 1024 to 2048 elements, 32 to a workgroup: the next row asked for ahead (ln_bwd_wide_ahead_kernel), or not.  Rows of 8 KB are ahead
+// fp32 rows of 1024 to 2048 elements, 32 to a workgroup: the next row asked for ahead (ln_bwd_wide_kernel), or not (ln_bwd_wide_f32_kernel).  Rows of 8 KB are ahead
 // without where a few CUs hold a third workgroup (why was not found: the waits, the order of the loads and the descriptors alone are not it).  us, not |
 // ahead, forward pass with it: d = 2048, 125 blocks 69.6 | 52.6, 250 87.9 | 80.4, 512 168.4 | 161.5, 532 176.7 | 188.4, 564 185.5 | 196.4, 626 201.6 | 206.6,
 // 750 242.2 | 238.9, 1024 325.7 | 322.5; 564 blocks, d = 2040 193.7 | 199.9, 1536 150.9 | 147.4, 1288 138.5 | 127.7.

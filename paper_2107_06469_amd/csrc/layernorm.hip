@@ -314,27 +314,27 @@ __device__ __forceinline__ void ln_bwd_row(const LnBwdArgs& a, int g, int row, i
     if (desc) store8_rows<T>(*rows, row, c, o);
   }
 }
-// Many rows: workgroups of 4 waves, each with its next row's loads in flight while it reduces the current one; bound by memory.  DESC: by
+// Many rows: workgroups of 4 waves, each with its next row's loads in flight while it reduces the current one; bound by memory.  By
 // descriptors, two rows' operands in turn.  With conditional loads and the next row's copied over the current one's, a row began when its
 // own loads and the last row's stores were through, and read its pointers anew after them.  us, before | now, forward pass with it:
 // 4 x [16384, 768] bf16 123.3 | 121.4, 2 x [12000, 640] 50.9 | 47.7, [65536, 128] 50.1 | 45.4, 4 x [16384, 512] 82.6 | 78.7; fp32 4 x [12000, 256]
-// 65.2 | 61.5, 2 x [9000, 1000] 118 | 109.  Matrices of 16-bit elements that do not start on a word keep the loop it replaces.
+// 65.2 | 61.5, 2 x [9000, 1000] 118 | 109.  16-bit matrices may start at any element: the target's unaligned access mode holds for descriptors, too
+// (a test compares such matrices with ones that start on a word; the old loops, which they had for a while, took longer: backward alone
+// 4 x [16384, 768] 98 | 93, 4 x [16384, 512] 56.6 | 54.5, 3 x [8000, 1536] 77 | 72.5, [2000, 3000] 46.2 | 38.2).
 // FOUR (bf16 rows wider than 512): gamma in LDS, 124 registers instead of 141, so that four workgroups share a CU and not three;
 // ahead where they are one pass that way and two the other: 4 x [16384, 768] (1024 workgroups) 95.7 | 91.1 us.
-template <typename T, int C, bool DESC, bool FOUR = false>
+template <typename T, int C, bool FOUR = false>
 __global__ __launch_bounds__(256, FOUR ? 4 : 1) void ln_bwd_kernel(const LnBwdArgs a) {
   extern __shared__ float red[];  // [4][2][d], FOUR: gamma [d]
   float* const gl = red + 8 * a.d;
-  const int g = blockIdx.y, lane = threadIdx.x & 63, wave = DESC ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
+  const int g = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nch = a.d >> 3;
   const int first = blockIdx.x * LN_ROWS_PER_WG, row0 = first + wave, end = first + min(a.rows - first, LN_ROWS_PER_WG);
   const LnRows rows = {a.x[g], a.dy[g], a.add[g], a.dx[g], a.mean[g], a.rstd[g], a.d, a.ld};
   float ga[C][8], sg[C][8], sb[C][8];
   LnRow<T, C> cur, nxt;
-  if constexpr (DESC) {
-    cur.fetch(rows, row0, row0 < end, lane);
-    nxt.fetch(rows, row0 + 4, row0 + 4 < end, lane);
-  }
+  cur.fetch(rows, row0, row0 < end, lane);
+  nxt.fetch(rows, row0 + 4, row0 + 4 < end, lane);
   if constexpr (FOUR)
     for (int j = 4 * threadIdx.x; j < a.d; j += 1024) *reinterpret_cast<float4*>(gl + j) = *reinterpret_cast<const float4*>(a.gamma[g] + j);
 #pragma unroll
@@ -347,26 +347,17 @@ __global__ __launch_bounds__(256, FOUR ? 4 : 1) void ln_bwd_kernel(const LnBwdAr
   if constexpr (FOUR) __syncthreads();
   auto add_row = [&](int row, const LnRow<T, C>& r) {
     if constexpr (FOUR) ln_bwd_row<T, C, true>(a, g, row, lane, nch, r, GammaLds{gl}, sg, sb, &rows);
-    else ln_bwd_row<T, C, true>(a, g, row, lane, nch, r, GammaRegs<C>{ga}, sg, sb, DESC ? &rows : nullptr);
+    else ln_bwd_row<T, C, true>(a, g, row, lane, nch, r, GammaRegs<C>{ga}, sg, sb, &rows);
   };
-  if constexpr (DESC) {
-    // The first row stands ahead of the loop, so that at its head the same loads and stores are on their way from either side
-    if (row0 < end) add_row(row0, cur);
-    for (int row = row0 + 4; row < end; row += 4) {
-      cur.fetch(rows, row + 4, row + 4 < end, lane);
-      add_row(row, nxt);
-      row += 4;
-      if (row >= end) break;
-      nxt.fetch(rows, row + 4, row + 4 < end, lane);
-      add_row(row, cur);
-    }
-  } else {
-    if (row0 < end) nxt.fetch(a, g, row0, lane, nch);
-    for (int row = row0; row < end; row += 4) {
-      cur = nxt;
-      if (row + 4 < end) nxt.fetch(a, g, row + 4, lane, nch);
-      add_row(row, cur);
-    }
+  // The first row stands ahead of the loop, so that at its head the same loads and stores are on their way from either side
+  if (row0 < end) add_row(row0, cur);
+  for (int row = row0 + 4; row < end; row += 4) {
+    cur.fetch(rows, row + 4, row + 4 < end, lane);
+    add_row(row, nxt);
+    row += 4;
+    if (row >= end) break;
+    nxt.fetch(rows, row + 4, row + 4 < end, lane);
+    add_row(row, cur);
   }
   // the waves' partial sums are added in wave order
 #pragma unroll
@@ -595,72 +586,51 @@ __device__ __forceinline__ void ln_wide_dx(const float (&xh)[8], const float (&g
 }
 // Rows of more than 1024 elements: a wave per row would need 32 or 64 values of x-hat and g per lane (one or two waves
 // per SIMD, and up to 128 KB of LDS for the cross-wave column sums).  Here the four waves of a workgroup share each
-// row: thread t owns chunks t, t + 256 (MAXW of them), the two row sums cross the waves through LDS (added in wave
+// row: thread t owns chunks t, t + 256, the two row sums cross the waves through LDS (added in wave
 // order), and every column belongs to exactly one thread, which adds its dgamma/dbeta terms over the workgroup's 32
-// rows in row order and writes them to part[g][b][2][d] itself.  16-bit rows are prefetched one row ahead.
-template <typename T, int MAXW>
-__global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const LnBwdArgs a) {
+// rows in row order and writes them to part[g][b][2][d] itself.
+//
+// fp32 rows of up to 2048 elements where this kernel, which asks for a row when it comes to it, is ahead (ln_wide_ahead).
+__global__ __launch_bounds__(256) void ln_bwd_wide_f32_kernel(const LnBwdArgs a) {
 #pragma clang fp contract(off)
   __shared__ float xs[2][4][2];  // [row parity][wave][s1, s2]
   const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nch = a.d >> 3;
-  constexpr bool PF = sizeof(T) == 2;
-  constexpr int RW = sizeof(T) == 2 ? 1 : 2;  // 16-byte pieces per 8 elements
   const float* gamma = a.gamma[g];
-  float ga[MAXW][8], sg[MAXW][8], sb[MAXW][8];
+  float ga[8], sg[8], sb[8];
 #pragma unroll
-  for (int i = 0; i < MAXW; ++i) {
-    const int c = tid + 256 * i;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) sg[i][e] = sb[i][e] = ga[i][e] = 0.f;
-    if (c < nch) ld8<float>(gamma + 8 * c, ga[i]);
-  }
-  uint4 nx[MAXW][RW], ndy[MAXW][RW], nadd[MAXW][RW];
-  float nmu = 0.f, nrstd = 0.f;
+  for (int e = 0; e < 8; ++e) sg[e] = sb[e] = ga[e] = 0.f;
+  if (tid < nch) ld8<float>(gamma + 8 * tid, ga);
   const bool has_add = a.add[g] != nullptr;
-  auto fetch_row = [&](int row) {
-    const uint4* x = reinterpret_cast<const uint4*>(static_cast<const T*>(a.x[g]) + (size_t)row * a.ld);
-    const uint4* dy = reinterpret_cast<const uint4*>(static_cast<const T*>(a.dy[g]) + (size_t)row * a.ld);
-    const uint4* add = has_add ? reinterpret_cast<const uint4*>(static_cast<const T*>(a.add[g]) + (size_t)row * a.ld) : nullptr;
-#pragma unroll
-    for (int i = 0; i < MAXW; ++i) {
-      const int c = tid + 256 * i;
-      if (c < nch) {
-#pragma unroll
-        for (int q = 0; q < RW; ++q) {
-          nx[i][q] = x[c * RW + q];
-          ndy[i][q] = dy[c * RW + q];
-          if (has_add) nadd[i][q] = add[c * RW + q];
-        }
-      }
-    }
-    nmu = a.mean[g][row];
-    nrstd = a.rstd[g][row];
-  };
   const int row0 = blockIdx.x * LN_WIDE_ROWS_PER_WG;
   const int nrow = min(LN_WIDE_ROWS_PER_WG, a.rows - row0);  // the same for every thread: the barriers below are uniform
-  if (PF && nrow > 0) fetch_row(row0);
+  uint4 x[2], dy[2], add[2];
+  float mu = 0.f, rstd = 0.f;
+  auto fetch_row = [&](int row) {
+    const uint4* px = reinterpret_cast<const uint4*>(static_cast<const float*>(a.x[g]) + (size_t)row * a.ld);
+    const uint4* pdy = reinterpret_cast<const uint4*>(static_cast<const float*>(a.dy[g]) + (size_t)row * a.ld);
+    const uint4* padd = has_add ? reinterpret_cast<const uint4*>(static_cast<const float*>(a.add[g]) + (size_t)row * a.ld) : nullptr;
+    if (tid < nch) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        x[q] = px[tid * 2 + q];
+        dy[q] = pdy[tid * 2 + q];
+        if (has_add) add[q] = padd[tid * 2 + q];
+      }
+    }
+    mu = a.mean[g][row];
+    rstd = a.rstd[g][row];
+  };
   for (int r = 0; r < nrow; ++r) {
     const int row = row0 + r;
-    if (!PF) fetch_row(row);
-    uint4 cx[MAXW][RW], cdy[MAXW][RW], cadd[MAXW][RW];
-#pragma unroll
-    for (int i = 0; i < MAXW; ++i)
-#pragma unroll
-      for (int q = 0; q < RW; ++q) { cx[i][q] = nx[i][q]; cdy[i][q] = ndy[i][q]; cadd[i][q] = nadd[i][q]; }
-    const float mu = nmu, rstd = nrstd;
-    if (PF && r + 1 < nrow) fetch_row(row + 1);
-    float xh[MAXW][8], gg[MAXW][8];
+    fetch_row(row);
+    float xh[8], gg[8];
     float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-    for (int i = 0; i < MAXW; ++i) {
-      const int c = tid + 256 * i;
-      if (c < nch) {
-        float xv[8], dv[8];
-        unpack8<T>(cx[i], xv);
-        unpack8<T>(cdy[i], dv);
-        ln_wide_terms(xv, dv, ga[i], mu, rstd, xh[i], gg[i], s1, s2, sg[i], sb[i]);
-      }
+    if (tid < nch) {
+      float xv[8], dv[8];
+      unpack8<float>(x, xv);
+      unpack8<float>(dy, dv);
+      ln_wide_terms(xv, dv, ga, mu, rstd, xh, gg, s1, s2, sg, sb);
     }
     // Two LDS slots by row parity and one barrier per row: a wave can write the slot of row r + 2 only after the
     // barrier of row r + 1, which every wave reaches after it has read the slot of row r.
@@ -678,40 +648,31 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const LnBwdArgs a) {
       t2 += xs[r & 1][w][1];
     }
     const float c1 = t1 / (float)a.d, c2 = t2 / (float)a.d;
-    T* dx = static_cast<T*>(a.dx[g]) + (size_t)row * a.ld;
+    float* dx = static_cast<float*>(a.dx[g]) + (size_t)row * a.ld;
+    if (tid < nch) {
+      float o[8];
+      ln_wide_dx(xh, gg, rstd, c1, c2, o);
+      if (has_add) {
+        float av[8];
+        unpack8<float>(add, av);
 #pragma unroll
-    for (int i = 0; i < MAXW; ++i) {
-      const int c = tid + 256 * i;
-      if (c < nch) {
-        float o[8];
-        ln_wide_dx(xh[i], gg[i], rstd, c1, c2, o);
-        if (has_add) {
-          float av[8];
-          unpack8<T>(cadd[i], av);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] += av[e];
-        }
-        st8<T>(dx + 8 * c, o);
+        for (int e = 0; e < 8; ++e) o[e] += av[e];
       }
+      st8<float>(dx + 8 * tid, o);
     }
   }
   float* part = a.part[g] + (size_t)blockIdx.x * 2 * a.d;
-#pragma unroll
-  for (int i = 0; i < MAXW; ++i) {
-    const int c = tid + 256 * i;
-    if (c < nch) {
-      st8<float>(part + 8 * c, sg[i]);
-      st8<float>(part + a.d + 8 * c, sb[i]);
-    }
+  if (tid < nch) {
+    st8<float>(part + 8 * tid, sg);
+    st8<float>(part + a.d + 8 * tid, sb);
   }
 }
 
-// The same with every row on its way while the one before it is reduced, as in ln_bwd_kernel, and the operands of two rows in turn.  us, before | now,
-// forward pass with it: 2 x [16384, 4096] bf16 350 | 335, 3 x [8000, 1536] 94.9 | 92.1, [2000, 3000] 51.7 | 39.9; fp32 2 x [16384, 4096] 668 | 629,
-// 2 x [4000, 2560] 147 | 105, 2 x [9000, 1288] 138 | 128.  ln_bwd_wide_kernel keeps bf16 matrices that do not start on a word and the fp32 ones where it is
-// ahead (ln_wide_ahead).
+// All others: every row on its way while the one before it is reduced, as in ln_bwd_kernel, and the operands of two rows in turn.  us, a row asked
+// for when it is due (bf16: one ahead, under conditions) | this, forward pass with it: 2 x [16384, 4096] bf16 350 | 335, 3 x [8000, 1536] 94.9 | 92.1,
+// [2000, 3000] 51.7 | 39.9; fp32 2 x [16384, 4096] 668 | 629, 2 x [4000, 2560] 147 | 105, 2 x [9000, 1288] 138 | 128.
 template <typename T, int MAXW>
-__global__ __launch_bounds__(256) void ln_bwd_wide_ahead_kernel(const LnBwdArgs a) {
+__global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const LnBwdArgs a) {
 #pragma clang fp contract(off)
   __shared__ float xs[2][4][2];  // [row parity][wave][s1, s2]
   const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -860,22 +821,14 @@ static hipError_t ln_bwd_pick(const LnBwdArgs& a, hipStream_t s) {
   const size_t lds = (size_t)4 * 8 * a.d;
   // at most one 16-wave workgroup per CU; wide fp32 rows gain nothing when every CU has one
   const long blocks = (long)grid.x * a.G;
-  // accesses through descriptors are of whole words
-  uintptr_t at = 0;
-  for (int g = 0; g < a.G; ++g) at |= (uintptr_t)a.x[g] | (uintptr_t)a.dy[g] | (uintptr_t)a.add[g] | (uintptr_t)a.dx[g];
-  const bool desc = (at & 3) == 0;
   const bool chain = a.d <= 512 && blocks <= 256 && (sizeof(T) == 2 || blocks * a.d <= 96 * 1024);
   if (chain) hipLaunchKernelGGL((ln_bwd_chain_kernel<T>), grid, dim3(1024), 0, s, a);
-  else if (a.d <= 512 && desc) hipLaunchKernelGGL((ln_bwd_kernel<T, 1, true>), grid, dim3(256), lds, s, a);
-  else if (a.d <= 512) hipLaunchKernelGGL((ln_bwd_kernel<T, 1, false>), grid, dim3(256), lds, s, a);
-  else if (sizeof(T) == 2 && a.d <= LN_WAVE_ROW_MAX && desc && ln_four_to_a_cu(blocks))
-    hipLaunchKernelGGL((ln_bwd_kernel<bf16_t, 2, true, true>), grid, dim3(256), lds + 4 * a.d, s, a);
-  else if (a.d <= LN_WAVE_ROW_MAX && desc) hipLaunchKernelGGL((ln_bwd_kernel<T, 2, true>), grid, dim3(256), lds, s, a);
-  else if (a.d <= LN_WAVE_ROW_MAX) hipLaunchKernelGGL((ln_bwd_kernel<T, 2, false>), grid, dim3(256), lds, s, a);
-  else if (a.d <= 2048 && desc && (sizeof(T) == 2 || ln_wide_ahead(blocks, a.d)))
-    hipLaunchKernelGGL((ln_bwd_wide_ahead_kernel<T, 1>), grid, dim3(256), 0, s, a);
+  else if (a.d <= 512) hipLaunchKernelGGL((ln_bwd_kernel<T, 1>), grid, dim3(256), lds, s, a);
+  else if (sizeof(T) == 2 && a.d <= LN_WAVE_ROW_MAX && ln_four_to_a_cu(blocks))
+    hipLaunchKernelGGL((ln_bwd_kernel<bf16_t, 2, true>), grid, dim3(256), lds + 4 * a.d, s, a);
+  else if (a.d <= LN_WAVE_ROW_MAX) hipLaunchKernelGGL((ln_bwd_kernel<T, 2>), grid, dim3(256), lds, s, a);
+  else if (sizeof(T) == 4 && a.d <= 2048 && !ln_wide_ahead(blocks, a.d)) hipLaunchKernelGGL(ln_bwd_wide_f32_kernel, grid, dim3(256), 0, s, a);
   else if (a.d <= 2048) hipLaunchKernelGGL((ln_bwd_wide_kernel<T, 1>), grid, dim3(256), 0, s, a);
-  else if (desc) hipLaunchKernelGGL((ln_bwd_wide_ahead_kernel<T, 2>), grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL((ln_bwd_wide_kernel<T, 2>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }

@@ -477,9 +477,9 @@ def test_layernorm_backward_in_place(torch, ops, dtype, over, G, rows, d):
 @pytest.mark.parametrize("rows,d,ld", [(16449, 184, 192), (16449, 512, 512), (16449, 520, 1040), (57345, 776, 776), (16449, 1016, 1024), (16449, 1800, 1800),
                                        (22529, 2048, 2048), (99, 1032, 1040), (4129, 2056, 2064)])
 def test_layernorm_backward_from_any_address(torch, ops, dtype, with_add, rows, d, ld):
-    """Matrices that start anywhere give the bits of matrices that start on a word (bf16 ones that do not are loaded another way), a third of
-    the rows, which may be another kernel's, has the same dx, the last block of rows holds few of them, and what lies behind a row's end is
-    not written."""
+    """Matrices that start one element behind a 16-byte boundary (bf16: half a word, through the same descriptors) give the bits of matrices that
+    start on one, a third of the rows, which may be another kernel's, has the same dx, the last block of rows holds few of them, and what lies
+    behind a row's end is not written."""
     t = torch.bfloat16 if dtype == "bf16" else torch.float32
     gen = torch.Generator(device="cuda").manual_seed(rows + d)
     src = [torch.randn(rows, ld, generator=gen, device="cuda").to(t) for _ in range(3)]
