@@ -84,9 +84,17 @@ def _tabs(*tables):
     return out
 
 
-def _hp(hp_rows):
-    """Hyper-parameters of all problems as doubles, and their address."""
-    flat = array("d", [x for row in hp_rows for x in row])
+def _hp(hp_rows, problems):
+    """Hyper-parameters of all problems as doubles, six to a problem, and their address: zeros where fewer are given, more are refused."""
+    try:
+        flat = array("d", [x for row in hp_rows for x in row])
+    except TypeError:  # what only float() makes a number of
+        flat = array("d", [float(x) for row in hp_rows for x in row])
+    missing = 6 * problems - len(flat)
+    if missing:
+        if missing < 0:
+            raise IndexError(f"{len(flat)} hyper-parameters for {problems} problems")
+        flat.extend([0.0] * missing)
     return flat, flat.buffer_info()[0]
 
 
@@ -122,7 +130,7 @@ def hydra_op_gemm_update(dtype, M, N, K, X, W, opt, p, m, v, w16, hp_rows, *, ld
     keep, tx, tw, to, tr, ts, tp, tm, tv, t16 = _tabs(X, W, out, rowsum, ws, p, m, v, w16)
     d = _desc(dtype, M, N, K, 0, 0, ldx, ldw, ldo, 0, 0, EPI_NONE, 1, tile, len(X), tx or 0, tw or 0, 0, to or 0, 0, 0, 0, tr or 0, ts or 0,
               _nbytes(ws))
-    flat, hp = _hp(hp_rows)
+    flat, hp = _hp(hp_rows, len(p))
     _check(_L().hydra_op_gemm_update(d, opt, tp, tm, tv, t16, hp, _stream()))
 
 
@@ -156,7 +164,7 @@ def hydra_op_softmax_ce(dtype, M, Cn, ldz, lddz, inv_n, logits, labels, dz, rowl
 def hydra_op_optim(opt, n, p, g, m, v, w16, hp_rows):
     """hp_rows: per problem (lr, b1, b2, eps, bc1, bc2)."""
     keep, *at = _tabs(p, g, m, v, w16)
-    flat, hp = _hp(hp_rows)
+    flat, hp = _hp(hp_rows, len(p))
     _check(_L().hydra_op_optim(opt, n, len(p), *at, hp, _stream()))
 
 

@@ -538,6 +538,43 @@ def test_packed_descriptors_have_the_fields_of_hydra_gemm_desc():
     assert [getattr(x, n) for n, _ in x._fields_] == list(range(1, 16)) + list(range(2 ** 47, 2 ** 47 + 9)) + [2 ** 40]
 
 
+def test_updates_are_given_six_hyper_parameters_to_a_problem(monkeypatch):
+    """The library reads six doubles to a problem: fewer are filled up with zeros, so that it does not read past them, and more are refused."""
+    import ctypes as C
+    from paper_2107_06469_amd import ops
+
+    got = []
+
+    class Library:
+        def hydra_op_optim(self, opt, n, G, p, g, m, v, w16, hp, stream):
+            got.append(list((C.c_double * (6 * G)).from_address(hp)))
+            return 0
+
+        def hydra_op_gemm_update(self, d, opt, p, m, v, w16, hp, stream):
+            got.append(list((C.c_double * 12).from_address(hp)))
+            return 0
+
+    class T:
+        def data_ptr(self):
+            return 4096
+
+    monkeypatch.setattr(ops, "_L", Library)
+    monkeypatch.setattr(ops, "_stream", lambda: 0)
+    two, calls = [T(), T()], []
+    calls.append(lambda hp: ops.hydra_op_optim(0, 8, two, two, None, None, None, hp))
+    calls.append(lambda hp: ops.hydra_op_gemm_update(ops.F32, 8, 8, 8, two, two, 0, two, None, None, None, hp, ldx=8, ldw=8, ldo=8))
+    for call in calls:
+        for hp, want in (([(1e-3,), ("0.5",)], [1e-3, 0.5] + [0.0] * 10), ([], [0.0] * 12), ([range(1, 7), range(7, 13)], list(range(1, 13)))):
+            flat, _ = ops._hp(hp, 2)
+            assert len(flat) == 12                 # before the address is read from
+            call(hp)
+            assert got.pop() == want
+        for hp in ([range(6)] * 3, [range(13), ()]):
+            with pytest.raises(IndexError):
+                call(hp)
+        assert not got
+
+
 def test_layernorm_s_multiply_adds_are_written_out(tmp_path):
     """Which LayerNorm kernel runs depends on how many problems share a launch, and the bits must not: no product is left to the compiler to join
     with a sum, so that every kernel has the same multiply-adds, products and sums whether it may join them or not."""
