@@ -34,9 +34,9 @@ def _L():
     global _ready
     L = lib()
     if not _ready:
-        vp = pp = C.c_void_p                       # tables go by address
-        L.hydra_op_gemm.argtypes = [C.c_char_p, vp]
-        L.hydra_op_gemm_update.argtypes = [C.c_char_p, C.c_int, pp, pp, pp, pp, vp, vp]
+        vp = pp = C.c_void_p                       # tables go by address, descriptors as bytes or by reference
+        L.hydra_op_gemm.argtypes = [vp, vp]
+        L.hydra_op_gemm_update.argtypes = [vp, C.c_int, pp, pp, pp, pp, vp, vp]
         L.hydra_op_colsum.argtypes = [C.c_int] * 5 + [pp, pp, pp, vp]
         L.hydra_op_colsum_part_floats.argtypes = [C.c_int, C.c_int]
         L.hydra_op_colsum_part_floats.restype = C.c_size_t

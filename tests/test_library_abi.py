@@ -538,6 +538,18 @@ def test_packed_descriptors_have_the_fields_of_hydra_gemm_desc():
     assert [getattr(x, n) for n, _ in x._fields_] == list(range(1, 16)) + list(range(2 ** 47, 2 ** 47 + 9)) + [2 ** 40]
 
 
+def test_descriptors_go_by_reference_or_as_bytes():
+    """The library's own entry points take a hydra_gemm_desc by reference, a pointer to one, or its bytes (an empty one is refused by the library, before
+    it asks for a device)."""
+    import ctypes as C
+    from paper_2107_06469_amd import ops
+
+    L, d = ops._L(), ops.hydra_gemm_desc()
+    for x in (C.byref(d), C.pointer(d), bytes(d), None):
+        assert L.hydra_op_gemm(x, None) == 1 and b"NULL table" in L.hydra_ops_last_error()
+        assert L.hydra_op_gemm_update(x, 0, None, None, None, None, (C.c_double * 6)(), None) == 1
+
+
 def test_updates_are_given_six_hyper_parameters_to_a_problem(monkeypatch):
     """The library reads six doubles to a problem: fewer are filled up with zeros, so that it does not read past them, and more are refused."""
     import ctypes as C
