@@ -1491,6 +1491,7 @@ __global__ __launch_bounds__(256) void gemm_small_f32_kernel(const GemmArgs a, c
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1, r16 = lane & 15, q = lane >> 4;
   const int g = blockIdx.z, m0 = blockIdx.x * BM, n0 = blockIdx.y * BN, K = a.K;
+  if (NS == 1 && m0 >= a.M) return;  // f32_update_tile_rows
   RX ox;
   RW ow;
   ox.init(static_cast<const T*>(a.X[g]), a.ldx, m0, a.M, K, wave, lane);
@@ -1707,7 +1708,9 @@ struct SmallTile {
   }
   template <bool XK, bool WK, bool UPD, typename U>
   static hipError_t go(const GemmArgs& a, const U& u, hipStream_t s) {
-    hipLaunchKernelGGL((kernel<XK, WK, UPD>()), dim3((a.M + BT - 1) / BT, (a.N + BT - 1) / BT, a.G), dim3(256), LDS, s, a, u);
+    long high = (a.M + BT - 1) / BT;
+    if constexpr (UPD && NS == 1) high = f32_update_tile_rows(high, a.ldo, u.opt == 1);
+    hipLaunchKernelGGL((kernel<XK, WK, UPD>()), dim3((unsigned)high, (a.N + BT - 1) / BT, a.G), dim3(256), LDS, s, a, u);
     return hipGetLastError();
   }
   static hipError_t run(const GemmArgs& a, hipStream_t s) {
@@ -2089,18 +2092,15 @@ int choose_tile(const GemmArgs& a) {
 }
 
 // Weight gradient with the update: the epilogue moves 14-26 bytes per output element, the k-loop is as long as the batch.
-int choose_update_tile(const GemmArgs& a) {
+int choose_update_tile(const GemmArgs& a, bool adam) {
   if (a.tile) return a.tile;
   auto tiles = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.G; };
   const long big = tiles(256, 256);
   const bool small = small_eligible(a);
   if (a.dtype == GEMM_F32) {
     // 32x32 tiles are ahead until there are many of them over a short sum (us, 32x32 | 128x128 | 32x128: 2400 tiles, K = 256 25 | 41 | 32;
-    // 2048 tiles, K = 2048 89 | 161 | 106).  Up to 64 rows the one-stage kernel is ahead of 32x128 tiles, too (SGD and Adam, 2400 tiles, K = 8
-    // 8.2 | 8.3 and 12.4 | 16.5, K = 48 8.3 | 9.9 and 12.5 | 18.8; 1200 tiles, K = 16 5.3 | 5.9; 4050 tiles 20.7 | 21.7) but where rows
-    // of the state lie 2 KB apart (2048 tiles of 512 x 512, K = 16 12.0 | 9.6, K = 32 12.6 | 12.0, K = 64 12.4 | 13.4 with two stages).
-    const long sm = tiles(32, 32);
-    if (small && (sm <= 1024 || (sm <= 4096 && (a.K > 32 || a.ldo % 512)))) return TILE_SMALL;
+    // 2048 tiles, K = 2048 89 | 161 | 106)
+    if (small && f32_update_few(tiles(32, 32), (a.M + 31) / 32, tiles(32, 128), a.ldo, a.K, adam)) return TILE_SMALL;
     if (big < 192) return 3;
   } else {
     // 64x64 tiles: the state of a tile is small enough to hide behind the other workgroups' k-loops (us, 64x64 | 128x128:
@@ -2129,7 +2129,7 @@ int choose_update_tile(const GemmArgs& a) {
 template <typename T>
 hipError_t dispatch_update(const GemmArgs& a, const GemmUpdate& u, hipStream_t s) {
   if (const int S = split_for(a); S > 1) return run_split(a, &u, S, s);
-  const int tile = choose_update_tile(a);
+  const int tile = choose_update_tile(a, u.opt == 1);
   if constexpr (sizeof(T) == 2) {
     if (tile == TILE_SMALL) return SmallBf16::run_update(a, u, s);
     if (tile == TILE_SMALL_DEEP) return SmallBf16Deep::run_update(a, u, s);
@@ -2181,7 +2181,7 @@ hipError_t run_pair(const GemmArgs& d, const GemmArgs& w, const GemmUpdate& u, h
   gr.d_tm = (d.M + 63) / 64; gr.d_tn = (d.N + 63) / 64; gr.r_dtm = rcp(gr.d_tm); gr.r_dtn = rcp(gr.d_tn);
   const dim3 grid(gr.n_w + (unsigned)pair_side(d));
   static_assert(SmallBf16::LDS == SmallBf16Deep::LDS, "one LDS size for both sides");
-  if (choose_update_tile(w) == TILE_SMALL)
+  if (choose_update_tile(w, u.opt == 1) == TILE_SMALL)
     hipLaunchKernelGGL((gemm_small_pair_kernel<16, 2>), grid, dim3(256), SmallBf16::LDS, s, d, w, u, gr);
   else
     hipLaunchKernelGGL((gemm_small_pair_kernel<8, 4>), grid, dim3(256), SmallBf16::LDS, s, d, w, u, gr);
@@ -2289,7 +2289,7 @@ hipError_t launch_gemm_update(const GemmArgs& a, const GemmUpdate& u, hipStream_
 
 bool gemm_pair_waits(const GemmArgs& w) {
   if (w.dtype != GEMM_BF16 || w.tile || split_for(w) > 1) return false;
-  const int t = choose_update_tile(w);
+  const int t = choose_update_tile(w, true);  // bf16: the optimizer does not matter
   return t == TILE_SMALL || t == TILE_SMALL_DEEP;
 }
 // The update takes 64x64 tiles by its own rule; the input gradient does too, or would take 128x128 ones.  us, one after the other | as one launch

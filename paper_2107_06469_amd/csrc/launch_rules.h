@@ -44,6 +44,37 @@ inline bool mid_tiles_for_long_update(long big, long mid, int K) {
   return tile_passes(big) > 1 && K <= 8192;
 }
 
+// ---- fp32 weight gradients with an update over fewer than 64 rows: 32x32 tiles in one stage or 32x128 ones -------------------------------
+// Rows of the state that are no whole number of 128-byte lines: neighbours along a row share the lines at their seam, through one L2 only if they run
+// on one XCD, ids a multiple of 8 apart.  32x32 tiles are numbered down the columns, so their grid is made that high (workgroups past the
+// matrix end at once), if these are half as many as the others at most, for SGD, which moves a third of Adam's bytes, fewer than a third
+// (2 x [547 x 2128] of 18 tile rows 9.5 | 9.9 and 16.4 | 15.2, 10 x [320 x 496] of 10 Adam 13.1 | 13.8).  us, SGD and Adam, as it is | so: 1 x [1742 x 792], K = 32 8.3 | 5.9 and 13.7 | 9.6; 2 x [1616 x 712], 32
+// 11.1 | 8.6 and 19.5 | 13.2; 3 x [800 x 1000], 16 11.2 | 9.1 and 19.8 | 14.3; of 3 and 4 tile rows 12.2 | 22.1 and 9.8 | 11.1.  Whole lines gain nothing and
+// pay for the empty workgroups (4 x [784 x 768], 8 8.8 | 9.5 and 14.1 | 15.8).
+inline long f32_update_tile_rows(long rows, int ldo, bool adam) {
+  const long high = (rows + 7) / 8 * 8;
+  return ldo % 32 && rows > 8 && (adam ? 2 * high <= 3 * rows : 3 * high < 4 * rows) ? high : rows;
+}
+// tiles: of 32x32; rows: tile rows of a problem.  us, 32x128 | 32x32, six sets of buffers in turn:
+//   seams   SGD 1 x [1750 x 584], K = 32 7.2 | 5.0, 2 x [1616 x 712], 32 9.4 | 8.6, 4 x [1158 x 560], 16 9.3 | 9.2, 9 x [554 x 760] (a third of the grid past the
+//     matrix), 16 11.8 | 12.9;  Adam 13 | 8, 21 | 13, 19 | 14, 33 | 29;  few tile rows, 8 x [100 x 1944], 32 7.6 | 9.8 and 14.4 | 16.3; nine to twelve, 16 with those past the
+//     matrix, SGD 32x128 ahead by 3 to 10 %, Adam 11 % ahead to 35 % behind; 120 random shapes by this rule, 1 to 63 rows: 1.06 and 1.09 times
+//     as fast as 32x128 tiles on average, 0.97 at worst
+//   whole lines, up to 32 rows   SGD 1280 tiles 6.8 | 5.6, 1600 6.7 | 6.9, 2048 7.2 | 7.6, 2400 8.3 | 8.8, 4096 11 | 12;  Adam 1280 11.4 | 9.4, 1600 12.4 | 11.2, 2048 (two
+//     full passes of 32x128) 12.6 | 12.7 and 13.1 | 13.7, 2400 16.2 | 14.1, 2808 16.6 | 16.3, 3072 16.7 | 17.5, 4096 23 | 25
+//   whole lines, 33 to 63 rows   SGD 2400 tiles 10.1 | 9.0, 3584 12.7 | 11.7;  Adam 18.5 | 14.7 and 24.0 | 23.6, 2048 (full passes, K = 60)
+//     32x128 ahead by 6 %, 3072 19 | 21, 3696 24 | 26
+inline bool f32_update_few(long tiles, long rows, long wide, int ldo, int K, bool adam) {
+  if (tiles <= 1024 || tiles > 4096) return tiles <= 1024;
+  if (K >= 64) return true;
+  if (ldo % 32) {
+    const long high = f32_update_tile_rows(rows, ldo, adam), grid = tiles / rows * high;
+    return high % 8 == 0 && (adam ? grid <= 5376 : K > 32 || grid <= (high > rows ? 3200 : 4096));
+  }
+  if (adam) return tiles <= 2816 && (wide - 1) % 256 < (K > 32 ? 255 : 240);
+  return K > 32 || tiles <= 1600;
+}
+
 // ---- launches that two products share ---------------------------------------------------------------------------------------------
 // A weight gradient with its update, n_w tiles of 64x64 over k_w rows, and an input gradient, n_d such tiles over k_d, as one launch of them.
 // 512 tiles run at a time.  d_small: the input gradient takes 64x64 tiles alone, too; then the launch is never slower (2531 measured pairs of up

@@ -761,10 +761,11 @@ def test_k_rows_megabytes_apart(torch, ops, dtype, K, ld, tile):
 
 
 @pytest.mark.parametrize("opt", [0, 1])
-@pytest.mark.parametrize("M,N,K", [(520, 544, 1), (545, 528, 17), (513, 552, 63), (520, 544, 64), (512, 512, 33), (512, 512, 32), (520, 544, 65)])
+@pytest.mark.parametrize("M,N,K", [(520, 544, 1), (545, 528, 17), (513, 552, 63), (520, 544, 64), (1024, 512, 33), (1024, 512, 32), (520, 544, 65)])
 def test_fp32_updates_over_a_small_batch(torch, ops, M, N, K, opt):
     """Weight gradients of more than 1024 32x32 tiles over up to 64 rows take a kernel of one stage that reads the state ahead: the bits of the
-    32x128 tiles, at the edges of tiles and on either side of both limits."""
+    32x128 tiles, at the edges of tiles, in grids as high as the matrix and higher (rows that end inside a line), and on either side of the
+    limits of 64 rows and, where a pass is full, of 32."""
     G, gen = 4, torch.Generator(device="cuda").manual_seed(M + N + K)
     mk = lambda *sh: torch.randn(*sh, generator=gen, device="cuda")  # noqa: E731
     ldm = (M + 7) // 8 * 8
