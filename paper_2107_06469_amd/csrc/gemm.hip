@@ -157,17 +157,18 @@ struct LoaderT {
   static constexpr int N_LOAD = NBT * KR, N_STORE = NBT * E;
   static constexpr int OW = KR * (int)sizeof(T) / 4;            // dwords written per output row (4, 2 or 1)
   uint4 r[NBT][KR];
-  // Buffer loads: the descriptor starts at element (k0, row0) and ends with k row K-1, so k rows past K
-  // read as zero without a guard.  Tile rows past the matrix read whatever follows (padding or the next
-  // k row, zero behind the last one); they only feed outputs that are never stored.
+  // Buffer loads: the descriptor starts at element (k0, row0) and ends after k row K-1, so k rows past K
+  // read as zero without a guard.  Tile rows past the matrix are sent out of range: behind the last k row the operand's buffer may end (columns
+  // of a wider matrix).  (A descriptor that ends there, as the ring's does, costs the loop scalar registers that the 256x256 tile does not
+  // have: a spill and 4 %, 5 x [548 x 3296] fp32 over 2996 rows with Adam 780 | 812 us.)
   __device__ __forceinline__ void load(const T* base, int ld, int row0, int nrows, int k0, int K, int tid) {
     const long first = ((long)k0 * ld + row0) * (long)sizeof(T);
-    const __amdgpu_buffer_rsrc_t rs = tile_rsrc(base, first, k_slow_bytes(K, ld, nrows, sizeof(T)));
+    const __amdgpu_buffer_rsrc_t rs = tile_rsrc(base, first, (long)K * ld * (long)sizeof(T));
 #pragma unroll
     for (int i = 0; i < NBT; ++i) {
       const int u = tid + NT * i, half = (u / LO) % SPLIT, rest = u / (LO * SPLIT);
       const int mb = u % LO + LO * (rest % (RB / LO)), kb = rest / (RB / LO);
-      const unsigned voff = ((unsigned)(kb * E + half * KR) * (unsigned)ld + (unsigned)(mb * E)) * (unsigned)sizeof(T);
+      const unsigned voff = row0 + mb * E < nrows ? ((unsigned)(kb * E + half * KR) * (unsigned)ld + (unsigned)(mb * E)) * (unsigned)sizeof(T) : 0x80000000u;
 #pragma unroll
       for (int j = 0; j < KR; ++j) {
         const unsigned off = u < NU ? voff + (unsigned)j * (unsigned)ld * (unsigned)sizeof(T) : 0xfffffff0u;
