@@ -739,10 +739,29 @@ def test_tiles_of_a_thin_last_pass_give_the_same_bits(torch, ops, G, M, N, K):
     assert all(torch.equal(a, c) for a, c in zip(*got))
 
 
+@pytest.mark.parametrize("tile", [0, 1, 2])
+@pytest.mark.parametrize("ld", [4067192, 4067208, 6000000])
+def test_k_rows_megabytes_apart(torch, ops, ld, tile):
+    """Operands whose k-rows lie 8 to 12 MB apart give the bits of packed ones, by every kernel that takes them."""
+    M, N, K = 72, 80, 13
+    gen = torch.Generator(device="cuda").manual_seed(ld + tile)
+    x, w = (torch.randn(K, n, generator=gen, device="cuda").to(torch.bfloat16) for n in (M, N))
+    got = []
+    for far in (False, True):
+        lx, lw = (ld, ld) if far else (M, N)
+        xs, ws = (torch.full((K, n), 7.0, device="cuda", dtype=torch.bfloat16) for n in (lx, lw))
+        xs[:, :M], ws[:, :N] = x, w
+        out, rs = torch.zeros(M, N, device="cuda"), torch.zeros(M, device="cuda")
+        ops.hydra_op_gemm(ops.BF16, M, N, K, [xs], [ws], [out], x_kmajor=False, w_kmajor=False, ldx=lx, ldw=lw, ldo=N, out_f32=True,
+                          rowsum=[rs], tile=tile)
+        got.append((out, rs))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
 @pytest.mark.parametrize("dtype,K,ld,tile", [("bf16", 13, 6000000, 0), ("bf16", 13, 17200000, 0),  # sub-tiles of 128 k: row 125 comes round
                                              ("bf16", 5, 70000000, 0), ("bf16", 5, 70000000, 1), ("bf16", 5, 70000000, 2),  # 32 k: row 31
                                              ("f32", 5, 17200000, 0)])  # 64 k: row 63
-def test_k_rows_megabytes_apart(torch, ops, dtype, K, ld, tile):
+def test_k_rows_past_the_sum_do_not_come_round(torch, ops, dtype, K, ld, tile):
     """The last sub-tile's k-rows past K, whose offsets would pass 32 bits and come round to rows that are there (filled with sevens beside the
     operand), add nothing: the bits of packed operands."""
     M, N, t, dt = 72, 80, torch.float32 if dtype == "f32" else torch.bfloat16, ops.F32 if dtype == "f32" else ops.BF16
@@ -761,11 +780,10 @@ def test_k_rows_megabytes_apart(torch, ops, dtype, K, ld, tile):
 
 
 @pytest.mark.parametrize("opt", [0, 1])
-@pytest.mark.parametrize("M,N,K", [(520, 544, 1), (545, 528, 17), (513, 552, 63), (520, 544, 64), (1024, 512, 33), (1024, 512, 32), (520, 544, 65)])
+@pytest.mark.parametrize("M,N,K", [(520, 544, 1), (545, 528, 17), (513, 552, 63), (520, 544, 64), (512, 512, 33), (512, 512, 32), (520, 544, 65)])
 def test_fp32_updates_over_a_small_batch(torch, ops, M, N, K, opt):
     """Weight gradients of more than 1024 32x32 tiles over up to 64 rows take a kernel of one stage that reads the state ahead: the bits of the
-    32x128 tiles, at the edges of tiles, in grids as high as the matrix and higher (rows that end inside a line), and on either side of the
-    limits of 64 rows and, where a pass is full, of 32."""
+    32x128 tiles, at the edges of tiles and on either side of both limits."""
     G, gen = 4, torch.Generator(device="cuda").manual_seed(M + N + K)
     mk = lambda *sh: torch.randn(*sh, generator=gen, device="cuda")  # noqa: E731
     ldm = (M + 7) // 8 * 8
@@ -783,3 +801,10 @@ def test_fp32_updates_over_a_small_batch(torch, ops, M, N, K, opt):
     if opt == 0:  # one chain of K products, its rounding and the update's: (K + 2) 2^-24 of the sum's terms
         bound = (K + 2) * EPS32 * (hp[0][0] * (dy[0][:, :M].double().abs().t() @ x[0].double().abs()) + state[0][0].double().abs())
         assert ((got[0][0].double() - want).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("opt", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(1024, 512, 33), (1024, 512, 32)])
+def test_fp32_updates_over_a_small_batch_in_full_passes(torch, ops, M, N, K, opt):
+    """The same on either side of 32 rows, where a pass of 32x128 tiles is full."""
+    test_fp32_updates_over_a_small_batch(torch, ops, M, N, K, opt)
