@@ -107,6 +107,9 @@ template <int DH>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_at(const bf16_t* first, int rows, int ld) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(first), 0, span_of<DH>(min(rows, 32), ld), 0x00020000);
 }
+// A lane's row, from a tile's or a block's first, for offsets into such descriptors.  Past a sequence shorter than 64 rows it is the end of the
+// sequence: attn_ok bounds that many rows only, and the offsets of more than those come round to rows that are there.
+__device__ __forceinline__ unsigned row_or_end(int row, int S) { return (unsigned)min(row, S); }
 __device__ __forceinline__ uint4 row_chunk(__amdgpu_buffer_rsrc_t rs, unsigned voff) {
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, 0, 0));
 }
@@ -132,11 +135,11 @@ template <int DH, bool ONE = false, bool SETTLE = false>
 struct TileDma {
   static constexpr int NCH = DH / 8, N = 64 * NCH / 256, STEP = 256 / NCH;  // loads per wave, rows between them
   unsigned voff[ONE ? 1 : N];
-  __device__ __forceinline__ void init(int ld, int wave, int lane) {
+  __device__ __forceinline__ void init(int ld, int S, int wave, int lane) {
 #pragma unroll
     for (int i = 0; i < (ONE ? 1 : N); ++i) {
       const int sl = (4 * i + wave) * 64 + lane, row = sl / NCH;
-      voff[i] = ((unsigned)row * (unsigned)ld + (unsigned)((sl % NCH) ^ swz<DH>(row)) * 8u) * 2u;
+      voff[i] = (row_or_end(row, S) * (unsigned)ld + (unsigned)((sl % NCH) ^ swz<DH>(row)) * 8u) * 2u;
     }
   }
   // first: the tile's first row at the head's columns; rows: how many there are from it on (at least one)
@@ -263,8 +266,8 @@ __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const A
   const int d = a.H * DH, ld = a.ld_qkv;
   const float sc = a.scale * LOG2E;
   TileDma<DH> dma;
-  dma.init(ld, wave, lane);
-  const unsigned lds0 = lds_byte_addr(lds), q_off = (unsigned)li * (unsigned)ld * 2u + 16u * g;
+  dma.init(ld, a.S, wave, lane);
+  const unsigned lds0 = lds_byte_addr(lds), q_off = row_or_end(li, a.S) * (unsigned)ld * 2u + 16u * g;
   auto fetch = [&](const bf16_t* k, int rows, unsigned buf) {  // k: the tile's first key
     dma.issue(k, rows, ld, lds0 + buf, wave);
     dma.issue(k + d, rows, ld, lds0 + buf + 64 * NCH * 16, wave);
@@ -371,7 +374,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const A
     const float inv = 1.f / l_run;
     const __amdgpu_buffer_rsrc_t o_rows = rows_at<DH>(a.o[item.gi] + ((size_t)item.b * a.S + row0) * a.ld_o + item.h * DH, a.S - row0, a.ld_o);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) store_block(oacc[c], inv, o_rows, (unsigned)li * (unsigned)a.ld_o * 2u + c * 64u, g);
+    for (int c = 0; c < NC; ++c) store_block(oacc[c], inv, o_rows, row_or_end(li, a.S) * (unsigned)a.ld_o * 2u + c * 64u, g);
     store_stat((m_run + log2f(l_run)) * LN2, a.lse[item.gi] + (size_t)item.bh * a.S + row0, a.S - row0, li, g);
     item.blk = item.then, item.then = -1;
     begin();
@@ -411,7 +414,7 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, const AttnGrid& gr
   const int d = a.H * DH, ld = a.ld_qkv;
   const float sc = a.scale * LOG2E;
   TileDma<DH, false, SETTLE> dma;
-  dma.init(ld, wave, lane);
+  dma.init(ld, a.S, wave, lane);
   const unsigned lds0 = lds_byte_addr(lds);
   // every pointer at once, so that their loads are one wait
   const size_t seq = (size_t)item.b * a.S;
@@ -434,8 +437,8 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, const AttnGrid& gr
     const bf16_t* const orow = obase + (size_t)min(row0 + li, a.S - 1) * a.ld_o + 8 * g;  // past the end: a row whose products nobody stores
 #pragma unroll
     for (int kk = 0; kk < NK; ++kk) {
-      qf[kk] = row_chunk(q_rows, (unsigned)li * (unsigned)ld * 2u + 32u * kk + 16u * g);
-      dof[kk] = row_chunk(do_rows, (unsigned)li * (unsigned)a.ld_o * 2u + 32u * kk + 16u * g);
+      qf[kk] = row_chunk(q_rows, row_or_end(li, a.S) * (unsigned)ld * 2u + 32u * kk + 16u * g);
+      dof[kk] = row_chunk(do_rows, row_or_end(li, a.S) * (unsigned)a.ld_o * 2u + 32u * kk + 16u * g);
       of[kk] = *reinterpret_cast<const uint4*>(orow + 16 * kk);
     }
     const __amdgpu_buffer_rsrc_t lse_rows =
@@ -504,7 +507,7 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, const AttnGrid& gr
     if (!last) return true;
     const __amdgpu_buffer_rsrc_t dq_rows = rows_at<DH>(dqbase + (size_t)row0 * ld, a.S - row0, ld);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) store_block(acc[c], a.scale, dq_rows, (unsigned)li * (unsigned)ld * 2u + c * 64u, g);
+    for (int c = 0; c < NC; ++c) store_block(acc[c], a.scale, dq_rows, row_or_end(li, a.S) * (unsigned)ld * 2u + c * 64u, g);
     store_stat(delta, delta_out + row0, a.S - row0, li, g);
     item.blk = item.then, item.then = -1;
     t = 0;
@@ -541,9 +544,9 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, const AttnGrid& g
   const int d = a.H * DH, ld = a.ld_qkv, n_tiles = (a.S + 63) / 64;
   const float sc = a.scale * LOG2E;
   TileDma<DH, DH == 128, OWN> dma_q, dma_o;
-  dma_q.init(ld, wave, lane);
-  dma_o.init(a.ld_o, wave, lane);
-  const unsigned lds0 = lds_byte_addr(lds), row_off = (unsigned)li * (unsigned)ld * 2u + 16u * g;
+  dma_q.init(ld, a.S, wave, lane);
+  dma_o.init(a.ld_o, a.S, wave, lane);
+  const unsigned lds0 = lds_byte_addr(lds), row_off = row_or_end(li, a.S) * (unsigned)ld * 2u + 16u * g;
   const size_t seq = (size_t)item.b * a.S;
   const bf16_t* const base = a.qkv[item.gi] + seq * ld + item.h * DH;
   const bf16_t* const dobase = a.dout[item.gi] + seq * a.ld_o + item.h * DH;
@@ -666,8 +669,8 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, const AttnGrid& g
     const __amdgpu_buffer_rsrc_t dk_rows = rows_at<DH>(ok, a.S - row0, ld), dv_rows = rows_at<DH>(ok + d, a.S - row0, ld);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      store_block(dk[c], a.scale, dk_rows, (unsigned)li * (unsigned)ld * 2u + c * 64u, g);
-      store_block(dv[c], 1.f, dv_rows, (unsigned)li * (unsigned)ld * 2u + c * 64u, g);
+      store_block(dk[c], a.scale, dk_rows, row_or_end(li, a.S) * (unsigned)ld * 2u + c * 64u, g);
+      store_block(dv[c], 1.f, dv_rows, row_or_end(li, a.S) * (unsigned)ld * 2u + c * 64u, g);
     }
     item.blk = item.then, item.then = -1;
     t = first_tile(item.blk);

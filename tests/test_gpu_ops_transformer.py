@@ -273,6 +273,27 @@ def test_attention_reads_nothing_past_its_sequence(torch, ops, S, DH, causal):
         assert (lse[h * S:(h + 1) * S].double() - ls).abs().max() <= 1e-5
 
 
+@pytest.mark.parametrize("S,H,DH,ld", [(3, 1, 64, 2 ** 27), (3, 1, 128, 2 ** 27), (5, 1, 64, 2 ** 26 + 8), (1, 2, 128, 2 ** 28), (3, 257, 64, 2 ** 27),
+                                       (3, 161, 128, 2 ** 27)])
+def test_attention_rows_of_a_short_sequence_far_apart(torch, ops, S, H, DH, ld):
+    """Rows of some hundred megabytes: offsets of a block's rows past the sequence would come round to rows that are there.  The bits of packed matrices,
+    and nothing but the heads' own columns is written, with both halves of the backward pass in one launch and in two."""
+    d, gen = H * DH, torch.Generator(device="cuda").manual_seed(S + DH)
+    qkv0, do0 = (torch.randn(S, n, generator=gen, device="cuda").to(torch.bfloat16) for n in (3 * d, d))
+    got = []
+    for far in (False, True):
+        lq, lo = (ld, ld) if far else (3 * d, d)
+        qkv, dqkv, o, do = (torch.full((S, n), float("nan"), device="cuda", dtype=torch.bfloat16) for n in (lq, lq, lo, lo))
+        qkv[:, :3 * d], do[:, :d] = qkv0, do0
+        lse, delta = torch.zeros(S * H, device="cuda"), torch.zeros(S * H, device="cuda")
+        ops.hydra_op_attention_fwd(1, S, H, DH, lq, lo, True, DH ** -0.5, [qkv], [o], [lse])
+        ops.hydra_op_attention_bwd(1, S, H, DH, lq, lo, True, DH ** -0.5, [qkv], [o], [do], [lse], [delta], [dqkv])
+        assert torch.isnan(o[:, d:]).all() and torch.isnan(dqkv[:, 3 * d:]).all()
+        got.append((o[:, :d].clone(), dqkv[:, :3 * d].clone(), lse, delta))
+        assert all(torch.isfinite(x).all() for x in got[-1])
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
 @pytest.mark.parametrize("B,S,H,DH,causal", [(1, 200, 2, 64, False), (2, 77, 3, 64, True), (1, 300, 2, 128, True), (3, 64, 1, 128, False)])
 def test_attention_backward_in_one_launch_equals_two(torch, ops, B, S, H, DH, causal):
     """Small launches run both halves of the backward pass as one kernel; the same problem in a group too large for that must give
