@@ -101,11 +101,15 @@ inline bool pair_ahead(long n_d, long n_w, bool d_small, int k_d, int k_w) {
 // 205 | 208, 2340 level.
 inline bool ln_four_to_a_cu(long blocks) { return blocks > 768 && blocks <= 1024; }
 
-// fp32 rows of 1024 to 2048 elements, 32 to a workgroup: the next row asked for ahead (ln_bwd_wide_kernel), or not (ln_bwd_wide_f32_kernel).  Rows of 8 KB are ahead
-// without where a few CUs hold a third workgroup (why was not found: the waits, the order of the loads and the descriptors alone are not it).  us, not |
-// ahead, forward pass with it: d = 2048, 125 blocks 69.6 | 52.6, 250 87.9 | 80.4, 512 168.4 | 161.5, 532 176.7 | 188.4, 564 185.5 | 196.4, 626 201.6 | 206.6,
-// 750 242.2 | 238.9, 1024 325.7 | 322.5; 564 blocks, d = 2040 193.7 | 199.9, 1536 150.9 | 147.4, 1288 138.5 | 127.7.
-inline bool ln_wide_ahead(long blocks, int d) { return d <= 1792 || blocks <= 512 || blocks > 704; }
+// fp32 rows of 1024 to 2048 elements, 32 to a workgroup: the next row asked for ahead (ln_bwd_wide_kernel), or not (ln_bwd_wide_f32_kernel).  Up to
+// two workgroups to a CU are ahead with it.  From there to two and a half, where few CUs hold a third one, those few are waited for (two
+// that ask ahead fill a CU's share of the memory, it seems: 512 to 514 blocks 110 -> 134 us at d = 2048); without it a workgroup goes at the pace of its own
+// waits, whatever stands beside it.  us, not | ahead, backward pass of two problems, 512, 514, 564, 596, 626 and 656 blocks:
+//   d = 2048  119 | 110, 122 | 134, 133 | 141, 134 | 141, 139 | 147, 146 | 147;  712 158 | 153
+//        1792  106 | 100, 109 | 118, 119 | 124, 121 | 125, 124 | 127, 132 | 131
+//        1536  92 | 86, 98 | 103, 105 | 108, 107 | 109, level, 114 | 112, and with the forward pass 564 151 | 147: the line lies here
+//        1288  14, 2, 4, 5, 6 and 7 % behind without;  1032  20 to 30 % behind
+inline bool ln_wide_ahead(long blocks, int d) { return d <= 1536 || blocks <= 512 || blocks > 640; }
 
 // ---- attention under a causal mask: two row blocks of a head to a workgroup, or one --------------------------------------------------
 // `blocks` 128-row blocks in all, n_blk to a head; per_cu: workgroups that fit a CU.  One to a workgroup suffers most where the blocks of a

@@ -73,6 +73,11 @@ def test_layernorm_backward_of_wide_fp32_rows_asks_for_the_next_row_unless_a_few
     assert _chosen(tmp_path, [f"ln_wide_ahead({b}, {d})" for b, d, _ in cases]) == [f for _, _, f in cases]
 
 
+def test_layernorm_backward_of_wide_fp32_rows_where_a_few_units_hold_a_third_workgroup(tmp_path):
+    cases = [(512, 1544, 1), (513, 1544, 0), (516, 1664, 0), (640, 2048, 0), (641, 2048, 1), (704, 2048, 1), (516, 1480, 1), (516, 1032, 1)]
+    assert _chosen(tmp_path, [f"ln_wide_ahead({b}, {d})" for b, d, _ in cases]) == [f for _, _, f in cases]
+
+
 def test_causal_attention_takes_pairs_of_row_blocks(tmp_path):
     # (row blocks of a head, of the launch, workgroups to a CU, pairs are ahead)
     cases = [(8, 768, 4, 1), (8, 768, 3, 1), (8, 2048, 3, 1), (8, 320, 2, 1), (16, 288, 4, 1), (16, 512, 2, 1), (32, 768, 2, 1), (4, 1280, 4, 1),
