@@ -107,9 +107,11 @@ template <int DH>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_at(const bf16_t* first, int rows, int ld) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(first), 0, span_of<DH>(min(rows, 32), ld), 0x00020000);
 }
-// A lane's row, from a tile's or a block's first, for offsets into such descriptors.  Past a sequence shorter than 64 rows it is the end of the
-// sequence: attn_ok bounds that many rows only, and the offsets of more than those come round to rows that are there.
-__device__ __forceinline__ unsigned row_or_end(int row, int S) { return (unsigned)min(row, S); }
+// A lane's row, from a tile's or a block's first, for offsets into such descriptors.  FAR: a sequence shorter than 64 rows may have rows of up to 2 GiB in
+// all, and the offsets of the 64 rows of a tile then come round, past 32 bits, to rows that are there; past the sequence a row counts as its end.
+// Kernels of their own: the minimum costs the others, whose registers are then dealt out another way, up to 1 %.
+template <bool FAR>
+__device__ __forceinline__ unsigned lane_row(int row, int S) { return (unsigned)(FAR ? min(row, S) : row); }
 __device__ __forceinline__ uint4 row_chunk(__amdgpu_buffer_rsrc_t rs, unsigned voff) {
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, 0, 0));
 }
@@ -131,7 +133,7 @@ __device__ __forceinline__ int swz(int row) {
 // offset is the same for every tile).  ONE: the rows of load i are those of load 0 plus 16 or 32 i, which have the same XOR
 // terms, so one offset per lane serves every load and the descriptor, in scalar registers, moves on: for the kernel
 // that has no vector register to spare (the others would only spill scalar registers for it).
-template <int DH, bool ONE = false, bool SETTLE = false>
+template <int DH, bool ONE = false, bool SETTLE = false, bool FAR = false>
 struct TileDma {
   static constexpr int NCH = DH / 8, N = 64 * NCH / 256, STEP = 256 / NCH;  // loads per wave, rows between them
   unsigned voff[ONE ? 1 : N];
@@ -139,7 +141,7 @@ struct TileDma {
 #pragma unroll
     for (int i = 0; i < (ONE ? 1 : N); ++i) {
       const int sl = (4 * i + wave) * 64 + lane, row = sl / NCH;
-      voff[i] = (row_or_end(row, S) * (unsigned)ld + (unsigned)((sl % NCH) ^ swz<DH>(row)) * 8u) * 2u;
+      voff[i] = (lane_row<FAR>(row, S) * (unsigned)ld + (unsigned)((sl % NCH) ^ swz<DH>(row)) * 8u) * 2u;
     }
   }
   // first: the tile's first row at the head's columns; rows: how many there are from it on (at least one)
@@ -252,7 +254,7 @@ __device__ __forceinline__ void store_stat(float v, float* first, int rows, int 
 // Bound by the VALU: a score costs a multiply-add, an exponential (four times a plain instruction's cycles), an addition, half a
 // maximum, half a conversion and (where a maximum grew) a multiplication, 8 issue slots for 1.3 of MFMA at DH = 64.  120
 // registers (four waves per SIMD; 153 when tiles passed through registers).
-template <int DH>
+template <int DH, bool FAR = false>
 __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const AttnArgs a, const AttnGrid gr) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
   extern __shared__ __attribute__((aligned(256))) uint4 lds[];
@@ -265,9 +267,9 @@ __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const A
   if (!attn_item<true>(blockIdx.x, gr, item)) return;
   const int d = a.H * DH, ld = a.ld_qkv;
   const float sc = a.scale * LOG2E;
-  TileDma<DH> dma;
+  TileDma<DH, false, false, FAR> dma;
   dma.init(ld, a.S, wave, lane);
-  const unsigned lds0 = lds_byte_addr(lds), q_off = row_or_end(li, a.S) * (unsigned)ld * 2u + 16u * g;
+  const unsigned lds0 = lds_byte_addr(lds), q_off = lane_row<FAR>(li, a.S) * (unsigned)ld * 2u + 16u * g;
   auto fetch = [&](const bf16_t* k, int rows, unsigned buf) {  // k: the tile's first key
     dma.issue(k, rows, ld, lds0 + buf, wave);
     dma.issue(k + d, rows, ld, lds0 + buf + 64 * NCH * 16, wave);
@@ -374,7 +376,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 4 : 2) void attn_fwd_kernel(const A
     const float inv = 1.f / l_run;
     const __amdgpu_buffer_rsrc_t o_rows = rows_at<DH>(a.o[item.gi] + ((size_t)item.b * a.S + row0) * a.ld_o + item.h * DH, a.S - row0, a.ld_o);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) store_block(oacc[c], inv, o_rows, row_or_end(li, a.S) * (unsigned)a.ld_o * 2u + c * 64u, g);
+    for (int c = 0; c < NC; ++c) store_block(oacc[c], inv, o_rows, lane_row<FAR>(li, a.S) * (unsigned)a.ld_o * 2u + c * 64u, g);
     store_stat((m_run + log2f(l_run)) * LN2, a.lse[item.gi] + (size_t)item.bh * a.S + row0, a.S - row0, li, g);
     item.blk = item.then, item.then = -1;
     begin();
@@ -401,7 +403,7 @@ __device__ __forceinline__ float delta_part(const uint4 (&dof)[NK], const uint4 
   return delta;
 }
 
-template <int DH, bool ONE_ITEM, bool SETTLE = ONE_ITEM>
+template <int DH, bool ONE_ITEM, bool SETTLE = ONE_ITEM, bool FAR = false>
 __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, const AttnGrid& gr, int wg) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
   extern __shared__ __attribute__((aligned(256))) uint4 lds[];
@@ -413,7 +415,7 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, const AttnGrid& gr
   if (!attn_item<true>(wg, gr, item)) return;
   const int d = a.H * DH, ld = a.ld_qkv;
   const float sc = a.scale * LOG2E;
-  TileDma<DH, false, SETTLE> dma;
+  TileDma<DH, false, SETTLE, FAR> dma;
   dma.init(ld, a.S, wave, lane);
   const unsigned lds0 = lds_byte_addr(lds);
   // every pointer at once, so that their loads are one wait
@@ -437,8 +439,8 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, const AttnGrid& gr
     const bf16_t* const orow = obase + (size_t)min(row0 + li, a.S - 1) * a.ld_o + 8 * g;  // past the end: a row whose products nobody stores
 #pragma unroll
     for (int kk = 0; kk < NK; ++kk) {
-      qf[kk] = row_chunk(q_rows, row_or_end(li, a.S) * (unsigned)ld * 2u + 32u * kk + 16u * g);
-      dof[kk] = row_chunk(do_rows, row_or_end(li, a.S) * (unsigned)a.ld_o * 2u + 32u * kk + 16u * g);
+      qf[kk] = row_chunk(q_rows, lane_row<FAR>(li, a.S) * (unsigned)ld * 2u + 32u * kk + 16u * g);
+      dof[kk] = row_chunk(do_rows, lane_row<FAR>(li, a.S) * (unsigned)a.ld_o * 2u + 32u * kk + 16u * g);
       of[kk] = *reinterpret_cast<const uint4*>(orow + 16 * kk);
     }
     const __amdgpu_buffer_rsrc_t lse_rows =
@@ -507,7 +509,7 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, const AttnGrid& gr
     if (!last) return true;
     const __amdgpu_buffer_rsrc_t dq_rows = rows_at<DH>(dqbase + (size_t)row0 * ld, a.S - row0, ld);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) store_block(acc[c], a.scale, dq_rows, row_or_end(li, a.S) * (unsigned)ld * 2u + c * 64u, g);
+    for (int c = 0; c < NC; ++c) store_block(acc[c], a.scale, dq_rows, lane_row<FAR>(li, a.S) * (unsigned)ld * 2u + c * 64u, g);
     store_stat(delta, delta_out + row0, a.S - row0, li, g);
     item.blk = item.then, item.then = -1;
     t = 0;
@@ -530,7 +532,7 @@ __device__ __forceinline__ unsigned own_lane() {
   asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
   return l;
 }
-template <int DH, bool OWN, bool ONE_ITEM = OWN>
+template <int DH, bool OWN, bool ONE_ITEM = OWN, bool FAR = false>
 __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, const AttnGrid& gr, int wg) {
   constexpr int NK = DH / 16, NC = DH / 32, NCH = DH / 8;
   extern __shared__ __attribute__((aligned(256))) uint4 lds[];
@@ -543,10 +545,10 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, const AttnGrid& g
   if (!attn_item<false>(wg, gr, item)) return;
   const int d = a.H * DH, ld = a.ld_qkv, n_tiles = (a.S + 63) / 64;
   const float sc = a.scale * LOG2E;
-  TileDma<DH, DH == 128, OWN> dma_q, dma_o;
+  TileDma<DH, DH == 128, OWN, FAR> dma_q, dma_o;
   dma_q.init(ld, a.S, wave, lane);
   dma_o.init(a.ld_o, a.S, wave, lane);
-  const unsigned lds0 = lds_byte_addr(lds), row_off = row_or_end(li, a.S) * (unsigned)ld * 2u + 16u * g;
+  const unsigned lds0 = lds_byte_addr(lds), row_off = lane_row<FAR>(li, a.S) * (unsigned)ld * 2u + 16u * g;
   const size_t seq = (size_t)item.b * a.S;
   const bf16_t* const base = a.qkv[item.gi] + seq * ld + item.h * DH;
   const bf16_t* const dobase = a.dout[item.gi] + seq * a.ld_o + item.h * DH;
@@ -669,8 +671,8 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, const AttnGrid& g
     const __amdgpu_buffer_rsrc_t dk_rows = rows_at<DH>(ok, a.S - row0, ld), dv_rows = rows_at<DH>(ok + d, a.S - row0, ld);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      store_block(dk[c], a.scale, dk_rows, row_or_end(li, a.S) * (unsigned)ld * 2u + c * 64u, g);
-      store_block(dv[c], 1.f, dv_rows, row_or_end(li, a.S) * (unsigned)ld * 2u + c * 64u, g);
+      store_block(dk[c], a.scale, dk_rows, lane_row<FAR>(li, a.S) * (unsigned)ld * 2u + c * 64u, g);
+      store_block(dv[c], 1.f, dv_rows, lane_row<FAR>(li, a.S) * (unsigned)ld * 2u + c * 64u, g);
     }
     item.blk = item.then, item.then = -1;
     t = first_tile(item.blk);
@@ -683,13 +685,13 @@ __device__ __forceinline__ void dkv_body(const AttnBwdArgs& a, const AttnGrid& g
 
 // Single row blocks need 128 registers at DH = 64, four waves per SIMD; pairs, with the rows of the next block on their way, 156 (us, all as
 // pairs | apart, both halves of the pass: 4 x [32 x 12 heads, 512, 64] 433 | 422, 4 x [8 x 12, 2048, 64] 1358 | 1326).
-template <int DH, bool PAIRS>
+template <int DH, bool PAIRS, bool FAR = false>
 __global__ __launch_bounds__(256, DH == 64 ? (PAIRS ? 3 : 4) : 2) void attn_bwd_dq_kernel(const AttnBwdArgs a, const AttnGrid gr) {
-  dq_body<DH, !PAIRS, false>(a, gr, blockIdx.x);
+  dq_body<DH, !PAIRS, false, FAR>(a, gr, blockIdx.x);
 }
-template <int DH>
+template <int DH, bool FAR = false>
 __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_bwd_dkv_kernel(const AttnBwdArgs a, const AttnGrid gr) {
-  dkv_body<DH, false>(a, gr, blockIdx.x);
+  dkv_body<DH, false, false, FAR>(a, gr, blockIdx.x);
 }
 // Small launches: both halves of the backward pass side by side, dk/dv (the longer one) first.  They share nothing but delta,
 // which the dk/dv workgroups then work out themselves from rows of dO and O (same bits): a few percent more work for
@@ -755,20 +757,35 @@ dim3 attn_grid_causal(int B, int S, int H, int G, int causal, int per_cu, AttnGr
   return pairs;
 }
 
+// Rows past the sequence whose offsets would pass 32 bits (lane_row)
+bool rows_far(int ld_qkv, int ld_o) { return 64L * std::max(ld_qkv, ld_o) * 2 > 0xffffffffL; }
+template <int DH>
+void launch_bwd_far(const AttnBwdArgs& a, const AttnGrid& gr, dim3 grid, hipStream_t s) {
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<DH, false, true>), grid, dim3(256), dq_lds<DH>(), s, a, gr);
+  hipLaunchKernelGGL((attn_bwd_dkv_kernel<DH, true>), grid, dim3(256), dkv_lds<DH>(), s, a, gr);
+}
+
 }  // namespace
 
 hipError_t attn_init() {  // the other kernels stay within the default LDS limit
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dkv_kernel<128>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_lds<128>());
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_both_kernel<128>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)dkv_lds<128>());
+  const void* const kernels[] = {reinterpret_cast<const void*>(&attn_bwd_dkv_kernel<128>), reinterpret_cast<const void*>(&attn_bwd_dkv_kernel<128, true>),
+                                 reinterpret_cast<const void*>(&attn_bwd_both_kernel<128>)};
+  for (const void* k : kernels) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_lds<128>());
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
   if (!attn_ok(a.B, a.S, a.H, a.DH, a.ld_qkv, a.ld_o, a.G) || !tiles_ok(a.qkv, a.G)) return hipErrorInvalidValue;
   AttnGrid gr;
   const dim3 grid = attn_grid_causal(a.B, a.S, a.H, a.G, a.causal, a.DH == 64 ? 4 : 2, gr);
+  if (rows_far(a.ld_qkv, a.ld_o)) {
+    if (a.DH == 64) hipLaunchKernelGGL((attn_fwd_kernel<64, true>), grid, dim3(256), fwd_lds<64>(), s, a, gr);
+    else hipLaunchKernelGGL((attn_fwd_kernel<128, true>), grid, dim3(256), fwd_lds<128>(), s, a, gr);
+    return hipGetLastError();
+  }
   if (a.DH == 64) hipLaunchKernelGGL(attn_fwd_kernel<64>, grid, dim3(256), fwd_lds<64>(), s, a, gr);
   else hipLaunchKernelGGL(attn_fwd_kernel<128>, grid, dim3(256), fwd_lds<128>(), s, a, gr);
   return hipGetLastError();
@@ -779,6 +796,11 @@ hipError_t launch_attn_bwd(const AttnBwdArgs& a, hipStream_t s) {
     return hipErrorInvalidValue;
   AttnGrid gr;
   const dim3 grid = attn_grid(a.B, a.S, a.H, a.G, gr);
+  if (rows_far(a.ld_qkv, a.ld_o)) {
+    if (a.DH == 64) launch_bwd_far<64>(a, gr, grid, s);
+    else launch_bwd_far<128>(a, gr, grid, s);
+    return hipGetLastError();
+  }
   // The halves' workgroups fit the chip together: two per CU at DH = 64, one at DH = 128 (490 registers), where a second round of
   // the shorter dq workgroups still pays a little past that.  us, two launches | one: DH = 64, 256 row blocks 53.4 | 43.0;
   // DH = 128, 128 blocks 89.1 | 72.9, 160 56.5 | 46.2, 192 57.7 | 63.5 and 94.9 | 109 (causal 163 | 138), 256 98.9 | 114.

@@ -273,11 +273,11 @@ def test_attention_reads_nothing_past_its_sequence(torch, ops, S, DH, causal):
         assert (lse[h * S:(h + 1) * S].double() - ls).abs().max() <= 1e-5
 
 
-@pytest.mark.parametrize("S,H,DH,ld", [(3, 1, 64, 2 ** 27), (3, 1, 128, 2 ** 27), (5, 1, 64, 2 ** 26 + 8), (1, 2, 128, 2 ** 28), (3, 257, 64, 2 ** 27),
+@pytest.mark.parametrize("S,H,DH,ld", [(3, 1, 64, 2 ** 27), (3, 1, 128, 2 ** 27), (5, 1, 64, 2 ** 26 + 8), (1, 2, 128, 2 ** 28), (3, 257, 64, 2 ** 27), (5, 2, 64, 2 ** 25 - 8),
                                        (3, 161, 128, 2 ** 27)])
 def test_attention_rows_of_a_short_sequence_far_apart(torch, ops, S, H, DH, ld):
     """Rows of some hundred megabytes: offsets of a block's rows past the sequence would come round to rows that are there.  The bits of packed matrices,
-    and nothing but the heads' own columns is written, with both halves of the backward pass in one launch and in two."""
+    and nothing but the heads' own columns is written, against both halves of the backward pass in one launch and in two."""
     d, gen = H * DH, torch.Generator(device="cuda").manual_seed(S + DH)
     qkv0, do0 = (torch.randn(S, n, generator=gen, device="cuda").to(torch.bfloat16) for n in (3 * d, d))
     got = []
