@@ -259,15 +259,15 @@ __device__ __forceinline__ void store8_rows(const LnRows& a, int row, int c, con
     }
   }
 }
-// One row: its dx is stored, its terms are added to the column sums where SUMS (the kernels for many rows, which store through descriptors and
-// pass `rows`).  Every multiply-add is written out, so that all kernels give the same bits.
+// One row: its dx is stored, its terms are added to the column sums where SUMS.  Every multiply-add is written out, so that all
+// kernels give the same bits.
 template <typename T, int C, bool SUMS, typename GA>
 __device__ __forceinline__ void ln_bwd_row(const LnBwdArgs& a, int g, int row, int lane, int nch, const LnRow<T, C>& r,
                                            const GA& gam, float (&sg)[C][8], float (&sb)[C][8], const LnRows* rows = nullptr) {
 #pragma clang fp contract(off)
-  // One chunk per lane: the test stands where the residual is added, ahead of the sums it costs launches of few rows 0.1 of 4.1 us
-  constexpr bool LATE = !SUMS && C == 1;
-  const bool has_add = SUMS ? rows->add != nullptr : !LATE && a.add[g] != nullptr;
+  // The test for a residual stands here, ahead of the sums, and all loads with it.  At the end, ln_bwd_split_kernel, us, here | there: bf16 4 x [1024, 256]
+  // 5.64 | 5.79, 4 x [512, 512] 4.46 | 4.53; few rows 7 x [21, 360] 4.24 | 4.12
+  const bool desc = rows != nullptr, has_add = desc ? rows->add != nullptr : a.add[g] != nullptr;
   float xh[C][8], gg[C][8];
   float s1 = 0.f, s2 = 0.f;
 #pragma unroll
@@ -305,15 +305,15 @@ __device__ __forceinline__ void ln_bwd_row(const LnBwdArgs& a, int g, int row, i
       }
 #pragma unroll
       for (int e = 0; e < 8; ++e) o[e] = r.rstd * fmaf(-xh[i][e], c2, gg[i][e] - c1);
-      if (LATE ? a.add[g] != nullptr : has_add) {
+      if (has_add) {
         float av[8];
         unpack8<T>(r.add[i], av);
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[e] += av[e];
       }
-      if (!SUMS) st8<T>(static_cast<T*>(a.dx[g]) + (size_t)row * a.ld + 8 * c, o);
+      if (!desc) st8<T>(static_cast<T*>(a.dx[g]) + (size_t)row * a.ld + 8 * c, o);
     }
-    if (SUMS) store8_rows<T>(*rows, row, c, o);
+    if (desc) store8_rows<T>(*rows, row, c, o);
   }
 }
 // Many rows: workgroups of 4 waves, each with its next row's loads in flight while it reduces the current one; bound by memory.  By
