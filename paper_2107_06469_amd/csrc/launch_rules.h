@@ -55,24 +55,17 @@ inline long f32_update_tile_rows(long rows, int ldo, bool adam) {
   const long high = (rows + 7) / 8 * 8;
   return ldo % 32 && rows > 8 && (adam ? 2 * high <= 3 * rows : 3 * high < 4 * rows) ? high : rows;
 }
-// tiles: of 32x32; rows: tile rows of a problem.  us, 32x128 | 32x32, six sets of buffers in turn:
-//   seams   SGD 1 x [1750 x 584], K = 32 7.2 | 5.0, 2 x [1616 x 712], 32 9.4 | 8.6, 4 x [1158 x 560], 16 9.3 | 9.2, 9 x [554 x 760] (a third of the grid past the
-//     matrix), 16 11.8 | 12.9;  Adam 13 | 8, 21 | 13, 19 | 14, 33 | 29;  few tile rows, 8 x [100 x 1944], 32 7.6 | 9.8 and 14.4 | 16.3; nine to twelve, 16 with those past the
-//     matrix, SGD 32x128 ahead by 3 to 10 %, Adam 11 % ahead to 35 % behind; 120 random shapes by this rule, 1 to 63 rows: 1.06 and 1.09 times
-//     as fast as 32x128 tiles on average, 0.97 at worst
-//   whole lines, up to 32 rows   SGD 1280 tiles 6.8 | 5.6, 1600 6.7 | 6.9, 2048 7.2 | 7.6, 2400 8.3 | 8.8, 4096 11 | 12;  Adam 1280 11.4 | 9.4, 1600 12.4 | 11.2, 2048 (two
-//     full passes of 32x128) 12.6 | 12.7 and 13.1 | 13.7, 2400 16.2 | 14.1, 2808 16.6 | 16.3, 3072 16.7 | 17.5, 4096 23 | 25
-//   whole lines, 33 to 63 rows   SGD 2400 tiles 10.1 | 9.0, 3584 12.7 | 11.7;  Adam 18.5 | 14.7 and 24.0 | 23.6, 2048 (full passes, K = 60)
-//     32x128 ahead by 6 %, 3072 19 | 21, 3696 24 | 26
+// tiles: of 32x32; rows: tile rows of a problem; wide: tiles of 32x128.  Up to 1600 small tiles
+// hide the state's way behind one another; Adam's three matrices and sums over more than 32 rows keep them ahead beyond.  SGD over few rows is ahead
+// with 32x128 tiles, unless two in seven of their columns lie past the matrix or the seams above are taken care of.  us, 32x128 | 32x32, four sets of
+// buffers in turn:  1 x [2300 x 480] over 25 rows, SGD 6.6 | 5.3;  9 x [1229 x 352] over 41, SGD 16.1 | 12.7;  9 x [830 x 544] over 42, Adam 28.5 | 22.5;
+//   SGD, 10 x [522 x 376] over 30 rows 8.5 | 10.8, 14 x [203 x 736] over 28 8.3 | 9.4, 12 x [2073 x 160] over 20 15.1 | 12.2;  of 72 tile rows with seams
+//   5 x [2283 x 168] over 31 9.3 | 8.0.  640 random shapes over 1 to 63 rows, this rule against 32x128 tiles throughout: 1.11 (SGD) and 1.18 (Adam) times as
+//   fast, 0.87 at worst (few tile rows with seams, 16 x [75 x 1032] over 12 7.4 | 8.5).
 inline bool f32_update_few(long tiles, long rows, long wide, int ldo, int K, bool adam) {
-  if (tiles <= 1024 || tiles > 4096) return tiles <= 1024;
-  if (K >= 64) return true;
-  if (ldo % 32) {
-    const long high = f32_update_tile_rows(rows, ldo, adam), grid = tiles / rows * high;
-    return high % 8 == 0 && (adam ? grid <= 5376 : K > 32 || grid <= (high > rows ? 3200 : 4096));
-  }
-  if (adam) return tiles <= 2816 && (wide - 1) % 256 < (K > 32 ? 255 : 240);
-  return K > 32 || tiles <= 1600;
+  if (tiles <= 1600 || tiles > 4096) return tiles <= 1600;
+  if (adam || K > 32) return true;
+  return (ldo % 32 && f32_update_tile_rows(rows, ldo, adam) % 8 == 0) || 20 * wide >= 7 * tiles;
 }
 
 // ---- launches that two products share ---------------------------------------------------------------------------------------------

@@ -804,7 +804,7 @@ def test_fp32_updates_over_a_small_batch(torch, ops, M, N, K, opt):
 
 
 @pytest.mark.parametrize("opt", [0, 1])
-@pytest.mark.parametrize("M,N,K", [(1024, 512, 33), (1024, 512, 32)])
-def test_fp32_updates_over_a_small_batch_in_full_passes(torch, ops, M, N, K, opt):
-    """The same on either side of 32 rows, where a pass of 32x128 tiles is full."""
+@pytest.mark.parametrize("M,N,K", [(1024, 512, 33), (1024, 512, 32), (800, 520, 16)])
+def test_fp32_updates_over_more_and_fewer_than_32_rows(torch, ops, M, N, K, opt):
+    """The same on either side of 32 rows, where SGD changes tiles, and in a grid that is higher than the matrix for SGD, too."""
     test_fp32_updates_over_a_small_batch(torch, ops, M, N, K, opt)
