@@ -66,7 +66,7 @@ __device__ __forceinline__ f32x16 mfma(const uint4& a, const uint4& b, f32x16 c)
 // blocks that read the same K/V (or Q/dO) tiles then run on one XCD and share them through its L2, instead of
 // each XCD fetching them from memory.  Returns false for the padding ids at the end of the grid.
 // What a workgroup does before its first tile has landed is a third of its life at 8 tiles, so that part is kept short in all kernels:
-// three multiplications instead of four integer divisions, every pointer read at once, rows read without branches (rows_from), and
+// three multiplications instead of four integer divisions, every pointer read at once, rows read without branches (rows_at), and
 // nothing that waits for one load before the next is issued.  us, before | now: forward 4 x [32 x 12 heads, 512, 64] 172 | 161,
 // 8 x 32 heads, 2048, 128, causal 411 | 385; backward 490 | 453, 1239 | 1187, 4 x [8 x 16, 384, 64] 102 | 96.6.  Then descriptors of a tile by 32-bit
 // scalar arithmetic from its first row (64-bit from the matrix's before, which took all scalar registers and spilled some on
@@ -521,7 +521,7 @@ __device__ __forceinline__ void dq_body(const AttnBwdArgs& a, const AttnGrid& gr
 
 // ---- backward, dk and dv -----------------------------------------------------------------------------------
 // Two waves per SIMD at DH = 128 (256 registers, no scratch: values that a tile needs once are worked out again from own_lane; 376, one wave, when tiles passed through registers and the
-// accumulators moved between the two register files on every tile), three at DH = 64 (168; 200 before).  Together with
+// accumulators moved between the two register files on every tile), three at DH = 64 (164; 200 before).  Together with
 // the dq kernel, us before | now: 8 x 32 heads, 2048, 128, causal 1645 | 1250, 2 x [4 x 16, 1024, 128] 360 | 269,
 // 4 x [32 x 12 heads, 512, 64] 527 | 480.  Held to one wave per SIMD at DH = 128: 1440; with its 16 LDS bases kept instead of
 // bases128 (64 bytes of scratch, K and V fragments among them): 1362.
@@ -801,7 +801,7 @@ hipError_t launch_attn_bwd(const AttnBwdArgs& a, hipStream_t s) {
     else launch_bwd_far<128>(a, gr, grid, s);
     return hipGetLastError();
   }
-  // The halves' workgroups fit the chip together: two per CU at DH = 64, one at DH = 128 (490 registers), where a second round of
+  // The halves' workgroups fit the chip together: two per CU at DH = 64, one at DH = 128 (476 registers), where a second round of
   // the shorter dq workgroups still pays a little past that.  us, two launches | one: DH = 64, 256 row blocks 53.4 | 43.0;
   // DH = 128, 128 blocks 89.1 | 72.9, 160 56.5 | 46.2, 192 57.7 | 63.5 and 94.9 | 109 (causal 163 | 138), 256 98.9 | 114.
   if (grid.x <= (a.DH == 64 ? 256 : 160) && !o_in_dqkv(a)) {
